@@ -147,13 +147,15 @@ typedef struct { int32_t points_per_axis; } mf_quadrature;   /* Gauss-Legendre: 
                                                                   3 for MF_HEX20 and MF_QUAD8,
                                                                   4 for MF_TET10 (collapsed) */
 
-/* Assembly strategies.  AUTO picks the owner-computes gather for structured grids, and
-   otherwise (or for a form without a gather kernel) the element-parallel scatter colour
+/* Assembly strategies.  AUTO picks an owner-computes gather for 8-node bricks (on a small
+   structured grid the column kernel, else the rows kernels, which take any mesh), and
+   otherwise (or without memory for their workspace) the element-parallel scatter colour
    by colour with plain adds, whose sums are the same on every run.  ATOMIC is the
    element-parallel scatter with hardware atomics in one launch (the paper's scheme).  In
-   ATOMIC and in the gather (which sums a node's element blocks with LDS atomics) the
+   ATOMIC and in the column kernel (which sums a node's element blocks with LDS atomics) the
    order of the additions, and so the last bits, may vary between runs.  GATHER asks for
-   the owner-computes kernel. */
+   an owner-computes kernel.  A pattern keeps a workspace for the element data (at most
+   1 GiB or half of K) and up to eight more for calls that were captured. */
 typedef enum { MF_SCATTER_AUTO = 0, MF_SCATTER_ATOMIC = 1, MF_SCATTER_GATHER = 2 } mf_scatter;
 
 /*
@@ -165,8 +167,8 @@ typedef enum { MF_SCATTER_AUTO = 0, MF_SCATTER_ATOMIC = 1, MF_SCATTER_GATHER = 2
  *   dN_a/dxi, with det J > 0 required, g_a = J^-T dN_a/dxi and weight w_q det J.
  * precision MF_F64: everything in FP64.  MF_F32: geometry (J, det J, J^-1, g, weights)
  *   in FP64, rounded to FP32; coefficients and the element contractions in FP32 (the
- *   structured-grid path sums the element contributions of a row in FP64 and rounds
- *   once); K, d, elem_param, nodal_src and lin_state are float.  coords are FP64 always.
+ *   owner-computes kernels sum the element contributions of a row in FP64 and round
+ *   once; the rows kernels form them in FP64 too); K, d, elem_param, nodal_src and lin_state are float.  coords are FP64 always.
  * K_values [nnz] and d [n_rows] are overwritten entirely (no prior clear needed).
  * Async on `stream`.  A device-side det J <= 0 is reported by mf_status_poll.
  * The pattern's n_fields must match the form (1, 1, dim, dim+1).

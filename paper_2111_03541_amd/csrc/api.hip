@@ -38,6 +38,24 @@ mf_status hip_error(hipError_t e, const char* what)
 
 using namespace mf;
 
+// On a small structured grid the one launch of the column kernel beats the two of assemble_rows
+// (FP64, column against rows: conduction 20^3 17 us against 20, 28^3 33 against 31, 64^3 255
+// against 125; elasticity 24^3 32 against 33, 28^3 46 against 43, 64^3 356 against 320).  The
+// rows sum in FP64 also in FP32 builds, where the column kernel's traffic halves: conduction
+// 32^3 31 us against 34, 40^3 52 against 43; elasticity 48^3 124 against 116, but 64^3 262
+// against 289 and 32^3 46 against 52; the flow form (matrix cores in the column kernel) 20^3 50
+// against 55, 24^3 76 against 63, 48^3 431 against 419.
+static bool column_wins(const AssembleArgs& A)
+{
+    if (!A.P->is_grid || A.P->dim != 3) return false;
+    const bool f32 = A.prec == MF_F32;
+    switch (A.form->kind) {
+        case MF_FORM_NS_SUPG: return f32 && A.P->n_elems < 10000;  // FP64: no column kernel
+        case MF_FORM_ELASTICITY: return f32 || A.P->n_elems < 20000;
+        default: return A.P->n_elems < (f32 ? 50000 : 20000);
+    }
+}
+
 static void free_pattern(mf_pattern_s* P)
 {
     if (!P) return;
@@ -47,6 +65,12 @@ static void free_pattern(mf_pattern_s* P)
     (void)hipFree(P->row_ptr);
     (void)hipFree(P->col_idx);
     (void)hipFree(P->rank);
+    (void)hipFree(P->adj_ptr);
+    (void)hipFree(P->adj);
+    (void)hipFree(P->rank_t);
+    (void)hipFree(P->ws);
+    for (const auto& w : P->cap_ws) (void)hipFree(w.p);
+    if (P->ws_done) (void)hipEventDestroy(P->ws_done);
     (void)hipFree(P->status);
     (void)hipFree(P->color_elems);
     (void)hipFree(P->elem_color);
@@ -61,7 +85,7 @@ const char* mf_last_error(void) { return g_err; }
 
 // The assembly kernel revision is part of the string so that measurements taken on one
 // revision (for example HBM byte counters) can be matched to it.
-const char* mf_version(void) { return "metafem-mi 0.2 (gfx950; assembly column-4x2 r10; flow mfma-4x4 r3)"; }
+const char* mf_version(void) { return "metafem-mi 0.2 (gfx950; assembly rows r1; column-4x2 r10; flow mfma-4x4 r3)"; }
 
 mf_status mf_pattern(const mf_mesh* mesh, mf_elem_type type, int32_t order, const mf_dofs* dofs,
                      void* stream, mf_pattern_t** out)
@@ -213,15 +237,21 @@ mf_status mf_assemble_ex(const mf_pattern_t* P, const mf_form* form, const doubl
     }
     st = reset_status(P, A.stream);
     if (st != MF_OK) return st;
-    if (P->order == 2) {  // quadratic elements: colour by colour, one workgroup per element
+    bool gathered = false;
+    if (P->order == 2) {
         st = assemble_quadratic(A);
         if (st != MF_OK) return st;
         return apply_dirichlet(A);
     }
-    // AUTO: the owner-computes gather on structured grids, else (and for forms without a
-    // gather kernel) the element-parallel scatter colour by colour, whose sums do not
-    // depend on the run; ATOMIC asks for the paper's atomic scatter explicitly.
+    // AUTO and GATHER on 8-node bricks: the owner-computes rows, on any mesh.  Without a
+    // workspace (no memory for it) and in 2D: the column kernel on structured grids, else (and
+    // for forms without a gather kernel) the element-parallel scatter colour by colour, whose
+    // sums do not depend on the run.  ATOMIC asks for the paper's atomic scatter explicitly.
     const bool auto_mode = scatter == MF_SCATTER_AUTO;
+    if (scatter != MF_SCATTER_ATOMIC && !column_wins(A)) {
+        st = assemble_rows(A);  // applies the Dirichlet elimination while writing K
+        if (st != MF_ERR_UNSUPPORTED) return st;
+    }
     if (auto_mode) scatter = P->is_grid ? MF_SCATTER_GATHER : MF_SCATTER_ATOMIC;
     // the coloured scatter: the flow form on 8-node bricks runs one workgroup per element
     // (geometry once per element), the other forms one thread per (element, row)
@@ -232,7 +262,6 @@ mf_status mf_assemble_ex(const mf_pattern_t* P, const mf_form* form, const doubl
         }
         return assemble_atomic(A, true);
     };
-    bool gathered = false;
     if (scatter == MF_SCATTER_GATHER) {
         st = assemble_column(A);  // applies the Dirichlet elimination while writing K
         gathered = st == MF_OK;

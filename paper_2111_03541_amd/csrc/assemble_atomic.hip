@@ -287,7 +287,7 @@ mf_status launch_atomic(const AssembleArgs& A, bool coloured)
         MF_HIP(hipGetLastError());
         return MF_OK;
     }
-    const mf_status st = ensure_coloring(P, A.stream);
+    const mf_status st = ensure_coloring(P);
     if (st != MF_OK) return st;
     for (size_t c = 0; c + 1 < P->color_ptr.size(); ++c) {
         p.elems = P->color_elems + P->color_ptr[c];
@@ -365,7 +365,7 @@ mf_status assemble_small(const AssembleArgs& A)
 {
     const mf_pattern_s* P = A.P;
     if (P->dim != 2 || P->order != 1 || P->n_elems == 0) return MF_ERR_UNSUPPORTED;
-    mf_status st = ensure_coloring(P, A.stream);
+    mf_status st = ensure_coloring(P);
     if (st != MF_OK) return st;
     const int n_col = (int)P->color_ptr.size() - 1;
     if (n_col < 1 || n_col > kSmallMaxColors) return MF_ERR_UNSUPPORTED;

@@ -543,7 +543,7 @@ mf_status launch(const AssembleArgs& A)
     if (P->n_rows > 0) k_fill<T><<<blocks_for(P->n_rows), kFillThreads, 0, A.stream>>>((T*)A.d, P->n_rows);
     MF_HIP(hipGetLastError());
     if (P->n_elems == 0) return MF_OK;
-    mf_status st = ensure_coloring(P, A.stream);
+    mf_status st = ensure_coloring(P);
     if (st != MF_OK) return st;
     for (size_t c = 0; c + 1 < P->color_ptr.size(); ++c) {
         p.elems = P->color_elems + P->color_ptr[c];

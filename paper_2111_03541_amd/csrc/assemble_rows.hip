@@ -1,0 +1,1225 @@
+// Owner-computes assembly for meshes of any numbering (Sec. 2.2 D-2, D-3): every row of K
+// and d is summed and written once, by the wave that owns its node, from element data that
+// a first kernel has left in the pattern's workspace.  No atomics on K, no clearing pass, no
+// colours, and the sums do not depend on the run.
+//
+//  element blocks (k_gather_blocks; scalar forms on 8-node bricks here, every form on the
+//     quadratic elements in assemble_quadratic.hip): the first kernel stores the element's
+//     rows [e][a][i][b][j]; the wave of node v adds the row blocks of its incidence list
+//     (entry e*nen + a is the block's index) in LDS and writes its rows.
+//  point records (k_brick_points, k_brick_rows; elasticity and the flow form on 8-node
+//     bricks): a block is 4.6 kB (elasticity) or 8 kB (flow) and would cross HBM twice, so
+//     the first kernel stores only the geometry (and the flow state) of the 8 Gauss points,
+//     and the wave that owns the node forms the products.
+//
+// Workspaces are bounded: elements go in chunks of ascending id, and a node whose incidence
+// list spans several chunks adds onto its rows from the chunk before.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "mf_internal.h"
+#include "rows.h"
+
+namespace mf {
+
+RelaxedCapture::RelaxedCapture()
+{
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) (void)hipGetLastError();
+}
+
+RelaxedCapture::~RelaxedCapture()
+{
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) (void)hipGetLastError();
+}
+
+Workspace::Workspace(const mf_pattern_s* Pc, size_t bytes, hipStream_t stream)
+    : P(const_cast<mf_pattern_s*>(Pc)), s(stream), lock(P->ws_mu)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (hipStreamGetCaptureInfo(s, &cap, &id) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    auto alloc = [&]() -> char* {
+        void* q = nullptr;
+        if (hipMalloc(&q, bytes) == hipSuccess) return (char*)q;
+        (void)hipGetLastError();
+        return nullptr;
+    };
+    if (cap != hipStreamCaptureStatusNone) {
+        // calls in a capture share a workspace with their own stream's calls in that capture
+        // only: a replay may overlap any later call, and a fork of it the other branches
+        for (const auto& w : P->cap_ws)
+            if (w.id == id && w.s == s && w.bytes >= bytes) {
+                p = w.p;
+                return;
+            }
+        if (P->cap_ws.size() >= kCaptured) return;
+        RelaxedCapture relaxed;
+        p = alloc();
+        if (p) P->cap_ws.push_back({p, bytes, id, s});
+        return;
+    }
+    if (!P->ws_done && hipEventCreateWithFlags(&P->ws_done, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        P->ws_done = nullptr;
+        return;
+    }
+    if (P->ws_bytes < bytes) {
+        if (P->ws) {
+            (void)hipEventSynchronize(P->ws_done);
+            (void)hipFree(P->ws);
+            P->ws = nullptr;
+            P->ws_bytes = 0;
+        }
+        P->ws = alloc();
+        if (!P->ws) return;
+        P->ws_bytes = bytes;
+    }
+    // (an event that was never recorded counts as complete)
+    if (hipStreamWaitEvent(s, P->ws_done, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    p = P->ws;
+    record = true;
+}
+
+Workspace::~Workspace()
+{
+    if (record && hipEventRecord(P->ws_done, s) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipStreamSynchronize(s);
+    }
+}
+
+int64_t ws_chunk_elems(const mf_pattern_s* P, size_t bytes_per_elem, size_t value_bytes)
+{
+    const size_t cap = std::max<size_t>((size_t)1 << 30, (size_t)P->nnz * value_bytes / 2);
+    const int64_t n = std::max<int64_t>(1, (int64_t)(cap / bytes_per_elem));
+    return std::min<int64_t>(P->n_elems, n);
+}
+
+namespace {
+
+constexpr int kWave = 64;
+
+// ---------------------------------------------------------------- writing a node's rows
+
+struct RowOut {
+    const int32_t* nbr;
+    const uint8_t* mask;  // Dirichlet flags or nullptr
+    int64_t n_nodes, n_pairs;
+};
+
+// Entry (i, c) of a node's rows, c = r * NF + j node-major and j * deg + r field-major (r: the
+// neighbour's rank, P: the node's offset in the node graph): its place in K.
+template <int NF, bool FM>
+__device__ __forceinline__ int64_t row_entry(const RowOut& o, int64_t P, int deg, int i, int c)
+{
+    return FM ? (int64_t)i * NF * o.n_pairs + NF * P + c : P * (NF * NF) + i * NF * deg + c;
+}
+
+// Homogeneous elimination (structure kept) in the row buffers of a wave's nodes, before they
+// are written: a constrained column is zeroed, a constrained row becomes a unit row.  The nodes'
+// neighbours are consecutive in the node graph, [P0, P0 + n): lane l looks at l, l + 64, ...
+template <int NF, bool FM>
+__device__ __forceinline__ uint32_t elim_flag(const RowOut& o, int64_t w)
+{
+    uint32_t f = 0;
+#pragma unroll
+    for (int j = 0; j < NF; ++j) f |= (uint32_t)(o.mask[FM ? j * o.n_nodes + w : NF * w + j] != 0) << j;
+    return f;
+}
+
+// v0 .. v0 + nodes: the wave's nodes, P and deg lane n's (n < nodes) offset and neighbour count;
+// `part` (lane n): the node takes part.  buf: the wave's row buffers, [i][c], or [i][j][r] (SPLIT).
+template <int NF, bool FM, bool SPLIT>
+__device__ __forceinline__ void eliminate(const RowOut& o, int64_t v0, int nodes, int P0, int n, int P, int deg, bool part,
+                                          double* buf, int lane)
+{
+    for (int t0 = 0; t0 < n; t0 += kWave) {
+        const int t = t0 + lane;
+        const uint32_t f = t < n ? elim_flag<NF, FM>(o, o.nbr[P0 + t]) : 0;
+        if (!__ballot(f != 0)) continue;
+        int own = 0, ownP = P0, ownDeg = 0;  // the node whose neighbour this is
+        for (int m = 0; m < nodes; ++m) {
+            const int Pm = __shfl(P, m), dm = __shfl(deg, m);
+            if (t >= Pm - P0 && t < Pm - P0 + dm) own = m, ownP = Pm, ownDeg = dm;
+        }
+        if (!__shfl((int)part, own) || f == 0) continue;
+        const int r = t - (ownP - P0);
+#pragma unroll
+        for (int j = 0; j < NF; ++j)
+            if ((f >> j) & 1)
+#pragma unroll
+                for (int i = 0; i < NF; ++i)
+                    buf[(ownP - P0) * NF * NF + i * NF * ownDeg + (SPLIT ? j * ownDeg + r : r * NF + j)] = 0.0;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const uint32_t rows = lane < nodes && part ? elim_flag<NF, FM>(o, v0 + lane) : 0;
+    for (unsigned long long left = __ballot(rows != 0); left; left &= left - 1) {
+        const int m = __ffsll((long long)left) - 1;
+        const int Pm = __shfl(P, m), dm = __shfl(deg, m);
+        const uint32_t f = __shfl(rows, m);
+        for (int r = lane; r < dm; r += kWave) {
+            const bool self = o.nbr[Pm + r] == v0 + m;
+#pragma unroll
+            for (int i = 0; i < NF; ++i)
+                if ((f >> i) & 1)
+#pragma unroll
+                    for (int j = 0; j < NF; ++j)
+                        buf[(Pm - P0) * NF * NF + i * NF * dm + (SPLIT ? j * dm + r : r * NF + j)] =
+                            self && i == j ? 1.0 : 0.0;
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// The rows of one node from LDS to K by one wave.  buf: [i][c], or [i][j][r] when SPLIT.
+template <int NF, bool FM, bool SPLIT, typename T>
+__device__ __forceinline__ void write_rows(const RowOut& o, int64_t P, int deg, const double* buf, T* K, int lane)
+{
+    const int n = NF * deg;
+    for (int c = lane; c < n; c += kWave) {
+        const int r = c / NF, j = c - r * NF;
+#pragma unroll
+        for (int i = 0; i < NF; ++i)
+            __builtin_nontemporal_store((T)buf[i * n + (SPLIT && !FM ? j * deg + r : c)],
+                                        K + row_entry<NF, FM>(o, P, deg, i, c));
+    }
+}
+
+// ------------------------------------------------------------------------ element blocks
+
+struct GatherParams {
+    const int32_t* adj_ptr;
+    const int32_t* adj;
+    const int32_t* nbr_ptr;
+    const uint8_t* rank_t;
+    RowOut out;
+    const void* Ke;  // [c1 - c0][NF][NEN][NF] row blocks of the incidence entries c0..c1
+    const void* fe;  // [c1 - c0][NF] residual entries (d = sum)
+    const uint8_t* emask;  // flags of the chunk's elements (with out.mask)
+    int32_t c0, c1;  // incidence entries of this chunk: element * NEN + local node
+    int parts;       // more than one chunk
+    int buf_len;     // doubles of LDS per wave
+    double lam, mu;  // Lame parameters of E = 1
+    void* K;
+    void* d;
+};
+
+// One wave takes NPW nodes next to each other, whose incidence lists and neighbours are consecutive
+// too: it reads the entries of all of them at once, so that the chain offsets - entries - blocks
+// is paid once for many blocks.  A block row is contiguous (NF * NEN * NF values), so a wave
+// reads whole lines, each once: CH values per lane of one block row, or one value per lane of SPP
+// short ones, UN such passes in flight.  The wave's own LDS additions run in program order:
+// ascending incidence entry, whatever the run.  Bound by the reads of the element blocks:
+// conduction 64^3 FP64 55 us for 151 MB of blocks and 57 MB of rows (3.8 TB/s), elasticity on
+// 24^3 20-node bricks 190 us for 401 MB and 300 MB (3.7 TB/s).  The nodes run from last to first,
+// since the end of the blocks is what the first kernel left in the last-level cache.  LAME: the blocks hold E int dN_a,i dN_b,j, and
+// the elastic combination is formed once per node pair, from the sums.
+template <int NEN, int NF>
+struct GatherShape {
+    static constexpr int RB = NF * NEN * NF;
+    static constexpr int SPP = RB >= kWave ? 1 : kWave / RB, CH = RB >= kWave ? (RB + kWave - 1) / kWave : 1;
+    static constexpr int UN = CH >= 4 ? 2 : CH >= 2 ? 4 : 8;
+    // nodes per wave on large meshes: short rows leave lanes and loads to spare
+    static constexpr int NPW = RB >= kWave ? 1 : 8;
+};
+
+template <int NEN, int NF, int NPW, typename T, bool FM, bool LAME>
+__global__ void __launch_bounds__(256) k_gather_blocks(GatherParams p)
+{
+    using G = GatherShape<NEN, NF>;
+    constexpr int RB = G::RB, SPP = G::SPP, CH = G::CH, UN = G::UN;
+    extern __shared__ double sh[];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, n_nodes = (int)p.out.n_nodes;
+    // from the last node to the first: the blocks written last are the ones still in the cache
+    const int v0 = ((int)(gridDim.x - 1 - xcd_block(blockIdx.x, gridDim.x)) * (blockDim.x / kWave) + wave) * NPW;
+    if (v0 >= n_nodes) return;
+    double* buf = sh + wave * p.buf_len;  // row buffers of the nodes, one after another
+    double* dbuf = buf + p.buf_len - NPW * NF;
+    T* K = (T*)p.K;
+    T* d = (T*)p.d;
+    // lane n (mod NPW): node v0 + n (nodes past the end: no entries, no neighbours)
+    const int v = v0 + lane % NPW, vc = min(v, n_nodes), vn = min(v + 1, n_nodes);
+    const int a0 = p.adj_ptr[vc], a1 = p.adj_ptr[vn], P = p.nbr_ptr[vc], deg = p.nbr_ptr[vn] - P;
+    const int A0 = __shfl(a0, 0), A1 = __shfl(a1, NPW - 1), P0 = __shfl(P, 0);
+    const int n_nbr = __shfl(P + deg, NPW - 1) - P0;
+    int k0 = a0, k1 = a1;
+    if (p.parts) {  // the node's entries of this chunk (ascending list)
+        while (k0 < k1 && p.adj[k0] < p.c0) ++k0;
+        while (k0 < k1 && p.adj[k1 - 1] >= p.c1) --k1;
+    }
+    const bool first = k0 == a0, last = k1 == a1;
+    // a node without elements has no columns; its d is written with the first chunk
+    const bool on = v < n_nodes && (k0 < k1 || (a0 == a1 && p.c0 == 0));
+    if (!__any(on)) return;
+    const bool elim = p.out.mask && last;
+    int touched = p.parts;  // an element around a node has a constrained DOF (other chunks: unknown)
+    for (int t = lane; t < n_nbr * NF * NF; t += kWave) buf[t] = 0.0;
+    for (int t = lane; t < NPW * NF; t += kWave) {
+        const int m = t / NF, j = t - m * NF;
+        const bool add = __shfl((int)(on && !first), m) != 0;
+        dbuf[t] = add ? (double)d[FM ? (int64_t)j * n_nodes + v0 + m : (int64_t)NF * (v0 + m) + j] : 0.0;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // the lane's values of a block row: column node, row and column field
+    const int sl = SPP > 1 ? lane / RB : 0;
+    int tb[CH], ti[CH], tj[CH];
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+        const int t = SPP > 1 ? lane - sl * RB : lane + u * kWave;
+        const int i = t / (NEN * NF), c = t - i * (NEN * NF), b = c / NF;
+        tb[u] = (SPP > 1 ? sl < SPP : t < RB) ? b : -1;
+        ti[u] = i;
+        tj[u] = c - b * NF;
+        if (NPW == 1) ti[u] = i * NF * deg + (FM ? tj[u] * deg : tj[u]);  // its place but for the rank
+    }
+    for (int kb = A0; kb < A1; kb += kWave) {
+        const int m = min(kWave, A1 - kb);
+        // lane's entry: its index in the chunk (-1: of another chunk), its node's buffer and width
+        int mine = -1, at = 0, width = 0, mydb = 0;
+        double fd[NF];
+        {
+            const int k = kb + lane;
+            const int code = lane < m ? p.adj[k] : -1;
+            int nd = 0;
+#pragma unroll
+            for (int n = 1; n < NPW; ++n) nd += k >= __shfl(a0, n);
+            if (code >= p.c0 && code < p.c1) mine = code - p.c0;
+            at = (__shfl(P, nd) - P0) * NF * NF;
+            width = __shfl(deg, nd);
+            if (p.out.mask && mine >= 0) touched |= p.emask[mine / NEN];
+#pragma unroll
+            for (int j = 0; j < NF; ++j) fd[j] = mine >= 0 ? (double)((const T*)p.fe)[(int64_t)mine * NF + j] : 0.0;
+            mydb = nd * NF;
+        }
+        for (int s0 = 0; s0 < m; s0 += SPP * UN) {
+            // (loads without conditions, past the end from entry 0: all of them in flight together)
+            double val[UN][CH];
+            int rk[UN][CH], base[UN], dg[UN];
+            bool live[UN];
+#pragma unroll
+            for (int w = 0; w < UN; ++w) {
+                const int s = s0 + w * SPP + sl, sc = s < m ? s : 0;
+                const int c = SPP > 1 ? __shfl(mine, sc) : __builtin_amdgcn_readlane(mine, sc);
+                base[w] = NPW > 1 ? __shfl(at, sc) : 0;
+                dg[w] = NPW > 1 ? __shfl(width, sc) : 0;
+                live[w] = s < m && c >= 0;
+                const int64_t code = c >= 0 ? c : 0;
+#pragma unroll
+                for (int u = 0; u < CH; ++u) {
+                    const int t = SPP > 1 ? lane - sl * RB : min(lane + u * kWave, RB - 1);
+                    rk[w][u] = p.rank_t[(code + p.c0) * NEN + (tb[u] >= 0 ? tb[u] : 0)];
+                    val[w][u] = (double)__builtin_nontemporal_load((const T*)p.Ke + code * RB + t);
+                }
+            }
+#pragma unroll
+            for (int w = 0; w < UN; ++w)
+#pragma unroll
+                for (int u = 0; u < CH; ++u) {
+                    const int r = rk[w][u];
+                    const int pos = NPW == 1 ? ti[u] + (FM ? r : r * NF)
+                                             : base[w] + ti[u] * NF * dg[w] + (FM ? tj[u] * dg[w] + r : r * NF + tj[u]);
+                    if (live[w] && tb[u] >= 0) unsafeAtomicAdd(buf + pos, val[w][u]);
+                }
+        }
+        if (mine >= 0)
+#pragma unroll
+            for (int j = 0; j < NF; ++j) unsafeAtomicAdd(dbuf + mydb + j, fd[j]);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if constexpr (LAME) {
+        // K_ij = lam T_ij + mu T_ji + mu delta_ij tr T, in place, a node pair per lane
+        for (int t0 = 0; t0 < n_nbr; t0 += kWave) {
+            const int t = t0 + lane;
+            int nd = 0;  // (every lane takes part in the exchanges)
+#pragma unroll
+            for (int n = 1; n < NPW; ++n) nd += t >= __shfl(P, n) - P0;
+            const int Pn = __shfl(P, nd), dg = __shfl(deg, nd);
+            if (t >= n_nbr) continue;
+            double* pair = buf + (Pn - P0) * NF * NF;
+            const int r = t - (Pn - P0);
+            double x[NF][NF], tr = 0.0;
+#pragma unroll
+            for (int i = 0; i < NF; ++i) {
+#pragma unroll
+                for (int j = 0; j < NF; ++j) x[i][j] = pair[i * NF * dg + (FM ? j * dg + r : r * NF + j)];
+                tr = fma(p.mu, x[i][i], tr);
+            }
+#pragma unroll
+            for (int i = 0; i < NF; ++i)
+#pragma unroll
+                for (int j = 0; j < NF; ++j)
+                    pair[i * NF * dg + (FM ? j * dg + r : r * NF + j)] =
+                        fma(p.lam, x[i][j], p.mu * x[j][i]) + (i == j ? tr : 0.0);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    if (__any(on && !first))  // rows of an earlier chunk
+        for (int n = 0; n < NPW; ++n) {
+            if (!__shfl((int)(on && !first), n)) continue;
+            const int Pn = __shfl(P, n), dg = __shfl(deg, n);
+            for (int c = lane; c < NF * dg; c += kWave)
+#pragma unroll
+                for (int i = 0; i < NF; ++i)
+                    buf[(Pn - P0) * NF * NF + i * NF * dg + c] += (double)K[row_entry<NF, FM>(p.out, Pn, dg, i, c)];
+        }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (p.out.mask && __any(touched)) eliminate<NF, FM, FM>(p.out, v0, NPW, P0, n_nbr, P, deg, on && elim, buf, lane);
+    for (int t = lane; t < NPW * NF; t += kWave) {
+        const int m = t / NF, j = t - m * NF;
+        const int64_t row = FM ? (int64_t)j * n_nodes + v0 + m : (int64_t)NF * (v0 + m) + j;
+        const bool gone = __shfl((int)elim, m) != 0;
+        if (__shfl((int)on, m)) d[row] = (T)(gone && p.out.mask[row] ? 0.0 : dbuf[t]);
+    }
+    if (!FM && __all(on || v >= n_nodes)) {
+        T* out = K + (int64_t)P0 * (NF * NF);
+#pragma unroll 4
+        for (int t = lane; t < n_nbr * NF * NF; t += kWave) __builtin_nontemporal_store((T)buf[t], out + t);
+        return;
+    }
+#pragma unroll 1
+    for (int n = 0; n < NPW; ++n) {
+        if (!__shfl((int)on, n)) continue;
+        const int Pn = __shfl(P, n);
+        write_rows<NF, FM, FM, T>(p.out, Pn, __shfl(deg, n), buf + (Pn - P0) * (NF * NF), K, lane);
+    }
+}
+
+template <int NEN, int NF, typename T, bool LAME = false>
+mf_status launch_gather(const AssembleArgs& A, const void* Ke, const void* fe, const uint8_t* emask, int64_t e0,
+                        int64_t e1)
+{
+    const mf_pattern_s* P = A.P;
+    GatherParams p{};
+    p.adj_ptr = P->adj_ptr;
+    p.adj = P->adj;
+    p.nbr_ptr = P->nbr_ptr;
+    p.rank_t = P->rank_t;
+    p.out = {P->nbr, A.dirichlet, P->n_nodes, P->n_pairs};
+    p.Ke = Ke;
+    p.fe = fe;
+    p.emask = emask;
+    p.c0 = (int32_t)(e0 * NEN);
+    p.c1 = (int32_t)(e1 * NEN);
+    p.parts = e1 - e0 < P->n_elems;
+    const double nu = A.form->nu;
+    p.lam = nu / ((1.0 + nu) * (1.0 - 2.0 * nu));
+    p.mu = 1.0 / (2.0 * (1.0 + nu));
+    p.K = A.K;
+    p.d = A.d;
+    auto run = [&](auto npw) {
+        constexpr int NPW = decltype(npw)::value;
+        p.buf_len = NPW * (NF * NF * std::max(1, P->max_deg) + NF);
+        const size_t per_wave = sizeof(double) * (size_t)p.buf_len;
+        const int waves = per_wave * 4 <= 65536 ? 4 : per_wave * 2 <= 65536 ? 2 : 1;
+        const unsigned blocks = (unsigned)((P->n_nodes + waves * NPW - 1) / (waves * NPW));
+        const size_t lds = per_wave * waves;
+        if (P->numbering == MF_FIELD_MAJOR)
+            k_gather_blocks<NEN, NF, NPW, T, true, LAME><<<blocks, waves * kWave, lds, A.stream>>>(p);
+        else
+            k_gather_blocks<NEN, NF, NPW, T, false, LAME><<<blocks, waves * kWave, lds, A.stream>>>(p);
+    };
+    // 64^3 conduction: 55 us with eight nodes a wave, 95 with one; on 25 thousand nodes of
+    // tetrahedra 24 against 19 (too few waves)
+    constexpr int kMany = GatherShape<NEN, NF>::NPW;
+    if (kMany > 1 && P->n_nodes >= 30000) run(std::integral_constant<int, kMany>{});
+    else run(std::integral_constant<int, 1>{});
+    MF_HIP(hipGetLastError());
+    return MF_OK;
+}
+
+// ------------------------------------------------------- geometry of an 8-node brick point
+
+constexpr double kHi = 0.5 * (1.0 + kGaussPt), kLo = 0.5 * (1.0 - kGaussPt);  // Q1 factors at a Gauss point
+
+// N_a at Gauss point q: one factor per axis, kHi where the bits of a and q agree
+__device__ __forceinline__ double brick_N(int a, int q)
+{
+    const int d = a ^ q;
+    return ((d & 1) ? kLo : kHi) * ((d & 2) ? kLo : kHi) * ((d & 4) ? kLo : kHi);
+}
+
+__device__ __forceinline__ void brick_dN(int a, int q, double (&g)[3])
+{
+    const int d = a ^ q;
+    const double fx = (d & 1) ? kLo : kHi, fy = (d & 2) ? kLo : kHi, fz = (d & 4) ? kLo : kHi;
+    g[0] = ((a & 1) ? 0.5 : -0.5) * fy * fz;
+    g[1] = ((a & 2) ? 0.5 : -0.5) * fx * fz;
+    g[2] = ((a & 4) ? 0.5 : -0.5) * fx * fy;
+}
+
+// det J and the cofactors of J at Gauss point q: C[n][m] = det J * dxi_n/dx_m.  X [8][3] in LDS.
+__device__ __forceinline__ double brick_cofactors(const double* X, int q, double (&C)[3][3])
+{
+    double J[3][3];
+#pragma unroll
+    for (int m = 0; m < 3; ++m)
+#pragma unroll
+        for (int n = 0; n < 3; ++n) J[m][n] = 0.0;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        double g[3];
+        brick_dN(b, q, g);
+#pragma unroll
+        for (int m = 0; m < 3; ++m)
+#pragma unroll
+            for (int n = 0; n < 3; ++n) J[m][n] = fma(X[b * 3 + m], g[n], J[m][n]);
+    }
+    C[0][0] = J[1][1] * J[2][2] - J[1][2] * J[2][1];
+    C[0][1] = J[0][2] * J[2][1] - J[0][1] * J[2][2];
+    C[0][2] = J[0][1] * J[1][2] - J[0][2] * J[1][1];
+    C[1][0] = J[1][2] * J[2][0] - J[1][0] * J[2][2];
+    C[1][1] = J[0][0] * J[2][2] - J[0][2] * J[2][0];
+    C[1][2] = J[0][2] * J[1][0] - J[0][0] * J[1][2];
+    C[2][0] = J[1][0] * J[2][1] - J[1][1] * J[2][0];
+    C[2][1] = J[0][1] * J[2][0] - J[0][0] * J[2][1];
+    C[2][2] = J[0][0] * J[1][1] - J[0][1] * J[1][0];
+    return J[0][0] * C[0][0] + J[0][1] * C[1][0] + J[0][2] * C[2][0];
+}
+
+struct BrickParams {
+    ElemMask em;
+    mf_form form;
+    int64_t n_el, n_nodes;
+    int64_t e0, e1;  // the elements of this chunk
+    const int32_t* conn;
+    const double* coords;
+    const void* elem_param;
+    const void* src;  // nodal sources, or the flow state
+    void* Ke;         // element blocks (scalar forms) or point records
+    void* fe;         // [e1 - e0][8][NF]
+    unsigned long long* status;
+};
+
+// Coordinates and sources of node b of element e into LDS, and whether it has a constrained DOF
+// into *masked (cleared before, behind a barrier).  Returns the sum of the sources read,
+// non-finite when one is.
+template <int NSRC, typename T>
+__device__ __forceinline__ double brick_load(const BrickParams& p, int64_t e, int b, bool live, double* X, double* S,
+                                             int* masked)
+{
+    const int64_t node = live ? p.conn[(int64_t)b * p.n_el + e] : 0;
+#pragma unroll
+    for (int m = 0; m < 3; ++m) X[b * 3 + m] = live ? p.coords[(int64_t)m * p.n_nodes + node] : 0.0;
+    double chk = 0.0;
+#pragma unroll
+    for (int j = 0; j < NSRC; ++j) {
+        const double s = live && p.src ? (double)((const T*)p.src)[(int64_t)j * p.n_nodes + node] : 0.0;
+        S[b * NSRC + j] = s;
+        chk += s;
+    }
+    if (p.em.mask && live && p.em.node<NSRC>(node)) *masked = 1;
+    return chk;
+}
+
+// Blocks of kBE elements: thread (point or node q, element el), elements fastest, so that the
+// connectivity, the records and the blocks move in runs of kBE values.
+constexpr int kBE = 32;
+
+// Flags a bad Jacobian or a non-finite value of element el in LDS (cleared by the caller
+// before a barrier; the caller's next barrier makes the flags visible) and in the status.
+__device__ __forceinline__ void brick_flag(const BrickParams& p, int64_t e, bool live, double det, double chk, int* bad)
+{
+    if (!live) return;
+    if (!(det > 0.0)) {
+        *bad = 1;
+        atomicMin(p.status, (unsigned long long)e);
+    }
+    if (!isfinite(chk)) atomicMin(p.status + 2, (unsigned long long)e);
+}
+
+// Mass and conduction on 8-node bricks: the element block.  Thread (point, element) forms the
+// metric W c J^-1 J^-T (W c for the mass form) and W f in LDS, then thread (node a, element)
+// sums row a over the points; the rows leave through LDS as whole lines.  Conduction 64^3 FP64:
+// 63 us, of which 151 MB of stores take 23; the rest is the FP64 geometry and two barriers, with
+// five waves per SIMD to hide them.  With the gather 118 us, where the column kernel, which
+// forms each element in up to 8 workgroups' halos, took 255.
+template <int FORM, typename T>
+__global__ void __launch_bounds__(8 * kBE, 5) k_brick_scalar(BrickParams p)
+{
+    constexpr int NG = FORM == MF_FORM_MASS ? 2 : 7;  // metric, then W f
+    // metrics [8 NG][kBE], then the blocks [kBE][64] (padded: elements on different banks)
+    constexpr int kLen = 8 * NG * kBE > kBE * 65 ? 8 * NG * kBE : kBE * 65;
+    __shared__ double sX[kBE][25], sS[kBE][9], sW[kLen];
+    double(*sG)[kBE] = (double(*)[kBE])sW;
+    __shared__ int sBad[kBE], sMask[kBE];
+    const int el = threadIdx.x % kBE, q = threadIdx.x / kBE;
+    const int64_t e = p.e0 + (int64_t)blockIdx.x * kBE + el;
+    const bool live = e < p.e1;
+    if (q == 0) sBad[el] = sMask[el] = 0;
+    if (p.em.mask) __syncthreads();
+    double chk = brick_load<1, T>(p, e, q, live, sX[el], sS[el], &sMask[el]);
+    const double c = p.form.coef * (live && p.elem_param ? (double)((const T*)p.elem_param)[e] : 1.0);
+    __syncthreads();
+    double C[3][3], f = 0.0;
+    const double det = brick_cofactors(sX[el], q, C);
+#pragma unroll
+    for (int b = 0; b < 8; ++b) f = fma(brick_N(b, q), sS[el][b], f);
+    brick_flag(p, e, live, det, chk + c + f, &sBad[el]);
+    double g[NG];
+    if constexpr (FORM == MF_FORM_MASS) {
+        g[0] = det * c;
+        g[1] = det * c * f;
+    } else {
+        const double s = c / det;  // W c (1/det)^2
+#pragma unroll
+        for (int n = 0, k = 0; n < 3; ++n)
+#pragma unroll
+            for (int m = n; m < 3; ++m, ++k)
+                g[k] = s * (C[n][0] * C[m][0] + C[n][1] * C[m][1] + C[n][2] * C[m][2]);
+        g[6] = det * f;
+    }
+#pragma unroll
+    for (int k = 0; k < NG; ++k) sG[q * NG + k][el] = g[k];
+    __syncthreads();
+    const int a = q;
+    double row[8], load = 0.0;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) row[b] = 0.0;
+#pragma unroll 2
+    for (int k = 0; k < 8; ++k) {
+        double h[NG];
+#pragma unroll
+        for (int m = 0; m < NG; ++m) h[m] = sG[k * NG + m][el];
+        load = fma(brick_N(a, k), h[NG - 1], load);
+        if constexpr (FORM == MF_FORM_MASS) {
+            const double wa = h[0] * brick_N(a, k);
+#pragma unroll
+            for (int b = 0; b < 8; ++b) row[b] = fma(wa, kRefHex.N[k][b], row[b]);
+        } else {
+            double da[3];
+            brick_dN(a, k, da);
+            const double v0 = h[0] * da[0] + h[1] * da[1] + h[2] * da[2];
+            const double v1 = h[1] * da[0] + h[3] * da[1] + h[4] * da[2];
+            const double v2 = h[2] * da[0] + h[4] * da[1] + h[5] * da[2];
+#pragma unroll
+            for (int b = 0; b < 8; ++b)
+                row[b] = fma(v0, kRefHex.dN[k][b][0], fma(v1, kRefHex.dN[k][b][1], fma(v2, kRefHex.dN[k][b][2], row[b])));
+        }
+    }
+    const bool bad = sBad[el] != 0;  // such an element adds nothing
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < 8; ++b) sW[el * 65 + a * 8 + b] = bad ? 0.0 : row[b];
+    if (live) {
+        if (p.em.mask && q == 0) p.em.flag[e - p.e0] = (uint8_t)sMask[el];
+        ((T*)p.fe)[(e - p.e0) * 8 + a] = bad ? T(0) : (T)load;
+    }
+    __syncthreads();
+    // the blocks of the workgroup's elements are one contiguous range
+    const int64_t e1 = p.e0 + (int64_t)blockIdx.x * kBE;
+    const int n = (int)(p.e1 - e1 < kBE ? p.e1 - e1 : kBE) * 64;
+    T* K = (T*)p.Ke + (e1 - p.e0) * 64;
+#pragma unroll
+    for (int t = threadIdx.x; t < kBE * 64; t += 8 * kBE)
+        if (t < n) K[t] = (T)sW[t / 64 * 65 + t % 64];
+}
+
+// ------------------------------------------------------------------------- point records
+
+// Per form: fields, values of a record, column nodes per lane and workgroups per CU of the
+// row kernel.  Records are stored as pairs of values, [NR / 2][8 points][elements of the
+// chunk][2], then the last value [8 points][elements]: a lane's load takes 16 bytes, and the
+// lanes of consecutive elements one run.
+template <int FORM>
+struct Rec;
+// elasticity: sqrt(det J) J^-1 (so that a product of two gradients carries the weight)
+template <>
+struct Rec<MF_FORM_ELASTICITY> {
+    static constexpr int NF = 3, NR = 9, BPL = 8, WG = 2;
+};
+// flow: J^-1, W, u, c_0, grad u (row i, column l), c_1, c_2 with c = W (tau_m rho Rm - rho u);
+// the first 14 are what a point's first products need
+template <>
+struct Rec<MF_FORM_NS_SUPG> {
+    static constexpr int NF = 4, NR = 25, BPL = 4, WG = 2;
+};
+
+// Thread (point, element): the geometry once per element instead of once per row, as records
+// of value pairs so that the lanes' stores and the row waves' loads are 16 bytes.  Bound by the
+// latency of the node gathers and the stores: elasticity 64^3 60 us for 151 MB, flow 48^3 76 us
+// for 177 MB.
+template <int FORM, typename T>
+__global__ void __launch_bounds__(8 * kBE) k_brick_points(BrickParams p)
+{
+    constexpr int NF = Rec<FORM>::NF, NR = Rec<FORM>::NR;
+    constexpr bool NS = FORM == MF_FORM_NS_SUPG;
+    // LDS per point: W f, or the record and W(tau_c div - p), W div, W tau_m Rm
+    constexpr int NL = NS ? NR + 5 : 3;
+    __shared__ double sX[kBE][25], sS[kBE][8 * NF + 1], sL[8 * NL][kBE];
+    __shared__ int sBad[kBE], sMask[kBE];
+    const int el = threadIdx.x % kBE, q = threadIdx.x / kBE;
+    const int64_t e = p.e0 + (int64_t)blockIdx.x * kBE + el;
+    const bool live = e < p.e1;
+    const double* S = sS[el];
+    if (q == 0) sBad[el] = sMask[el] = 0;
+    if (p.em.mask) __syncthreads();
+    double chk = brick_load<NF, T>(p, e, q, live, sX[el], sS[el], &sMask[el]);
+    if (NS) chk += p.form.rho + p.form.mu + p.form.tau_m + p.form.tau_c;
+    else chk += p.form.coef * (live && p.elem_param ? (double)((const T*)p.elem_param)[e] : 1.0);
+    __syncthreads();
+    double C[3][3], u[NF], R[NR];
+    const double det = brick_cofactors(sX[el], q, C);
+#pragma unroll
+    for (int j = 0; j < NF; ++j) u[j] = 0.0;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        const double N = brick_N(b, q);
+#pragma unroll
+        for (int j = 0; j < NF; ++j) u[j] = fma(N, S[b * NF + j], u[j]);
+    }
+    double* L = &sL[q * NL][el];  // value k at L[k * kBE]
+    if constexpr (!NS) {
+        const double s = rsqrt(det);
+#pragma unroll
+        for (int n = 0; n < 3; ++n)
+#pragma unroll
+            for (int m = 0; m < 3; ++m) R[n * 3 + m] = s * C[n][m];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            chk += u[j];
+            L[j * kBE] = det * u[j];
+        }
+    } else {
+        const double r = 1.0 / det;
+        double dU[4][3];
+#pragma unroll
+        for (int n = 0; n < 3; ++n)
+#pragma unroll
+            for (int m = 0; m < 3; ++m) R[n * 3 + m] = C[n][m] * r;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            double d[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                double g[3];
+                brick_dN(b, q, g);
+#pragma unroll
+                for (int n = 0; n < 3; ++n) d[n] = fma(g[n], S[b * 4 + j], d[n]);
+            }
+#pragma unroll
+            for (int m = 0; m < 3; ++m) dU[j][m] = d[0] * R[m] + d[1] * R[3 + m] + d[2] * R[6 + m];
+        }
+        const double rho = p.form.rho, tm = p.form.tau_m, W = det;
+        const double div = dU[0][0] + dU[1][1] + dU[2][2];
+        R[9] = W;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const double Rm = rho * (u[0] * dU[i][0] + u[1] * dU[i][1] + u[2] * dU[i][2]) + dU[3][i];
+            chk += Rm;
+            R[10 + i] = u[i];
+#pragma unroll
+            for (int l = 0; l < 3; ++l) R[14 + 3 * i + l] = dU[i][l];
+            R[i == 0 ? 13 : 22 + i] = W * rho * (tm * Rm - u[i]);
+            L[(NR + 2 + i) * kBE] = W * tm * Rm;
+        }
+        chk += div;
+        L[NR * kBE] = W * (p.form.tau_c * div - u[3]);
+        L[(NR + 1) * kBE] = W * div;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) L[k * kBE] = R[k];
+    }
+    brick_flag(p, e, live, det, chk, &sBad[el]);
+    __syncthreads();
+    if (!live) return;
+    if (p.em.mask && q == 0) p.em.flag[e - p.e0] = (uint8_t)sMask[el];
+    const bool bad = sBad[el] != 0;  // such an element adds nothing
+    const int64_t chunk = p.e1 - p.e0;
+    double2* rec = (double2*)p.Ke + q * chunk + (e - p.e0);
+#pragma unroll
+    for (int k = 0; k < NR / 2; ++k)
+        rec[k * 8 * chunk] = bad ? make_double2(0.0, 0.0) : make_double2(R[2 * k], R[2 * k + 1]);
+    ((double*)p.Ke)[(NR - 1) * 8 * chunk + q * chunk + (e - p.e0)] = bad ? 0.0 : R[NR - 1];
+    // residual entries of node a
+    const int a = q;
+    double f[NF];
+#pragma unroll
+    for (int j = 0; j < NF; ++j) f[j] = 0.0;
+#pragma unroll 2
+    for (int k = 0; k < 8; ++k) {
+        const double* x = &sL[k * NL][el];
+        const double N = brick_N(a, k);
+        if constexpr (!NS) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) f[j] = fma(N, x[j * kBE], f[j]);
+        } else {
+            double da[3], g[3], adv = 0.0;
+            brick_dN(a, k, da);
+#pragma unroll
+            for (int m = 0; m < 3; ++m) {
+                g[m] = da[0] * x[m * kBE] + da[1] * x[(3 + m) * kBE] + da[2] * x[(6 + m) * kBE];
+                adv = fma(x[(10 + m) * kBE], g[m], adv);
+            }
+            const double muW = p.form.mu * x[9 * kBE];
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                f[i] -= adv * x[(i == 0 ? 13 : 22 + i) * kBE] + g[i] * x[NR * kBE] +
+                        muW * (g[0] * x[(14 + 3 * i) * kBE] + g[1] * x[(15 + 3 * i) * kBE] + g[2] * x[(16 + 3 * i) * kBE]);
+            f[3] -= N * x[(NR + 1) * kBE] + g[0] * x[(NR + 2) * kBE] + g[1] * x[(NR + 3) * kBE] + g[2] * x[(NR + 4) * kBE];
+        }
+    }
+    T* fe = (T*)p.fe + (int64_t)a * NF * chunk + (e - p.e0);
+#pragma unroll
+    for (int j = 0; j < NF; ++j) fe[j * chunk] = bad ? T(0) : (T)f[j];
+}
+
+// x and y factors of the trilinear basis at a point: the value, and the two derivatives
+struct RefTablesQuad {
+    double N[4][4];
+    double dN[4][4][2];
+    constexpr RefTablesQuad() : N{}, dN{}
+    {
+        for (int q = 0; q < 4; ++q)
+            for (int a = 0; a < 4; ++a) {
+                N[q][a] = ref_N<2>(a, q);
+                for (int d = 0; d < 2; ++d) dN[q][a][d] = ref_dN<2>(a, q, d);
+            }
+    }
+};
+__constant__ constexpr RefTablesQuad kRefQuad{};
+
+struct RowParams {
+    mf_form form;
+    const int32_t* adj_ptr;
+    const int32_t* adj;
+    const int32_t* nbr_ptr;
+    const uint8_t* rank_t;
+    RowOut out;
+    const void* elem_param;
+    const double* rec;  // [NR][8][chunk]
+    const void* fe;     // [8][NF][chunk]
+    const uint8_t* emask;  // flags of the chunk's elements (with out.mask)
+    int64_t chunk;
+    int32_t c0, c1;     // incidence entries of this chunk
+    int parts;          // more than one chunk
+    int buf_len, wave_len;  // doubles of LDS per node and per wave
+    void* K;
+    void* d;
+};
+
+// Products of one Gauss point: adds the blocks (a, b) of the lane's BPL column nodes.
+// Elasticity: acc_ij += h_a,i h_b,j (the Lame combination follows once per block).
+template <int BPL>
+__device__ __forceinline__ void point_elasticity(int a, int q, const double (&h)[9], double (&acc)[BPL][3][3])
+{
+    double da[3], ga[3];
+    brick_dN(a, q, da);
+#pragma unroll
+    for (int m = 0; m < 3; ++m) ga[m] = da[0] * h[m] + da[1] * h[3 + m] + da[2] * h[6 + m];
+#pragma unroll
+    for (int bb = 0; bb < BPL; ++bb) {
+        const double* db = kRefHex.dN[q][bb];  // uniform: scalar loads
+        double gb[3];
+#pragma unroll
+        for (int m = 0; m < 3; ++m) gb[m] = db[0] * h[m] + db[1] * h[3 + m] + db[2] * h[6 + m];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) acc[bb][i][j] = fma(ga[i], gb[j], acc[bb][i][j]);
+    }
+}
+
+// Flow: with the factors of the row node gathered first, every entry is a combination of
+// N_b, grad N_b, u . grad N_b and one scalar product.  Column node bb + 4 half: the z factor is
+// the lane's, the others are uniform.
+struct FlowPoint {
+    double ga[3], Pg[3], tAr, rWadv, c0, zf;  // what the second part needs of the first
+};
+
+// First part, from the first 14 values of the record: all entries but the products with c
+// and grad u.
+template <int BPL, typename Issue>
+__device__ __forceinline__ void point_flow_head(const mf_form& fm, int a, int half, int q, const double (&h)[14],
+                                                FlowPoint& f, double (&acc)[BPL][4][4], const Issue& issue)
+{
+    double da[3];
+    brick_dN(a, q, da);
+#pragma unroll
+    for (int m = 0; m < 3; ++m) f.ga[m] = da[0] * h[m] + da[1] * h[3 + m] + da[2] * h[6 + m];
+    const double W = h[9], rtm = fm.rho * fm.tau_m;
+    const double Wadv = W * (h[10] * f.ga[0] + h[11] * f.ga[1] + h[12] * f.ga[2]);
+    const double tA = rtm * Wadv;  // W tau_m rho (u . grad N_a)
+    const double WN = W * brick_N(a, q);
+    const double zf = (half == (q >> 2)) ? kHi : kLo, sz = half ? 1.0 : -1.0;
+    f.tAr = fm.rho * tA;
+    f.rWadv = fm.rho * Wadv;
+    f.c0 = h[13];
+    f.zf = zf;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        f.Pg[i] = W * f.ga[i];
+    }
+#pragma unroll
+    for (int bb = 0; bb < BPL; ++bb) {
+        if (bb == BPL - 1) issue();  // the second part's loads
+        const double cN = kRefQuad.N[q & 3][bb], c0 = kRefQuad.dN[q & 3][bb][0], c1 = kRefQuad.dN[q & 3][bb][1];
+        const double c0z = c0 * zf, c1z = c1 * zf, c2z = (0.5 * cN) * sz, Nb = cN * zf;
+        double gb[3];
+#pragma unroll
+        for (int m = 0; m < 3; ++m) gb[m] = c0z * h[m] + c1z * h[3 + m] + c2z * h[6 + m];
+        const double ug = h[10] * gb[0] + h[11] * gb[1] + h[12] * gb[2], ub = rtm * ug;
+        const double pb = f.Pg[0] * gb[0] + f.Pg[1] * gb[1] + f.Pg[2] * gb[2];
+        const double yb = fma(fm.mu, pb, f.tAr * ug);
+        const double tcg[3] = {fm.tau_c * gb[0], fm.tau_c * gb[1], fm.tau_c * gb[2]};
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+#pragma unroll
+            for (int l = 0; l < 3; ++l) acc[bb][i][l] = fma(f.Pg[i], tcg[l], acc[bb][i][l]);
+            acc[bb][i][i] += yb;
+            acc[bb][i][3] = fma(tA, gb[i], fma(-f.Pg[i], Nb, acc[bb][i][3]));
+            acc[bb][3][i] = fma(WN, gb[i], fma(f.Pg[i], ub, acc[bb][3][i]));
+        }
+        acc[bb][3][3] = fma(fm.tau_m, pb, acc[bb][3][3]);
+    }
+}
+
+// Second part: r holds grad u (9), c_1, c_2.
+template <int BPL>
+__device__ __forceinline__ void point_flow_tail(const mf_form& fm, int q, const double (&r)[11], const FlowPoint& f,
+                                                double (&acc)[BPL][4][4])
+{
+    const double rtm = fm.rho * fm.tau_m;
+    double Nb[BPL];
+#pragma unroll
+    for (int bb = 0; bb < BPL; ++bb) Nb[bb] = kRefQuad.N[q & 3][bb] * f.zf;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+#pragma unroll
+        for (int l = 0; l < 3; ++l) {
+            double X = fma(i == 0 ? f.c0 : r[8 + i], f.ga[l], f.tAr * r[3 * i + l]);
+            if (l == i) X -= f.rWadv;
+#pragma unroll
+            for (int bb = 0; bb < BPL; ++bb) acc[bb][i][l] = fma(X, Nb[bb], acc[bb][i][l]);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // row by row: the factors of all rows would not fit the registers
+    }
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+        const double S = rtm * (f.Pg[0] * r[l] + f.Pg[1] * r[3 + l] + f.Pg[2] * r[6 + l]);
+#pragma unroll
+        for (int bb = 0; bb < BPL; ++bb) acc[bb][3][l] = fma(S, Nb[bb], acc[bb][3][l]);
+    }
+}
+
+// Lane (node, slot of its incidence list, group of BPL column nodes): the lane reads its
+// element's records (consecutive nodes have consecutive elements on a mesh numbered with
+// some locality, so a wave's load is a few runs), sums its BPL node blocks over the 8 points
+// in registers, adds them to the node's row buffer in LDS, and the rows of the wave's nodes
+// leave as one contiguous run.  Two waves per SIMD (the node blocks take half the registers),
+// the next point's record is in flight during the products of the present one.  Elasticity 64^3
+// FP64: 260 us, VALU busy 48 %; with k_brick_points 318 us, the column kernel 356 and the coloured
+// scatter on a renumbered mesh 1600.  Flow 48^3 FP64: 385 + 76 us, the coloured kernel 1540.
+// FP32 builds sum in FP64 too: without packed math the rates are the same.
+template <int FORM, typename T, bool FM>
+__global__ void __launch_bounds__(256, (Rec<FORM>::WG)) k_brick_rows(RowParams p)
+{
+    using R = Rec<FORM>;
+    constexpr int NF = R::NF, NR = R::NR, BPL = R::BPL;
+    constexpr int GRP = 8 / BPL, LPN = 8 * GRP, NPW = kWave / LPN;
+    constexpr int NH = FORM == MF_FORM_NS_SUPG ? 14 : NR;  // values of a record read together
+    static_assert(BPL == 8 || BPL == 4, "the column node's z bit is a literal or the lane's group");
+    // row buffers as K has them, or [i][j][r]: four values per neighbour next to each other
+    // would put all lanes' additions into a quarter of the LDS banks
+    constexpr bool SPLIT = FM || NF == 4;
+    extern __shared__ __align__(16) double sh[];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    // lanes: node fastest, then group of column nodes, then slot
+    const int grp = lane % NPW, half = lane / NPW % GRP, slot = lane / (NPW * GRP), sub = lane / NPW;
+    const int waves = blockDim.x / kWave, n_nodes = (int)p.out.n_nodes;
+    const int v0 = ((int)xcd_block(blockIdx.x, gridDim.x) * waves + wave) * NPW, v = v0 + grp;
+    if (v0 >= n_nodes) return;
+    const int wbase = wave * p.wave_len;  // the wave's row buffers, one after another
+    double* dbuf = sh + wbase + NPW * p.buf_len + grp * NF;
+    // (nodes past the end read the last offset: no entries, no neighbours)
+    const int vc = min(v, n_nodes), vn = min(v + 1, n_nodes);
+    const int a0 = p.adj_ptr[vc], a1 = p.adj_ptr[vn], P = p.nbr_ptr[vc], deg = p.nbr_ptr[vn] - P;
+    const int P0 = __shfl(P, 0), n_wave = (__shfl(P + deg, NPW - 1) - P0) * NF * NF;
+    int k0 = a0, k1 = a1;
+    if (p.parts) {  // the node's entries of this chunk (ascending list)
+        while (k0 < k1 && p.adj[k0] < p.c0) ++k0;
+        while (k0 < k1 && p.adj[k1 - 1] >= p.c1) --k1;
+    }
+    const bool first = k0 == a0, last = k1 == a1;
+    // a node without elements: d with the first chunk
+    const bool on = v < n_nodes && (k0 < k1 || (a0 == a1 && p.c0 == 0));
+    const int base = wbase + (P - P0) * (NF * NF);
+    const int64_t drow = FM ? (int64_t)sub * n_nodes + v : (int64_t)NF * v + sub;
+    T* K = (T*)p.K;
+    T* d = (T*)p.d;
+    const bool elim = p.out.mask && last;
+    int touched = p.parts;  // an element around the node has a constrained DOF (other chunks: unknown)
+    for (int t = 2 * lane; t < n_wave; t += 2 * kWave) *(double2*)(sh + wbase + t) = make_double2(0.0, 0.0);
+    if (sub < NF) dbuf[sub] = on && !first ? (double)d[drow] : 0.0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (on && !first)
+        for (int c = sub; c < NF * deg; c += LPN)
+#pragma unroll
+            for (int i = 0; i < NF; ++i)
+                sh[base + i * NF * deg + (SPLIT && !FM ? c % NF * deg + c / NF : c)] =
+                    (double)K[row_entry<NF, FM>(p.out, P, deg, i, c)];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int k = k0 + slot; k < k1; k += 8) {
+        const int code = p.adj[k];  // element * 8 + local node
+        const int a = code & 7;
+        const uint32_t e = (uint32_t)(code - p.c0) >> 3;
+        if (p.out.mask) touched |= p.emask[e];
+        // value pairs [m0, m1) of the record at point q: uniform bases, 32-bit lane offset
+        auto load_pairs = [&](int q, int m0, int m1, double* h) {
+            uint32_t e16 = e * 16;
+            asm volatile("" : "+v"(e16));  // (a 64-bit lane address per value would not fit the registers)
+            const char* b2 = (const char*)p.rec + (int64_t)q * p.chunk * 16;
+#pragma unroll
+            for (int m = m0; m < m1; ++m) {
+                const double2 x = *(const double2*)(b2 + (int64_t)m * p.chunk * 128 + e16);
+                h[2 * (m - m0)] = x.x;
+                h[2 * (m - m0) + 1] = x.y;
+            }
+        };
+        auto load_last = [&](int q) {
+            uint32_t e8 = e * 8;
+            asm volatile("" : "+v"(e8));
+            return *(const double*)((const char*)p.rec + ((int64_t)(NR - 1) * 8 + q) * p.chunk * 8 + e8);
+        };
+        auto load_head = [&](int q, double (&h)[NH]) {
+            load_pairs(q, 0, NH / 2, h);
+            if constexpr (NH % 2) h[NH - 1] = load_last(q);
+        };
+        double acc[BPL][NF][NF];
+#pragma unroll
+        for (int bb = 0; bb < BPL; ++bb)
+#pragma unroll
+            for (int i = 0; i < NF; ++i)
+#pragma unroll
+                for (int j = 0; j < NF; ++j) acc[bb][i][j] = 0.0;
+        double h0[NH];
+        load_head(0, h0);
+        // the next point's record is on its way while this one's products are formed
+        if constexpr (FORM == MF_FORM_ELASTICITY) {
+            double h1[NH];
+#pragma unroll 1
+            for (int q = 0; q < 8; q += 2) {
+                load_head(q + 1, h1);
+                point_elasticity<BPL>(a, q, h0, acc);
+                load_head(q < 6 ? q + 2 : 7, h0);
+                point_elasticity<BPL>(a, q + 1, h1, acc);
+            }
+        } else {
+#pragma unroll 1
+            for (int q = 0; q < 8; ++q) {
+                double r[11];
+                FlowPoint f;
+                point_flow_head<BPL>(p.form, a, half, q, h0, f, acc, [&] {
+                    load_pairs(q, 7, 12, r);
+                    r[10] = load_last(q);
+                });
+                load_head(q < 7 ? q + 1 : 7, h0);
+                point_flow_tail<BPL>(p.form, q, r, f, acc);
+            }
+        }
+        uint32_t ranks[BPL / 4];
+#pragma unroll
+        for (int u = 0; u < BPL / 4; ++u) ranks[u] = *(const uint32_t*)(p.rank_t + (int64_t)code * 8 + (half + u) * 4);
+        const T* fe = (const T*)p.fe + (int64_t)a * NF * p.chunk + e;
+        double fd[NF];
+#pragma unroll
+        for (int j = 0; j < NF; ++j) fd[j] = half == 0 ? (double)fe[j * p.chunk] : 0.0;
+        double lam = 0.0, mu = 0.0;
+        if constexpr (FORM == MF_FORM_ELASTICITY) {
+            const double ep = p.elem_param ? (double)((const T*)p.elem_param)[code >> 3] : 1.0;
+            const double E = p.form.coef * ep, nu = p.form.nu;
+            lam = E * nu / ((1.0 + nu) * (1.0 - 2.0 * nu));
+            mu = E / (2.0 * (1.0 + nu));
+        }
+#pragma unroll
+        for (int bb = 0; bb < BPL; ++bb) {
+            const int r = (ranks[bb >> 2] >> (8 * (bb & 3))) & 0xff;
+            double tr = 0.0;
+            if constexpr (FORM == MF_FORM_ELASTICITY) tr = mu * (acc[bb][0][0] + acc[bb][1][1] + acc[bb][2][2]);
+#pragma unroll
+            for (int i = 0; i < NF; ++i) {
+                double* row = sh + base + i * NF * deg + (SPLIT ? r : r * NF);
+#pragma unroll
+                for (int j = 0; j < NF; ++j) {
+                    double x = acc[bb][i][j];
+                    if constexpr (FORM == MF_FORM_ELASTICITY) {
+                        x = fma(lam, x, mu * acc[bb][j][i]);
+                        if (i == j) x += tr;
+                    }
+                    unsafeAtomicAdd(row + (SPLIT ? j * deg : j), x);
+                }
+            }
+        }
+        if (half == 0)
+#pragma unroll
+            for (int j = 0; j < NF; ++j) unsafeAtomicAdd(dbuf + j, fd[j]);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (on && sub < NF) d[drow] = (T)(elim && p.out.mask[drow] ? 0.0 : dbuf[sub]);
+    // (every lane takes part from here on)
+    if (p.out.mask && __any(touched))
+        eliminate<NF, FM, SPLIT>(p.out, v0, NPW, P0, n_wave / (NF * NF), P, deg, on && elim, sh + wbase, lane);
+    if (!SPLIT && __all(on || v >= n_nodes)) {
+        T* out = K + (int64_t)P0 * (NF * NF);
+#pragma unroll 4
+        for (int t = lane; t < n_wave; t += kWave) __builtin_nontemporal_store((T)sh[wbase + t], out + t);
+        return;
+    }
+#pragma unroll 1
+    for (int n = 0; n < NPW; ++n) {
+        if (!__shfl((int)on, n)) continue;
+        const int Pn = __shfl(P, n);
+        write_rows<NF, FM, SPLIT, T>(p.out, Pn, __shfl(deg, n), sh + wbase + (Pn - P0) * (NF * NF), K, lane);
+    }
+}
+
+template <typename T>
+BrickParams brick_params(const AssembleArgs& A, int64_t e0, int64_t e1, void* Ke, void* fe, uint8_t* emask)
+{
+    const mf_pattern_s* P = A.P;
+    BrickParams p{};
+    p.form = *A.form;
+    p.n_el = P->n_elems;
+    p.n_nodes = P->n_nodes;
+    p.e0 = e0;
+    p.e1 = e1;
+    p.conn = P->conn;
+    p.coords = A.coords;
+    p.elem_param = A.elem_param;
+    p.src = A.form->kind == MF_FORM_NS_SUPG ? A.lin_state : A.nodal_src;
+    p.Ke = Ke;
+    p.fe = fe;
+    p.em = {A.dirichlet, emask, P->n_nodes, P->numbering == MF_FIELD_MAJOR};
+    p.status = P->status;
+    return p;
+}
+
+template <int FORM, typename T>
+mf_status launch_scalar(const AssembleArgs& A)
+{
+    const mf_pattern_s* P = A.P;
+    if (!gather_fits(P, 8, 1)) return MF_ERR_UNSUPPORTED;
+    const size_t per = sizeof(T) * (64 + 8) + 1;
+    const int64_t chunk = ws_chunk_elems(P, per, sizeof(T));
+    const Workspace ws(P, per * (size_t)chunk, A.stream);
+    char* w = ws.p;
+    if (!w) return MF_ERR_UNSUPPORTED;
+    void* fe = w + sizeof(T) * 64 * (size_t)chunk;
+    uint8_t* emask = (uint8_t*)w + sizeof(T) * 72 * (size_t)chunk;
+    for (int64_t e0 = 0; e0 < P->n_elems; e0 += chunk) {
+        const int64_t e1 = std::min(P->n_elems, e0 + chunk);
+        const BrickParams p = brick_params<T>(A, e0, e1, w, fe, emask);
+        k_brick_scalar<FORM, T><<<(unsigned)((e1 - e0 + kBE - 1) / kBE), 8 * kBE, 0, A.stream>>>(p);
+        MF_HIP(hipGetLastError());
+        const mf_status st = launch_gather<8, 1, T>(A, w, fe, emask, e0, e1);
+        if (st != MF_OK) return st;
+    }
+    return MF_OK;
+}
+
+template <int FORM, typename T>
+mf_status launch_rows(const AssembleArgs& A)
+{
+    using R = Rec<FORM>;
+    constexpr int NPW = kWave * R::BPL / 64;
+    const mf_pattern_s* P = A.P;
+    const int buf_len = R::NF * R::NF * std::max(1, P->max_deg);
+    const int wave_len = (buf_len + R::NF) * NPW + 2 & ~1;  // 16-byte aligned, one double of slack
+    const size_t per_wave = sizeof(double) * (size_t)wave_len;
+    if (per_wave > 65536) return MF_ERR_UNSUPPORTED;  // hundreds of neighbours: the scatter
+    const int waves = 4 * per_wave <= 65536 ? 4 : 2 * per_wave <= 65536 ? 2 : 1;
+    const size_t rec = sizeof(double) * 8 * R::NR, per = rec + sizeof(T) * 8 * R::NF + 1;
+    const int64_t chunk = ws_chunk_elems(P, per, sizeof(T));
+    const Workspace ws(P, per * (size_t)chunk, A.stream);
+    char* w = ws.p;
+    if (!w) return MF_ERR_UNSUPPORTED;
+    void* fe = w + rec * (size_t)chunk;
+    uint8_t* emask = (uint8_t*)w + (per - 1) * (size_t)chunk;
+    for (int64_t e0 = 0; e0 < P->n_elems; e0 += chunk) {
+        const int64_t e1 = std::min(P->n_elems, e0 + chunk);
+        const BrickParams b = brick_params<T>(A, e0, e1, w, fe, emask);
+        k_brick_points<FORM, T><<<(unsigned)((e1 - e0 + kBE - 1) / kBE), 8 * kBE, 0, A.stream>>>(b);
+        MF_HIP(hipGetLastError());
+        RowParams p{};
+        p.form = *A.form;
+        p.adj_ptr = P->adj_ptr;
+        p.adj = P->adj;
+        p.nbr_ptr = P->nbr_ptr;
+        p.rank_t = P->rank_t;
+        p.out = {P->nbr, A.dirichlet, P->n_nodes, P->n_pairs};
+        p.elem_param = A.elem_param;
+        p.rec = (const double*)w;
+        p.fe = fe;
+        p.emask = emask;
+        p.chunk = e1 - e0;
+        p.c0 = (int32_t)(e0 * 8);
+        p.c1 = (int32_t)(e1 * 8);
+        p.parts = e1 - e0 < P->n_elems;
+        p.buf_len = buf_len;
+        p.wave_len = wave_len;
+        p.K = A.K;
+        p.d = A.d;
+        const int64_t per_block = (int64_t)waves * NPW;
+        const unsigned blocks = (unsigned)((P->n_nodes + per_block - 1) / per_block);
+        if (P->numbering == MF_FIELD_MAJOR) k_brick_rows<FORM, T, true><<<blocks, waves * kWave, per_wave * waves, A.stream>>>(p);
+        else k_brick_rows<FORM, T, false><<<blocks, waves * kWave, per_wave * waves, A.stream>>>(p);
+        MF_HIP(hipGetLastError());
+    }
+    return MF_OK;
+}
+
+template <typename T>
+mf_status dispatch_rows(const AssembleArgs& A)
+{
+    switch (A.form->kind) {
+        case MF_FORM_MASS: return launch_scalar<MF_FORM_MASS, T>(A);
+        case MF_FORM_POISSON: return launch_scalar<MF_FORM_POISSON, T>(A);
+        case MF_FORM_ELASTICITY: return launch_rows<MF_FORM_ELASTICITY, T>(A);
+        case MF_FORM_NS_SUPG: return launch_rows<MF_FORM_NS_SUPG, T>(A);
+    }
+    return MF_ERR_UNSUPPORTED;
+}
+
+}  // namespace
+
+bool gather_fits(const mf_pattern_s* P, int nen, int nf)
+{
+    const int nodes = nf * nen * nf >= kWave ? 1 : GatherShape<8, 1>::NPW;
+    return sizeof(double) * (size_t)nodes * (nf * nf * (size_t)std::max(1, P->max_deg) + nf) <= 65536;
+}
+
+mf_status gather_blocks(const AssembleArgs& A, int nen, int nf, const void* Ke, const void* fe, const uint8_t* emask,
+                        int64_t e0, int64_t e1)
+{
+    auto run = [&](auto zero) -> mf_status {
+        using T = decltype(zero);
+        switch (nen * 8 + nf) {
+            case 20 * 8 + 1: return launch_gather<20, 1, T>(A, Ke, fe, emask, e0, e1);
+            case 20 * 8 + 3: return launch_gather<20, 3, T, true>(A, Ke, fe, emask, e0, e1);
+            case 20 * 8 + 4: return launch_gather<20, 4, T>(A, Ke, fe, emask, e0, e1);
+            case 10 * 8 + 1: return launch_gather<10, 1, T>(A, Ke, fe, emask, e0, e1);
+            case 10 * 8 + 3: return launch_gather<10, 3, T, true>(A, Ke, fe, emask, e0, e1);
+            case 10 * 8 + 4: return launch_gather<10, 4, T>(A, Ke, fe, emask, e0, e1);
+            case 8 * 8 + 1: return launch_gather<8, 1, T>(A, Ke, fe, emask, e0, e1);
+            case 8 * 8 + 2: return launch_gather<8, 2, T, true>(A, Ke, fe, emask, e0, e1);
+            case 8 * 8 + 3: return launch_gather<8, 3, T>(A, Ke, fe, emask, e0, e1);
+        }
+        return set_error(MF_ERR_ARG, "no gather for %d nodes and %d fields", nen, nf);
+    };
+    return A.prec == MF_F64 ? run(0.0) : run(0.0f);
+}
+
+mf_status assemble_rows(const AssembleArgs& A)
+{
+    const mf_pattern_s* P = A.P;
+    if (P->dim != 3 || P->nen != 8 || P->n_elems == 0 || !P->full_coupling) return MF_ERR_UNSUPPORTED;
+    return A.prec == MF_F64 ? dispatch_rows<double>(A) : dispatch_rows<float>(A);
+}
+
+}  // namespace mf

@@ -789,7 +789,7 @@ mf_status launch_boundary(BParams p, const mf_pattern_s* Pc, hipStream_t s)
 {
     mf_pattern_s* P = const_cast<mf_pattern_s*>(Pc);
     if (p.n_faces == 0 || P->n_elems == 0) return MF_OK;
-    mf_status st = ensure_coloring(P, s);
+    mf_status st = ensure_coloring(P);
     if (st != MF_OK) return st;
     const int n_col = (int)P->color_ptr.size() - 1;
     // workspace: mask [n_el], counts [6 n_el], colour lists [n_el], list lengths [n_col],
@@ -872,7 +872,7 @@ mf_status bucket_faces(const mf_pattern_s* Pc, int n_local, const int32_t* fe, c
                        hipStream_t s, std::vector<int64_t>& off, const int32_t*& order)
 {
     mf_pattern_s* P = const_cast<mf_pattern_s*>(Pc);
-    mf_status st = ensure_coloring(P, s);
+    mf_status st = ensure_coloring(P);
     if (st != MF_OK) return st;
     const int n_colors = std::max(0, (int)P->color_ptr.size() - 1);
     const int n_keys = n_colors * n_local + 1;

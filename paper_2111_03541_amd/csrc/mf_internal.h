@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -24,6 +25,27 @@ struct mf_pattern_s {
     int32_t* row_ptr = nullptr;  // [n_rows+1]
     int32_t* col_idx = nullptr;  // [nnz]
     uint8_t* rank = nullptr;     // [nen*nen][n_elems]
+    // node-element incidence: entry e*nen + a for every element e with node v at local
+    // position a, ascending within adj[adj_ptr[v] .. adj_ptr[v+1])
+    int32_t* adj_ptr = nullptr;  // [n_nodes+1]
+    int32_t* adj = nullptr;      // [nen*n_elems]
+    uint8_t* rank_t = nullptr;   // rank element by element: [n_elems][nen][nen]
+    int max_deg = 0;             // largest neighbour count of a node
+    // assembly workspace, grown on first use and owned by the pattern: per-element records
+    // written by one kernel of a call and read by its next.  ws_done marks the end of the
+    // last call that used it, so that a call on another stream waits for it.
+    char* ws = nullptr;
+    size_t ws_bytes = 0;
+    hipEvent_t ws_done = nullptr;
+    std::mutex ws_mu;  // held from a call's first kernel that uses the workspace to its last
+    // workspaces of captured calls: one for each capture and stream in it
+    struct Captured {
+        char* p;
+        size_t bytes;
+        unsigned long long id;
+        hipStream_t s;
+    };
+    std::vector<Captured> cap_ws;
     unsigned long long* status = nullptr;  // [3] first element with det J <= 0, first bad face, first element
                                            // with a non-finite input or coefficient (each ~0 when none)
     // element colouring (no two elements of one colour share a node), made on first use:
@@ -34,7 +56,8 @@ struct mf_pattern_s {
     // boundary-face buckets (boundary.hip): device workspace, grown on demand
     int32_t* face_work = nullptr;
     int64_t face_work_cap = 0;
-    // 8-node hexahedra faces per element (boundary.hip): mask [n_elems], counts [6][n_elems]
+    // 8-node hexahedra, faces per element of the colour-by-colour scatter (boundary.hip): mask
+    // [n_elems], counts [n_elems][6], colour lists
     uint32_t* face_elem_work = nullptr;
     // structured lexicographic grid detection
     int is_grid = 0;
@@ -43,6 +66,23 @@ struct mf_pattern_s {
 };
 
 namespace mf {
+
+// While it lives, this thread may allocate and copy although a stream is being captured.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture();
+    ~RelaxedCapture();
+};
+
+// A stream of its own for setup that ends before the call goes on, also under capture.
+struct SideStream : RelaxedCapture {
+    hipStream_t s = nullptr;
+    hipError_t status = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    ~SideStream()
+    {
+        if (s) (void)hipStreamDestroy(s);
+    }
+};
 
 mf_status set_error(mf_status s, const char* fmt, ...);
 mf_status hip_error(hipError_t e, const char* what);
@@ -57,7 +97,7 @@ void clear_error();  // empties the thread's last-error message
 // pattern.hip
 mf_status build_pattern(mf_pattern_s* P, const int32_t* conn_in, hipStream_t s);
 // greedy element colouring, cached in the pattern (sync on first call)
-mf_status ensure_coloring(const mf_pattern_s* P, hipStream_t s);
+mf_status ensure_coloring(const mf_pattern_s* P);
 
 struct PcgArgs;
 // mf_bicgstab; with P (the pattern whose CSR structure A uses) the SpMV of node-major
@@ -95,8 +135,28 @@ mf_status assemble_atomic(const AssembleArgs& a, bool coloured);
 // as assemble_atomic(a, true) + apply_dirichlet.  MF_ERR_UNSUPPORTED (nothing launched,
 // no error recorded) for any other mesh.
 mf_status assemble_small(const AssembleArgs& a);
-mf_status assemble_quadratic(const AssembleArgs& a);  // assemble_quadratic.hip: MF_HEX20, MF_QUAD8
+// assemble_quadratic.hip: the quadratic elements, and the flow form on 8-node bricks where it
+// goes colour by colour
+mf_status assemble_quadratic(const AssembleArgs& a);
 mf_status assemble_column(const AssembleArgs& a);
+// assemble_rows.hip: owner-computes rows on any mesh of 8-node bricks, from element records
+// in the pattern's workspace; applies the Dirichlet elimination.  MF_ERR_UNSUPPORTED (nothing
+// launched, no error recorded) for other elements and where no workspace can be had.
+mf_status assemble_rows(const AssembleArgs& a);
+// The pattern's workspace of at least `bytes` for kernels queued on the stream during its
+// lifetime (calls that are being captured get one of their own).  p is nullptr when there is
+// no memory for it, or kCaptured captures have one already.
+struct Workspace {
+    static constexpr size_t kCaptured = 8;
+    mf_pattern_s* P;
+    hipStream_t s;
+    std::unique_lock<std::mutex> lock;
+    char* p = nullptr;
+    bool record = false;
+    Workspace(const mf_pattern_s* P, size_t bytes, hipStream_t stream);
+    ~Workspace();
+    Workspace(const Workspace&) = delete;
+};
 mf_status apply_dirichlet(const AssembleArgs& a);
 mf_status reset_status(const mf_pattern_s* P, hipStream_t s);
 

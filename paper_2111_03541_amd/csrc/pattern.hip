@@ -50,15 +50,46 @@ __global__ void k_fill_incidence(const int32_t* __restrict__ conn, int64_t n_el,
 {
     int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n_el * nen) return;
-    int64_t e = t % n_el;
+    int32_t e = (int32_t)(t % n_el), a = (int32_t)(t / n_el);
     int32_t v = conn[t];
     int32_t pos = atomicAdd(&cursor[v], 1);
-    inc[inc_ptr[v] + pos] = (int32_t)e;
+    inc[inc_ptr[v] + pos] = e * nen + a;
+}
+
+// The entries of each node in ascending order (the counting sort's atomics leave them in
+// any order): an insertion sort per node, of about eight entries on bricks.
+__global__ void k_sort_incidence(const int64_t* __restrict__ inc_ptr, int64_t n_nodes, int32_t* __restrict__ inc)
+{
+    int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= n_nodes) return;
+    const int64_t k0 = inc_ptr[v], k1 = inc_ptr[v + 1];
+    for (int64_t k = k0 + 1; k < k1; ++k) {
+        const int32_t x = inc[k];
+        int64_t m = k;
+        for (; m > k0 && inc[m - 1] > x; --m) inc[m] = inc[m - 1];
+        inc[m] = x;
+    }
+}
+
+__global__ void k_max_i32(const int32_t* __restrict__ in, int64_t n, int* __restrict__ out)
+{
+    __shared__ int32_t sh[kThreads];
+    int32_t m = 0;
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads)
+        m = in[i] > m ? in[i] : m;
+    sh[threadIdx.x] = m;
+    __syncthreads();
+    for (int w = kThreads / 2; w > 0; w /= 2) {
+        if ((int)threadIdx.x < w && sh[threadIdx.x + w] > sh[threadIdx.x]) sh[threadIdx.x] = sh[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) atomicMax(out, sh[0]);
 }
 
 // Distinct neighbours of v in ascending order, by repeated selection of the smallest
 // candidate above the last one taken.  write == nullptr: count only.
-__global__ void k_node_neighbours(const int32_t* __restrict__ conn, int64_t n_el, int nen,
+template <int nen>
+__global__ void k_node_neighbours(const int32_t* __restrict__ conn, int64_t n_el,
                                   int64_t n_nodes, const int64_t* __restrict__ inc_ptr,
                                   const int32_t* __restrict__ inc, int32_t* __restrict__ deg,
                                   const int64_t* __restrict__ out_ptr, int32_t* __restrict__ out,
@@ -72,7 +103,7 @@ __global__ void k_node_neighbours(const int32_t* __restrict__ conn, int64_t n_el
     while (true) {
         int32_t next = INT_MAX;
         for (int64_t k = k0; k < k1; ++k) {
-            int32_t e = inc[k];
+            int32_t e = inc[k] / nen;
             for (int b = 0; b < nen; ++b) {
                 int32_t c = conn[(int64_t)b * n_el + e];
                 if (c > last && c < next) next = c;
@@ -146,25 +177,40 @@ __global__ void k_col_idx(const int64_t* __restrict__ nbr_ptr, const int32_t* __
     }
 }
 
-__global__ void k_rank(const int32_t* __restrict__ conn, int64_t n_el, int nen,
+template <int nen>
+__global__ void k_rank(const int32_t* __restrict__ conn, int64_t n_el,
                        const int64_t* __restrict__ nbr_ptr, const int32_t* __restrict__ nbr,
-                       uint8_t* __restrict__ rank)
+                       uint8_t* __restrict__ rank, uint8_t* __restrict__ rank_t)
 {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n_el * nen * nen) return;
-    int64_t e = t % n_el;
-    int ab = (int)(t / n_el);
-    int a = ab / nen, b = ab % nen;
-    int32_t va = conn[(int64_t)a * n_el + e], vb = conn[(int64_t)b * n_el + e];
-    int64_t lo = nbr_ptr[va], hi = nbr_ptr[va + 1] - 1;
-    int64_t r = 255;
-    while (lo <= hi) {
-        int64_t mid = (lo + hi) >> 1;
-        int32_t x = nbr[mid];
-        if (x == vb) { r = mid - nbr_ptr[va]; break; }
-        if (x < vb) lo = mid + 1; else hi = mid - 1;
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= n_el) return;
+    const int a = blockIdx.y;
+    const int32_t va = conn[a * n_el + e];
+    const int32_t first = (int32_t)nbr_ptr[va], last = (int32_t)nbr_ptr[va + 1] - 1;
+    uint8_t row[nen];
+#pragma unroll
+    for (int b = 0; b < nen; ++b) {
+        const int32_t vb = conn[b * n_el + e];
+        int32_t lo = first, hi = last, r = 255;
+        while (lo <= hi) {
+            const int32_t mid = lo + ((hi - lo) >> 1);
+            const int32_t x = nbr[mid];
+            if (x == vb) { r = mid - first; break; }
+            if (x < vb) lo = mid + 1; else hi = mid - 1;
+        }
+        row[b] = (uint8_t)r;
+        rank[(a * nen + b) * n_el + e] = (uint8_t)r;
     }
-    rank[t] = (uint8_t)r;
+    // (rank_t is 256-byte aligned: four bytes at a time where a row of nen bytes allows it)
+    uint8_t* out = rank_t + (e * nen + a) * nen;
+    if constexpr (nen % 4 == 0) {
+#pragma unroll
+        for (int b = 0; b < nen; b += 4)
+            *(uint32_t*)(out + b) = row[b] | row[b + 1] << 8 | row[b + 2] << 16 | (uint32_t)row[b + 3] << 24;
+    } else {
+#pragma unroll
+        for (int b = 0; b < nen; ++b) out[b] = row[b];
+    }
 }
 
 // Does conn equal the lexicographic grid numbering for (nx, ny, nz)?
@@ -303,13 +349,13 @@ mf_status build_pattern(mf_pattern_s* P, const int32_t* conn_in, hipStream_t s)
     const int64_t n_el = P->n_elems, n_nodes = P->n_nodes;
     const int64_t n_ent = n_el * nen;
     Scratch tmp;
-    int* flag = nullptr;
-    int32_t *cnt = nullptr, *cursor = nullptr, *inc = nullptr, *deg = nullptr;
+    int *flag = nullptr, *max_deg = nullptr;
+    int32_t *cnt = nullptr, *cursor = nullptr, *deg = nullptr;
     int64_t *inc_ptr = nullptr, *nbr_ptr64 = nullptr;
     MF_TRY(tmp.alloc(&flag, 1));
+    MF_TRY(tmp.alloc(&max_deg, 1));
     MF_TRY(tmp.alloc(&cnt, n_nodes));
     MF_TRY(tmp.alloc(&cursor, n_nodes));
-    MF_TRY(tmp.alloc(&inc, n_ent));
     MF_TRY(tmp.alloc(&deg, n_nodes));
     MF_TRY(tmp.alloc(&inc_ptr, n_nodes + 1));
     MF_TRY(tmp.alloc(&nbr_ptr64, n_nodes + 1));
@@ -319,8 +365,12 @@ mf_status build_pattern(mf_pattern_s* P, const int32_t* conn_in, hipStream_t s)
     if (n_ent > 0)
         MF_HIP(hipMemcpyAsync(P->conn, conn_in, sizeof(int32_t) * (size_t)n_ent, hipMemcpyDeviceToDevice, s));
     const int32_t* conn = P->conn;
+    MF_HIP(hipMalloc(&P->adj_ptr, sizeof(int32_t) * (size_t)(n_nodes + 1)));
+    MF_HIP(hipMalloc(&P->adj, sizeof(int32_t) * (size_t)(n_ent > 0 ? n_ent : 1)));
+    int32_t* inc = P->adj;
 
     k_fill_i32<<<1, 1, 0, s>>>((int32_t*)flag, 1, 0);
+    k_fill_i32<<<1, 1, 0, s>>>((int32_t*)max_deg, 1, 0);
     if (n_nodes > 0) {
         k_fill_i32<<<blocks_for(n_nodes, kThreads), kThreads, 0, s>>>(cnt, n_nodes, 0);
         k_fill_i32<<<blocks_for(n_nodes, kThreads), kThreads, 0, s>>>(cursor, n_nodes, 0);
@@ -336,12 +386,27 @@ mf_status build_pattern(mf_pattern_s* P, const int32_t* conn_in, hipStream_t s)
     MF_TRY(exclusive_scan<int32_t>(cnt, n_nodes, inc_ptr, s));
     if (n_ent > 0)
         k_fill_incidence<<<blocks_for(n_ent, kThreads), kThreads, 0, s>>>(conn, n_el, nen, inc_ptr, cursor, inc);
-    if (n_nodes > 0)
-        k_node_neighbours<<<blocks_for(n_nodes, kThreads), kThreads, 0, s>>>(
-            conn, n_el, nen, n_nodes, inc_ptr, inc, deg, nullptr, nullptr, flag);
+    k_i64_to_i32<<<blocks_for(n_nodes + 1, kThreads), kThreads, 0, s>>>(inc_ptr, n_nodes + 1, P->adj_ptr);
+    auto node_neighbours = [&](const int64_t* out_ptr, int32_t* out) {
+        const unsigned b = blocks_for(n_nodes, kThreads);
+        auto run = [&](auto k) { k<<<b, kThreads, 0, s>>>(conn, n_el, n_nodes, inc_ptr, inc, deg, out_ptr, out, flag); };
+        switch (nen) {
+            case 4: return run(k_node_neighbours<4>);
+            case 8: return run(k_node_neighbours<8>);
+            case 10: return run(k_node_neighbours<10>);
+            default: return run(k_node_neighbours<20>);
+        }
+    };
+    if (n_nodes > 0) {
+        k_sort_incidence<<<blocks_for(n_nodes, kThreads), kThreads, 0, s>>>(inc_ptr, n_nodes, inc);
+        node_neighbours(nullptr, nullptr);
+        k_max_i32<<<(unsigned)std::min<int64_t>(256, blocks_for(n_nodes, kThreads)), kThreads, 0, s>>>(deg, n_nodes,
+                                                                                                      max_deg);
+    }
     MF_HIP(hipGetLastError());
     MF_TRY(exclusive_scan<int32_t>(deg, n_nodes, nbr_ptr64, s));
     MF_HIP(hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, s));
+    MF_HIP(hipMemcpyAsync(&P->max_deg, max_deg, sizeof(int), hipMemcpyDeviceToHost, s));
     int64_t n_pairs = 0;
     MF_HIP(hipMemcpyAsync(&n_pairs, nbr_ptr64 + n_nodes, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     MF_HIP(hipStreamSynchronize(s));
@@ -372,12 +437,11 @@ mf_status build_pattern(mf_pattern_s* P, const int32_t* conn_in, hipStream_t s)
     MF_HIP(hipMalloc(&P->row_ptr, sizeof(int32_t) * (size_t)(P->n_rows + 1)));
     MF_HIP(hipMalloc(&P->col_idx, sizeof(int32_t) * (size_t)(nnz > 0 ? nnz : 1)));
     MF_HIP(hipMalloc(&P->rank, (size_t)(nen * nen * (n_el > 0 ? n_el : 1))));
+    MF_HIP(hipMalloc(&P->rank_t, (size_t)(nen * nen * (n_el > 0 ? n_el : 1))));
     MF_HIP(hipMalloc(&P->status, 3 * sizeof(unsigned long long)));  // bad element, bad face, non-finite element
 
     k_i64_to_i32<<<blocks_for(n_nodes + 1, kThreads), kThreads, 0, s>>>(nbr_ptr64, n_nodes + 1, P->nbr_ptr);
-    if (n_nodes > 0)
-        k_node_neighbours<<<blocks_for(n_nodes, kThreads), kThreads, 0, s>>>(
-            conn, n_el, nen, n_nodes, inc_ptr, inc, deg, nbr_ptr64, P->nbr, flag);
+    if (n_nodes > 0) node_neighbours(nbr_ptr64, P->nbr);
     int fm = P->numbering == MF_FIELD_MAJOR ? 1 : 0;
     if (n_nodes > 0) {
         k_row_ptr<<<blocks_for(n_nodes, kThreads), kThreads, 0, s>>>(nbr_ptr64, n_nodes, n_pairs, ft, fm,
@@ -387,9 +451,16 @@ mf_status build_pattern(mf_pattern_s* P, const int32_t* conn_in, hipStream_t s)
     } else {
         k_fill_i32<<<1, 1, 0, s>>>(P->row_ptr, 1, 0);
     }
-    if (n_el > 0)
-        k_rank<<<blocks_for(n_el * nen * nen, kThreads), kThreads, 0, s>>>(conn, n_el, nen, nbr_ptr64,
-                                                                           P->nbr, P->rank);
+    if (n_el > 0) {
+        const dim3 b(blocks_for(n_el, kThreads), nen);
+        auto run = [&](auto k) { k<<<b, kThreads, 0, s>>>(conn, n_el, nbr_ptr64, P->nbr, P->rank, P->rank_t); };
+        switch (nen) {
+            case 4: run(k_rank<4>); break;
+            case 8: run(k_rank<8>); break;
+            case 10: run(k_rank<10>); break;
+            default: run(k_rank<20>);
+        }
+    }
     MF_HIP(hipGetLastError());
 
     // structured-grid detection from the first element's nodes
@@ -434,10 +505,15 @@ mf_status build_pattern(mf_pattern_s* P, const int32_t* conn_in, hipStream_t s)
 // Greedy colouring of the elements in id order: each element takes the smallest colour
 // not used by an element that shares one of its nodes.  Host work over the node-element
 // incidence, once per pattern; elements are then listed colour by colour on the device.
-mf_status ensure_coloring(const mf_pattern_s* Pc, hipStream_t s)
+mf_status ensure_coloring(const mf_pattern_s* Pc)
 {
     mf_pattern_s* P = const_cast<mf_pattern_s*>(Pc);
     if (P->color_elems || P->n_elems == 0) return MF_OK;
+    // copies on a stream of its own: the caller's may be in capture (conn is complete since the
+    // pattern was made)
+    SideStream side;
+    MF_HIP(side.status);
+    const hipStream_t s = side.s;
     const int64_t n_el = P->n_elems, nn = P->n_nodes;
     const int nen = P->nen;
     std::vector<int32_t> conn((size_t)(n_el * nen));
