@@ -239,9 +239,9 @@ mf_status mf_assemble_ex(const mf_pattern_t* P, const mf_form* form, const doubl
     if (st != MF_OK) return st;
     bool gathered = false;
     if (P->order == 2) {
-        st = assemble_quadratic(A);
+        st = assemble_quadratic(A, &gathered);
         if (st != MF_OK) return st;
-        return apply_dirichlet(A);
+        return gathered ? MF_OK : apply_dirichlet(A);
     }
     // AUTO and GATHER on 8-node bricks: the owner-computes rows, on any mesh.  Without a
     // workspace (no memory for it) and in 2D: the column kernel on structured grids, else (and
@@ -257,7 +257,7 @@ mf_status mf_assemble_ex(const mf_pattern_t* P, const mf_form* form, const doubl
     // (geometry once per element), the other forms one thread per (element, row)
     auto coloured = [&]() -> mf_status {
         if (form->kind == MF_FORM_NS_SUPG && P->dim == 3) {
-            mf_status s2 = assemble_quadratic(A);
+            mf_status s2 = assemble_quadratic(A, &gathered);
             if (s2 != MF_ERR_UNSUPPORTED) return s2;
         }
         return assemble_atomic(A, true);

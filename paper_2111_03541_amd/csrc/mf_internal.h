@@ -136,8 +136,8 @@ mf_status assemble_atomic(const AssembleArgs& a, bool coloured);
 // no error recorded) for any other mesh.
 mf_status assemble_small(const AssembleArgs& a);
 // assemble_quadratic.hip: the quadratic elements, and the flow form on 8-node bricks where it
-// goes colour by colour
-mf_status assemble_quadratic(const AssembleArgs& a);
+// goes colour by colour; *eliminated: the Dirichlet elimination is done
+mf_status assemble_quadratic(const AssembleArgs& a, bool* eliminated);
 mf_status assemble_column(const AssembleArgs& a);
 // assemble_rows.hip: owner-computes rows on any mesh of 8-node bricks, from element records
 // in the pattern's workspace; applies the Dirichlet elimination.  MF_ERR_UNSUPPORTED (nothing
