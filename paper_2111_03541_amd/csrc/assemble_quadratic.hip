@@ -552,9 +552,9 @@ __global__ void __launch_bounds__((Cfg<ET, FORM>::THREADS), (q2_min_blocks<ET, F
 // v_mfma_f64_16x16x4_f64.  Rows and columns take the same operand register (lane l holds row
 // l % 16, summand l / 16), so a lane forms ceil(rows / 16) * ceil(sum / 4) values once, and
 // the products need no LDS.  Elasticity on 24^3 20-node bricks FP64: 114 us, 401 MB of blocks
-// (3.5 TB/s), with the gather 300 where the coloured vector kernel took 930; conduction on 82944
+// (3.5 TB/s), with the gather 300 where the coloured vector kernel took 930; conduction on 15288
 // 10-node tetrahedra: 73 us, bound by the table reads (LDS) of the 64 points, with the gather 97
-// where the coloured kernel took 1100.
+// where 30 launches of the coloured kernel took 441.
 using d4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
 
 template <int ET, int FORM>

@@ -540,7 +540,7 @@ __device__ __forceinline__ void brick_flag(const BrickParams& p, int64_t e, bool
 // sums row a over the points; the rows leave through LDS as whole lines.  Conduction 64^3 FP64:
 // 63 us, of which 151 MB of stores take 23; the rest is the FP64 geometry and two barriers, with
 // five waves per SIMD to hide them.  With the gather 118 us, where the column kernel, which
-// forms each element in up to 8 workgroups' halos, took 255.
+// forms the elements between two columns in both, took 272.
 template <int FORM, typename T>
 __global__ void __launch_bounds__(8 * kBE, 5) k_brick_scalar(BrickParams p)
 {
@@ -914,8 +914,8 @@ __device__ __forceinline__ void point_flow_tail(const mf_form& fm, int q, const 
 // in registers, adds them to the node's row buffer in LDS, and the rows of the wave's nodes
 // leave as one contiguous run.  Two waves per SIMD (the node blocks take half the registers),
 // the next point's record is in flight during the products of the present one.  Elasticity 64^3
-// FP64: 260 us, VALU busy 48 %; with k_brick_points 318 us, the column kernel 356 and the coloured
-// scatter on a renumbered mesh 1600.  Flow 48^3 FP64: 385 + 76 us, the coloured kernel 1540.
+// FP64: 260 us, VALU busy 48 %; with k_brick_points 318 us, the column kernel 356; 41x40x37 renumbered
+// bricks 333 us, the coloured scatter 1600.  Flow 48^3 FP64: 385 + 76 us, the coloured kernel 1540.
 // FP32 builds sum in FP64 too: without packed math the rates are the same.
 template <int FORM, typename T, bool FM>
 __global__ void __launch_bounds__(256, (Rec<FORM>::WG)) k_brick_rows(RowParams p)

@@ -5,24 +5,22 @@
 // reading of the domain forms: R = -d_paper for the thermal and elastic physics,
 // R = +d_paper for the flow, K = dR/dU, exported d = -R(U).
 //
-// 8-node hexahedra (all forms): one thread per (element, element node a, field i), one
-// launch per element colour.  The faces are first marked per element (a bit per listed
-// local face and its count); a thread of an element with listed faces loops over them,
-// integrates the 2x2 Gauss rule of each face (xi_axis = -1 or +1) with the element's
-// trilinear map in FP64 (surface measure |t_u x t_v|, outward unit normal, and for the
-// flux term the volume gradients J^-T grad_xi N_b), and accumulates row (a, i) of the
-// face tangent and residual.  The row nodes of a face are its four nodes, or every node
-// of the element for the flow forms, whose inflow and fix terms carry the test gradient.
-// Elements of one colour share no node, so each row is added by a single thread of the
-// launch with plain stores through the element-to-nonzero rank map, and the colours run
-// in stream order: the sums are the same on every run, with no host synchronisation.
+// Penalty, convection, radiation, traction and flux go in two steps:
+//   rows    one thread per (listed face, row node of the face, field) integrates its row
+//           (a, i) of the face tangent and residual with the face rule and stores it in
+//           the pattern's workspace;
+//   gather  one wave per node of a listed face adds the rows of the faces around the node
+//           (its incidence list, faces in local order) in LDS, and then each value of K and
+//           d is read, added to and written once.
+// A marking pass finds the distinct faces (a face listed n times counts n times) and their
+// nodes.  No atomics on K and nothing ordered by them, so the sums are the same on every
+// run, and nothing waits on the host.
 //
-// 20-node hexahedra, 10-node tetrahedra and quadrilateral edges: one thread per (face,
-// row node, field), atomics through the rank map, with the faces in buckets keyed by
-// (colour of the face's element, local face), one launch per bucket in key order.
-// Within a bucket every value of K and d receives contributions of one face only (or of
-// identical copies of it, when a face is listed twice): again run-to-run identical sums;
-// the call synchronises once to size the buckets.
+// The flow forms on 8-node hexahedra carry the test gradient: all eight nodes get rows of
+// four fields, 8 kB per face.  They go element by element, one launch per element colour:
+// elements of one colour share no node, so each row is added by a single thread of the launch
+// with plain stores.  The other forms on these elements go the same way when there is no memory
+// for a workspace.
 //
 // A face whose element id or local face is out of range is skipped and its index
 // recorded in the pattern's second status word.
@@ -56,15 +54,147 @@ struct BParams {
     void* K;
     void* d;
     unsigned long long* status;
-    // faces of this launch: order[f_begin + k] for k < n_faces (one colour bucket)
-    const int32_t* order;
-    int64_t f_begin;
-    // 8-node hexahedra: per element, the listed local faces (bit fid) and their counts
+    // colour by colour: per element, the listed local faces (bit fid); both ways: how often
+    // each local face is listed
     const uint32_t* face_mask;  // [n_el]
-    const uint32_t* face_cnt;   // [n_el][6]
+    const uint32_t* face_cnt;   // [n_el][local faces]
+    // rows and gather: distinct faces (element * local faces + local face) and their number,
+    // and the rows [face][row node][field][columns + 1], the residual entry last
+    const int32_t* list;
+    const uint32_t* n_list;
+    double* rows;
 };
 
-__device__ __forceinline__ int64_t face_of(const BParams& p, int64_t k) { return p.order[p.f_begin + k]; }
+// Local faces (edges in 2D) of an element type: their nodes in ascending local order, and a
+// node's position among them (-1: not on the face).
+template <int NEN>
+struct FaceTable {
+    static constexpr int NLOC = NEN == 8 || NEN == 20 ? 6 : 4;
+    static constexpr int NFN = NEN == 20 ? 8 : NEN == 10 ? 6 : 4;
+    int8_t node[NLOC][NFN];
+    int8_t at[NLOC][NEN];
+    constexpr FaceTable() : node{}, at{}
+    {
+        for (int f = 0; f < NLOC; ++f) {
+            int n = 0;
+            for (int a = 0; a < NEN; ++a) {
+                bool on = false;
+                if (NEN == 10) {  // face k: the vertices but k, and the edges without vertex k
+                    constexpr int EI[6] = {0, 1, 2, 0, 1, 2}, EJ[6] = {1, 2, 0, 3, 3, 3};
+                    on = a < 4 ? a != f : EI[a - 4] != f && EJ[a - 4] != f;
+                } else {
+                    const int axis = f >> 1, side = f & 1;
+                    if (a < 8) {
+                        on = ((a >> axis) & 1) == side;
+                    } else {  // midpoint of an edge along ax, at the bits of the other two axes
+                        const int ax = (a - 8) >> 2, k = (a - 8) & 3, o0 = ax == 0 ? 1 : 0;
+                        on = ax != axis && (axis == o0 ? (k & 1) : (k >> 1)) == side;
+                    }
+                }
+                at[f][a] = on ? (int8_t)n : (int8_t)-1;
+                if (on) node[f][n++] = (int8_t)a;
+            }
+        }
+    }
+};
+// edges of the 4- and 8-node quadrilaterals
+template <int NEN>
+struct EdgeTable {
+    static constexpr int NLOC = 4, NFN = NEN == 8 ? 3 : 2;
+    int8_t node[NLOC][NFN];
+    int8_t at[NLOC][NEN];
+    constexpr EdgeTable() : node{}, at{}
+    {
+        for (int f = 0; f < NLOC; ++f) {
+            const int axis = f >> 1, side = f & 1;
+            int n = 0;
+            for (int a = 0; a < NEN; ++a) {
+                const bool on = a < 4 ? ((a >> axis) & 1) == side : a == (axis == 0 ? 6 + side : 4 + side);
+                at[f][a] = on ? (int8_t)n : (int8_t)-1;
+                if (on) node[f][n++] = (int8_t)a;
+            }
+        }
+    }
+};
+__constant__ constexpr FaceTable<8> kFaces8{};
+__constant__ constexpr FaceTable<20> kFaces20{};
+__constant__ constexpr FaceTable<10> kFaces10{};
+__constant__ constexpr EdgeTable<4> kEdges4{};
+__constant__ constexpr EdgeTable<8> kEdges8{};
+
+// Per element type: its table, and the columns of a face's rows (8-node hexahedra: all nodes of
+// the element, as the flux form needs them; else the nodes of the face).
+template <int DIM, int NEN>
+struct Faces;
+template <>
+struct Faces<3, 8> {
+    static constexpr int NLOC = 6, NFN = 4, COLS = 8;
+    static __device__ __forceinline__ int at(int f, int a) { return kFaces8.at[f][a]; }
+    static __device__ __forceinline__ int node(int f, int k) { return kFaces8.node[f][k]; }
+    static __device__ __forceinline__ int col(int f, int b) { return b; }
+};
+template <>
+struct Faces<3, 20> {
+    static constexpr int NLOC = 6, NFN = 8, COLS = 8;
+    static __device__ __forceinline__ int at(int f, int a) { return kFaces20.at[f][a]; }
+    static __device__ __forceinline__ int node(int f, int k) { return kFaces20.node[f][k]; }
+    static __device__ __forceinline__ int col(int f, int b) { return kFaces20.node[f][b]; }
+};
+template <>
+struct Faces<3, 10> {
+    static constexpr int NLOC = 4, NFN = 6, COLS = 6;
+    static __device__ __forceinline__ int at(int f, int a) { return kFaces10.at[f][a]; }
+    static __device__ __forceinline__ int node(int f, int k) { return kFaces10.node[f][k]; }
+    static __device__ __forceinline__ int col(int f, int b) { return kFaces10.node[f][b]; }
+};
+template <>
+struct Faces<2, 4> {
+    static constexpr int NLOC = 4, NFN = 2, COLS = 2;
+    static __device__ __forceinline__ int at(int f, int a) { return kEdges4.at[f][a]; }
+    static __device__ __forceinline__ int node(int f, int k) { return kEdges4.node[f][k]; }
+    static __device__ __forceinline__ int col(int f, int b) { return kEdges4.node[f][b]; }
+};
+template <>
+struct Faces<2, 8> {
+    static constexpr int NLOC = 4, NFN = 3, COLS = 3;
+    static __device__ __forceinline__ int at(int f, int a) { return kEdges8.at[f][a]; }
+    static __device__ __forceinline__ int node(int f, int k) { return kEdges8.node[f][k]; }
+    static __device__ __forceinline__ int col(int f, int b) { return kEdges8.node[f][b]; }
+};
+
+// One thread of the row kernels: its face (index in the list), element, local face, row node
+// (position on the face), field, and how often the face is listed.
+struct RowItem {
+    int64_t slot, e;
+    int fid, k, i;
+    double mult;
+    bool live;
+};
+template <class F, int NF>
+__device__ __forceinline__ RowItem row_item(const BParams& p)
+{
+    RowItem r{};
+    const int64_t n = *p.n_list, t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    r.live = t < n * F::NFN * NF;
+    if (!r.live) return r;
+    r.slot = t % n;
+    const int ki = (int)(t / n);
+    r.k = ki / NF;
+    r.i = ki % NF;
+    const int key = p.list[r.slot];
+    r.e = key / F::NLOC;
+    r.fid = key % F::NLOC;
+    r.mult = (double)p.face_cnt[key];
+    return r;
+}
+template <class F, int NF>
+__device__ __forceinline__ void store_row(const BParams& p, const RowItem& r, const double (&krow)[F::COLS], double rrow)
+{
+    double* out = p.rows + ((r.slot * F::NFN + r.k) * NF + r.i) * (F::COLS + 1);
+#pragma unroll
+    for (int b = 0; b < F::COLS; ++b) out[b] = r.mult * krow[b];
+    out[F::COLS] = -r.mult * rrow;
+}
 
 __device__ __forceinline__ double lin1(int s, double xi) { return 0.5 * (1.0 + (s ? xi : -xi)); }
 
@@ -89,56 +219,24 @@ __device__ __forceinline__ bool inverse_jacobian(const double (&J)[3][3], double
     return true;
 }
 
-// row nodes per face: the flow forms (four fields) take every node of the element
-// Row (a, i) of element e over the listed faces of e (local faces in `fmask`, each
-// counted cnt[6 e + fid] times), for 8-node hexahedra.  FI >= 0 fixes the field at compile
-// time (the flow forms, so that every per-field array index is static); FI < 0 takes the
-// runtime field fi, and then only field fi of the state and target and the (a, fi) x
-// (b, fi) block are held.  The caller runs one element colour per launch: no other
-// thread of the launch touches row a, so the row is added with plain stores.
+// Row (a, i) of one face (local face fid) of an 8-node hexahedron by the 2x2 Gauss rule,
+// times mult, added to krow and rrow.  FI >= 0 fixes the field at compile time (the flow forms,
+// so that every per-field array index is static); FI < 0 takes the runtime field fi, and then
+// only field fi of the state and target and the (a, fi) x (b, fi) block are held.  Returns false
+// (status set) on a degenerate face or element.
 template <int NF, int FI, typename T>
-__device__ __forceinline__ void boundary_row(const BParams& p, int64_t e, uint32_t fmask, int a, int fi)
+__device__ __forceinline__ bool face_integral(const BParams& p, int64_t e, int fid, double mult, int a, int fi,
+                                              const double (&x)[8][3], const double (&U)[8][NF == 4 ? 4 : 1],
+                                              const double (&G)[8][NF == 4 ? 4 : 1],
+                                              double (&krow)[8][NF == 4 ? 4 : 1], double& rrow)
 {
     const int i = FI >= 0 ? FI : fi;
-
-    // fields of the state and target held: all four for the flow forms, else the
-    // thread's own field i (slot li)
     constexpr int NL = NF == 4 ? 4 : 1;
     const int li = NL == 1 ? 0 : i;
-    int32_t node[8];
-    double x[8][3];
-    double U[8][NL], G[8][NL];
-    const T* st = (const T*)p.state;
     const T* tg = (const T*)p.target;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        node[b] = p.conn[(int64_t)b * p.n_el + e];
-#pragma unroll
-        for (int m = 0; m < 3; ++m) x[b][m] = p.coords[(int64_t)m * p.n_nodes + node[b]];
-#pragma unroll
-        for (int l = 0; l < NL; ++l) {
-            const int j = NL == 1 ? i : l;
-            U[b][l] = st ? (double)st[(int64_t)j * p.n_nodes + node[b]] : 0.0;
-            G[b][l] = tg ? (double)tg[(int64_t)j * p.n_nodes + node[b]] : p.form.value[j];
-        }
-    }
     const mf_bform_kind kind = p.form.kind;
     const double c = p.form.coef;
-    constexpr int KC = NL;  // columns held per node: all fields, or field i alone (slot li)
-    double krow[8][KC];
-#pragma unroll
-    for (int b = 0; b < 8; ++b)
-#pragma unroll
-        for (int j = 0; j < KC; ++j) krow[b][j] = 0.0;
-    double rrow = 0.0;
-
-    for (int fid = 0; fid < 6; ++fid) {
-    if (!((fmask >> fid) & 1)) continue;
     const int axis = fid >> 1, side = fid & 1;
-    // the row nodes of a face are its four nodes (every node of the element for the
-    // flow forms, whose terms carry the test gradient)
-    if (NF != 4 && ((a >> axis) & 1) != side) continue;
-    const double mult = (double)p.face_cnt[6 * e + fid];
     const int u = (axis + 1) % 3, v = (axis + 2) % 3;
     for (int q = 0; q < 4; ++q) {
         double xi[3];
@@ -169,7 +267,7 @@ __device__ __forceinline__ void boundary_row(const BParams& p, int64_t e, uint32
         const double dS = sqrt(nr[0] * nr[0] + nr[1] * nr[1] + nr[2] * nr[2]);
         if (!(dS > 0.0)) {
             atomicMin(p.status, (unsigned long long)e);
-            return;
+            return false;
         }
         const double nv[3] = {nr[0] / dS, nr[1] / dS, nr[2] / dS};
         const double w = mult * dS;  // unit Gauss weights on [-1, 1]^2, times the face's count
@@ -190,7 +288,7 @@ __device__ __forceinline__ void boundary_row(const BParams& p, int64_t e, uint32
             double Ji[3][3];
             if (!inverse_jacobian(J, Ji)) {
                 atomicMin(p.status, (unsigned long long)e);
-                return;
+                return false;
             }
             double gn[8];  // n . grad N_b
 #pragma unroll
@@ -257,7 +355,7 @@ __device__ __forceinline__ void boundary_row(const BParams& p, int64_t e, uint32
             double Ji[3][3];
             if (!inverse_jacobian(J, Ji)) {
                 atomicMin(p.status, (unsigned long long)e);
-                return;
+                return false;
             }
             double ngT = 0.0;
 #pragma unroll
@@ -272,6 +370,76 @@ __device__ __forceinline__ void boundary_row(const BParams& p, int64_t e, uint32
             rrow -= c * w * Na * ngT;
         }
     }
+    return true;
+}
+
+// Coordinates of the element's nodes, and the state and target there: all four fields for the
+// flow forms, else field i alone.
+template <int NF, typename T>
+__device__ __forceinline__ void load_element(const BParams& p, int64_t e, int i, int32_t (&node)[8], double (&x)[8][3],
+                                             double (&U)[8][NF == 4 ? 4 : 1], double (&G)[8][NF == 4 ? 4 : 1])
+{
+    constexpr int NL = NF == 4 ? 4 : 1;
+    const T* st = (const T*)p.state;
+    const T* tg = (const T*)p.target;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        node[b] = p.conn[(int64_t)b * p.n_el + e];
+#pragma unroll
+        for (int m = 0; m < 3; ++m) x[b][m] = p.coords[(int64_t)m * p.n_nodes + node[b]];
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+            const int j = NL == 1 ? i : l;
+            U[b][l] = st ? (double)st[(int64_t)j * p.n_nodes + node[b]] : 0.0;
+            G[b][l] = tg ? (double)tg[(int64_t)j * p.n_nodes + node[b]] : p.form.value[j];
+        }
+    }
+}
+
+// Rows of the listed faces of 8-node hexahedra (penalty, convection, radiation, traction, flux).
+template <int NF, typename T>
+__global__ void __launch_bounds__(kThreads) k_face_rows8(BParams p)
+{
+    using F = Faces<3, 8>;
+    const RowItem r = row_item<F, NF>(p);
+    if (!r.live) return;
+    int32_t node[8];
+    double x[8][3], U[8][1], G[8][1], krow[8][1], out[8], rrow = 0.0;
+    load_element<NF, T>(p, r.e, r.i, node, x, U, G);
+#pragma unroll
+    for (int b = 0; b < 8; ++b) krow[b][0] = 0.0;
+    const bool ok = face_integral<NF, -1, T>(p, r.e, r.fid, 1.0, F::node(r.fid, r.k), r.i, x, U, G, krow, rrow);
+#pragma unroll
+    for (int b = 0; b < 8; ++b) out[b] = ok ? krow[b][0] : 0.0;
+    store_row<F, NF>(p, r, out, ok ? rrow : 0.0);
+}
+
+// Row (a, i) of element e over the listed faces of e (local faces in `fmask`, each
+// counted cnt[6 e + fid] times), for 8-node hexahedra.  The caller runs one element colour
+// per launch: no other thread of the launch touches row a, so the row is added with plain
+// stores.
+template <int NF, int FI, typename T>
+__device__ __forceinline__ void boundary_row(const BParams& p, int64_t e, uint32_t fmask, int a, int fi)
+{
+    const int i = FI >= 0 ? FI : fi;
+    constexpr int NL = NF == 4 ? 4 : 1;
+    int32_t node[8];
+    double x[8][3];
+    double U[8][NL], G[8][NL];
+    load_element<NF, T>(p, e, i, node, x, U, G);
+    constexpr int KC = NL;  // columns held per node: all fields, or field i alone (slot 0)
+    double krow[8][KC];
+#pragma unroll
+    for (int b = 0; b < 8; ++b)
+#pragma unroll
+        for (int j = 0; j < KC; ++j) krow[b][j] = 0.0;
+    double rrow = 0.0;
+    for (int fid = 0; fid < 6; ++fid) {
+        if (!((fmask >> fid) & 1)) continue;
+        // the row nodes of a face are its four nodes (every node of the element for the
+        // flow forms, whose terms carry the test gradient)
+        if (NF != 4 && ((a >> (fid >> 1)) & 1) != (fid & 1)) continue;
+        if (!face_integral<NF, FI, T>(p, e, fid, (double)p.face_cnt[6 * e + fid], a, fi, x, U, G, krow, rrow)) return;
     }
 
     const int64_t va = node[a];
@@ -339,24 +507,18 @@ __global__ void __launch_bounds__(kThreads) k_boundary(BParams p, const int32_t*
 // tangential derivatives) and the 3x3 Gauss rule of the face; penalty, convection,
 // radiation and traction as above.
 template <int NF, typename T>
-__global__ void __launch_bounds__(kThreads) k_boundary20(BParams p)
+__global__ void __launch_bounds__(kThreads) k_face_rows20(BParams p)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= p.n_faces * 8 * NF) return;
-    const int64_t f = face_of(p, t % p.n_faces);
-    const int ki = (int)(t / p.n_faces);
-    const int kf = ki / NF, i = ki % NF;
-    const int64_t e = p.face_elem[f];
-    const int fid = p.face_id[f];
-    if (e < 0 || e >= p.n_el || fid > 5) {
-        if (ki == 0) atomicMin(p.status + 1, (unsigned long long)f);
-        return;
-    }
-    const int axis = fid >> 1, side = fid & 1;
+    using F = Faces<3, 20>;
+    const RowItem r = row_item<F, NF>(p);
+    if (!r.live) return;
+    const int64_t e = r.e;
+    const int i = r.i;
+    const int kf = r.k, axis = r.fid >> 1, side = r.fid & 1;
     const int u = (axis + 1) % 3, v = (axis + 2) % 3;
     int loc[8];  // local ids of the face nodes, ascending
-    for (int a = 0, k = 0; a < 20; ++a)
-        if (on_face20(a, axis, side)) loc[k++] = a;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) loc[b] = F::node(r.fid, b);
     double x[8][3], U[8], G[8];  // coordinates, and field i of the state and target
     int32_t node[8];
     const T* st = (const T*)p.state;
@@ -400,6 +562,8 @@ __global__ void __launch_bounds__(kThreads) k_boundary20(BParams p)
         const double dS = sqrt(nr[0] * nr[0] + nr[1] * nr[1] + nr[2] * nr[2]);
         if (!(dS > 0.0)) {
             atomicMin(p.status, (unsigned long long)e);
+            double none[F::COLS] = {};
+            store_row<F, NF>(p, r, none, 0.0);
             return;
         }
         const double w = wq * dS;
@@ -424,21 +588,7 @@ __global__ void __launch_bounds__(kThreads) k_boundary20(BParams p)
             rrow -= w * Na * ti;
         }
     }
-    const int a = loc[kf];
-    const int64_t va = node[kf];
-    const int64_t row = p.field_major ? (int64_t)i * p.n_nodes + va : (int64_t)NF * va + i;
-    const int64_t rs = p.row_ptr[row];
-    const int64_t deg = p.nbr_ptr[va + 1] - p.nbr_ptr[va];
-    T* K = (T*)p.K;
-    T* d = (T*)p.d;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        if (krow[b] == 0.0) continue;
-        const int64_t rk = p.rank[(int64_t)(a * 20 + loc[b]) * p.n_el + e];
-        const int64_t pos = p.field_major ? rs + i * deg + rk : rs + rk * NF + i;
-        unsafeAtomicAdd(K + pos, (T)krow[b]);
-    }
-    if (rrow != 0.0) unsafeAtomicAdd(d + row, (T)(-rrow));
+    store_row<F, NF>(p, r, krow, rrow);
 }
 
 // Faces of 10-node tetrahedra: one thread per (face f, face node m, field i).  Face k is
@@ -447,27 +597,18 @@ __global__ void __launch_bounds__(kThreads) k_boundary20(BParams p)
 // integrated with the collapsed 4 x 4 Gauss rule of the triangle; the normal points away
 // from vertex k.  Penalty, convection, radiation and traction as above.
 template <int NF, typename T>
-__global__ void __launch_bounds__(kThreads) k_boundary_tet10(BParams p)
+__global__ void __launch_bounds__(kThreads) k_face_rows10(BParams p)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= p.n_faces * 6 * NF) return;
-    const int64_t f = face_of(p, t % p.n_faces);
-    const int ki = (int)(t / p.n_faces);
-    const int mf = ki / NF, i = ki % NF;
-    const int64_t e = p.face_elem[f];
-    const int k = p.face_id[f];
-    if (e < 0 || e >= p.n_el || k > 3) {
-        if (ki == 0) atomicMin(p.status + 1, (unsigned long long)f);
-        return;
-    }
-    // face nodes: the vertices other than k, then the edges among them (local ids 4..9 are
-    // the edges (0,1), (1,2), (2,0), (0,3), (1,3), (2,3))
-    constexpr int EI[6] = {0, 1, 2, 0, 1, 2}, EJ[6] = {1, 2, 0, 3, 3, 3};
+    using F = Faces<3, 10>;
+    const RowItem r = row_item<F, NF>(p);
+    if (!r.live) return;
+    const int64_t e = r.e;
+    const int i = r.i;
+    const int mf = r.k, k = r.fid;
+    // face nodes: the vertices other than k, then the edges among them
     int loc[6];
-    for (int v = 0, c = 0; v < 4; ++v)
-        if (v != k) loc[c++] = v;
-    for (int m = 0, c = 3; m < 6; ++m)
-        if (EI[m] != k && EJ[m] != k) loc[c++] = 4 + m;
+#pragma unroll
+    for (int b = 0; b < 6; ++b) loc[b] = F::node(k, b);
     double pv[3][3];  // reference coordinates of the face vertices
 #pragma unroll
     for (int c = 0; c < 3; ++c)
@@ -532,6 +673,8 @@ __global__ void __launch_bounds__(kThreads) k_boundary_tet10(BParams p)
         const double dS = sqrt(nr[0] * nr[0] + nr[1] * nr[1] + nr[2] * nr[2]);
         if (!(dS > 0.0)) {
             atomicMin(p.status, (unsigned long long)e);
+            double none[F::COLS] = {};
+            store_row<F, NF>(p, r, none, 0.0);
             return;
         }
         const double w = wq * dS;
@@ -556,21 +699,7 @@ __global__ void __launch_bounds__(kThreads) k_boundary_tet10(BParams p)
             rrow -= w * Na * ti;
         }
     }
-    const int a = loc[mf];
-    const int64_t va = node[mf];
-    const int64_t row = p.field_major ? (int64_t)i * p.n_nodes + va : (int64_t)NF * va + i;
-    const int64_t rs = p.row_ptr[row];
-    const int64_t deg = p.nbr_ptr[va + 1] - p.nbr_ptr[va];
-    T* K = (T*)p.K;
-    T* d = (T*)p.d;
-#pragma unroll
-    for (int b = 0; b < 6; ++b) {
-        if (krow[b] == 0.0) continue;
-        const int64_t rk = p.rank[(int64_t)(a * 10 + loc[b]) * p.n_el + e];
-        const int64_t pos = p.field_major ? rs + i * deg + rk : rs + rk * NF + i;
-        unsafeAtomicAdd(K + pos, (T)krow[b]);
-    }
-    if (rrow != 0.0) unsafeAtomicAdd(d + row, (T)(-rrow));
+    store_row<F, NF>(p, r, krow, rrow);
 }
 
 // Edges of quadrilaterals (NEN = 4 or 8): one thread per (edge, edge node, field).  Edge
@@ -579,25 +708,18 @@ __global__ void __launch_bounds__(kThreads) k_boundary_tet10(BParams p)
 // the unit normal pointing away from the element's centre.  Penalty, convection,
 // radiation and traction (sigma^l: the leading 2x2 block of value, or a nodal target).
 template <int NEN, int NF, typename T>
-__global__ void __launch_bounds__(kThreads) k_boundary_2d(BParams p)
+__global__ void __launch_bounds__(kThreads) k_edge_rows(BParams p)
 {
-    constexpr int NE = NEN == 8 ? 3 : 2;  // nodes per edge, and Gauss points
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= p.n_faces * NE * NF) return;
-    const int64_t f = face_of(p, t % p.n_faces);
-    const int ki = (int)(t / p.n_faces);
-    const int me = ki / NF, i = ki % NF;
-    const int64_t e = p.face_elem[f];
-    const int eid = p.face_id[f];
-    if (e < 0 || e >= p.n_el || eid > 3) {
-        if (ki == 0) atomicMin(p.status + 1, (unsigned long long)f);
-        return;
-    }
-    const int axis = eid >> 1, side = eid & 1, other = 1 - axis;
-    int loc[3];
-    for (int a = 0, c = 0; a < 4; ++a)
-        if (((a >> axis) & 1) == side) loc[c++] = a;
-    if (NEN == 8) loc[2] = axis == 0 ? 6 + side : 4 + side;
+    using F = Faces<2, NEN>;
+    const RowItem r = row_item<F, NF>(p);
+    if (!r.live) return;
+    const int64_t e = r.e;
+    const int i = r.i;
+    constexpr int NE = F::NFN;  // nodes per edge, and Gauss points
+    const int me = r.k, axis = r.fid >> 1, side = r.fid & 1, other = 1 - axis;
+    int loc[NE];
+#pragma unroll
+    for (int b = 0; b < NE; ++b) loc[b] = F::node(r.fid, b);
     double x[NE][2], U[NE], G[NE], centre[2] = {0.0, 0.0};
     int32_t node[NE];
     const T* st = (const T*)p.state;
@@ -652,6 +774,8 @@ __global__ void __launch_bounds__(kThreads) k_boundary_2d(BParams p)
         const double ds = sqrt(tang[0] * tang[0] + tang[1] * tang[1]);
         if (!(ds > 0.0)) {
             atomicMin(p.status, (unsigned long long)e);
+            double none[F::COLS] = {};
+            store_row<F, NF>(p, r, none, 0.0);
             return;
         }
         double nv[2] = {tang[1] / ds, -tang[0] / ds};
@@ -681,55 +805,7 @@ __global__ void __launch_bounds__(kThreads) k_boundary_2d(BParams p)
             rrow -= w * Na * ti;
         }
     }
-    const int a = loc[me];
-    const int64_t va = node[me];
-    const int64_t row = p.field_major ? (int64_t)i * p.n_nodes + va : (int64_t)NF * va + i;
-    const int64_t rs = p.row_ptr[row];
-    const int64_t deg = p.nbr_ptr[va + 1] - p.nbr_ptr[va];
-    T* K = (T*)p.K;
-    T* d = (T*)p.d;
-#pragma unroll
-    for (int b = 0; b < NE; ++b) {
-        if (krow[b] == 0.0) continue;
-        const int64_t rk = p.rank[(int64_t)(a * NEN + loc[b]) * p.n_el + e];
-        const int64_t pos = p.field_major ? rs + i * deg + rk : rs + rk * NF + i;
-        unsafeAtomicAdd(K + pos, (T)krow[b]);
-    }
-    if (rrow != 0.0) unsafeAtomicAdd(d + row, (T)(-rrow));
-}
-
-template <int NEN, int NF, typename T>
-mf_status launch_boundary_2d(const BParams& p, hipStream_t s)
-{
-    constexpr int NE = NEN == 8 ? 3 : 2;
-    const int64_t n = p.n_faces * NE * NF;
-    if (n == 0) return MF_OK;
-    if (n > 0xffffffffLL - kThreads) return set_error(MF_ERR_ARG, "too many edges for one launch");
-    k_boundary_2d<NEN, NF, T><<<(unsigned)((n + kThreads - 1) / kThreads), kThreads, 0, s>>>(p);
-    MF_HIP(hipGetLastError());
-    return MF_OK;
-}
-
-template <int NF, typename T>
-mf_status launch_boundary_tet10(const BParams& p, hipStream_t s)
-{
-    const int64_t n = p.n_faces * 6 * NF;
-    if (n == 0) return MF_OK;
-    if (n > 0xffffffffLL - kThreads) return set_error(MF_ERR_ARG, "too many faces for one launch");
-    k_boundary_tet10<NF, T><<<(unsigned)((n + kThreads - 1) / kThreads), kThreads, 0, s>>>(p);
-    MF_HIP(hipGetLastError());
-    return MF_OK;
-}
-
-template <int NF, typename T>
-mf_status launch_boundary20(const BParams& p, hipStream_t s)
-{
-    const int64_t n = p.n_faces * 8 * NF;
-    if (n == 0) return MF_OK;
-    if (n > 0xffffffffLL - kThreads) return set_error(MF_ERR_ARG, "too many faces for one launch");
-    k_boundary20<NF, T><<<(unsigned)((n + kThreads - 1) / kThreads), kThreads, 0, s>>>(p);
-    MF_HIP(hipGetLastError());
-    return MF_OK;
+    store_row<F, NF>(p, r, krow, rrow);
 }
 
 __global__ void k_face_zero(uint32_t* __restrict__ w, int64_t n)
@@ -780,6 +856,190 @@ __global__ void k_face_mark(const int32_t* __restrict__ fe, const uint8_t* __res
     }
 }
 
+// (Conduction on 64^3 bricks, 8192 faces and 16384 faces a call, mean: clear 5 us, lists 12, rows
+// 14, gather 17; the eight colour launches took 132 and the marking 20.  15288 tetrahedra with all
+// 2240 boundary faces: 4 + 10 + 26 + 10 us, where 41 bucket launches took 1242.  Latency chains: a
+// face reads its element's nodes, their coordinates and state, then a node its incidence list,
+// counts and rows.)
+// Distinct listed faces and their nodes: cnt[element * NLOC + local face] counts a face, the
+// first to do so appends it to the list and its nodes, each once, to the node list.
+template <class F>
+__global__ void k_face_list(const int32_t* __restrict__ fe, const uint8_t* __restrict__ fid, int64_t n, int64_t n_el,
+                            const int32_t* __restrict__ conn, uint32_t* __restrict__ cnt, int32_t* __restrict__ slot,
+                            int32_t* __restrict__ list, uint32_t* __restrict__ node_on, int32_t* __restrict__ nodes,
+                            uint32_t* __restrict__ counts, unsigned long long* __restrict__ status)
+{
+    const int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = (int)(threadIdx.x & 63);
+    // one counter update per wave: the lanes that append take consecutive places
+    auto place = [&](bool take, uint32_t* counter) -> uint32_t {
+        const unsigned long long group = __ballot(take);
+        uint32_t base = 0;
+        if (lane == 0 && group) base = atomicAdd(counter, (uint32_t)__popcll(group));
+        base = (uint32_t)__shfl((int)base, 0, 64);
+        return base + (uint32_t)__popcll(group & ((1ull << lane) - 1ull));
+    };
+    int64_t e = -1;
+    int lf = 0;
+    if (f < n) {
+        e = fe[f];
+        lf = fid[f];
+        if (e < 0 || e >= n_el || lf >= F::NLOC) {
+            atomicMin(status + 1, (unsigned long long)f);
+            e = -1;
+        }
+    }
+    const int32_t key = (int32_t)(e * F::NLOC + lf);
+    const bool first = e >= 0 && atomicAdd(cnt + key, 1u) == 0u;
+    const uint32_t at = place(first, counts);
+    if (first) {
+        list[at] = key;
+        slot[key] = (int32_t)at;
+    }
+    for (int k = 0; k < F::NFN; ++k) {
+        const int32_t v = first ? conn[(int64_t)F::node(lf, k) * n_el + e] : 0;
+        const bool fresh = first && atomicExch(node_on + v, 1u) == 0u;
+        const uint32_t w = place(fresh, counts + 1);
+        if (fresh) nodes[w] = v;
+    }
+}
+
+struct FaceGather {
+    const int32_t* adj_ptr;
+    const int32_t* adj;
+    const int32_t* nbr_ptr;
+    const uint8_t* rank_t;
+    const uint32_t* cnt;
+    const int32_t* slot;
+    const int32_t* nodes;
+    const uint32_t* n_nodes_on;
+    const double* rows;
+    int64_t n_nodes, n_pairs;
+    int field_major, buf_len;
+    void* K;
+    void* d;
+};
+
+// One wave per listed node (strided over the grid): the rows of the faces around it, then its
+// values of K and d.  The (i, i) blocks only: these forms do not couple fields.
+template <int DIM, int NEN, int NF, typename T>
+__global__ void __launch_bounds__(kThreads) k_face_gather(FaceGather p)
+{
+    using F = Faces<DIM, NEN>;
+    constexpr int ROW = F::COLS + 1;
+    extern __shared__ double sh[];
+    const int lane = threadIdx.x & 63, waves = blockDim.x / 64, wave = threadIdx.x / 64;
+    double* buf = sh + wave * p.buf_len;  // [i][r], then the residual entries
+    double* dbuf = buf + p.buf_len - NF;
+    const int n = (int)*p.n_nodes_on;
+    for (int w = blockIdx.x * waves + wave; w < n; w += gridDim.x * waves) {
+        const int64_t v = p.nodes[w];
+        const int k0 = p.adj_ptr[v], k1 = p.adj_ptr[v + 1];
+        const int64_t P = p.nbr_ptr[v];
+        const int deg = p.nbr_ptr[v + 1] - (int)P;
+        for (int t = lane; t < NF * deg; t += 64) buf[t] = 0.0;
+        if (lane < NF) dbuf[lane] = 0.0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        for (int kb = k0; kb < k1; kb += 64) {
+            const int code = kb + lane < k1 ? p.adj[kb + lane] : -1;
+            const int e = code / NEN, a = code - e * NEN;
+            for (int f = 0; f < F::NLOC; ++f) {
+                const int at = code >= 0 ? F::at(f, a) : -1;
+                const bool on = at >= 0 && p.cnt[(int64_t)e * F::NLOC + f] != 0u;
+                const int mine = on ? p.slot[(int64_t)e * F::NLOC + f] * F::NFN + at : 0;
+                for (unsigned long long left = __ballot(on); left; left &= left - 1) {
+                    const int src = __ffsll((long long)left) - 1;
+                    const double* row = p.rows + (int64_t)__shfl(mine, src) * (NF * ROW);
+                    const int64_t c = __shfl(code, src);
+                    if (lane < NF * ROW) {
+                        const int i = lane / ROW, b = lane - i * ROW;
+                        const double x = row[lane];
+                        if (b < F::COLS) unsafeAtomicAdd(buf + i * deg + p.rank_t[c * NEN + F::col(f, b)], x);
+                        else unsafeAtomicAdd(dbuf + i, x);
+                    }
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        T* K = (T*)p.K;
+        T* d = (T*)p.d;
+        for (int t = lane; t < NF * deg; t += 64) {
+            const int i = t / deg, r = t - i * deg;
+            const int64_t at = p.field_major ? (int64_t)i * NF * p.n_pairs + NF * P + i * deg + r
+                                             : P * (NF * NF) + i * NF * deg + r * NF + i;
+            if (buf[t] != 0.0) K[at] = (T)((double)K[at] + buf[t]);
+        }
+        if (lane < NF && dbuf[lane] != 0.0) {
+            const int64_t row = p.field_major ? lane * p.n_nodes + v : NF * v + lane;
+            d[row] = (T)((double)d[row] + dbuf[lane]);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+}
+
+template <int DIM, int NEN, int NF, typename T>
+void launch_rows(const BParams& p, unsigned blocks, hipStream_t s)
+{
+    if constexpr (DIM == 2) k_edge_rows<NEN, NF, T><<<blocks, kThreads, 0, s>>>(p);
+    else if constexpr (NEN == 8) k_face_rows8<NF, T><<<blocks, kThreads, 0, s>>>(p);
+    else if constexpr (NEN == 20) k_face_rows20<NF, T><<<blocks, kThreads, 0, s>>>(p);
+    else k_face_rows10<NF, T><<<blocks, kThreads, 0, s>>>(p);
+}
+
+// Marking, rows and gather; *done is false (nothing launched) when no workspace can be had.
+template <int DIM, int NEN, int NF, typename T>
+mf_status launch_faces(BParams p, const mf_pattern_s* P, hipStream_t s, bool* done)
+{
+    using F = Faces<DIM, NEN>;
+    *done = true;
+    if (p.n_faces == 0 || P->n_elems == 0) return MF_OK;
+    const int64_t keys = P->n_elems * F::NLOC, most = std::min(p.n_faces, keys), nodes_most = std::min(most * F::NFN, P->n_nodes);
+    if (most * F::NFN * NF > (int64_t)0x7fffffff * kThreads) return set_error(MF_ERR_ARG, "too many faces for one launch");
+    // cnt [keys], node flags [n_nodes], two counters; slot [keys], list [most], nodes [most]; rows
+    const int64_t clear = keys + P->n_nodes + 2, words = clear + keys + most + nodes_most;
+    const size_t rows_at = (sizeof(uint32_t) * (size_t)words + 255) / 256 * 256;
+    const size_t rows = sizeof(double) * (size_t)most * F::NFN * NF * (F::COLS + 1);
+    const Workspace held(P, rows_at + rows, s);
+    char* ws = held.p;
+    *done = ws != nullptr;
+    if (!ws) return MF_OK;
+    uint32_t* cnt = (uint32_t*)ws;
+    uint32_t* node_on = cnt + keys;
+    uint32_t* counts = node_on + P->n_nodes;
+    int32_t* slot = (int32_t*)(counts + 2);
+    int32_t* list = slot + keys;
+    int32_t* nodes = list + most;
+    k_face_zero<<<(unsigned)((clear + kThreads - 1) / kThreads), kThreads, 0, s>>>(cnt, clear);
+    k_face_list<F><<<(unsigned)((p.n_faces + kThreads - 1) / kThreads), kThreads, 0, s>>>(
+        p.face_elem, p.face_id, p.n_faces, P->n_elems, P->conn, cnt, slot, list, node_on, nodes, counts, P->status);
+    p.face_cnt = cnt;
+    p.list = list;
+    p.n_list = counts;
+    p.rows = (double*)(ws + rows_at);
+    launch_rows<DIM, NEN, NF, T>(p, (unsigned)((most * F::NFN * NF + kThreads - 1) / kThreads), s);
+    FaceGather g{};
+    g.adj_ptr = P->adj_ptr;
+    g.adj = P->adj;
+    g.nbr_ptr = P->nbr_ptr;
+    g.rank_t = P->rank_t;
+    g.cnt = cnt;
+    g.slot = slot;
+    g.nodes = nodes;
+    g.n_nodes_on = counts + 1;
+    g.rows = p.rows;
+    g.n_nodes = P->n_nodes;
+    g.n_pairs = P->n_pairs;
+    g.field_major = p.field_major;
+    g.buf_len = NF * std::max(1, P->max_deg) + NF;
+    g.K = p.K;
+    g.d = p.d;
+    // at most 255 neighbours and 3 fields: 25 kB for the four waves
+    const unsigned blocks = (unsigned)std::min<int64_t>(8192, (nodes_most + 3) / 4);
+    k_face_gather<DIM, NEN, NF, T><<<blocks, kThreads, sizeof(double) * 4 * (size_t)g.buf_len, s>>>(g);
+    MF_HIP(hipGetLastError());
+    return MF_OK;
+}
+
 // 8-node hexahedra: mark the listed faces per element, then one launch per element
 // colour (elements of a colour share no node, so each row is added by one thread of the
 // launch, and the colours follow each other in the stream: the sums do not depend on
@@ -797,10 +1057,19 @@ mf_status launch_boundary(BParams p, const mf_pattern_s* Pc, hipStream_t s)
     const int64_t n_el = P->n_elems;
     const int64_t words = 8 * n_el + n_col + 2 * (n_col + 1) + 2;
     if (!P->face_elem_work) {
-        MF_HIP(hipMalloc(&P->face_elem_work, sizeof(uint32_t) * (size_t)words));
-        int64_t* cptr = (int64_t*)(P->face_elem_work + 8 * n_el + n_col + ((8 * n_el + n_col) & 1));
-        MF_HIP(hipMemcpyAsync(cptr, P->color_ptr.data(), sizeof(int64_t) * (n_col + 1), hipMemcpyHostToDevice, s));
-        MF_HIP(hipStreamSynchronize(s));
+        // on a stream of its own: the caller's may be in capture
+        SideStream side;
+        MF_HIP(side.status);
+        uint32_t* w = nullptr;
+        MF_HIP(hipMalloc(&w, sizeof(uint32_t) * (size_t)words));
+        int64_t* at = (int64_t*)(w + 8 * n_el + n_col + ((8 * n_el + n_col) & 1));
+        hipError_t err = hipMemcpyAsync(at, P->color_ptr.data(), sizeof(int64_t) * (n_col + 1), hipMemcpyHostToDevice, side.s);
+        if (err == hipSuccess) err = hipStreamSynchronize(side.s);
+        if (err != hipSuccess) {
+            (void)hipFree(w);
+            return hip_error(err, "colour offsets");
+        }
+        P->face_elem_work = w;
     }
     uint32_t* mask = P->face_elem_work;
     uint32_t* cnt = mask + n_el;
@@ -821,85 +1090,6 @@ mf_status launch_boundary(BParams p, const mf_pattern_s* Pc, hipStream_t s)
         k_boundary<NF, T><<<blocks, kThreads, 0, s>>>(p, clist + P->color_ptr[c], ccount + c);
     }
     MF_HIP(hipGetLastError());
-    return MF_OK;
-}
-
-__global__ void k_face_clear(int32_t* p, int n)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
-}
-
-// bucket of a face: colour of its element x local faces + local face; the last bucket
-// holds the faces whose element or local face is out of range (the kernels report them)
-__device__ __forceinline__ int face_key(const int32_t* fe, const uint8_t* fid, int64_t f, const int32_t* ecol,
-                                        int64_t n_el, int n_local, int n_keys)
-{
-    const int64_t e = fe[f];
-    const int lf = fid[f];
-    return (e >= 0 && e < n_el && lf < n_local) ? ecol[e] * n_local + lf : n_keys - 1;
-}
-
-__global__ void k_face_hist(const int32_t* fe, const uint8_t* fid, int64_t n, const int32_t* ecol, int64_t n_el,
-                            int n_local, int n_keys, int32_t* cnt)
-{
-    const int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (f < n) atomicAdd(cnt + face_key(fe, fid, f, ecol, n_el, n_local, n_keys), 1);
-}
-
-// cursor := exclusive scan of cnt (a few hundred buckets at most: one lane)
-__global__ void k_face_scan(const int32_t* cnt, int n_keys, int32_t* cursor)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    int32_t acc = 0;
-    for (int k = 0; k < n_keys; ++k) {
-        cursor[k] = acc;
-        acc += cnt[k];
-    }
-}
-
-__global__ void k_face_place(const int32_t* fe, const uint8_t* fid, int64_t n, const int32_t* ecol, int64_t n_el,
-                             int n_local, int n_keys, int32_t* cursor, int32_t* order)
-{
-    const int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (f < n) order[atomicAdd(cursor + face_key(fe, fid, f, ecol, n_el, n_local, n_keys), 1)] = (int32_t)f;
-}
-
-// Sorts the faces into colour buckets: order (device, in the pattern's workspace) lists
-// the faces bucket by bucket, bucket k being order[off[k] .. off[k+1]).  Synchronises the
-// stream once to read the bucket sizes.
-mf_status bucket_faces(const mf_pattern_s* Pc, int n_local, const int32_t* fe, const uint8_t* fid, int64_t n,
-                       hipStream_t s, std::vector<int64_t>& off, const int32_t*& order)
-{
-    mf_pattern_s* P = const_cast<mf_pattern_s*>(Pc);
-    mf_status st = ensure_coloring(P);
-    if (st != MF_OK) return st;
-    const int n_colors = std::max(0, (int)P->color_ptr.size() - 1);
-    const int n_keys = n_colors * n_local + 1;
-    const int64_t need = 2 * (int64_t)n_keys + n;
-    if (P->face_work_cap < need) {
-        MF_HIP(hipStreamSynchronize(s));
-        (void)hipFree(P->face_work);
-        P->face_work = nullptr;
-        P->face_work_cap = 0;
-        MF_HIP(hipMalloc(&P->face_work, sizeof(int32_t) * (size_t)need));
-        P->face_work_cap = need;
-    }
-    int32_t* cnt = P->face_work;
-    int32_t* cursor = cnt + n_keys;
-    int32_t* ord = cursor + n_keys;
-    const unsigned blocks = (unsigned)((n + kThreads - 1) / kThreads);
-    k_face_clear<<<(n_keys + kThreads - 1) / kThreads, kThreads, 0, s>>>(cnt, n_keys);
-    k_face_hist<<<blocks, kThreads, 0, s>>>(fe, fid, n, P->elem_color, P->n_elems, n_local, n_keys, cnt);
-    k_face_scan<<<1, 64, 0, s>>>(cnt, n_keys, cursor);
-    k_face_place<<<blocks, kThreads, 0, s>>>(fe, fid, n, P->elem_color, P->n_elems, n_local, n_keys, cursor, ord);
-    MF_HIP(hipGetLastError());
-    std::vector<int32_t> h((size_t)n_keys);
-    MF_HIP(hipMemcpyAsync(h.data(), cnt, sizeof(int32_t) * (size_t)n_keys, hipMemcpyDeviceToHost, s));
-    MF_HIP(hipStreamSynchronize(s));
-    off.assign((size_t)n_keys + 1, 0);
-    for (int k = 0; k < n_keys; ++k) off[(size_t)k + 1] = off[(size_t)k] + h[(size_t)k];
-    order = ord;
     return MF_OK;
 }
 
@@ -969,44 +1159,23 @@ extern "C" mf_status mf_assemble_boundary(const mf_pattern_t* P, const mf_bform*
     p.d = d;
     p.status = P->status;
     const_cast<mf_pattern_s*>(P)->last_stream = s;
-    using Launch = mf_status (*)(const BParams&, hipStream_t);
-    Launch launch = nullptr;
+    if (two_d && nf != 1 && nf != 2) return set_error(MF_ERR_ARG, "edge forms need 1 or 2 fields, pattern has %d", nf);
     const bool f64 = prec == MF_F64;
-    int n_local = 6;  // local faces (edges in 2D) per element
-    if (two_d) {
-        if (nf != 1 && nf != 2) return set_error(MF_ERR_ARG, "edge forms need 1 or 2 fields, pattern has %d", nf);
-        n_local = 4;
-        if (P->nen == 8)
-            launch = f64 ? (nf == 1 ? launch_boundary_2d<8, 1, double> : launch_boundary_2d<8, 2, double>)
-                         : (nf == 1 ? launch_boundary_2d<8, 1, float> : launch_boundary_2d<8, 2, float>);
-        else
-            launch = f64 ? (nf == 1 ? launch_boundary_2d<4, 1, double> : launch_boundary_2d<4, 2, double>)
-                         : (nf == 1 ? launch_boundary_2d<4, 1, float> : launch_boundary_2d<4, 2, float>);
-    } else if (tet) {
-        n_local = 4;
-        launch = f64 ? (nf == 1 ? launch_boundary_tet10<1, double> : launch_boundary_tet10<3, double>)
-                     : (nf == 1 ? launch_boundary_tet10<1, float> : launch_boundary_tet10<3, float>);
-    } else if (quad) {
-        launch = f64 ? (nf == 1 ? launch_boundary20<1, double> : launch_boundary20<3, double>)
-                     : (nf == 1 ? launch_boundary20<1, float> : launch_boundary20<3, float>);
-    } else {
-        // 8-node hexahedra: element by element, colour by colour (no buckets)
-        if (nf == 4) return f64 ? launch_boundary<4, double>(p, P, s) : launch_boundary<4, float>(p, P, s);
-        if (nf == 1) return f64 ? launch_boundary<1, double>(p, P, s) : launch_boundary<1, float>(p, P, s);
-        return f64 ? launch_boundary<3, double>(p, P, s) : launch_boundary<3, float>(p, P, s);
-    }
-    if (n_faces == 0) return MF_OK;
-    std::vector<int64_t> off;
-    const int32_t* order = nullptr;
-    mf_status st = bucket_faces(P, n_local, face_elem, face_id, n_faces, s, off, order);
-    if (st != MF_OK) return st;
-    p.order = order;
-    for (size_t k = 0; k + 1 < off.size(); ++k) {
-        if (off[k + 1] == off[k]) continue;
-        p.f_begin = off[k];
-        p.n_faces = off[k + 1] - off[k];
-        st = launch(p, s);
-        if (st != MF_OK) return st;
-    }
-    return MF_OK;
+    if (nf == 4) return f64 ? launch_boundary<4, double>(p, P, s) : launch_boundary<4, float>(p, P, s);
+    bool done = false;
+    auto run = [&](auto zero) -> mf_status {
+        using T = decltype(zero);
+        if (two_d && P->nen == 8)
+            return nf == 1 ? launch_faces<2, 8, 1, T>(p, P, s, &done) : launch_faces<2, 8, 2, T>(p, P, s, &done);
+        if (two_d) return nf == 1 ? launch_faces<2, 4, 1, T>(p, P, s, &done) : launch_faces<2, 4, 2, T>(p, P, s, &done);
+        if (tet) return nf == 1 ? launch_faces<3, 10, 1, T>(p, P, s, &done) : launch_faces<3, 10, 3, T>(p, P, s, &done);
+        if (quad) return nf == 1 ? launch_faces<3, 20, 1, T>(p, P, s, &done) : launch_faces<3, 20, 3, T>(p, P, s, &done);
+        return nf == 1 ? launch_faces<3, 8, 1, T>(p, P, s, &done) : launch_faces<3, 8, 3, T>(p, P, s, &done);
+    };
+    const mf_status st = f64 ? run(0.0) : run(0.0f);
+    if (st != MF_OK || done) return st;
+    if (P->nen != 8 || two_d)
+        return set_error(MF_ERR_OOM, "no memory for the boundary faces' workspace");
+    if (nf == 1) return f64 ? launch_boundary<1, double>(p, P, s) : launch_boundary<1, float>(p, P, s);
+    return f64 ? launch_boundary<3, double>(p, P, s) : launch_boundary<3, float>(p, P, s);
 }

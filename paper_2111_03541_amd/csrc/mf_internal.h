@@ -53,9 +53,6 @@ struct mf_pattern_s {
     int32_t* color_elems = nullptr;  // device [n_elems]
     int32_t* elem_color = nullptr;   // device [n_elems]: colour of each element
     std::vector<int64_t> color_ptr;
-    // boundary-face buckets (boundary.hip): device workspace, grown on demand
-    int32_t* face_work = nullptr;
-    int64_t face_work_cap = 0;
     // 8-node hexahedra, faces per element of the colour-by-colour scatter (boundary.hip): mask
     // [n_elems], counts [n_elems][6], colour lists
     uint32_t* face_elem_work = nullptr;
