@@ -229,9 +229,8 @@ mf_status mf_assemble_ex(const mf_pattern_t* P, const mf_form* form, const doubl
     const_cast<mf_pattern_s*>(P)->last_stream = A.stream;
 
     mf_status st;
-    if (scatter == MF_SCATTER_AUTO && P->dim == 2 && P->order == 1) {
-        // small 2D meshes: the whole call as one launch
-        st = assemble_small(A);
+    if (scatter != MF_SCATTER_ATOMIC) {
+        st = assemble_quads(A);  // resets the status, applies the Dirichlet elimination
         if (st != MF_ERR_UNSUPPORTED) return st;
     }
     st = reset_status(P, A.stream);
@@ -243,9 +242,9 @@ mf_status mf_assemble_ex(const mf_pattern_t* P, const mf_form* form, const doubl
         return gathered ? MF_OK : apply_dirichlet(A);
     }
     // AUTO and GATHER on 8-node bricks: the owner-computes rows, on any mesh.  Without a
-    // workspace (no memory for it) and in 2D: the column kernel on structured grids, else (and
-    // for forms without a gather kernel) the element-parallel scatter colour by colour, whose
-    // sums do not depend on the run.  ATOMIC asks for the paper's atomic scatter explicitly.
+    // workspace (no memory for it): the column kernel on structured grids, else (and for forms
+    // without a gather kernel) the element-parallel scatter colour by colour, whose sums do not
+    // depend on the run.  ATOMIC asks for the paper's atomic scatter explicitly.
     const bool auto_mode = scatter == MF_SCATTER_AUTO;
     if (scatter != MF_SCATTER_ATOMIC && !column_wins(A)) {
         st = assemble_rows(A);  // applies the Dirichlet elimination while writing K

@@ -127,11 +127,10 @@ struct AssembleArgs {
 // element-parallel scatter: hardware atomics, or colour by colour with plain adds
 // (deterministic sums)
 mf_status assemble_atomic(const AssembleArgs& a, bool coloured);
-// small 2D meshes (at most 16 colours of at most 16k rows each): status reset, clear,
-// coloured scatter and Dirichlet elimination in one single-workgroup launch; the same sums
-// as assemble_atomic(a, true) + apply_dirichlet.  MF_ERR_UNSUPPORTED (nothing launched,
-// no error recorded) for any other mesh.
-mf_status assemble_small(const AssembleArgs& a);
+// assemble_quads.hip: owner-computes rows on any mesh of 4-node quadrilaterals, with the
+// status reset and the Dirichlet elimination.  MF_ERR_UNSUPPORTED (nothing launched, no error recorded) for other
+// elements and for meshes with hundreds of neighbours at a node.
+mf_status assemble_quads(const AssembleArgs& a);
 // assemble_quadratic.hip: the quadratic elements, and the flow form on 8-node bricks where it
 // goes colour by colour; *eliminated: the Dirichlet elimination is done
 mf_status assemble_quadratic(const AssembleArgs& a, bool* eliminated);
