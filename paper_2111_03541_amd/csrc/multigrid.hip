@@ -16,15 +16,17 @@
 // cleared with memset, so a cycle can be captured in a HIP graph):
 //   k_mg_sweep     one Jacobi sweep, out of place, with the SpMV fused (8 lanes per row for
 //                  the 4-field flow rows of up to 108 entries, 4 otherwise); the same kernel
-//                  forms the first sweep from x = 0 (no SpMV) and the residual b - A x;
-//                  scalar patterns run it on a slot-major ELL copy, one row per thread
-//                  (k_mg_sweep_ell), node-major flow rows with the columns taken from
+//                  forms the residual b - A x; scalar levels run it on a slot-major copy of
+//                  the values whose columns the grid implies, one row per thread
+//                  (k_mg_sweep_stencil), node-major flow rows with the columns taken from
 //                  the node graph (k_mg_sweep_nodes)
+//   k_mg_first     the first sweep from x = 0
 //   k_mg_restrict  one thread per coarse node and field gathers its 27 fine neighbours
 //   k_mg_prolong   one thread per fine node interpolates from its 1, 2, 4 or 8 parents
 //   k_mg_coarse    the coarsest level in one workgroup, the iterate in LDS, all sweeps in
 //                  one launch, rows cached in registers when there are at most 256 (levels
-//                  of more than kCoarseMax rows use k_mg_sweep)
+//                  of more than kCoarseMax rows use k_mg_sweep); scalar levels of at most
+//                  1024 rows with one row per thread (k_mg_coarse_stencil)
 // Sweeps alternate between two buffers per level; the first one is chosen so that the last
 // sweep writes the level's output and no copy is needed.
 #include <hip/hip_runtime.h>
@@ -35,6 +37,8 @@
 
 #include "mf_internal.h"
 #include "pcg.h"
+#include "rows.h"
+#include "stencil.h"
 
 struct mf_mg_s {
     struct Level {
@@ -52,10 +56,8 @@ struct mf_mg_s {
         double* x = nullptr;               // l >= 1: the cycle's output on this level
         double* b = nullptr;               // l >= 1: the restricted right side
         double* t = nullptr;               // second sweep buffer and residual
-        // scalar patterns: the operator in slot-major ELL form (slot k of row i at
-        // k * n_rows + i; padding has value 0 and column i), refreshed at every update
-        int width = 0;
-        int32_t* ecol = nullptr;
+        // scalar patterns: the operator as a stencil (its values owned), refreshed at every update
+        mf::Stencil st;
         double* eval = nullptr;
         // node-major rows of four fields: sweeps take the columns from the node graph
         bool node_cols = false;
@@ -78,12 +80,6 @@ constexpr int kMaxBlocks = 8192;
 constexpr int kCoarseMax = 4096;      // rows of a coarsest level solved in one workgroup
 constexpr int kCoarseThreads = 1024;
 constexpr int kCoarseLanes = 4;       // lanes per row in the coarsest-level kernel
-// field counts whose levels sweep on an ELL copy (index: fields per node): scalar rows
-// (27 entries; 96^3 conduction 10.8 -> 9.7 ms per PCG solve).  The flow's 108-entry rows
-// stay on the 8-lane CSR sweep: with ELL, one thread per row, the 48^3 Newton solve took
-// 155-157 ms against 144 ms.
-constexpr bool kEllFields[5] = {false, true, false, false, false};
-
 __device__ __forceinline__ int64_t dof_of(int64_t node, int f, int64_t n_nodes, int nf, int fm)
 {
     return fm ? (int64_t)f * n_nodes + node : node * nf + f;
@@ -235,49 +231,74 @@ __global__ void __launch_bounds__(kThreads) k_mg_dinv(int64_t n, const int32_t* 
     }
 }
 
-enum SweepMode { kSweep = 0, kFirst = 1, kResidual = 2 };
+enum SweepMode { kSweep = 0, kResidual = 1 };
 
-// ELL columns of a CSR pattern (fixed with the pattern)
-__global__ void __launch_bounds__(kThreads) k_mg_ell_cols(int64_t n, int width, const int32_t* __restrict__ rp,
-                                                          const int32_t* __restrict__ ci, int32_t* __restrict__ ecol)
+// The values of kStencilRows consecutive rows are one run of A: it goes through LDS, so that both
+// sides are whole lines.  97^3 rows: 125 us, 394 MB; the copy of a row by one thread took 235, and
+// 577 with the columns.  COMPARE: *differ is set where v is not, bit for bit, what it would be.
+constexpr int kStencilRows = 128;
+template <bool COMPARE>
+__global__ void __launch_bounds__(kStencilRows) k_stencil_values(Stencil S, const int32_t* __restrict__ rp,
+                                                                 const double* __restrict__ A, double* __restrict__ v,
+                                                                 double* __restrict__ dinv, int* __restrict__ differ)
 {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int k0 = rp[i], len = rp[i + 1] - k0;
-        for (int k = 0; k < width; ++k) ecol[k * n + i] = k < len ? ci[k0 + k] : (int32_t)i;
+    __shared__ double sh[kStencilRows * 27];
+    const int n = S.sx * S.sy * S.sz;
+    const int r0 = blockIdx.x * kStencilRows, r1 = min(n, r0 + kStencilRows);
+    const int k0 = rp[r0], total = rp[r1] - k0;
+    for (int k = threadIdx.x; k < total; k += kStencilRows) sh[k] = A[k0 + k];
+    const int i = r0 + threadIdx.x;
+    const int at = i < n ? rp[i] - k0 : 0;
+    __syncthreads();
+    if (i >= n) return;
+    int ix, iy, iz;
+    stencil_node(S, (uint32_t)i, ix, iy, iz);
+    const bool ok[3][3] = {{ix > 0, true, ix + 1 < S.sx}, {iy > 0, true, iy + 1 < S.sy}, {iz > 0, true, iz + 1 < S.sz}};
+    int c = at;
+    double diag = 0.0;
+    bool same = true;
+#pragma unroll
+    for (int k = 0; k < 27; ++k) {
+        const bool in = ok[0][k % 3] && ok[1][k / 3 % 3] && ok[2][k / 9];
+        const double a = in ? sh[c] : 0.0;
+        c += in;
+        if (COMPARE) same &= __double_as_longlong(S.v[(int64_t)k * n + i]) == __double_as_longlong(a);
+        else v[(int64_t)k * n + i] = a;
+        if (k == 13) diag = a;
     }
+    if (COMPARE && !same) *differ = 1;
+    if (dinv) dinv[i] = diag != 0.0 ? 1.0 / diag : 0.0;
 }
 
-// ELL values of the level's operator
-__global__ void __launch_bounds__(kThreads) k_mg_ell_vals(int64_t n, int width, const int32_t* __restrict__ rp,
-                                                          const double* __restrict__ A, double* __restrict__ eval)
-{
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int k0 = rp[i], len = rp[i + 1] - k0;
-        for (int k = 0; k < width; ++k) eval[k * n + i] = k < len ? A[k0 + k] : 0.0;
-    }
-}
-
-// The sweep of k_mg_sweep on the ELL copy, one row per thread: consecutive rows read
-// consecutive addresses of every slot.
+// k_mg_sweep on a stencil's values, one row per thread: consecutive rows read consecutive
+// addresses of every slot, 27 values and 27 neighbours in flight.  Bound by the values' bytes: 97^3 rows 32 us for 226 MB
+// (7 TB/s: the 197 MB of values stay in the last-level cache) against 67 on an ELL copy, whose
+// columns are 99 MB more and which the solve did not share.
 template <int MODE>
-__global__ void __launch_bounds__(kThreads) k_mg_sweep_ell(int64_t n, int width, const int32_t* __restrict__ ecol,
-                                                           const double* __restrict__ eval,
-                                                           const double* __restrict__ dinv,
-                                                           const double* __restrict__ b,
-                                                           const double* __restrict__ in, double* __restrict__ out,
-                                                           double omega)
+__global__ void __launch_bounds__(kThreads) k_mg_sweep_stencil(Stencil S, int back, const double* __restrict__ dinv,
+                                                               const double* __restrict__ b,
+                                                               const double* __restrict__ in, double* __restrict__ out,
+                                                               double omega)
 {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        double s = 0.0;
-#pragma unroll 9
-        for (int k = 0; k < width; ++k) s = fma(eval[k * n + i], in[ecol[k * n + i]], s);
-        if (MODE == kSweep) out[i] = in[i] + omega * dinv[i] * (b[i] - s);
-        else out[i] = b[i] - s;
-    }
+    const int n = S.sx * S.sy * S.sz;
+    const unsigned blk = xcd_block(blockIdx.x, gridDim.x);
+    const int64_t i = (int64_t)(back ? gridDim.x - 1 - blk : blk) * kThreads + threadIdx.x;
+    if (i >= n) return;
+    const double s = stencil_dot(S, (int32_t)i, in);
+    if (MODE == kSweep) out[i] = in[i] + omega * dinv[i] * (b[i] - s);
+    else out[i] = b[i] - s;
+}
+
+// out = omega dinv b: the sweep from x = 0
+__global__ void __launch_bounds__(kThreads) k_mg_first(int64_t n, const double* __restrict__ dinv,
+                                                       const double* __restrict__ b, double* __restrict__ out,
+                                                       double omega)
+{
+    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (i < n) out[i] = omega * dinv[i] * b[i];
 }
 
 // kSweep:    out = in + omega dinv (b - A in)
-// kFirst:    out = omega dinv b            (the sweep from x = 0; A and in unused)
 // kResidual: out = b - A in
 // LANES consecutive threads share a row; every lane of a row group runs the same trip
 // count, so the group's shuffles see only active lanes.
@@ -294,16 +315,13 @@ __global__ void __launch_bounds__(kThreads) k_mg_sweep(int64_t n, const int32_t*
     const int64_t rows_per_pass = (int64_t)gridDim.x * (kThreads / LANES);
     for (int64_t row = (blockIdx.x * (int64_t)kThreads + threadIdx.x) / LANES; row < n; row += rows_per_pass) {
         double s = 0.0;
-        if (MODE != kFirst) {
-            const int k0 = rp[row], k1 = rp[row + 1];
+        const int k0 = rp[row], k1 = rp[row + 1];
 #pragma unroll 4
-            for (int k = k0 + lane; k < k1; k += LANES) s = fma(A[k], in[ci[k]], s);
+        for (int k = k0 + lane; k < k1; k += LANES) s = fma(A[k], in[ci[k]], s);
 #pragma unroll
-            for (int off = LANES / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, LANES);
-        }
+        for (int off = LANES / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, LANES);
         if (lane == 0) {
-            if (MODE == kFirst) out[row] = omega * dinv[row] * b[row];
-            else if (MODE == kSweep) out[row] = in[row] + omega * dinv[row] * (b[row] - s);
+            if (MODE == kSweep) out[row] = in[row] + omega * dinv[row] * (b[row] - s);
             else out[row] = b[row] - s;
         }
     }
@@ -482,28 +500,62 @@ __global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse(int n, const int32
     for (int i = threadIdx.x; i < n; i += kCoarseThreads) x[i] = xs[cur][i];
 }
 
+// k_mg_coarse on a stencil, one row per thread with its values in registers (n <= kCoarseThreads): a
+// sweep is 27 LDS reads and a barrier.  343 rows, 20 sweeps: 19 us against 54 with four lanes per
+// row that read the values again in every sweep.
+__global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse_stencil(Stencil S, const double* __restrict__ dinv,
+                                                                      const double* __restrict__ b,
+                                                                      double* __restrict__ x, double omega, int sweeps)
+{
+    __shared__ double xs[2][kCoarseThreads];
+    const int n = S.sx * S.sy * S.sz, i = threadIdx.x, row = min(i, n - 1);
+    double v[27];
+#pragma unroll
+    for (int k = 0; k < 27; ++k) v[k] = S.v[k * n + row];
+    int ix, iy, iz;
+    stencil_node(S, (uint32_t)row, ix, iy, iz);
+    const int dx[3] = {ix > 0 ? -1 : 0, 0, ix + 1 < S.sx ? 1 : 0};
+    const int dy[3] = {iy > 0 ? -S.sx : 0, 0, iy + 1 < S.sy ? S.sx : 0};
+    const int dz[3] = {iz > 0 ? -S.sx * S.sy : 0, 0, iz + 1 < S.sz ? S.sx * S.sy : 0};
+    const double di = omega * dinv[row], bi = b[row];
+    double xi = sweeps > 0 ? di * bi : 0.0;
+    xs[0][i] = xi;
+    __syncthreads();
+    for (int k = 1; k < sweeps; ++k) {
+        const double* in = xs[(k - 1) & 1] + row;
+        double s = 0.0;
+#pragma unroll
+        for (int t = 0; t < 27; ++t) s = fma(v[t], in[dz[t / 9] + dy[t / 3 % 3] + dx[t % 3]], s);
+        xi += di * (bi - s);
+        xs[k & 1][i] = xi;
+        __syncthreads();
+    }
+    if (i < n) x[i] = xi;
+}
+
 unsigned grid_for(int64_t work, int per_block)
 {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(kMaxBlocks, (work + per_block - 1) / per_block));
 }
 
+// back: the rows from last to first.  Consecutive passes over an operator go opposite ways, so
+// that one begins on what the other left in the last-level cache.
 void launch_sweep(int mode, const mf_mg_s::Level& Lv, int nf, const double* b, const double* in, double* out,
-                  double omega, hipStream_t s)
+                  double omega, int* back, hipStream_t s)
 {
     const int64_t n = Lv.n_rows;
     const int32_t* rp = Lv.Pv->row_ptr;
     const int32_t* ci = Lv.Pv->col_idx;
-    if (Lv.eval && mode != kFirst) {
-        const unsigned g = grid_for(n, kThreads);
-        if (mode == kSweep)
-            k_mg_sweep_ell<kSweep><<<g, kThreads, 0, s>>>(n, Lv.width, Lv.ecol, Lv.eval, Lv.dinv, b, in, out, omega);
-        else
-            k_mg_sweep_ell<kResidual><<<g, kThreads, 0, s>>>(n, Lv.width, Lv.ecol, Lv.eval, Lv.dinv, b, in, out, omega);
+    if (Lv.eval) {
+        const unsigned g = (unsigned)((n + kThreads - 1) / kThreads);
+        if (mode == kSweep) k_mg_sweep_stencil<kSweep><<<g, kThreads, 0, s>>>(Lv.st, *back, Lv.dinv, b, in, out, omega);
+        else k_mg_sweep_stencil<kResidual><<<g, kThreads, 0, s>>>(Lv.st, *back, Lv.dinv, b, in, out, omega);
+        *back ^= 1;
         return;
     }
     if (nf >= 4) {
         const unsigned g = grid_for(n * 8, kThreads);
-        if (Lv.node_cols && mode != kFirst) {
+        if (Lv.node_cols) {
             const int32_t* np = Lv.Pv->nbr_ptr;
             const int32_t* nb = Lv.Pv->nbr;
             if (mode == kSweep)
@@ -512,13 +564,11 @@ void launch_sweep(int mode, const mf_mg_s::Level& Lv, int nf, const double* b, c
                 k_mg_sweep_nodes<kResidual><<<g, kThreads, 0, s>>>(n, np, nb, Lv.Kv, Lv.dinv, b, in, out, omega);
             return;
         }
-        if (mode == kFirst) k_mg_sweep<8, kFirst><<<g, kThreads, 0, s>>>(n, rp, ci, Lv.Kv, Lv.dinv, b, in, out, omega);
-        else if (mode == kSweep) k_mg_sweep<8, kSweep><<<g, kThreads, 0, s>>>(n, rp, ci, Lv.Kv, Lv.dinv, b, in, out, omega);
+        if (mode == kSweep) k_mg_sweep<8, kSweep><<<g, kThreads, 0, s>>>(n, rp, ci, Lv.Kv, Lv.dinv, b, in, out, omega);
         else k_mg_sweep<8, kResidual><<<g, kThreads, 0, s>>>(n, rp, ci, Lv.Kv, Lv.dinv, b, in, out, omega);
     } else {
         const unsigned g = grid_for(n * 4, kThreads);
-        if (mode == kFirst) k_mg_sweep<4, kFirst><<<g, kThreads, 0, s>>>(n, rp, ci, Lv.Kv, Lv.dinv, b, in, out, omega);
-        else if (mode == kSweep) k_mg_sweep<4, kSweep><<<g, kThreads, 0, s>>>(n, rp, ci, Lv.Kv, Lv.dinv, b, in, out, omega);
+        if (mode == kSweep) k_mg_sweep<4, kSweep><<<g, kThreads, 0, s>>>(n, rp, ci, Lv.Kv, Lv.dinv, b, in, out, omega);
         else k_mg_sweep<4, kResidual><<<g, kThreads, 0, s>>>(n, rp, ci, Lv.Kv, Lv.dinv, b, in, out, omega);
     }
 }
@@ -526,11 +576,15 @@ void launch_sweep(int mode, const mf_mg_s::Level& Lv, int nf, const double* b, c
 // count sweeps; the first from x = 0 when *cur is null.  Buffers alternate: each sweep
 // writes the buffer *cur does not hold.
 void sweeps(const mf_mg_s::Level& Lv, int nf, const double* b, double** cur, double* first_dst, double* other,
-            int count, double omega, hipStream_t s)
+            int count, double omega, int* back, hipStream_t s)
 {
     for (int k = 0; k < count; ++k) {
         double* dst = *cur == nullptr ? first_dst : (*cur == first_dst ? other : first_dst);
-        launch_sweep(*cur == nullptr ? kFirst : kSweep, Lv, nf, b, *cur, dst, omega, s);
+        if (*cur == nullptr)
+            k_mg_first<<<(unsigned)((Lv.n_rows + kThreads - 1) / kThreads), kThreads, 0, s>>>(Lv.n_rows, Lv.dinv, b, dst,
+                                                                                             omega);
+        else
+            launch_sweep(kSweep, Lv, nf, b, *cur, dst, omega, back, s);
         *cur = dst;
     }
 }
@@ -541,11 +595,14 @@ void vcycle(const mf_mg_s* mg, int l, const double* b, double* out, hipStream_t 
     const mf_mg_s::Level& Lv = mg->L[l];
     const int nf = mg->nf, fm = mg->fm;
     const double omega = mg->opts.omega;
+    int back = 0;
     if (l == mg->n_levels - 1) {
         const int cs = mg->opts.coarse_sweeps;
         // a hexahedral grid row holds at most 27 nodes x 4 fields = 108 <= 128 entries
         static_assert(27 * 4 <= kCoarseLanes * kCoarseCache, "row cache too small");
-        if (Lv.n_rows <= kCoarseGroups) {
+        if (Lv.eval && Lv.n_rows <= kCoarseThreads) {
+            k_mg_coarse_stencil<<<1, ((unsigned)Lv.n_rows + 63) / 64 * 64, 0, s>>>(Lv.st, Lv.dinv, b, out, omega, cs);
+        } else if (Lv.n_rows <= kCoarseGroups) {
             k_mg_coarse<true><<<1, kCoarseThreads, 0, s>>>((int)Lv.n_rows, Lv.Pv->row_ptr, Lv.Pv->col_idx, Lv.Kv,
                                                            Lv.dinv, b, out, omega, cs);
         } else if (Lv.n_rows <= kCoarseMax) {
@@ -554,8 +611,8 @@ void vcycle(const mf_mg_s* mg, int l, const double* b, double* out, hipStream_t 
         } else {
             double* cur = nullptr;
             double* first = (cs % 2 == 1) ? out : Lv.t;  // the last of cs sweeps writes out
-            sweeps(Lv, nf, b, &cur, first, first == out ? Lv.t : out, cs, omega, s);
-            if (cs == 0) launch_sweep(kFirst, Lv, nf, b, nullptr, out, 0.0, s);  // x = 0
+            sweeps(Lv, nf, b, &cur, first, first == out ? Lv.t : out, cs, omega, &back, s);
+            if (cs == 0) sweeps(Lv, nf, b, &cur, out, Lv.t, 1, 0.0, &back, s);  // x = 0
         }
         return;
     }
@@ -567,11 +624,11 @@ void vcycle(const mf_mg_s* mg, int l, const double* b, double* out, hipStream_t 
     if (pre > 0) first = ((pre + post) % 2 == 1) ? out : Lv.t;
     else first = (post % 2 == 0) ? out : Lv.t;
     double* other = first == out ? Lv.t : out;
-    sweeps(Lv, nf, b, &cur, first, other, pre, omega, s);
+    sweeps(Lv, nf, b, &cur, first, other, pre, omega, &back, s);
     const double* res = b;  // the residual of x = 0
     if (cur) {
         double* rbuf = cur == first ? other : first;
-        launch_sweep(kResidual, Lv, nf, b, cur, rbuf, omega, s);
+        launch_sweep(kResidual, Lv, nf, b, cur, rbuf, omega, &back, s);
         res = rbuf;
     }
     k_mg_restrict<<<grid_for(Lc.n_nodes * nf, kThreads), kThreads, 0, s>>>(Lc.nx, Lc.ny, Lc.n_nodes, Lv.nx, Lv.ny, Lv.nz,
@@ -588,7 +645,7 @@ void vcycle(const mf_mg_s* mg, int l, const double* b, double* out, hipStream_t 
     }
     for (int k = 0; k < post; ++k) {
         double* dst = cur == first ? other : first;
-        launch_sweep(kSweep, Lv, nf, b, cur, dst, omega, s);
+        launch_sweep(kSweep, Lv, nf, b, cur, dst, omega, &back, s);
         cur = dst;
     }
 }
@@ -651,11 +708,11 @@ mf_status mg_update_combined(mf_mg_t* mg, const mf_form* fa, const double* elem_
     }
     for (int l = 0; l < mg->n_levels; ++l) {
         const mf_mg_s::Level& Lv = mg->L[l];
-        k_mg_dinv<<<grid_for(Lv.n_rows, kThreads), kThreads, 0, s>>>(Lv.n_rows, Lv.Pv->row_ptr, Lv.Pv->col_idx, Lv.Kv,
-                                                                     Lv.dinv);
         if (Lv.eval)
-            k_mg_ell_vals<<<grid_for(Lv.n_rows, kThreads), kThreads, 0, s>>>(Lv.n_rows, Lv.width, Lv.Pv->row_ptr,
-                                                                             Lv.Kv, Lv.eval);
+            stencil_values(Lv.st, Lv.Pv->row_ptr, Lv.Kv, Lv.eval, Lv.dinv, s);
+        else
+            k_mg_dinv<<<grid_for(Lv.n_rows, kThreads), kThreads, 0, s>>>(Lv.n_rows, Lv.Pv->row_ptr, Lv.Pv->col_idx,
+                                                                         Lv.Kv, Lv.dinv);
     }
     MF_HIP(hipGetLastError());
     MF_HIP(hipStreamSynchronize(s));
@@ -665,6 +722,7 @@ mf_status mg_update_combined(mf_mg_t* mg, const mf_form* fa, const double* elem_
 
 mf_status mg_bind_pcg(const mf_mg_t* mg, int64_t n_rows, const double* values, PcgArgs* a)
 {
+    const mf_mg_s::Level& L0 = mg->L[0];
     if (!mg->updated) return set_error(MF_ERR_ARG, "call mf_mg_update before the solve");
     if (n_rows != mg->L[0].n_rows)
         return set_error(MF_ERR_ARG, "multigrid level 0 has %lld rows, system %lld", (long long)mg->L[0].n_rows,
@@ -674,6 +732,28 @@ mf_status mg_bind_pcg(const mf_mg_t* mg, int64_t n_rows, const double* values, P
     a->apply = mg_apply_cb;
     a->apply_ctx = (void*)mg;
     a->apply_graph_safe = 1;
+    if (L0.eval && a->row_ptr == L0.Pv->row_ptr && a->col_idx == L0.Pv->col_idx) a->stencil = L0.st;
+    return MF_OK;
+}
+
+void stencil_values(const Stencil& S, const int32_t* row_ptr, const double* A, double* v, double* dinv, hipStream_t s)
+{
+    const int64_t n = (int64_t)S.sx * S.sy * S.sz;
+    const unsigned g = (unsigned)((n + kStencilRows - 1) / kStencilRows);
+    k_stencil_values<false><<<g, kStencilRows, 0, s>>>(S, row_ptr, A, v, dinv, nullptr);
+}
+
+mf_status stencil_holds(const Stencil& S, const int32_t* row_ptr, const double* A, int* flag, hipStream_t s, bool* same)
+{
+    const int64_t n = (int64_t)S.sx * S.sy * S.sz;
+    const unsigned g = (unsigned)((n + kStencilRows - 1) / kStencilRows);
+    int differ = 0;
+    k_mg_zero_int<<<1, 64, 0, s>>>(flag, 1);
+    k_stencil_values<true><<<g, kStencilRows, 0, s>>>(S, row_ptr, A, nullptr, nullptr, flag);
+    MF_HIP(hipGetLastError());
+    MF_HIP(hipMemcpyAsync(&differ, flag, sizeof(int), hipMemcpyDeviceToHost, s));
+    MF_HIP(hipStreamSynchronize(s));
+    *same = differ == 0;
     return MF_OK;
 }
 
@@ -793,23 +873,16 @@ extern "C" mf_status mf_mg_create(const mf_pattern_t* P, const mf_mg_opts* opts,
         mf_mg_s::Level& Lv = mg->L[l];
         Lv.node_cols = P->nf == 4 && !mg->fm && Lv.Pv->nnz == 16 * Lv.Pv->n_pairs;
     }
-    // ELL copies of every level but the one-workgroup coarsest (rows of a hexahedral grid
-    // hold at most 27 nodes x nf entries)
-    const int ell_width = 27 * P->nf;
-    for (int l = 0; l < n && st == MF_OK && kEllFields[P->nf]; ++l) {
+    // scalar levels as stencils, but for a coarsest one that goes in one workgroup from CSR rows
+    for (int l = 0; l < n && st == MF_OK && P->nf == 1; ++l) {
         mf_mg_s::Level& Lv = mg->L[l];
-        if (l == n - 1 && Lv.n_rows <= kCoarseMax) break;
-        Lv.width = ell_width;
-        Lv.ecol = (int32_t*)dalloc(sizeof(int32_t) * ell_width * (size_t)Lv.n_rows);
-        Lv.eval = (double*)dalloc(sizeof(double) * ell_width * (size_t)Lv.n_rows);
-        if (!Lv.ecol || !Lv.eval) {
+        if (l == n - 1 && Lv.n_rows > kCoarseThreads && Lv.n_rows <= kCoarseMax) break;
+        Lv.eval = (double*)dalloc(sizeof(double) * 27 * (size_t)Lv.n_rows);
+        if (!Lv.eval) {
             st = set_error(MF_ERR_OOM, "multigrid workspace allocation failed");
             break;
         }
-        k_mg_ell_cols<<<grid_for(Lv.n_rows, kThreads), kThreads, 0, s>>>(Lv.n_rows, ell_width, Lv.Pv->row_ptr,
-                                                                         Lv.Pv->col_idx, Lv.ecol);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) st = hip_error(e, "k_mg_ell_cols");
+        Lv.st = {(int32_t)Lv.nx + 1, (int32_t)Lv.ny + 1, (int32_t)Lv.nz + 1, Lv.eval};
     }
     if (st == MF_OK) {
         hipError_t e = hipStreamSynchronize(s);
@@ -963,11 +1036,11 @@ extern "C" mf_status mf_mg_update_ex(mf_mg_t* mg, const mf_form* form, const dou
     }
     for (int l = 0; l < mg->n_levels; ++l) {
         const mf_mg_s::Level& Lv = mg->L[l];
-        k_mg_dinv<<<grid_for(Lv.n_rows, kThreads), kThreads, 0, s>>>(Lv.n_rows, Lv.Pv->row_ptr, Lv.Pv->col_idx, Lv.Kv,
-                                                                     Lv.dinv);
         if (Lv.eval)
-            k_mg_ell_vals<<<grid_for(Lv.n_rows, kThreads), kThreads, 0, s>>>(Lv.n_rows, Lv.width, Lv.Pv->row_ptr,
-                                                                             Lv.Kv, Lv.eval);
+            stencil_values(Lv.st, Lv.Pv->row_ptr, Lv.Kv, Lv.eval, Lv.dinv, s);
+        else
+            k_mg_dinv<<<grid_for(Lv.n_rows, kThreads), kThreads, 0, s>>>(Lv.n_rows, Lv.Pv->row_ptr, Lv.Pv->col_idx,
+                                                                         Lv.Kv, Lv.dinv);
     }
     MF_HIP(hipGetLastError());
     MF_HIP(hipStreamSynchronize(s));

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include "mf.h"
+#include "stencil.h"
 
 namespace mf {
 
@@ -34,6 +35,9 @@ struct PcgArgs {
     // four fully coupled fields, whose SpMV then reads the columns from it; null otherwise
     const int32_t* node_ptr;
     const int32_t* node_nbr;
+    // the grid whose scalar rows row_ptr and col_idx are, with a copy of the values made earlier
+    // (v null otherwise)
+    Stencil stencil;
     hipStream_t stream;
 };
 

@@ -5,9 +5,11 @@
 //   k_spmv_ell_dot q = K p and block partial sums of p.q on an ELL copy of K made once
 //                  per solve (slot-major, one row per lane, so every load of a wave is
 //                  one contiguous access); CSR with four lanes per row when the padding
-//                  would be large.  Rows are split into one contiguous range per block,
-//                  laid out so that each XCD (workgroups go to the 8 XCDs round robin)
-//                  streams one contiguous eighth of K and gathers from one eighth of p.
+//                  would be large.  Systems on the rows of a multigrid cycle's scalar level 0
+//                  use that level's copy, without columns (k_spmv_stencil_dot).  Rows are
+//                  split into one contiguous range per block, laid out so that each XCD
+//                  (workgroups go to the 8 XCDs round robin) streams one contiguous eighth
+//                  of K and gathers from one eighth of p.
 //                  BiCGStab on node-major 4-field rows (the Newton tangent) uses
 //                  k_spmv_nodes_dot instead: K in place, columns from the node graph.
 //   k_reduce_alpha one block: alpha = (r.z) / (p.q) from the partials in a fixed order
@@ -184,6 +186,31 @@ __global__ void __launch_bounds__(kThreads) k_spmv_ell_dot(int n, int width, con
             const int64_t o = (int64_t)t * n + row;
             s = fma(eval[o], x[ecol[o]], s);
         }
+        y[row] = s;
+        if (w) acc_dot = fma(w[row], s, acc_dot);
+    }
+    if (partial) {
+        const double t = block_sum_all(acc_dot, sh);
+        if (threadIdx.x == 0) partial[blockIdx.x] = t;
+    }
+}
+
+// k_spmv_ell_dot on a stencil's values: 97^3 rows 38 us against 69 with the columns read (the
+// values, shared with the multigrid cycle, come from the last-level cache).
+__global__ void __launch_bounds__(kThreads) k_spmv_stencil_dot(Stencil S, const double* __restrict__ x,
+                                                               double* __restrict__ y, const double* __restrict__ w,
+                                                               double* __restrict__ partial)
+{
+    __shared__ double sh[kThreads / 64];
+    const int n = S.sx * S.sy * S.sz;
+    const int nb = gridDim.x;
+    const int per_xcd = nb / kXcds;
+    const int logical = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
+    const int rows = ((n + nb - 1) / nb + kThreads - 1) / kThreads * kThreads;
+    const int r0 = min((int64_t)n, (int64_t)logical * rows), r1 = min(n, r0 + rows);
+    double acc_dot = 0.0;
+    for (int row = r0 + threadIdx.x; row < r1; row += kThreads) {
+        const double s = stencil_dot(S, row, x);
         y[row] = s;
         if (w) acc_dot = fma(w[row], s, acc_dot);
     }
@@ -689,6 +716,25 @@ mf_status scratch_on_current_device(double** out)
 }
 }  // namespace
 
+// The solve's operator as a stencil: the copy that a.stencil names where it holds a.values (the
+// cycle and the solve then share what the last-level cache keeps, and comparing costs what a copy
+// would: 125 us at 97^3 rows), else a copy of its own, as a cycle may lag behind the matrix.
+// st->v stays null when there is no memory for that.
+template <typename F>
+static mf_status stencil_of(const PcgArgs& a, F&& dalloc, int* flag, Stencil* st)
+{
+    bool same = false;
+    const mf_status h = stencil_holds(a.stencil, a.row_ptr, a.values, flag, a.stream, &same);
+    if (h != MF_OK) return h;
+    *st = a.stencil;
+    if (same) return MF_OK;
+    double* v = (double*)dalloc(sizeof(double) * 27 * (size_t)a.n);
+    if (!v) (void)hipGetLastError();
+    else stencil_values(a.stencil, a.row_ptr, a.values, v, nullptr, a.stream);
+    st->v = v;
+    return MF_OK;
+}
+
 int64_t pcg_scratch_doubles(int64_t n) { return scratch_doubles_for(n); }
 
 int64_t pcg_noalloc_max_rows() { return kNoAllocMaxRows; }
@@ -778,7 +824,12 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
     // ELL copy of K for the iterations when the padding stays small (not with a
     // caller-provided workspace: the copy is as large as K)
     int width = 0, nnz32 = 0;
-    if (!scratch) {
+    Stencil grid;
+    if (a.stencil.v && !scratch) {
+        const mf_status h = stencil_of(a, dalloc, flag, &grid);
+        if (h != MF_OK) return h;
+    }
+    if (!grid.v && !scratch) {
         int* dmax = (int*)dalloc(sizeof(int));
         if (!dmax) return set_error(MF_ERR_OOM, "PCG workspace allocation failed");
         MF_HIP(hipMemsetAsync(dmax, 0, sizeof(int), s));
@@ -802,7 +853,9 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
         }
     }
     auto spmv_pq = [&]() {
-        if (ecol)
+        if (grid.v)
+            k_spmv_stencil_dot<<<spmv_blocks, kThreads, 0, s>>>(grid, p, q, p, pq_part);
+        else if (ecol)
             k_spmv_ell_dot<<<spmv_blocks, kThreads, 0, s>>>(n, width, ecol, eval, p, q, p, pq_part);
         else
             k_spmv_dot<<<spmv_blocks, kThreads, 0, s>>>(n, a.row_ptr, a.col_idx, a.values, p, q, p, pq_part);
@@ -1023,7 +1076,14 @@ mf_status run_bicgstab(const PcgArgs& a, mf_pcg_result* res)
 
     // ELL copy of K when the padding stays small (as in run_pcg); none with the node graph
     int width = 0, nnz32 = 0;
-    if (!a.node_ptr) {
+    Stencil grid;
+    if (a.stencil.v && !a.node_ptr) {
+        int* flag = (int*)dalloc(sizeof(int));
+        if (!flag) return set_error(MF_ERR_OOM, "BiCGStab workspace allocation failed");
+        const mf_status h = stencil_of(a, dalloc, flag, &grid);
+        if (h != MF_OK) return h;
+    }
+    if (!grid.v && !a.node_ptr) {
         int* dmax = (int*)dalloc(sizeof(int));
         if (!dmax) return set_error(MF_ERR_OOM, "BiCGStab workspace allocation failed");
         MF_HIP(hipMemsetAsync(dmax, 0, sizeof(int), s));
@@ -1046,7 +1106,9 @@ mf_status run_bicgstab(const PcgArgs& a, mf_pcg_result* res)
         }
     }
     auto spmv = [&](const double* x_in, double* y, const double* w, double* part) {
-        if (a.node_ptr)
+        if (grid.v)
+            k_spmv_stencil_dot<<<spmv_blocks, kThreads, 0, s>>>(grid, x_in, y, w, part);
+        else if (a.node_ptr)
             k_spmv_nodes_dot<<<spmv_blocks, kThreads, 0, s>>>(n, a.node_ptr, a.node_nbr, a.values, x_in, y, w, part);
         else if (ecol)
             k_spmv_ell_dot<<<spmv_blocks, kThreads, 0, s>>>(n, width, ecol, eval, x_in, y, w, part);
