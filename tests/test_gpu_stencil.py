@@ -71,3 +71,33 @@ def test_solves_on_the_cycles_rows(mf, dims, solver, changed):
     # relative residual 1e-11 times the condition number of these grids (below 1e3)
     for got in (x, xc):
         assert np.abs(got.cpu().numpy() - ref).max() <= 1e-8 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("pre,post", [(2, 2), (1, 0), (0, 1)])
+@pytest.mark.parametrize("numbering", [0, 1])
+@pytest.mark.parametrize("dims", [(4, 2, 6), (10, 8, 12)])
+def test_flow_cycle_on_ragged_boxes(mf, dims, numbering, pre, post, shift):
+    """Four fields, vectors at 16-byte addresses and (shift) 8 bytes past them."""
+    say("flow cycle", dims, "numbering", numbering, pre, post, "shift", shift)
+    import oracle.multigrid as MG
+    mesh = W.structured_mesh(dims, jitter=0.15, seed=3)
+    prm = [{"rho": 1.0, "mu": 0.05, "tau_m": 2e-3 * (l + 1), "tau_c": 1e-2} for l in range(8)]
+    st = W.uniform_nodal(4, mesh.n_nodes, -1, 1, 5)
+    mask = W.dof_mask(W.boundary_node_mask(mesh.shape), 4, field_major=bool(numbering), fields=[0, 1, 2])
+    r = np.random.default_rng(8).standard_normal(4 * mesh.n_nodes)
+    cuda = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    pat = mf.Pattern(cuda(mesh.conn), mesh.n_nodes, 3, 4, numbering=numbering)
+    form, coords, s, m = mf.Form(mf.NS_SUPG, **prm[0]), cuda(mesh.coords), cuda(st), cuda(mask)
+    room = torch.empty(pat.nnz + 1, dtype=torch.float64, device="cuda")
+    K, _ = pat.assemble(form, coords, lin_state=s, dirichlet=m, K=room[shift:shift + pat.nnz])
+    mg = mf.Multigrid(pat, coarse_rows=1, pre_sweeps=pre, post_sweeps=post, tau_m=[p["tau_m"] for p in prm],
+                      tau_c=[p["tau_c"] for p in prm])
+    mg.update(form, coords, K, lin_state=s, dirichlet=m)
+    rg, zg = (torch.zeros(r.size + 1, dtype=torch.float64, device="cuda")[shift:shift + r.size] for _ in range(2))
+    rg.copy_(torch.from_numpy(r))
+    z = mg.apply(rg, zg).cpu().numpy()
+    n = len(mg.levels())
+    levels = MG.build_levels(dims, mesh.coords, 4, O.NS_SUPG, prm[:n], n, state=st, dirichlet=mask, numbering=numbering)
+    zr = MG.vcycle(levels, r, omega=0.5, pre=pre, post=post, coarse_sweeps=20)
+    assert np.abs(z - zr).max() <= TOL * np.abs(zr).max()
