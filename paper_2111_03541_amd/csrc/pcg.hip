@@ -23,7 +23,7 @@
 //
 // Preconditioners: Jacobi (z = r / diag K), none, or an external apply (the learned
 // network) that writes z from r; for the external one the flexible beta
-// (z.(r - r_old)) / (r.z)_old is used, and any iteration with z.r <= 0 or a non-finite z
+// (z.(r - r_old)) / (r.z)_old, r - r_old = -alpha q, is used, and any iteration with z.r <= 0 or a non-finite z
 // falls back to the Jacobi z.
 #include <hip/hip_runtime.h>
 
@@ -44,6 +44,7 @@ constexpr int kSlots = kThreads / kLanesPerRow;  // rows per block per step
 constexpr int kUnroll = 8;                       // row loads issued together (32 entries)
 constexpr int kSpmvBlocks = 2048;                // a multiple of the 8 XCDs
 constexpr int kVecBlocks = 2048;
+constexpr int kReduceThreads = 1024;             // of a one-block reduction
 constexpr int kXcds = 8;
 
 // Scalars (device): RZ = r.z, PQ, ALPHA, BETA, RR, FALLBACK, BREAK
@@ -257,9 +258,9 @@ __global__ void __launch_bounds__(kThreads) k_spmv_nodes_dot(int n, const int32_
 }
 
 // one block: alpha = (r.z) / (p.q) from the SpMV partials
-__global__ void k_reduce_alpha(const double* __restrict__ pq_part, int nb, double* s)
+__global__ void __launch_bounds__(kReduceThreads) k_reduce_alpha(const double* __restrict__ pq_part, int nb, double* s)
 {
-    __shared__ double sh[kThreads / 64];
+    __shared__ double sh[kReduceThreads / 64];
     const double pq = sum_partials(pq_part, nb, sh);
     if (threadIdx.x == 0) {
         const bool ok = pq > 0.0 && isfinite(pq);
@@ -298,36 +299,24 @@ __global__ void __launch_bounds__(kThreads) k_update_dots(int n, const double* _
     }
 }
 
-// External preconditioner: x += alpha p; r_old = r; r -= alpha q (z comes from the apply)
+// External preconditioner: x += alpha p; r -= alpha q (z comes from the apply)
 __global__ void __launch_bounds__(kThreads) k_update_ext(int n, const double* __restrict__ s,
                                                          double* __restrict__ x, double* __restrict__ r,
-                                                         double* __restrict__ r_old, const double* __restrict__ p,
-                                                         const double* __restrict__ q)
+                                                         const double* __restrict__ p, const double* __restrict__ q)
 {
     const double alpha = s[S_ALPHA];
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         x[i] = fma(alpha, p[i], x[i]);
-        const double ro = r[i];
-        r_old[i] = ro;
-        r[i] = fma(-alpha, q[i], ro);
+        r[i] = fma(-alpha, q[i], r[i]);
     }
 }
 
-// partials [0..nb) r.z, [nb..2nb) r.r, [2nb..3nb) z.r_old (r_old may be null)
-__global__ void __launch_bounds__(kThreads) k_dots(int n, const double* __restrict__ r, const double* __restrict__ z,
-                                                   const double* __restrict__ r_old, double* __restrict__ partial)
+// partials [0..nb) r.z, [nb..2nb) r.r, [2nb..3nb) z.q (q may be null) of this thread's sums
+__device__ __forceinline__ void store_dots(double rz, double rr, double zq, double* sh, double* __restrict__ partial)
 {
-    __shared__ double sh[kThreads / 64];
-    double rz = 0.0, rr = 0.0, zro = 0.0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const double ri = r[i], zi = z[i];
-        rz = fma(ri, zi, rz);
-        rr = fma(ri, ri, rr);
-        if (r_old) zro = fma(zi, r_old[i], zro);
-    }
     const double a = block_sum_all(rz, sh);
     const double b = block_sum_all(rr, sh);
-    const double c = block_sum_all(zro, sh);
+    const double c = block_sum_all(zq, sh);
     if (threadIdx.x == 0) {
         partial[blockIdx.x] = a;
         partial[gridDim.x + blockIdx.x] = b;
@@ -335,22 +324,110 @@ __global__ void __launch_bounds__(kThreads) k_dots(int n, const double* __restri
     }
 }
 
-// one block: beta from the dot partials (flexible: (z.r - z.r_old) / rz_old); first
-// call (init != 0) only records r.z and r.r
-__global__ void k_reduce_beta(const double* __restrict__ partial, int nb, double* s, int flexible, int init)
+__global__ void __launch_bounds__(kThreads) k_dots(int n, const double* __restrict__ r, const double* __restrict__ z,
+                                                   const double* __restrict__ q, double* __restrict__ partial)
 {
     __shared__ double sh[kThreads / 64];
-    const double rz = sum_partials(partial, nb, sh);
-    const double rr = sum_partials(partial + nb, nb, sh);
-    const double zro = sum_partials(partial + 2 * nb, nb, sh);
-    if (threadIdx.x == 0) {
-        const double rz_old = s[S_RZ];
-        const double num = flexible ? rz - zro : rz;
-        s[S_BETA] = (!init && rz_old != 0.0) ? num / rz_old : 0.0;
-        s[S_RZ] = rz;
-        s[S_RR] = rr;
-        if (!(rz > 0.0) || !isfinite(rz)) s[S_BREAK] = 1.0;
+    double rz = 0.0, rr = 0.0, zq = 0.0;
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+        const double ri = r[i], zi = z[i];
+        rz = fma(ri, zi, rz);
+        rr = fma(ri, ri, rr);
+        if (q) zq = fma(zi, q[i], zq);
     }
+    store_dots(rz, rr, zq, sh, partial);
+}
+
+// The three sums of the dot partials, in a fixed order, in every thread of the one block.
+struct Dots {
+    double rz, rr, zq;
+};
+__device__ __forceinline__ Dots sum_dots(const double* __restrict__ partial, int nb, double (*sh)[3])
+{
+    double v[3] = {0.0, 0.0, 0.0};
+    for (int k = threadIdx.x; k < nb; k += kReduceThreads)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v[c] += partial[c * nb + k];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v[c] += __shfl_xor(v[c], off, 64);
+    if (threadIdx.x % 64 == 0)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) sh[threadIdx.x / 64][c] = v[c];
+    __syncthreads();
+    Dots d = {0.0, 0.0, 0.0};
+    for (int k = 0; k < kReduceThreads / 64; ++k) {
+        d.rz += sh[k][0];
+        d.rr += sh[k][1];
+        d.zq += sh[k][2];
+    }
+    return d;
+}
+
+// beta from the dots: (r.z) / (r.z)_old, for an external preconditioner (flexible) z.(r - r_old) /
+// (r.z)_old with r - r_old = -alpha q; the first call (init) only records r.z and r.r
+__device__ __forceinline__ void set_beta(const Dots& d, double* s, int flexible, int init)
+{
+    const double rz_old = s[S_RZ];
+    const double num = flexible ? -s[S_ALPHA] * d.zq : d.rz;
+    s[S_BETA] = (!init && rz_old != 0.0) ? num / rz_old : 0.0;
+    s[S_RZ] = d.rz;
+    s[S_RR] = d.rr;
+    if (!(d.rz > 0.0) || !isfinite(d.rz)) s[S_BREAK] = 1.0;
+}
+
+// one block: beta from the dot partials
+__global__ void __launch_bounds__(kReduceThreads) k_reduce_beta(const double* __restrict__ partial, int nb, double* s,
+                                                                int init)
+{
+    __shared__ double sh[kReduceThreads / 64][3];
+    const Dots d = sum_dots(partial, nb, sh);
+    if (threadIdx.x == 0) set_beta(d, s, 0, init);
+}
+
+// one block: beta, or where the external preconditioner failed (z.r <= 0 or non-finite z) the
+// flag, on which k_fallback takes the Jacobi z and its dots, and k_fallback_beta beta from them.
+// (One pass over the vectors for both: 97^3 rows, an iteration's dots 8 us and their reduction 5,
+// against 15 and 14 for the check and the flexible beta apart.)
+__global__ void __launch_bounds__(kReduceThreads) k_check_beta(const double* __restrict__ partial, int nb,
+                                                               double* __restrict__ s, int* flag, int flexible, int init)
+{
+    __shared__ double sh[kReduceThreads / 64][3];
+    const Dots d = sum_dots(partial, nb, sh);
+    if (threadIdx.x != 0) return;
+    const int bad = !(d.rz > 0.0) || !isfinite(d.rz);
+    *flag = bad;
+    if (bad) s[S_FALLBACK] += 1.0;
+    else set_beta(d, s, flexible, init);
+}
+
+__global__ void __launch_bounds__(kThreads) k_fallback(int n, const int* __restrict__ flag,
+                                                       const double* __restrict__ dinv, const double* __restrict__ r,
+                                                       const double* __restrict__ q, double* __restrict__ z,
+                                                       double* __restrict__ partial)
+{
+    __shared__ double sh[kThreads / 64];
+    if (!*flag) return;
+    double rz = 0.0, rr = 0.0, zq = 0.0;
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+        const double ri = r[i], zi = dinv[i] * ri;
+        z[i] = zi;
+        rz = fma(ri, zi, rz);
+        rr = fma(ri, ri, rr);
+        if (q) zq = fma(zi, q[i], zq);
+    }
+    store_dots(rz, rr, zq, sh, partial);
+}
+
+__global__ void __launch_bounds__(kReduceThreads) k_fallback_beta(const double* __restrict__ partial, int nb,
+                                                                  const int* __restrict__ flag, double* __restrict__ s,
+                                                                  int flexible, int init)
+{
+    __shared__ double sh[kReduceThreads / 64][3];
+    if (!*flag) return;
+    const Dots d = sum_dots(partial, nb, sh);
+    if (threadIdx.x == 0) set_beta(d, s, flexible, init);
 }
 
 __global__ void __launch_bounds__(kThreads) k_dir(int n, const double* __restrict__ s, const double* __restrict__ z,
@@ -361,22 +438,66 @@ __global__ void __launch_bounds__(kThreads) k_dir(int n, const double* __restric
         p[i] = fma(beta, p[i], z[i]);
 }
 
-// diag inverse, x = 0, r = b, z = M b, p = z
-__global__ void __launch_bounds__(kThreads) k_init(int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                                                   const double* __restrict__ v, const double* __restrict__ b,
-                                                   double* __restrict__ dinv, double* __restrict__ x,
-                                                   double* __restrict__ r, double* __restrict__ z,
-                                                   double* __restrict__ p, int jacobi)
+// The diagonal (0 where a row has none), eight lanes per row.
+constexpr int kDiagLanes = 8;
+__global__ void __launch_bounds__(kThreads) k_diag(int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
+                                                   const double* __restrict__ v, double* __restrict__ diag)
 {
+    const int lane = threadIdx.x % kDiagLanes, rows = gridDim.x * (kThreads / kDiagLanes);
+    for (int64_t i = (blockIdx.x * (int64_t)kThreads + threadIdx.x) / kDiagLanes; i < n; i += rows) {
+        int at = -1;
+        for (int k = rp[i] + lane; k < rp[i + 1]; k += kDiagLanes)
+            if (ci[k] == i) at = k;
+#pragma unroll
+        for (int off = kDiagLanes / 2; off > 0; off >>= 1) at = max(at, __shfl_xor(at, off, kDiagLanes));
+        if (lane == 0) diag[i] = at >= 0 ? v[at] : 0.0;
+    }
+}
+
+// diag inverse (diag may be dinv), x = 0, r = b, z = M b, p = z; partials [0..nb) 0, [nb..2nb) |b|^2
+// (97^3 rows: 13 us with a stencil's diagonal; a scan of each row by one thread took 277, and |b| a
+// product with x = 0, 91)
+__global__ void __launch_bounds__(kThreads) k_init(int n, const double* diag, const double* __restrict__ b, double* dinv,
+                                                   double* __restrict__ x, double* __restrict__ r,
+                                                   double* __restrict__ z, double* __restrict__ p, int jacobi,
+                                                   double* __restrict__ partial)
+{
+    __shared__ double sh[kThreads / 64];
+    double b2 = 0.0;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        double di = 0.0;
-        for (int k = rp[i]; k < rp[i + 1]; ++k)
-            if (ci[k] == i) di = v[k];
-        dinv[i] = di != 0.0 ? 1.0 / di : 1.0;
+        const double a = diag[i], bi = b[i], di = a != 0.0 ? 1.0 / a : 1.0;
+        dinv[i] = di;
         x[i] = 0.0;
-        r[i] = b[i];
-        z[i] = jacobi ? dinv[i] * b[i] : b[i];
+        r[i] = bi;
+        z[i] = jacobi ? di * bi : bi;
         p[i] = z[i];
+        b2 = fma(bi, bi, b2);
+    }
+    const double c = block_sum_all(b2, sh);
+    if (threadIdx.x == 0) {
+        partial[blockIdx.x] = 0.0;
+        partial[gridDim.x + blockIdx.x] = c;
+    }
+}
+
+// k_true_res on a stencil
+__global__ void __launch_bounds__(kThreads) k_true_res_stencil(Stencil S, const double* __restrict__ x,
+                                                               const double* __restrict__ b,
+                                                               double* __restrict__ partial)
+{
+    __shared__ double sh[kThreads / 64];
+    const int n = S.sx * S.sy * S.sz;
+    double e2 = 0.0, b2 = 0.0;
+    for (int64_t i = blockIdx.x * (int64_t)kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
+        const double bi = b[i], e = bi - stencil_dot(S, (int32_t)i, x);
+        e2 = fma(e, e, e2);
+        b2 = fma(bi, bi, b2);
+    }
+    const double a = block_sum_all(e2, sh);
+    const double c = block_sum_all(b2, sh);
+    if (threadIdx.x == 0) {
+        partial[blockIdx.x] = a;
+        partial[gridDim.x + blockIdx.x] = c;
     }
 }
 
@@ -447,26 +568,6 @@ __global__ void k_reduce2(const double* __restrict__ partial, int nb, double* __
         out[0] = A;
         out[1] = C;
     }
-}
-
-// z := Jacobi z where the external preconditioner failed (z.r <= 0 or non-finite z)
-__global__ void k_check_external(const double* __restrict__ partial_rz, int nb, double* __restrict__ s, int* flag)
-{
-    __shared__ double sh[kThreads / 64];
-    const double rz = sum_partials(partial_rz, nb, sh);
-    if (threadIdx.x == 0) {
-        const int bad = !(rz > 0.0) || !isfinite(rz);
-        *flag = bad;
-        if (bad) s[S_FALLBACK] += 1.0;
-    }
-}
-
-__global__ void __launch_bounds__(kThreads) k_jacobi_if(int n, const int* __restrict__ flag,
-                                                        const double* __restrict__ dinv,
-                                                        const double* __restrict__ r, double* __restrict__ z)
-{
-    if (!*flag) return;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) z[i] = dinv[i] * r[i];
 }
 
 __global__ void k_set(double* p, int n, double v)
@@ -678,17 +779,17 @@ mf_status run_spmv(const mf_csr* A, const double* x, double* y, hipStream_t s)
 }
 
 namespace {
-// dinv r r_old z p q | pq partials | dot partials [3 nb] | scalars | flag, each slot
+// dinv r z p q | pq partials | dot partials [3 nb] | scalars | flag, each slot
 // rounded up to 256 bytes
 constexpr int64_t slot256(int64_t v) { return (v + 31) / 32 * 32; }
 constexpr int64_t scratch_doubles_for(int64_t n)
 {
-    return 6 * slot256(n) + slot256(kSpmvBlocks) + slot256(3 * (kVecBlocks > kSpmvBlocks ? kVecBlocks : kSpmvBlocks)) +
+    return 5 * slot256(n) + slot256(kSpmvBlocks) + slot256(3 * (kVecBlocks > kSpmvBlocks ? kVecBlocks : kSpmvBlocks)) +
            slot256(S_COUNT + 2) + slot256(1);
 }
 
-// Fixed device workspace of mf_pcg_noalloc: 6 vectors of up to 2^20 rows and the
-// partial sums (about 48 MiB, held by every GPU the library runs on until the process
+// Fixed device workspace of mf_pcg_noalloc: 5 vectors of up to 2^20 rows and the
+// partial sums (about 40 MiB, held by every GPU the library runs on until the process
 // ends).  Host code reaches it only through the address hipGetSymbolAddress returns.
 constexpr int64_t kNoAllocMaxRows = (int64_t)1 << 20;
 constexpr int64_t kScratchDoubles = scratch_doubles_for(kNoAllocMaxRows);
@@ -717,8 +818,8 @@ mf_status scratch_on_current_device(double** out)
 }  // namespace
 
 // The solve's operator as a stencil: the copy that a.stencil names where it holds a.values (the
-// cycle and the solve then share what the last-level cache keeps, and comparing costs what a copy
-// would: 125 us at 97^3 rows), else a copy of its own, as a cycle may lag behind the matrix.
+// cycle and the solve then share what the last-level cache keeps, and comparing costs about
+// what a copy would: 110 us at 97^3 rows), else a copy of its own, as a cycle may lag behind the matrix.
 // st->v stays null when there is no memory for that.
 template <typename F>
 static mf_status stencil_of(const PcgArgs& a, F&& dalloc, int* flag, Stencil* st)
@@ -767,9 +868,7 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
     }
     const int vec_blocks = (int)std::min<int64_t>(kVecBlocks, (n + kThreads - 1) / kThreads);
     const int spmv_blocks = spmv_blocks_for(n);
-    const int nb = std::max(vec_blocks, spmv_blocks);
 
-    // workspace: dinv r r_old z p q | pq partials | dot partials [3 nb] | scalars | flag
     std::vector<void*> owned;
     auto dalloc = [&](size_t bytes) -> void* {
         void* p = nullptr;
@@ -781,42 +880,24 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
         std::vector<void*>* v;
         ~Free() { for (void* p : *v) (void)hipFree(p); }
     } fr{&owned};
-    double *dinv, *r, *r_old, *z, *p, *q, *pq_part, *partial, *sc;
-    int* flag;
-    if (scratch) {
-        // caller-provided workspace of pcg_scratch_doubles(n) doubles (256-byte slots);
-        // every value is written before it is read, so no clearing is needed
-        auto slot = [](int64_t v) { return (v + 31) / 32 * 32; };
-        double* w = scratch;
-        auto take = [&](int64_t cnt) {
-            double* t = w;
-            w += slot(cnt);
-            return t;
-        };
-        dinv = take(n);
-        r = take(n);
-        r_old = take(n);
-        z = take(n);
-        p = take(n);
-        q = take(n);
-        pq_part = take(kSpmvBlocks);
-        partial = take(3 * (int64_t)std::max(kVecBlocks, kSpmvBlocks));
-        sc = take(S_COUNT + 2);
-        flag = (int*)take(1);
-    } else {
-        dinv = (double*)dalloc(sizeof(double) * n);
-        r = (double*)dalloc(sizeof(double) * n);
-        r_old = (double*)dalloc(sizeof(double) * n);
-        z = (double*)dalloc(sizeof(double) * n);
-        p = (double*)dalloc(sizeof(double) * n);
-        q = (double*)dalloc(sizeof(double) * n);
-        pq_part = (double*)dalloc(sizeof(double) * spmv_blocks);
-        partial = (double*)dalloc(sizeof(double) * 3 * nb);
-        sc = (double*)dalloc(sizeof(double) * (S_COUNT + 2));
-        flag = (int*)dalloc(sizeof(int));
-        if (!dinv || !r || !r_old || !z || !p || !q || !pq_part || !partial || !sc || !flag)
-            return set_error(MF_ERR_OOM, "PCG workspace allocation failed");
-    }
+    // a caller's workspace, or one of the call's own, of pcg_scratch_doubles(n) doubles (256-byte
+    // slots); every value is written before it is read, so no clearing is needed
+    double* w = scratch ? scratch : (double*)dalloc(sizeof(double) * (size_t)scratch_doubles_for(n));
+    if (!w) return set_error(MF_ERR_OOM, "PCG workspace allocation failed");
+    auto take = [&](int64_t cnt) {
+        double* t = w;
+        w += slot256(cnt);
+        return t;
+    };
+    double* dinv = take(n);
+    double* r = take(n);
+    double* z = take(n);
+    double* p = take(n);
+    double* q = take(n);
+    double* pq_part = take(kSpmvBlocks);
+    double* partial = take(3 * (int64_t)std::max(kVecBlocks, kSpmvBlocks));
+    double* sc = take(S_COUNT + 2);
+    int* flag = (int*)take(1);
 
     bool external = a.precond == MF_PRECOND_EXTERNAL;  // false again after a restart
     const int jac = a.precond == MF_PRECOND_NONE ? 0 : 1;  // Jacobi z (also the external fallback)
@@ -862,24 +943,30 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
     };
 
     k_set<<<1, 64, 0, s>>>(sc, S_COUNT + 2, 0.0);
-    k_init<<<vec_blocks, kThreads, 0, s>>>(n, a.row_ptr, a.col_idx, a.values, a.b, dinv, a.x, r, z, p, jac);
-    if (external) {
-        mf_status st = a.apply(a.apply_ctx, r, z, s);
-        if (st != MF_OK) return st;
-        k_dots<<<vec_blocks, kThreads, 0, s>>>(n, r, z, nullptr, partial);
-        k_check_external<<<1, kThreads, 0, s>>>(partial, vec_blocks, sc, flag);
-        k_jacobi_if<<<vec_blocks, kThreads, 0, s>>>(n, flag, dinv, r, z);
-        MF_HIP(hipMemcpyAsync(p, z, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-    }
-    k_dots<<<vec_blocks, kThreads, 0, s>>>(n, r, z, nullptr, partial);
-    k_reduce_beta<<<1, kThreads, 0, s>>>(partial, vec_blocks, sc, 0, 1);
-    MF_HIP(hipGetLastError());
-
-    // |b|
+    if (!grid.v) k_diag<<<vec_blocks, kThreads, 0, s>>>(n, a.row_ptr, a.col_idx, a.values, dinv);
+    k_init<<<vec_blocks, kThreads, 0, s>>>(n, grid.v ? grid.v + 13 * (int64_t)n : dinv, a.b, dinv, a.x, r, z, p, jac,
+                                           partial);
+    k_reduce2<<<1, kThreads, 0, s>>>(partial, vec_blocks, sc + S_COUNT);
     double hb2[2] = {0, 0};
-    k_true_res<<<spmv_blocks, kThreads, 0, s>>>(n, a.row_ptr, a.col_idx, a.values, a.x, a.b, partial);
-    k_reduce2<<<1, kThreads, 0, s>>>(partial, spmv_blocks, sc + S_COUNT);
     MF_HIP(hipMemcpyAsync(hb2, sc + S_COUNT, sizeof(hb2), hipMemcpyDeviceToHost, s));
+    auto precondition = [&](const double* qv, int flexible, int init) -> mf_status {
+        const mf_status st = a.apply(a.apply_ctx, r, z, s);
+        if (st != MF_OK) return st;
+        k_dots<<<vec_blocks, kThreads, 0, s>>>(n, r, z, qv, partial);
+        k_check_beta<<<1, kReduceThreads, 0, s>>>(partial, vec_blocks, sc, flag, flexible, init);
+        k_fallback<<<vec_blocks, kThreads, 0, s>>>(n, flag, dinv, r, qv, z, partial);
+        k_fallback_beta<<<1, kReduceThreads, 0, s>>>(partial, vec_blocks, flag, sc, flexible, init);
+        return MF_OK;
+    };
+    if (external) {
+        const mf_status st = precondition(nullptr, 0, 1);
+        if (st != MF_OK) return st;
+        MF_HIP(hipMemcpyAsync(p, z, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
+    } else {
+        k_dots<<<vec_blocks, kThreads, 0, s>>>(n, r, z, nullptr, partial);
+        k_reduce_beta<<<1, kReduceThreads, 0, s>>>(partial, vec_blocks, sc, 1);
+    }
+    MF_HIP(hipGetLastError());
     MF_HIP(hipStreamSynchronize(s));
     const double bnorm = std::sqrt(hb2[1]);
     if (bnorm == 0.0) {
@@ -889,19 +976,14 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
 
     auto iteration = [&]() -> mf_status {
         spmv_pq();
-        k_reduce_alpha<<<1, kThreads, 0, s>>>(pq_part, spmv_blocks, sc);
+        k_reduce_alpha<<<1, kReduceThreads, 0, s>>>(pq_part, spmv_blocks, sc);
         if (!external) {
             k_update_dots<<<vec_blocks, kThreads, 0, s>>>(n, sc, a.x, r, p, q, dinv, z, jac, partial);
-            k_reduce_beta<<<1, kThreads, 0, s>>>(partial, vec_blocks, sc, 0, 0);
+            k_reduce_beta<<<1, kReduceThreads, 0, s>>>(partial, vec_blocks, sc, 0);
         } else {
-            k_update_ext<<<vec_blocks, kThreads, 0, s>>>(n, sc, a.x, r, r_old, p, q);
-            mf_status st = a.apply(a.apply_ctx, r, z, s);
+            k_update_ext<<<vec_blocks, kThreads, 0, s>>>(n, sc, a.x, r, p, q);
+            const mf_status st = precondition(q, 1, 0);
             if (st != MF_OK) return st;
-            k_dots<<<vec_blocks, kThreads, 0, s>>>(n, r, z, nullptr, partial);
-            k_check_external<<<1, kThreads, 0, s>>>(partial, vec_blocks, sc, flag);
-            k_jacobi_if<<<vec_blocks, kThreads, 0, s>>>(n, flag, dinv, r, z);
-            k_dots<<<vec_blocks, kThreads, 0, s>>>(n, r, z, r_old, partial);
-            k_reduce_beta<<<1, kThreads, 0, s>>>(partial, vec_blocks, sc, 1, 0);
         }
         k_dir<<<vec_blocks, kThreads, 0, s>>>(n, sc, z, p);
         return MF_OK;
@@ -953,7 +1035,7 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
         }
         k_restart<<<spmv_blocks, kThreads, 0, s>>>(n, a.row_ptr, a.col_idx, a.values, a.x, a.b, dinv, jac, r, z, p);
         k_dots<<<vec_blocks, kThreads, 0, s>>>(n, r, z, nullptr, partial);
-        k_reduce_beta<<<1, kThreads, 0, s>>>(partial, vec_blocks, sc, 0, 1);
+        k_reduce_beta<<<1, kReduceThreads, 0, s>>>(partial, vec_blocks, sc, 1);
         MF_HIP(hipGetLastError());
         ++res->restarts;
         it_best = it;
@@ -961,6 +1043,11 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
         return MF_OK;
     };
 
+    auto true_res = [&]() {
+        if (grid.v) k_true_res_stencil<<<spmv_blocks, kThreads, 0, s>>>(grid, a.x, a.b, partial);
+        else k_true_res<<<spmv_blocks, kThreads, 0, s>>>(n, a.row_ptr, a.col_idx, a.values, a.x, a.b, partial);
+        k_reduce2<<<1, kThreads, 0, s>>>(partial, spmv_blocks, sc + S_COUNT);
+    };
     double h[S_COUNT];
     const double tol = a.tol;
     while (it < a.maxit) {
@@ -985,8 +1072,7 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
         const double rel = std::sqrt(h[S_RR]) / bnorm;
         if (rel <= tol) {
             // true residual as judge
-            k_true_res<<<spmv_blocks, kThreads, 0, s>>>(n, a.row_ptr, a.col_idx, a.values, a.x, a.b, partial);
-            k_reduce2<<<1, kThreads, 0, s>>>(partial, spmv_blocks, sc + S_COUNT);
+            true_res();
             MF_HIP(hipMemcpyAsync(hb2, sc + S_COUNT, sizeof(hb2), hipMemcpyDeviceToHost, s));
             MF_HIP(hipStreamSynchronize(s));
             res->true_relres = std::sqrt(hb2[0]) / bnorm;
@@ -1009,8 +1095,7 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
             if (st != MF_OK) return st;
         }
     }
-    k_true_res<<<spmv_blocks, kThreads, 0, s>>>(n, a.row_ptr, a.col_idx, a.values, a.x, a.b, partial);
-    k_reduce2<<<1, kThreads, 0, s>>>(partial, spmv_blocks, sc + S_COUNT);
+    true_res();
     MF_HIP(hipMemcpyAsync(hb2, sc + S_COUNT, sizeof(hb2), hipMemcpyDeviceToHost, s));
     MF_HIP(hipStreamSynchronize(s));
     res->true_relres = std::sqrt(hb2[0]) / bnorm;
