@@ -36,6 +36,18 @@ mf_status hip_error(hipError_t e, const char* what)
 
 }  // namespace mf
 
+mf_status mf::status_of(const unsigned long long (&v)[3], int64_t* first_bad_elem)
+{
+    if (first_bad_elem) *first_bad_elem = v[0] != ~0ull ? (int64_t)v[0] : v[2] != ~0ull ? (int64_t)v[2] : -1;
+    if (v[1] != ~0ull)
+        return set_error(MF_ERR_ARG, "boundary face %lld: element id or local face out of range (skipped)",
+                         (long long)v[1]);
+    if (v[0] != ~0ull) return set_error(MF_ERR_BAD_JACOBIAN, "det J <= 0 in element %lld", (long long)v[0]);
+    if (v[2] != ~0ull)
+        return set_error(MF_ERR_NONFINITE, "non-finite input or coefficient in element %lld", (long long)v[2]);
+    return MF_OK;
+}
+
 using namespace mf;
 
 // On a small structured grid the one launch of the column kernel beats the two of assemble_rows
@@ -283,14 +295,7 @@ mf_status mf_status_poll(const mf_pattern_t* P, int64_t* first_bad_elem)
     unsigned long long v[3] = {0, 0, 0};
     if (P->last_stream) MF_HIP(hipStreamSynchronize(P->last_stream));
     MF_HIP(hipMemcpy(v, P->status, sizeof(v), hipMemcpyDeviceToHost));
-    if (first_bad_elem) *first_bad_elem = v[0] != ~0ull ? (int64_t)v[0] : v[2] != ~0ull ? (int64_t)v[2] : -1;
-    if (v[1] != ~0ull)
-        return set_error(MF_ERR_ARG, "boundary face %lld: element id or local face out of range (skipped)",
-                         (long long)v[1]);
-    if (v[0] != ~0ull) return set_error(MF_ERR_BAD_JACOBIAN, "det J <= 0 in element %lld", (long long)v[0]);
-    if (v[2] != ~0ull)
-        return set_error(MF_ERR_NONFINITE, "non-finite input or coefficient in element %lld", (long long)v[2]);
-    return MF_OK;
+    return status_of(v, first_bad_elem);
 }
 
 // Validates the arguments of mf_pcg / mf_pcg_noalloc and fills the solver arguments.

@@ -85,6 +85,9 @@ mf_status set_error(mf_status s, const char* fmt, ...);
 mf_status hip_error(hipError_t e, const char* what);
 void clear_error();  // empties the thread's last-error message
 
+// The error that a pattern's status words stand for.
+mf_status status_of(const unsigned long long (&v)[3], int64_t* first_bad_elem);
+
 #define MF_HIP(call)                                            \
     do {                                                        \
         hipError_t e_ = (call);                                 \

@@ -716,6 +716,31 @@ mf_status mg_apply_cb(void* ctx, const double* r, double* z, hipStream_t s)
 
 }  // namespace
 
+// The end of an update: every level's smoother, then the first error of the levels' assemblies, read
+// together, as each wait for the stream leaves it idle for some 50 us.
+static mf_status finish_update(mf_mg_t* mg, hipStream_t s)
+{
+    for (int l = 0; l < mg->n_levels; ++l) {
+        const mf_mg_s::Level& Lv = mg->L[l];
+        if (Lv.eval)
+            stencil_values(Lv.st, Lv.Pv->row_ptr, Lv.Kv, Lv.eval, Lv.dinv, s);
+        else
+            k_mg_dinv<<<grid_for(Lv.n_rows, kThreads), kThreads, 0, s>>>(Lv.n_rows, Lv.Pv->row_ptr, Lv.Pv->col_idx,
+                                                                         Lv.Kv, Lv.dinv);
+    }
+    MF_HIP(hipGetLastError());
+    unsigned long long v[MF_MG_MAX_LEVELS][3];
+    for (int l = 1; l < mg->n_levels; ++l)
+        MF_HIP(hipMemcpyAsync(v[l], mg->L[l].P->status, sizeof(v[l]), hipMemcpyDeviceToHost, s));
+    MF_HIP(hipStreamSynchronize(s));
+    for (int l = 1; l < mg->n_levels; ++l) {
+        const mf_status st = status_of(v[l], nullptr);
+        if (st != MF_OK) return st;
+    }
+    mg->updated = true;
+    return MF_OK;
+}
+
 // The cycle for A = wa Ka + wb Kb (two scalar forms, fa with the element field elem_param,
 // fb without), with the Dirichlet elimination, on every level; A0 is level 0's operator.
 mf_status mg_update_combined(mf_mg_t* mg, const mf_form* fa, const double* elem_param, double wa,
@@ -759,22 +784,8 @@ mf_status mg_update_combined(mf_mg_t* mg, const mf_form* fa, const double* elem_
                                                                        Lc.K, wa, wb, dirichlet ? Lc.mask : nullptr,
                                                                        Lc.K);
         MF_HIP(hipGetLastError());
-        int64_t bad = -1;
-        st = mf_status_poll(Lc.P, &bad);
-        if (st != MF_OK) return st;
     }
-    for (int l = 0; l < mg->n_levels; ++l) {
-        const mf_mg_s::Level& Lv = mg->L[l];
-        if (Lv.eval)
-            stencil_values(Lv.st, Lv.Pv->row_ptr, Lv.Kv, Lv.eval, Lv.dinv, s);
-        else
-            k_mg_dinv<<<grid_for(Lv.n_rows, kThreads), kThreads, 0, s>>>(Lv.n_rows, Lv.Pv->row_ptr, Lv.Pv->col_idx,
-                                                                         Lv.Kv, Lv.dinv);
-    }
-    MF_HIP(hipGetLastError());
-    MF_HIP(hipStreamSynchronize(s));
-    mg->updated = true;
-    return MF_OK;
+    return finish_update(mg, s);
 }
 
 mf_status mg_bind_pcg(const mf_mg_t* mg, int64_t n_rows, const double* values, PcgArgs* a)
@@ -1087,22 +1098,8 @@ extern "C" mf_status mf_mg_update_ex(mf_mg_t* mg, const mf_form* form, const dou
             st = apply_dirichlet(elim);
             if (st != MF_OK) return st;
         }
-        int64_t bad = -1;
-        st = mf_status_poll(Lc.P, &bad);
-        if (st != MF_OK) return st;
     }
-    for (int l = 0; l < mg->n_levels; ++l) {
-        const mf_mg_s::Level& Lv = mg->L[l];
-        if (Lv.eval)
-            stencil_values(Lv.st, Lv.Pv->row_ptr, Lv.Kv, Lv.eval, Lv.dinv, s);
-        else
-            k_mg_dinv<<<grid_for(Lv.n_rows, kThreads), kThreads, 0, s>>>(Lv.n_rows, Lv.Pv->row_ptr, Lv.Pv->col_idx,
-                                                                         Lv.Kv, Lv.dinv);
-    }
-    MF_HIP(hipGetLastError());
-    MF_HIP(hipStreamSynchronize(s));
-    mg->updated = true;
-    return MF_OK;
+    return finish_update(mg, s);
 }
 
 extern "C" mf_status mf_mg_update(mf_mg_t* mg, const mf_form* form, const double* coords, const mf_fields* fields,
