@@ -484,6 +484,23 @@ __device__ __forceinline__ double brick_cofactors(const double* X, int q, double
     return J[0][0] * C[0][0] + J[0][1] * C[1][0] + J[0][2] * C[2][0];
 }
 
+// Two layouts of the records.  By values, [NR / 2][8 points][elements of the chunk][2], then the last
+// value [8 points][elements]: the lanes of consecutive elements load one run.  By elements,
+// [elements][8 points][NR]: a lane's loads are one run, for meshes whose consecutive nodes have
+// elements anywhere, where a run of lanes would use 16 bytes of each line.  41x40x37 bricks, by
+// values against by elements: renumbered at random elasticity 317 us against 137, flow 973 against
+// 276; nodes shuffled among 64 neighbours 92 against 104 and 219 against 249; 64^3 in grid order 278
+// against 317 and 1000 against 1072.  Elements some thousand apart still meet in the L2 (4 MB), so
+// the line lies at a quarter of the nodes with a first element more than 1024 from the next node's.
+//
+// Byte offsets in the records: pair m of point q of element e at e * pe + q * pq + m * pm, the last
+// value at last + e * le + q * lq; residual entry (a, j) of element e at e * fe + a * fa + j * fj
+// values.
+struct RecLayout {
+    int64_t pe, pq, pm, last, le, lq, fe, fa, fj;
+};
+typedef double f64x2 __attribute__((ext_vector_type(2), aligned(8)));
+
 struct BrickParams {
     ElemMask em;
     mf_form form;
@@ -494,7 +511,8 @@ struct BrickParams {
     const void* elem_param;
     const void* src;  // nodal sources, or the flow state
     void* Ke;         // element blocks (scalar forms) or point records
-    void* fe;         // [e1 - e0][8][NF]
+    void* fe;
+    RecLayout lay;    // of point records and their fe
     unsigned long long* status;
 };
 
@@ -625,11 +643,10 @@ __global__ void __launch_bounds__(8 * kBE, 5) k_brick_scalar(BrickParams p)
 // ------------------------------------------------------------------------- point records
 
 // Per form: fields, values of a record, column nodes per lane and workgroups per CU of the
-// row kernel.  Records are stored as pairs of values, [NR / 2][8 points][elements of the
-// chunk][2], then the last value [8 points][elements]: a lane's load takes 16 bytes, and the
-// lanes of consecutive elements one run.
+// row kernel.  Records are read in pairs of values, 16 bytes a load.
 template <int FORM>
 struct Rec;
+
 // elasticity: sqrt(det J) J^-1 (so that a product of two gradients carries the weight)
 template <>
 struct Rec<MF_FORM_ELASTICITY> {
@@ -731,12 +748,14 @@ __global__ void __launch_bounds__(8 * kBE) k_brick_points(BrickParams p)
     if (!live) return;
     if (p.em.mask && q == 0) p.em.flag[e - p.e0] = (uint8_t)sMask[el];
     const bool bad = sBad[el] != 0;  // such an element adds nothing
-    const int64_t chunk = p.e1 - p.e0;
-    double2* rec = (double2*)p.Ke + q * chunk + (e - p.e0);
+    const int64_t ec = e - p.e0;
+    char* rec = (char*)p.Ke + ec * p.lay.pe + q * p.lay.pq;
 #pragma unroll
-    for (int k = 0; k < NR / 2; ++k)
-        rec[k * 8 * chunk] = bad ? make_double2(0.0, 0.0) : make_double2(R[2 * k], R[2 * k + 1]);
-    ((double*)p.Ke)[(NR - 1) * 8 * chunk + q * chunk + (e - p.e0)] = bad ? 0.0 : R[NR - 1];
+    for (int k = 0; k < NR / 2; ++k) {
+        const f64x2 x = {bad ? 0.0 : R[2 * k], bad ? 0.0 : R[2 * k + 1]};
+        *(f64x2*)(rec + k * p.lay.pm) = x;
+    }
+    *(double*)((char*)p.Ke + p.lay.last + ec * p.lay.le + q * p.lay.lq) = bad ? 0.0 : R[NR - 1];
     // residual entries of node a
     const int a = q;
     double f[NF];
@@ -765,9 +784,9 @@ __global__ void __launch_bounds__(8 * kBE) k_brick_points(BrickParams p)
             f[3] -= N * x[(NR + 1) * kBE] + g[0] * x[(NR + 2) * kBE] + g[1] * x[(NR + 3) * kBE] + g[2] * x[(NR + 4) * kBE];
         }
     }
-    T* fe = (T*)p.fe + (int64_t)a * NF * chunk + (e - p.e0);
+    T* fe = (T*)p.fe + ec * p.lay.fe + a * p.lay.fa;
 #pragma unroll
-    for (int j = 0; j < NF; ++j) fe[j * chunk] = bad ? T(0) : (T)f[j];
+    for (int j = 0; j < NF; ++j) fe[j * p.lay.fj] = bad ? T(0) : (T)f[j];
 }
 
 // x and y factors of the trilinear basis at a point: the value, and the two derivatives
@@ -793,10 +812,10 @@ struct RowParams {
     const uint8_t* rank_t;
     RowOut out;
     const void* elem_param;
-    const double* rec;  // [NR][8][chunk]
-    const void* fe;     // [8][NF][chunk]
+    const double* rec;
+    RecLayout lay;
+    const void* fe;
     const uint8_t* emask;  // flags of the chunk's elements (with out.mask)
-    int64_t chunk;
     int32_t c0, c1;     // incidence entries of this chunk
     int parts;          // more than one chunk
     int buf_len, wave_len;  // doubles of LDS per node and per wave
@@ -915,7 +934,7 @@ __device__ __forceinline__ void point_flow_tail(const mf_form& fm, int q, const 
 // leave as one contiguous run.  Two waves per SIMD (the node blocks take half the registers),
 // the next point's record is in flight during the products of the present one.  Elasticity 64^3
 // FP64: 260 us, VALU busy 48 %; with k_brick_points 318 us, the column kernel 356; 41x40x37 renumbered
-// bricks 333 us, the coloured scatter 1600.  Flow 48^3 FP64: 385 + 76 us, the coloured kernel 1540.
+// bricks 137 us, the coloured scatter 1600.  Flow 48^3 FP64: 385 + 76 us, the coloured kernel 1540.
 // FP32 builds sum in FP64 too: without packed math the rates are the same.
 template <int FORM, typename T, bool FM>
 __global__ void __launch_bounds__(256, (Rec<FORM>::WG)) k_brick_rows(RowParams p)
@@ -972,20 +991,20 @@ __global__ void __launch_bounds__(256, (Rec<FORM>::WG)) k_brick_rows(RowParams p
         if (p.out.mask) touched |= p.emask[e];
         // value pairs [m0, m1) of the record at point q: uniform bases, 32-bit lane offset
         auto load_pairs = [&](int q, int m0, int m1, double* h) {
-            uint32_t e16 = e * 16;
-            asm volatile("" : "+v"(e16));  // (a 64-bit lane address per value would not fit the registers)
-            const char* b2 = (const char*)p.rec + (int64_t)q * p.chunk * 16;
+            uint32_t eo = e * (uint32_t)p.lay.pe;
+            asm volatile("" : "+v"(eo));  // (a 64-bit lane address per value would not fit the registers)
+            const char* b2 = (const char*)p.rec + q * p.lay.pq;
 #pragma unroll
             for (int m = m0; m < m1; ++m) {
-                const double2 x = *(const double2*)(b2 + (int64_t)m * p.chunk * 128 + e16);
+                const f64x2 x = *(const f64x2*)(b2 + m * p.lay.pm + eo);
                 h[2 * (m - m0)] = x.x;
                 h[2 * (m - m0) + 1] = x.y;
             }
         };
         auto load_last = [&](int q) {
-            uint32_t e8 = e * 8;
-            asm volatile("" : "+v"(e8));
-            return *(const double*)((const char*)p.rec + ((int64_t)(NR - 1) * 8 + q) * p.chunk * 8 + e8);
+            uint32_t eo = e * (uint32_t)p.lay.le;
+            asm volatile("" : "+v"(eo));
+            return *(const double*)((const char*)p.rec + p.lay.last + q * p.lay.lq + eo);
         };
         auto load_head = [&](int q, double (&h)[NH]) {
             load_pairs(q, 0, NH / 2, h);
@@ -1026,10 +1045,10 @@ __global__ void __launch_bounds__(256, (Rec<FORM>::WG)) k_brick_rows(RowParams p
         uint32_t ranks[BPL / 4];
 #pragma unroll
         for (int u = 0; u < BPL / 4; ++u) ranks[u] = *(const uint32_t*)(p.rank_t + (int64_t)code * 8 + (half + u) * 4);
-        const T* fe = (const T*)p.fe + (int64_t)a * NF * p.chunk + e;
+        const T* fe = (const T*)p.fe + e * p.lay.fe + a * p.lay.fa;
         double fd[NF];
 #pragma unroll
-        for (int j = 0; j < NF; ++j) fd[j] = half == 0 ? (double)fe[j * p.chunk] : 0.0;
+        for (int j = 0; j < NF; ++j) fd[j] = half == 0 ? (double)fe[j * p.lay.fj] : 0.0;
         double lam = 0.0, mu = 0.0;
         if constexpr (FORM == MF_FORM_ELASTICITY) {
             const double ep = p.elem_param ? (double)((const T*)p.elem_param)[code >> 3] : 1.0;
@@ -1143,7 +1162,13 @@ mf_status launch_rows(const AssembleArgs& A)
     uint8_t* emask = (uint8_t*)w + (per - 1) * (size_t)chunk;
     for (int64_t e0 = 0; e0 < P->n_elems; e0 += chunk) {
         const int64_t e1 = std::min(P->n_elems, e0 + chunk);
-        const BrickParams b = brick_params<T>(A, e0, e1, w, fe, emask);
+        const int64_t n = e1 - e0;
+        // by elements on a scattered mesh (lane offsets have 32 bits)
+        const bool by_elem = P->scattered && n * 64 * R::NR < ((int64_t)1 << 32);
+        const RecLayout lay = by_elem ? RecLayout{64 * R::NR, 8 * R::NR, 16, 8 * (R::NR - 1), 64 * R::NR, 8 * R::NR, 8 * R::NF, R::NF, 1}
+                                      : RecLayout{16, 16 * n, 128 * n, 64 * (R::NR - 1) * n, 8, 8 * n, 1, R::NF * n, n};
+        BrickParams b = brick_params<T>(A, e0, e1, w, fe, emask);
+        b.lay = lay;
         k_brick_points<FORM, T><<<(unsigned)((e1 - e0 + kBE - 1) / kBE), 8 * kBE, 0, A.stream>>>(b);
         MF_HIP(hipGetLastError());
         RowParams p{};
@@ -1157,7 +1182,7 @@ mf_status launch_rows(const AssembleArgs& A)
         p.rec = (const double*)w;
         p.fe = fe;
         p.emask = emask;
-        p.chunk = e1 - e0;
+        p.lay = lay;
         p.c0 = (int32_t)(e0 * 8);
         p.c1 = (int32_t)(e1 * 8);
         p.parts = e1 - e0 < P->n_elems;

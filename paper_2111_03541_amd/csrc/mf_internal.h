@@ -31,6 +31,7 @@ struct mf_pattern_s {
     int32_t* adj = nullptr;      // [nen*n_elems]
     uint8_t* rank_t = nullptr;   // rank element by element: [n_elems][nen][nen]
     int max_deg = 0;             // largest neighbour count of a node
+    bool scattered = false;      // many consecutive nodes have elements far apart
     // assembly workspace, grown on first use and owned by the pattern: per-element records
     // written by one kernel of a call and read by its next.  ws_done marks the end of the
     // last call that used it, so that a call on another stream waits for it.

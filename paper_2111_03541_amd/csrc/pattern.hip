@@ -71,19 +71,32 @@ __global__ void k_sort_incidence(const int64_t* __restrict__ inc_ptr, int64_t n_
     }
 }
 
-__global__ void k_max_i32(const int32_t* __restrict__ in, int64_t n, int* __restrict__ out)
+// out[0]: the largest neighbour count; out[1]: consecutive nodes whose first elements are more
+// than kNear apart (inc holds e * nen + a).
+constexpr int kNear = 1024;
+__global__ void k_node_stats(const int32_t* __restrict__ deg, int64_t n, const int64_t* __restrict__ inc_ptr,
+                             const int32_t* __restrict__ inc, int nen, int* __restrict__ out)
 {
-    __shared__ int32_t sh[kThreads];
-    int32_t m = 0;
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads)
-        m = in[i] > m ? in[i] : m;
-    sh[threadIdx.x] = m;
+    __shared__ int32_t sh[2][kThreads];
+    int32_t m = 0, far = 0;
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
+        m = max(m, deg[i]);
+        if (i + 1 < n && deg[i] > 0 && deg[i + 1] > 0) far += abs(inc[inc_ptr[i]] / nen - inc[inc_ptr[i + 1]] / nen) > kNear;
+    }
+    sh[0][threadIdx.x] = m;
+    sh[1][threadIdx.x] = far;
     __syncthreads();
     for (int w = kThreads / 2; w > 0; w /= 2) {
-        if ((int)threadIdx.x < w && sh[threadIdx.x + w] > sh[threadIdx.x]) sh[threadIdx.x] = sh[threadIdx.x + w];
+        if ((int)threadIdx.x < w) {
+            sh[0][threadIdx.x] = max(sh[0][threadIdx.x], sh[0][threadIdx.x + w]);
+            sh[1][threadIdx.x] += sh[1][threadIdx.x + w];
+        }
         __syncthreads();
     }
-    if (threadIdx.x == 0) atomicMax(out, sh[0]);
+    if (threadIdx.x == 0) {
+        atomicMax(out, sh[0][0]);
+        atomicAdd(out + 1, sh[1][0]);
+    }
 }
 
 // Distinct neighbours of v in ascending order, by repeated selection of the smallest
@@ -349,11 +362,11 @@ mf_status build_pattern(mf_pattern_s* P, const int32_t* conn_in, hipStream_t s)
     const int64_t n_el = P->n_elems, n_nodes = P->n_nodes;
     const int64_t n_ent = n_el * nen;
     Scratch tmp;
-    int *flag = nullptr, *max_deg = nullptr;
+    int *flag = nullptr, *stats = nullptr;
     int32_t *cnt = nullptr, *cursor = nullptr, *deg = nullptr;
     int64_t *inc_ptr = nullptr, *nbr_ptr64 = nullptr;
     MF_TRY(tmp.alloc(&flag, 1));
-    MF_TRY(tmp.alloc(&max_deg, 1));
+    MF_TRY(tmp.alloc(&stats, 2));
     MF_TRY(tmp.alloc(&cnt, n_nodes));
     MF_TRY(tmp.alloc(&cursor, n_nodes));
     MF_TRY(tmp.alloc(&deg, n_nodes));
@@ -370,7 +383,7 @@ mf_status build_pattern(mf_pattern_s* P, const int32_t* conn_in, hipStream_t s)
     int32_t* inc = P->adj;
 
     k_fill_i32<<<1, 1, 0, s>>>((int32_t*)flag, 1, 0);
-    k_fill_i32<<<1, 1, 0, s>>>((int32_t*)max_deg, 1, 0);
+    k_fill_i32<<<1, 64, 0, s>>>((int32_t*)stats, 2, 0);
     if (n_nodes > 0) {
         k_fill_i32<<<blocks_for(n_nodes, kThreads), kThreads, 0, s>>>(cnt, n_nodes, 0);
         k_fill_i32<<<blocks_for(n_nodes, kThreads), kThreads, 0, s>>>(cursor, n_nodes, 0);
@@ -400,17 +413,20 @@ mf_status build_pattern(mf_pattern_s* P, const int32_t* conn_in, hipStream_t s)
     if (n_nodes > 0) {
         k_sort_incidence<<<blocks_for(n_nodes, kThreads), kThreads, 0, s>>>(inc_ptr, n_nodes, inc);
         node_neighbours(nullptr, nullptr);
-        k_max_i32<<<(unsigned)std::min<int64_t>(256, blocks_for(n_nodes, kThreads)), kThreads, 0, s>>>(deg, n_nodes,
-                                                                                                      max_deg);
+        k_node_stats<<<(unsigned)std::min<int64_t>(256, blocks_for(n_nodes, kThreads)), kThreads, 0, s>>>(
+            deg, n_nodes, inc_ptr, inc, nen, stats);
     }
     MF_HIP(hipGetLastError());
     MF_TRY(exclusive_scan<int32_t>(deg, n_nodes, nbr_ptr64, s));
     MF_HIP(hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, s));
-    MF_HIP(hipMemcpyAsync(&P->max_deg, max_deg, sizeof(int), hipMemcpyDeviceToHost, s));
+    int hstats[2] = {0, 0};
+    MF_HIP(hipMemcpyAsync(hstats, stats, sizeof(hstats), hipMemcpyDeviceToHost, s));
     int64_t n_pairs = 0;
     MF_HIP(hipMemcpyAsync(&n_pairs, nbr_ptr64 + n_nodes, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     MF_HIP(hipStreamSynchronize(s));
     if (hflag & 2) return set_error(MF_ERR_OVERFLOW, "a node has more than 255 neighbours");
+    P->max_deg = hstats[0];
+    P->scattered = hstats[1] > n_nodes / 4;
 
     // field table
     FieldTable ft{};

@@ -116,6 +116,27 @@ def test_rows_agree_with_scatter(mf, kind, prec, n, numbering):
     assert float((d - dr).abs().max() / dr.abs().max()) <= 2 * TOL[prec]
 
 
+@pytest.mark.parametrize("masked", [False, True], ids=["free", "dirichlet"])
+@pytest.mark.parametrize("prec", [0, 1], ids=["f64", "f32"])
+@pytest.mark.parametrize("numbering", [0, 1])
+@pytest.mark.parametrize("kind", [O.ELASTICITY, O.NS_SUPG])
+def test_scattered_numbering(mf, kind, numbering, prec, masked):
+    """Random numbering of enough elements for records by elements, against the scatter."""
+    say("scattered", kind, numbering, prec, masked)
+    mesh = W.permute_mesh(W.structured_mesh((22, 21, 20), jitter=0.2, seed=3), 4)[0]
+    first = mesh.n_elems * np.ones(mesh.n_nodes, np.int64)  # each node's first element
+    np.minimum.at(first, mesh.conn.ravel(), np.tile(np.arange(mesh.n_elems), 8))
+    assert (np.abs(np.diff(first)) > 1024).sum() > mesh.n_nodes // 4
+    nf, ep, src, st = inputs(kind, mesh, prec)
+    mask = (np.random.default_rng(8).random(nf * mesh.n_nodes) < 0.02).astype(np.uint8) if masked else None
+    pat = mf.Pattern(cuda(mesh.conn), mesh.n_nodes, 3, nf, numbering=numbering)
+    K, d = assemble(mf, pat, kind, mesh, prec, ep, src, st, mask)
+    Kr, dr = assemble(mf, pat, kind, mesh, prec, ep, src, st, mask, scatter=1)
+    # each side is within TOL of the exact rows
+    assert rowscaled_gpu(pat, K, Kr) <= 2 * TOL[prec]
+    assert float((d - dr).abs().max() / dr.abs().max()) <= 2 * TOL[prec]
+
+
 def test_calls_on_two_streams_and_threads(mf):
     say("two threads, a stream each, one pattern")
     mesh = W.permute_mesh(W.structured_mesh((14, 13, 12), jitter=0.2, seed=3), 4)[0]
