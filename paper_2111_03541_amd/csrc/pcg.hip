@@ -44,6 +44,7 @@ constexpr int kSlots = kThreads / kLanesPerRow;  // rows per block per step
 constexpr int kUnroll = 8;                       // row loads issued together (32 entries)
 constexpr int kSpmvBlocks = 2048;                // a multiple of the 8 XCDs
 constexpr int kVecBlocks = 2048;
+constexpr int kStencilBlocks = 4096;              // a multiple of the 8 XCDs
 constexpr int kReduceThreads = 1024;             // of a one-block reduction
 constexpr int kXcds = 8;
 
@@ -196,8 +197,9 @@ __global__ void __launch_bounds__(kThreads) k_spmv_ell_dot(int n, int width, con
     }
 }
 
-// k_spmv_ell_dot on a stencil's values: 97^3 rows 38 us against 69 with the columns read (the
-// values, shared with the multigrid cycle, come from the last-level cache).
+// k_spmv_ell_dot on a stencil's values: 97^3 rows 32 us against 69 with the columns read (the
+// values, shared with the multigrid cycle, come from the last-level cache); with 2048 workgroups,
+// most threads of two rows one after the other, 38.
 __global__ void __launch_bounds__(kThreads) k_spmv_stencil_dot(Stencil S, const double* __restrict__ x,
                                                                double* __restrict__ y, const double* __restrict__ w,
                                                                double* __restrict__ partial)
@@ -784,7 +786,7 @@ namespace {
 constexpr int64_t slot256(int64_t v) { return (v + 31) / 32 * 32; }
 constexpr int64_t scratch_doubles_for(int64_t n)
 {
-    return 5 * slot256(n) + slot256(kSpmvBlocks) + slot256(3 * (kVecBlocks > kSpmvBlocks ? kVecBlocks : kSpmvBlocks)) +
+    return 5 * slot256(n) + slot256(kStencilBlocks) + slot256(3 * (kVecBlocks > kSpmvBlocks ? kVecBlocks : kSpmvBlocks)) +
            slot256(S_COUNT + 2) + slot256(1);
 }
 
@@ -868,6 +870,8 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
     }
     const int vec_blocks = (int)std::min<int64_t>(kVecBlocks, (n + kThreads - 1) / kThreads);
     const int spmv_blocks = spmv_blocks_for(n);
+    // one row per thread while that takes no more than kStencilBlocks workgroups
+    const int stencil_blocks = std::min(kStencilBlocks, ((n + kThreads - 1) / kThreads + kXcds - 1) / kXcds * kXcds);
 
     std::vector<void*> owned;
     auto dalloc = [&](size_t bytes) -> void* {
@@ -894,7 +898,7 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
     double* z = take(n);
     double* p = take(n);
     double* q = take(n);
-    double* pq_part = take(kSpmvBlocks);
+    double* pq_part = take(kStencilBlocks);
     double* partial = take(3 * (int64_t)std::max(kVecBlocks, kSpmvBlocks));
     double* sc = take(S_COUNT + 2);
     int* flag = (int*)take(1);
@@ -935,7 +939,7 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
     }
     auto spmv_pq = [&]() {
         if (grid.v)
-            k_spmv_stencil_dot<<<spmv_blocks, kThreads, 0, s>>>(grid, p, q, p, pq_part);
+            k_spmv_stencil_dot<<<stencil_blocks, kThreads, 0, s>>>(grid, p, q, p, pq_part);
         else if (ecol)
             k_spmv_ell_dot<<<spmv_blocks, kThreads, 0, s>>>(n, width, ecol, eval, p, q, p, pq_part);
         else
@@ -976,7 +980,7 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
 
     auto iteration = [&]() -> mf_status {
         spmv_pq();
-        k_reduce_alpha<<<1, kReduceThreads, 0, s>>>(pq_part, spmv_blocks, sc);
+        k_reduce_alpha<<<1, kReduceThreads, 0, s>>>(pq_part, grid.v ? stencil_blocks : spmv_blocks, sc);
         if (!external) {
             k_update_dots<<<vec_blocks, kThreads, 0, s>>>(n, sc, a.x, r, p, q, dinv, z, jac, partial);
             k_reduce_beta<<<1, kReduceThreads, 0, s>>>(partial, vec_blocks, sc, 0);
