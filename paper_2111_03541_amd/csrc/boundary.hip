@@ -12,9 +12,17 @@
 //   gather  one wave per node of a listed face adds the rows of the faces around the node
 //           (its incidence list, faces in local order) in LDS, and then each value of K and
 //           d is read, added to and written once.
-// A marking pass finds the distinct faces (a face listed n times counts n times) and their
-// nodes.  No atomics on K and nothing ordered by them, so the sums are the same on every
-// run, and nothing waits on the host.
+// The first workgroups of the rows' launch meanwhile find which faces are listed (a face listed n
+// times counts n times) and their nodes; a call that names more faces than there are makes the
+// distinct ones a list first, which bounds the workspace.  No atomics on K and nothing ordered by
+// them, so the sums are the same on every run, and nothing waits on the host.
+// All three launches are latency chains (a face reads its element's nodes, their coordinates and
+// state, then a node its incidence list, counts and rows), so what helps is to have the loads of a
+// step in flight together.  Conduction on 64^3 bricks, 8192 faces and 16384 faces a call, mean:
+// clear 5 us, rows 14, gather 14; with the listing in a launch of its own and a node's rows read
+// one after another 5, 12, 14 and 17; the eight colour launches took 132 and their marking 20.
+// 15288 tetrahedra with all 2240 boundary faces: 4 + 11 + 7 us, before 4, 10, 26 and 10, where 41
+// bucket launches took 1242.
 //
 // The flow forms on 8-node hexahedra carry the test gradient: all eight nodes get rows of
 // four fields, 8 kB per face.  They go element by element, one launch per element colour:
@@ -38,6 +46,22 @@ namespace {
 
 constexpr int kThreads = 256;
 
+// The faces of a call.  A key is element * local faces + local face.
+struct FaceLists {
+    const int32_t* elem;
+    const uint8_t* fid;
+    int64_t n, n_el;
+    const int32_t* conn;
+    uint32_t* cnt;   // [keys] how often each face is listed
+    int32_t* slot;   // [keys] where the rows of a listed face are
+    int32_t* list;   // distinct faces (keys), or nullptr: the call's own order
+    uint32_t* node_on;  // [n_nodes]
+    int32_t* nodes;     // distinct nodes of the listed faces
+    uint32_t* counts;   // distinct faces (with a list) and nodes
+    uint32_t blocks;    // without a list: workgroups of the row kernel that list the faces
+    unsigned long long* status;
+};
+
 struct BParams {
     mf_bform form;
     int64_t n_el, n_nodes, n_faces;
@@ -54,14 +78,12 @@ struct BParams {
     void* K;
     void* d;
     unsigned long long* status;
-    // colour by colour: per element, the listed local faces (bit fid); both ways: how often
-    // each local face is listed
+    // colour by colour: per element, the listed local faces (bit fid), and how often each is
     const uint32_t* face_mask;  // [n_el]
     const uint32_t* face_cnt;   // [n_el][local faces]
-    // rows and gather: distinct faces (element * local faces + local face) and their number,
-    // and the rows [face][row node][field][columns + 1], the residual entry last
-    const int32_t* list;
-    const uint32_t* n_list;
+    // rows and gather: the rows [slot of the face][row node][field][columns + 1], the residual
+    // entry last
+    FaceLists lists;
     double* rows;
 };
 
@@ -162,29 +184,90 @@ struct Faces<2, 8> {
     static __device__ __forceinline__ int col(int f, int b) { return kEdges8.node[f][b]; }
 };
 
-// One thread of the row kernels: its face (index in the list), element, local face, row node
-// (position on the face), field, and how often the face is listed.
+// Counts listed face f of the call under its key (element * NLOC + local face); the first of a key
+// takes slot[key], and appends the face's nodes, each once, to the node list.  With a list, faces
+// are appended to it, and their slot is the place; else it is f.  Every lane of the wave takes part
+// (f >= n: no face).  Returns whether the face is in range.
+template <class F>
+__device__ __forceinline__ bool list_face(const FaceLists& L, int64_t f, int64_t& e, int& lf)
+{
+    const int lane = (int)(threadIdx.x & 63);
+    // one counter update per wave: the lanes that append take consecutive places
+    auto place = [&](bool take, uint32_t* counter) -> uint32_t {
+        const unsigned long long group = __ballot(take);
+        uint32_t base = 0;
+        if (lane == 0 && group) base = atomicAdd(counter, (uint32_t)__popcll(group));
+        base = (uint32_t)__shfl((int)base, 0, 64);
+        return base + (uint32_t)__popcll(group & ((1ull << lane) - 1ull));
+    };
+    e = -1;
+    lf = 0;
+    if (f < L.n) {
+        e = L.elem[f];
+        lf = L.fid[f];
+        if (e < 0 || e >= L.n_el || lf >= F::NLOC) {
+            atomicMin(L.status + 1, (unsigned long long)f);
+            e = -1;
+        }
+    }
+    const int32_t key = (int32_t)(e * F::NLOC + lf);
+    const bool first = e >= 0 && atomicAdd(L.cnt + key, 1u) == 0u;
+    if (L.list) {
+        const uint32_t at = place(first, L.counts);
+        if (first) {
+            L.list[at] = key;
+            L.slot[key] = (int32_t)at;
+        }
+    } else if (first) {
+        L.slot[key] = (int32_t)f;
+    }
+    int32_t v[F::NFN];
+    bool fresh[F::NFN];
+#pragma unroll
+    for (int k = 0; k < F::NFN; ++k) v[k] = first ? L.conn[(int64_t)F::node(lf, k) * L.n_el + e] : 0;
+#pragma unroll
+    for (int k = 0; k < F::NFN; ++k) fresh[k] = first && atomicExch(L.node_on + v[k], 1u) == 0u;
+#pragma unroll
+    for (int k = 0; k < F::NFN; ++k) {
+        const uint32_t w = place(fresh[k], L.counts + 1);
+        if (fresh[k]) L.nodes[w] = v[k];
+    }
+    return e >= 0;
+}
+
+// One thread of the row kernels: its face's slot, element, local face, row node (position on
+// the face) and field.  Without a list the first workgroups list the faces meanwhile.
 struct RowItem {
     int64_t slot, e;
     int fid, k, i;
-    double mult;
     bool live;
 };
-template <class F, int NF>
-__device__ __forceinline__ RowItem row_item(const BParams& p)
+template <class F, int NF, int LANES = 1>
+__device__ __forceinline__ RowItem row_item(const BParams& p)  // LANES threads have one item
 {
     RowItem r{};
-    const int64_t n = *p.n_list, t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const FaceLists& L = p.lists;
+    if (blockIdx.x < L.blocks) {
+        list_face<F>(L, (int64_t)blockIdx.x * kThreads + threadIdx.x, r.e, r.fid);
+        return r;
+    }
+    const int64_t t = ((int64_t)(blockIdx.x - L.blocks) * kThreads + threadIdx.x) / LANES;
+    const int64_t n = L.list ? (int64_t)*L.counts : L.n;
     r.live = t < n * F::NFN * NF;
     if (!r.live) return r;
     r.slot = t % n;
     const int ki = (int)(t / n);
     r.k = ki / NF;
     r.i = ki % NF;
-    const int key = p.list[r.slot];
-    r.e = key / F::NLOC;
-    r.fid = key % F::NLOC;
-    r.mult = (double)p.face_cnt[key];
+    if (L.list) {
+        const int key = L.list[r.slot];
+        r.e = key / F::NLOC;
+        r.fid = key % F::NLOC;
+        return r;
+    }
+    r.e = L.elem[r.slot];
+    r.fid = L.fid[r.slot];
+    r.live = r.e >= 0 && r.e < L.n_el && r.fid < F::NLOC;
     return r;
 }
 template <class F, int NF>
@@ -192,8 +275,8 @@ __device__ __forceinline__ void store_row(const BParams& p, const RowItem& r, co
 {
     double* out = p.rows + ((r.slot * F::NFN + r.k) * NF + r.i) * (F::COLS + 1);
 #pragma unroll
-    for (int b = 0; b < F::COLS; ++b) out[b] = r.mult * krow[b];
-    out[F::COLS] = -r.mult * rrow;
+    for (int b = 0; b < F::COLS; ++b) out[b] = krow[b];
+    out[F::COLS] = -rrow;
 }
 
 __device__ __forceinline__ double lin1(int s, double xi) { return 0.5 * (1.0 + (s ? xi : -xi)); }
@@ -591,7 +674,10 @@ __global__ void __launch_bounds__(kThreads) k_face_rows20(BParams p)
     store_row<F, NF>(p, r, krow, rrow);
 }
 
-// Faces of 10-node tetrahedra: one thread per (face f, face node m, field i).  Face k is
+constexpr int kTetLanes = 4;
+// Faces of 10-node tetrahedra: four threads per (face f, face node m, field i), one for each first
+// coordinate of the rule (2240 faces are 210 waves with one thread each: 26 us
+// against 11).  Face k is
 // the face opposite vertex k: its three vertices and the three edge midpoints among them.
 // The face is the reference triangle p0 + s (p1 - p0) + t (p2 - p0) over its vertices,
 // integrated with the collapsed 4 x 4 Gauss rule of the triangle; the normal points away
@@ -600,10 +686,10 @@ template <int NF, typename T>
 __global__ void __launch_bounds__(kThreads) k_face_rows10(BParams p)
 {
     using F = Faces<3, 10>;
-    const RowItem r = row_item<F, NF>(p);
+    const RowItem r = row_item<F, NF, kTetLanes>(p);
     if (!r.live) return;
     const int64_t e = r.e;
-    const int i = r.i;
+    const int i = r.i, sub = threadIdx.x % kTetLanes;
     const int mf = r.k, k = r.fid;
     // face nodes: the vertices other than k, then the edges among them
     int loc[6];
@@ -641,9 +727,12 @@ __global__ void __launch_bounds__(kThreads) k_face_rows10(BParams p)
                           0.5 * (1.0 + 0.3399810435848563), 0.5 * (1.0 + 0.8611363115940526)};
     const double w4[4] = {0.5 * 0.3478548451374538, 0.5 * 0.6521451548625461, 0.5 * 0.6521451548625461,
                           0.5 * 0.3478548451374538};
-    for (int q = 0; q < 16; ++q) {
-        const double s_ = g4[q & 3], t_ = g4[q >> 2] * (1.0 - s_);
-        const double wq = w4[q & 3] * w4[q >> 2] * (1.0 - s_);
+    const double s_ = g4[sub], ws = w4[sub] * (1.0 - s_);
+    bool ok = true;
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+        const double t_ = g4[q] * (1.0 - s_);
+        const double wq = ws * w4[q];
         double xi[3], e1[3], e2[3];
 #pragma unroll
         for (int m = 0; m < 3; ++m) {
@@ -671,12 +760,7 @@ __global__ void __launch_bounds__(kThreads) k_face_rows10(BParams p)
             for (int m = 0; m < 3; ++m) nr[m] = -nr[m];
         }
         const double dS = sqrt(nr[0] * nr[0] + nr[1] * nr[1] + nr[2] * nr[2]);
-        if (!(dS > 0.0)) {
-            atomicMin(p.status, (unsigned long long)e);
-            double none[F::COLS] = {};
-            store_row<F, NF>(p, r, none, 0.0);
-            return;
-        }
+        ok &= dS > 0.0;
         const double w = wq * dS;
         const double Na = N[mf];
         double uq = 0.0, gq = 0.0;
@@ -698,6 +782,20 @@ __global__ void __launch_bounds__(kThreads) k_face_rows10(BParams p)
             const double ti = tg ? gq : (S[3 * i] * nr[0] + S[3 * i + 1] * nr[1] + S[3 * i + 2] * nr[2]) / dS;
             rrow -= w * Na * ti;
         }
+    }
+#pragma unroll
+    for (int off = 1; off < kTetLanes; off *= 2) {
+#pragma unroll
+        for (int b = 0; b < 6; ++b) krow[b] += __shfl_xor(krow[b], off, kTetLanes);
+        rrow += __shfl_xor(rrow, off, kTetLanes);
+        ok &= __shfl_xor((int)ok, off, kTetLanes) != 0;
+    }
+    if (sub != 0) return;
+    if (!ok) {  // such a face adds nothing
+        atomicMin(p.status, (unsigned long long)e);
+        rrow = 0.0;
+#pragma unroll
+        for (int b = 0; b < 6; ++b) krow[b] = 0.0;
     }
     store_row<F, NF>(p, r, krow, rrow);
 }
@@ -856,53 +954,16 @@ __global__ void k_face_mark(const int32_t* __restrict__ fe, const uint8_t* __res
     }
 }
 
-// (Conduction on 64^3 bricks, 8192 faces and 16384 faces a call, mean: clear 5 us, lists 12, rows
-// 14, gather 17; the eight colour launches took 132 and the marking 20.  15288 tetrahedra with all
-// 2240 boundary faces: 4 + 10 + 26 + 10 us, where 41 bucket launches took 1242.  Latency chains: a
-// face reads its element's nodes, their coordinates and state, then a node its incidence list,
-// counts and rows.)
-// Distinct listed faces and their nodes: cnt[element * NLOC + local face] counts a face, the
-// first to do so appends it to the list and its nodes, each once, to the node list.
+// (More faces in the call than there are: the distinct ones, as a list.)
 template <class F>
-__global__ void k_face_list(const int32_t* __restrict__ fe, const uint8_t* __restrict__ fid, int64_t n, int64_t n_el,
-                            const int32_t* __restrict__ conn, uint32_t* __restrict__ cnt, int32_t* __restrict__ slot,
-                            int32_t* __restrict__ list, uint32_t* __restrict__ node_on, int32_t* __restrict__ nodes,
-                            uint32_t* __restrict__ counts, unsigned long long* __restrict__ status)
+__global__ void __launch_bounds__(kThreads) k_face_list(FaceLists L)
 {
-    const int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int lane = (int)(threadIdx.x & 63);
-    // one counter update per wave: the lanes that append take consecutive places
-    auto place = [&](bool take, uint32_t* counter) -> uint32_t {
-        const unsigned long long group = __ballot(take);
-        uint32_t base = 0;
-        if (lane == 0 && group) base = atomicAdd(counter, (uint32_t)__popcll(group));
-        base = (uint32_t)__shfl((int)base, 0, 64);
-        return base + (uint32_t)__popcll(group & ((1ull << lane) - 1ull));
-    };
-    int64_t e = -1;
-    int lf = 0;
-    if (f < n) {
-        e = fe[f];
-        lf = fid[f];
-        if (e < 0 || e >= n_el || lf >= F::NLOC) {
-            atomicMin(status + 1, (unsigned long long)f);
-            e = -1;
-        }
-    }
-    const int32_t key = (int32_t)(e * F::NLOC + lf);
-    const bool first = e >= 0 && atomicAdd(cnt + key, 1u) == 0u;
-    const uint32_t at = place(first, counts);
-    if (first) {
-        list[at] = key;
-        slot[key] = (int32_t)at;
-    }
-    for (int k = 0; k < F::NFN; ++k) {
-        const int32_t v = first ? conn[(int64_t)F::node(lf, k) * n_el + e] : 0;
-        const bool fresh = first && atomicExch(node_on + v, 1u) == 0u;
-        const uint32_t w = place(fresh, counts + 1);
-        if (fresh) nodes[w] = v;
-    }
+    int64_t e;
+    int lf;
+    list_face<F>(L, (int64_t)blockIdx.x * kThreads + threadIdx.x, e, lf);
 }
+
+constexpr int kMaxAt = 3;  // listed faces of an element around one of its nodes
 
 struct FaceGather {
     const int32_t* adj_ptr;
@@ -920,18 +981,20 @@ struct FaceGather {
     void* d;
 };
 
-// One wave per listed node (strided over the grid): the rows of the faces around it, then its
-// values of K and d.  The (i, i) blocks only: these forms do not couple fields.
+// One wave per listed node (strided over the grid): the rows of the faces around it, several at
+// once, then its values of K and d.  The (i, i) blocks only: these forms do not couple fields.
 template <int DIM, int NEN, int NF, typename T>
 __global__ void __launch_bounds__(kThreads) k_face_gather(FaceGather p)
 {
     using F = Faces<DIM, NEN>;
-    constexpr int ROW = F::COLS + 1;
-    extern __shared__ double sh[];
+    constexpr int ROW = F::COLS + 1, RL = NF * ROW, G = 64 / RL, UN = 2;
+    extern __shared__ __align__(16) double sh[];
     const int lane = threadIdx.x & 63, waves = blockDim.x / 64, wave = threadIdx.x / 64;
-    double* buf = sh + wave * p.buf_len;  // [i][r], then the residual entries
-    double* dbuf = buf + p.buf_len - NF;
+    int4* list = (int4*)(sh + wave * p.buf_len);  // rows of 64 entries: place, entry, count, local face
+    double* buf = (double*)(list + 64 * kMaxAt);  // [i][r], then the residual entries
+    double* dbuf = sh + (wave + 1) * p.buf_len - 4;
     const int n = (int)*p.n_nodes_on;
+    const int grp = lane / RL, l = lane - grp * RL, li = l / ROW, lb = l - li * ROW;
     for (int w = blockIdx.x * waves + wave; w < n; w += gridDim.x * waves) {
         const int64_t v = p.nodes[w];
         const int k0 = p.adj_ptr[v], k1 = p.adj_ptr[v + 1];
@@ -939,26 +1002,47 @@ __global__ void __launch_bounds__(kThreads) k_face_gather(FaceGather p)
         const int deg = p.nbr_ptr[v + 1] - (int)P;
         for (int t = lane; t < NF * deg; t += 64) buf[t] = 0.0;
         if (lane < NF) dbuf[lane] = 0.0;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         for (int kb = k0; kb < k1; kb += 64) {
-            const int code = kb + lane < k1 ? p.adj[kb + lane] : -1;
+            const bool in = kb + lane < k1;
+            const int code = in ? p.adj[kb + lane] : 0;
             const int e = code / NEN, a = code - e * NEN;
+            uint32_t cnt[F::NLOC];
+            int slot[F::NLOC];
+#pragma unroll
             for (int f = 0; f < F::NLOC; ++f) {
-                const int at = code >= 0 ? F::at(f, a) : -1;
-                const bool on = at >= 0 && p.cnt[(int64_t)e * F::NLOC + f] != 0u;
-                const int mine = on ? p.slot[(int64_t)e * F::NLOC + f] * F::NFN + at : 0;
-                for (unsigned long long left = __ballot(on); left; left &= left - 1) {
-                    const int src = __ffsll((long long)left) - 1;
-                    const double* row = p.rows + (int64_t)__shfl(mine, src) * (NF * ROW);
-                    const int64_t c = __shfl(code, src);
-                    if (lane < NF * ROW) {
-                        const int i = lane / ROW, b = lane - i * ROW;
-                        const double x = row[lane];
-                        if (b < F::COLS) unsafeAtomicAdd(buf + i * deg + p.rank_t[c * NEN + F::col(f, b)], x);
-                        else unsafeAtomicAdd(dbuf + i, x);
-                    }
-                }
+                cnt[f] = p.cnt[(int64_t)e * F::NLOC + f];
+                slot[f] = p.slot[(int64_t)e * F::NLOC + f];  // (anything where cnt is 0)
             }
+            // the rows, by local face and entry: the order of their sums
+            int total = 0;
+#pragma unroll
+            for (int f = 0; f < F::NLOC; ++f) {
+                const int at = in ? F::at(f, a) : -1;
+                const bool on = at >= 0 && cnt[f] != 0u;
+                const unsigned long long group = __ballot(on);
+                if (on)
+                    list[total + __popcll(group & ((1ull << lane) - 1ull))] =
+                        make_int4(slot[f] * F::NFN + at, code, (int)cnt[f], f);
+                total += __popcll(group);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            for (int j0 = 0; j0 < total; j0 += G * UN) {
+                double x[UN];
+                int r[UN];
+                bool on[UN];
+#pragma unroll
+                for (int u = 0; u < UN; ++u) {
+                    const int j = j0 + u * G + grp;
+                    on[u] = grp < G && j < total;
+                    const int4 it = list[on[u] ? j : 0];
+                    x[u] = p.rows[(int64_t)it.x * RL + l] * (double)it.z;
+                    r[u] = lb < F::COLS ? p.rank_t[(int64_t)it.y * NEN + F::col(it.w, lb < F::COLS ? lb : 0)] : 0;
+                }
+#pragma unroll
+                for (int u = 0; u < UN; ++u)
+                    if (on[u]) unsafeAtomicAdd(lb < F::COLS ? buf + li * deg + r[u] : dbuf + li, x[u]);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         T* K = (T*)p.K;
@@ -995,8 +1079,10 @@ mf_status launch_faces(BParams p, const mf_pattern_s* P, hipStream_t s, bool* do
     if (p.n_faces == 0 || P->n_elems == 0) return MF_OK;
     const int64_t keys = P->n_elems * F::NLOC, most = std::min(p.n_faces, keys), nodes_most = std::min(most * F::NFN, P->n_nodes);
     if (most * F::NFN * NF > (int64_t)0x7fffffff * kThreads) return set_error(MF_ERR_ARG, "too many faces for one launch");
-    // cnt [keys], node flags [n_nodes], two counters; slot [keys], list [most], nodes [most]; rows
-    const int64_t clear = keys + P->n_nodes + 2, words = clear + keys + most + nodes_most;
+    // cnt [keys], node flags [n_nodes], two counters; slot [keys], list [most] where the call names
+    // more faces than there are, nodes [most]; rows
+    const bool listed = p.n_faces > keys;
+    const int64_t clear = keys + P->n_nodes + 2, words = clear + keys + (listed ? most : 0) + nodes_most;
     const size_t rows_at = (sizeof(uint32_t) * (size_t)words + 255) / 256 * 256;
     const size_t rows = sizeof(double) * (size_t)most * F::NFN * NF * (F::COLS + 1);
     const Workspace held(P, rows_at + rows, s);
@@ -1007,16 +1093,14 @@ mf_status launch_faces(BParams p, const mf_pattern_s* P, hipStream_t s, bool* do
     uint32_t* node_on = cnt + keys;
     uint32_t* counts = node_on + P->n_nodes;
     int32_t* slot = (int32_t*)(counts + 2);
-    int32_t* list = slot + keys;
-    int32_t* nodes = list + most;
-    k_face_zero<<<(unsigned)((clear + kThreads - 1) / kThreads), kThreads, 0, s>>>(cnt, clear);
-    k_face_list<F><<<(unsigned)((p.n_faces + kThreads - 1) / kThreads), kThreads, 0, s>>>(
-        p.face_elem, p.face_id, p.n_faces, P->n_elems, P->conn, cnt, slot, list, node_on, nodes, counts, P->status);
-    p.face_cnt = cnt;
-    p.list = list;
-    p.n_list = counts;
+    int32_t* nodes = slot + keys;
+    p.lists = {p.face_elem, p.face_id, p.n_faces, P->n_elems, P->conn, cnt, slot, listed ? nodes + nodes_most : nullptr,
+               node_on, nodes, counts, listed ? 0u : (uint32_t)((p.n_faces + kThreads - 1) / kThreads), P->status};
     p.rows = (double*)(ws + rows_at);
-    launch_rows<DIM, NEN, NF, T>(p, (unsigned)((most * F::NFN * NF + kThreads - 1) / kThreads), s);
+    k_face_zero<<<(unsigned)((clear + kThreads - 1) / kThreads), kThreads, 0, s>>>(cnt, clear);
+    if (listed) k_face_list<F><<<(unsigned)((p.n_faces + kThreads - 1) / kThreads), kThreads, 0, s>>>(p.lists);
+    const int64_t threads = most * F::NFN * NF * (NEN == 10 ? kTetLanes : 1);
+    launch_rows<DIM, NEN, NF, T>(p, p.lists.blocks + (unsigned)((threads + kThreads - 1) / kThreads), s);
     FaceGather g{};
     g.adj_ptr = P->adj_ptr;
     g.adj = P->adj;
@@ -1030,10 +1114,10 @@ mf_status launch_faces(BParams p, const mf_pattern_s* P, hipStream_t s, bool* do
     g.n_nodes = P->n_nodes;
     g.n_pairs = P->n_pairs;
     g.field_major = p.field_major;
-    g.buf_len = NF * std::max(1, P->max_deg) + NF;
+    g.buf_len = (2 * 64 * kMaxAt + NF * std::max(1, P->max_deg) + 4 + 1) & ~1;  // 16-byte aligned
     g.K = p.K;
     g.d = p.d;
-    // at most 255 neighbours and 3 fields: 25 kB for the four waves
+    // at most 255 neighbours and 3 fields: 37 kB for the four waves
     const unsigned blocks = (unsigned)std::min<int64_t>(8192, (nodes_most + 3) / 4);
     k_face_gather<DIM, NEN, NF, T><<<blocks, kThreads, sizeof(double) * 4 * (size_t)g.buf_len, s>>>(g);
     MF_HIP(hipGetLastError());
