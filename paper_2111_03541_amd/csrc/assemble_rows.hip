@@ -819,9 +819,27 @@ struct RowParams {
     int32_t c0, c1;     // incidence entries of this chunk
     int parts;          // more than one chunk
     int buf_len, wave_len;  // doubles of LDS per node and per wave
+    int plane, slots;   // nodes of a grid plane, workgroups of a band in it (0: nodes in order)
     void* K;
     void* d;
 };
+
+// The workgroup's nodes, in units of per_block, or -1.  A record is read by the eight nodes around
+// its element.  In node order an XCD has passed a whole plane of the grid before the next reads it
+// again, and a plane above some 1 MB of records has left the XCD's 4 MB of L2 by then, with all of K
+// streaming through: each record was fetched twice (elasticity 64^3: 400 MB for 201).  So each XCD
+// takes a band of an eighth of every plane, and goes through the planes: 255 MB fetched, and the
+// flow form on 48^3 FP64 460 -> 432 us, FP32 419 -> 404 (elasticity 64^3 320 us both ways: it waits
+// for latencies rather than bytes).
+__device__ __forceinline__ int row_block(const RowParams& p, int per_block)
+{
+    if (p.plane == 0) return (int)xcd_block(blockIdx.x, gridDim.x);
+    const uint32_t band = blockIdx.x % kXcds, r = blockIdx.x / kXcds, z = r / (uint32_t)p.slots;
+    const int64_t at = (int64_t)z * p.plane;
+    const int64_t lo = at + (int64_t)band * p.plane / kXcds, hi = at + (int64_t)(band + 1) * p.plane / kXcds;
+    const int64_t b = (lo + per_block - 1) / per_block + (r - z * (uint32_t)p.slots);
+    return b < (hi + per_block - 1) / per_block ? (int)b : -1;
+}
 
 // Products of one Gauss point: adds the blocks (a, b) of the lane's BPL column nodes.
 // Elasticity: acc_ij += h_a,i h_b,j (the Lame combination follows once per block).
@@ -952,8 +970,9 @@ __global__ void __launch_bounds__(256, (Rec<FORM>::WG)) k_brick_rows(RowParams p
     // lanes: node fastest, then group of column nodes, then slot
     const int grp = lane % NPW, half = lane / NPW % GRP, slot = lane / (NPW * GRP), sub = lane / NPW;
     const int waves = blockDim.x / kWave, n_nodes = (int)p.out.n_nodes;
-    const int v0 = ((int)xcd_block(blockIdx.x, gridDim.x) * waves + wave) * NPW, v = v0 + grp;
-    if (v0 >= n_nodes) return;
+    const int blk = row_block(p, waves * NPW);
+    const int v0 = (blk * waves + wave) * NPW, v = v0 + grp;
+    if (blk < 0 || v0 >= n_nodes) return;
     const int wbase = wave * p.wave_len;  // the wave's row buffers, one after another
     double* dbuf = sh + wbase + NPW * p.buf_len + grp * NF;
     // (nodes past the end read the last offset: no entries, no neighbours)
@@ -1142,6 +1161,8 @@ mf_status launch_scalar(const AssembleArgs& A)
     return MF_OK;
 }
 
+constexpr int64_t kPlaneBytes = 1 << 20;  // records of a grid plane that stay in an XCD's L2
+
 template <int FORM, typename T>
 mf_status launch_rows(const AssembleArgs& A)
 {
@@ -1191,7 +1212,12 @@ mf_status launch_rows(const AssembleArgs& A)
         p.K = A.K;
         p.d = A.d;
         const int64_t per_block = (int64_t)waves * NPW;
-        const unsigned blocks = (unsigned)((P->n_nodes + per_block - 1) / per_block);
+        unsigned blocks = (unsigned)((P->n_nodes + per_block - 1) / per_block);
+        if (P->is_grid && (int64_t)per * P->gx * P->gy > kPlaneBytes) {
+            p.plane = (int)((P->gx + 1) * (P->gy + 1));
+            p.slots = (int)((p.plane / kXcds + per_block) / per_block) + 1;
+            blocks = (unsigned)(kXcds * (P->gz + 1) * p.slots);
+        }
         if (P->numbering == MF_FIELD_MAJOR) k_brick_rows<FORM, T, true><<<blocks, waves * kWave, per_wave * waves, A.stream>>>(p);
         else k_brick_rows<FORM, T, false><<<blocks, waves * kWave, per_wave * waves, A.stream>>>(p);
         MF_HIP(hipGetLastError());

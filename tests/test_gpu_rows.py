@@ -94,11 +94,12 @@ def rowscaled_gpu(pat, K, Kref):
 
 # both sides of each line between the grid kernel and the rows, the last sizes of one and the
 # first of the other; nodes above and below the 30000 of the eight-nodes-per-wave gather; element
-# records that go in two chunks
+# records that go in two chunks; planes above and below 1 MB of records
 SIDES = [(O.NS_SUPG, 1, (21, 21, 22)), (O.NS_SUPG, 1, (22, 22, 21)), (O.NS_SUPG, 0, (3, 2, 4)),
          (O.ELASTICITY, 0, (27, 27, 27)), (O.ELASTICITY, 0, (28, 27, 27)), (O.POISSON, 0, (27, 27, 27)),
          (O.POISSON, 0, (28, 27, 27)), (O.MASS, 0, (32, 32, 30)), (O.POISSON, 1, (37, 37, 36)),
-         (O.POISSON, 1, (37, 37, 37)), (O.POISSON, 0, (124, 123, 125)), (O.NS_SUPG, 1, (90, 88, 89))]
+         (O.POISSON, 1, (37, 37, 37)), (O.POISSON, 0, (124, 123, 125)), (O.NS_SUPG, 1, (90, 88, 89)),
+         (O.ELASTICITY, 0, (38, 37, 15)), (O.NS_SUPG, 0, (40, 39, 1)), (O.NS_SUPG, 0, (25, 23, 9))]
 
 
 @pytest.mark.parametrize("numbering", [0, 1])
