@@ -147,9 +147,9 @@ typedef struct { int32_t points_per_axis; } mf_quadrature;   /* Gauss-Legendre: 
                                                                   3 for MF_HEX20 and MF_QUAD8,
                                                                   4 for MF_TET10 (collapsed) */
 
-/* Assembly strategies.  AUTO picks an owner-computes gather for 8-node bricks (on a small
-   structured grid the column kernel, else the rows kernels, which take any mesh), and
-   otherwise (or without memory for their workspace) the element-parallel scatter colour
+/* Assembly strategies.  AUTO picks an owner-computes gather for 4-node quadrilaterals and
+   8-node bricks (elasticity and the FP32 flow form on a small structured grid: the column
+   kernel, else the rows kernels, which take any mesh), and otherwise (or without memory for their workspace) the element-parallel scatter colour
    by colour with plain adds, whose sums are the same on every run.  ATOMIC is the
    element-parallel scatter with hardware atomics in one launch (the paper's scheme).  In
    ATOMIC and in the column kernel (which sums a node's element blocks with LDS atomics) the

@@ -50,13 +50,13 @@ mf_status mf::status_of(const unsigned long long (&v)[3], int64_t* first_bad_ele
 
 using namespace mf;
 
-// On a small structured grid the one launch of the column kernel beats the two of assemble_rows
-// (FP64, column against rows: conduction 20^3 17 us against 20, 28^3 33 against 31, 64^3 255
-// against 125; elasticity 24^3 32 against 33, 28^3 46 against 43, 64^3 356 against 320).  The
-// rows sum in FP64 also in FP32 builds, where the column kernel's traffic halves: conduction
-// 32^3 31 us against 34, 40^3 52 against 43; elasticity 48^3 124 against 116, but 64^3 262
-// against 289 and 32^3 46 against 52; the flow form (matrix cores in the column kernel) 20^3 50
-// against 55, 24^3 76 against 63, 48^3 431 against 419.
+// On a small structured grid the one launch of the column kernel beats the two of the elasticity
+// and flow rows (FP64, column against rows: elasticity 24^3 32 us against 33, 28^3 46 against 43,
+// 64^3 356 against 320).  The rows sum in FP64 also in FP32 builds, where the column kernel's
+// traffic halves: elasticity 48^3 124 against 116, but 64^3 262 against 289 and 32^3 46 against 52;
+// the flow form (matrix cores in the column kernel) 20^3 50 against 55, 24^3 76 against 63, 48^3
+// 431 against 404.  The scalar rows are one launch too (conduction 8^3 13 us both ways, 20^3 14
+// against 18, 28^3 18 against 35).
 static bool column_wins(const AssembleArgs& A)
 {
     if (!A.P->is_grid || A.P->dim != 3) return false;
@@ -64,7 +64,7 @@ static bool column_wins(const AssembleArgs& A)
     switch (A.form->kind) {
         case MF_FORM_NS_SUPG: return f32 && A.P->n_elems < 10000;  // FP64: no column kernel
         case MF_FORM_ELASTICITY: return f32 || A.P->n_elems < 20000;
-        default: return A.P->n_elems < (f32 ? 50000 : 20000);
+        default: return false;
     }
 }
 

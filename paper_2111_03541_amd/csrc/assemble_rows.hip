@@ -1,11 +1,13 @@
 // Owner-computes assembly for meshes of any numbering (Sec. 2.2 D-2, D-3): every row of K
-// and d is summed and written once, by the wave that owns its node, from element data that
-// a first kernel has left in the pattern's workspace.  No atomics on K, no clearing pass, no
+// and d is summed and written once, by the wave that owns its node, mostly from element data
+// that a first kernel has left in the pattern's workspace.  No atomics on K, no clearing pass, no
 // colours, and the sums do not depend on the run.
 //
-//  element blocks (k_gather_blocks; scalar forms on 8-node bricks here, every form on the
-//     quadratic elements in assemble_quadratic.hip): the first kernel stores the element's
-//     rows [e][a][i][b][j]; the wave of node v adds the row blocks of its incidence list
+//  rows with the geometry (k_scalar_rows; scalar forms on 8-node bricks, up to some 40^3): the
+//     wave that owns the node forms everything, without a first kernel.
+//  element blocks (k_gather_blocks; scalar forms on larger meshes of 8-node bricks here,
+//     every form on the quadratic elements in assemble_quadratic.hip): the first kernel
+//     stores the element's rows [e][a][i][b][j]; the wave of node v adds the row blocks of its incidence list
 //     (entry e*nen + a is the block's index) in LDS and writes its rows.
 //  point records (k_brick_points, k_brick_rows; elasticity and the flow form on 8-node
 //     bricks): a block is 4.6 kB (elasticity) or 8 kB (flow) and would cross HBM twice, so
@@ -455,6 +457,21 @@ __device__ __forceinline__ void brick_dN(int a, int q, double (&g)[3])
     g[2] = ((a & 4) ? 0.5 : -0.5) * fx * fy;
 }
 
+// det J and its cofactors, C[n][m] = det J * dxi_n/dx_m.
+__device__ __forceinline__ double cofactors(const double (&J)[3][3], double (&C)[3][3])
+{
+    C[0][0] = J[1][1] * J[2][2] - J[1][2] * J[2][1];
+    C[0][1] = J[0][2] * J[2][1] - J[0][1] * J[2][2];
+    C[0][2] = J[0][1] * J[1][2] - J[0][2] * J[1][1];
+    C[1][0] = J[1][2] * J[2][0] - J[1][0] * J[2][2];
+    C[1][1] = J[0][0] * J[2][2] - J[0][2] * J[2][0];
+    C[1][2] = J[0][2] * J[1][0] - J[0][0] * J[1][2];
+    C[2][0] = J[1][0] * J[2][1] - J[1][1] * J[2][0];
+    C[2][1] = J[0][1] * J[2][0] - J[0][0] * J[2][1];
+    C[2][2] = J[0][0] * J[1][1] - J[0][1] * J[1][0];
+    return J[0][0] * C[0][0] + J[0][1] * C[1][0] + J[0][2] * C[2][0];
+}
+
 // det J and the cofactors of J at Gauss point q: C[n][m] = det J * dxi_n/dx_m.  X [8][3] in LDS.
 __device__ __forceinline__ double brick_cofactors(const double* X, int q, double (&C)[3][3])
 {
@@ -472,16 +489,7 @@ __device__ __forceinline__ double brick_cofactors(const double* X, int q, double
 #pragma unroll
             for (int n = 0; n < 3; ++n) J[m][n] = fma(X[b * 3 + m], g[n], J[m][n]);
     }
-    C[0][0] = J[1][1] * J[2][2] - J[1][2] * J[2][1];
-    C[0][1] = J[0][2] * J[2][1] - J[0][1] * J[2][2];
-    C[0][2] = J[0][1] * J[1][2] - J[0][2] * J[1][1];
-    C[1][0] = J[1][2] * J[2][0] - J[1][0] * J[2][2];
-    C[1][1] = J[0][0] * J[2][2] - J[0][2] * J[2][0];
-    C[1][2] = J[0][2] * J[1][0] - J[0][0] * J[1][2];
-    C[2][0] = J[1][0] * J[2][1] - J[1][1] * J[2][0];
-    C[2][1] = J[0][1] * J[2][0] - J[0][0] * J[2][1];
-    C[2][2] = J[0][0] * J[1][1] - J[0][1] * J[1][0];
-    return J[0][0] * C[0][0] + J[0][1] * C[1][0] + J[0][2] * C[2][0];
+    return cofactors(J, C);
 }
 
 // Two layouts of the records.  By values, [NR / 2][8 points][elements of the chunk][2], then the last
@@ -1117,6 +1125,154 @@ __global__ void __launch_bounds__(256, (Rec<FORM>::WG)) k_brick_rows(RowParams p
     }
 }
 
+struct ScalarParams {
+    mf_form form;
+    int64_t n_el;
+    const int32_t* conn;
+    const double* coords;
+    const int32_t* adj_ptr;
+    const int32_t* adj;
+    const int32_t* nbr_ptr;
+    const uint8_t* rank_t;
+    RowOut out;
+    const void* elem_param;
+    const void* src;
+    int wave_len;  // doubles of LDS per wave: row buffers, then d
+    void* K;
+    void* d;
+    unsigned long long* status;
+};
+
+// Mass and conduction without element data: lane (node, slot of its incidence list) forms its
+// element's geometry and its row over the 8 points in registers, and adds the row to the node's in
+// LDS.  Eight times the geometry of k_brick_scalar, but one launch, no workspace and nothing read
+// back: bound by the FP64 instructions (1717 a wave for conduction, VALU busy 70 %) at three waves
+// per SIMD; four spill (64^3 177 us against 126), and so does sharing the columns of J between the
+// points (30 % fewer instructions, 350 us).  Conduction 28^3 18 us, where the column kernel took 35.
+template <int FORM, typename T>
+__global__ void __launch_bounds__(256, 3) k_scalar_rows(ScalarParams p)
+{
+    constexpr int NPW = 8;
+    extern __shared__ __align__(16) double sh[];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int grp = lane % NPW, slot = lane / NPW;
+    const int waves = blockDim.x / kWave, n_nodes = (int)p.out.n_nodes;
+    const int v0 = ((int)xcd_block(blockIdx.x, gridDim.x) * waves + wave) * NPW, v = v0 + grp;
+    if (v0 >= n_nodes) return;
+    const int wbase = wave * p.wave_len;
+    double* dbuf = sh + wbase + p.wave_len - NPW;
+    const int vc = min(v, n_nodes), vn = min(v + 1, n_nodes);
+    const int a0 = p.adj_ptr[vc], a1 = p.adj_ptr[vn], P = p.nbr_ptr[vc], deg = p.nbr_ptr[vn] - P;
+    const int P0 = __shfl(P, 0), n_wave = __shfl(P + deg, NPW - 1) - P0;
+    const int base = wbase + P - P0;
+    int touched = 0;  // an element around the node has a constrained DOF
+    for (int t = lane; t < n_wave; t += kWave) sh[wbase + t] = 0.0;
+    if (lane < NPW) dbuf[lane] = 0.0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const T* src = (const T*)p.src;
+    for (int k = a0 + slot; k < a1; k += 8) {
+        const int code = p.adj[k];  // element * 8 + local node
+        const int a = code & 7;
+        const uint32_t e = (uint32_t)code >> 3;
+        const uint2 ranks = *(const uint2*)(p.rank_t + (int64_t)code * 8);
+        const double c = p.form.coef * (p.elem_param ? (double)((const T*)p.elem_param)[e] : 1.0);
+        double x[8][3], S[8], chk = c;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const uint32_t node = (uint32_t)p.conn[b * p.n_el + e];
+            if (p.out.mask) touched |= p.out.mask[node];
+#pragma unroll
+            for (int m = 0; m < 3; ++m) x[b][m] = p.coords[(int64_t)m * n_nodes + node];
+            S[b] = src ? (double)src[node] : 0.0;
+            chk += S[b];
+        }
+        double row[8], load = 0.0;
+        bool bad = false;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) row[b] = 0.0;
+#pragma unroll 1
+        for (int q = 0; q < 8; ++q) {
+            double J[3][3], C[3][3], u = 0.0;
+#pragma unroll
+            for (int m = 0; m < 3; ++m)
+#pragma unroll
+                for (int n = 0; n < 3; ++n) J[m][n] = 0.0;
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const double* g = kRefHex.dN[q][b];  // uniform: scalar loads
+#pragma unroll
+                for (int m = 0; m < 3; ++m)
+#pragma unroll
+                    for (int n = 0; n < 3; ++n) J[m][n] = fma(x[b][m], g[n], J[m][n]);
+                u = fma(kRefHex.N[q][b], S[b], u);
+            }
+            const double det = cofactors(J, C), N = brick_N(a, q);
+            bad |= !(det > 0.0);
+            if constexpr (FORM == MF_FORM_MASS) {
+                const double wN = det * c * N;
+                load = fma(wN, u, load);
+#pragma unroll
+                for (int b = 0; b < 8; ++b) row[b] = fma(wN, kRefHex.N[q][b], row[b]);
+            } else {
+                const double s = c / det;
+                double da[3], t[3], w[3];
+                brick_dN(a, q, da);
+#pragma unroll
+                for (int m = 0; m < 3; ++m) t[m] = s * (da[0] * C[0][m] + da[1] * C[1][m] + da[2] * C[2][m]);
+#pragma unroll
+                for (int n = 0; n < 3; ++n) w[n] = t[0] * C[n][0] + t[1] * C[n][1] + t[2] * C[n][2];
+                load = fma(det * N, u, load);
+#pragma unroll
+                for (int b = 0; b < 8; ++b) {
+                    const double* g = kRefHex.dN[q][b];
+                    row[b] = fma(w[0], g[0], fma(w[1], g[1], fma(w[2], g[2], row[b])));
+                }
+            }
+        }
+        if (bad) atomicMin(p.status, (unsigned long long)e);
+        if (!isfinite(chk)) atomicMin(p.status + 2, (unsigned long long)e);
+        if (!bad) {  // (such an element adds nothing)
+#pragma unroll
+            for (int b = 0; b < 8; ++b)
+                unsafeAtomicAdd(sh + base + (((b < 4 ? ranks.x : ranks.y) >> (8 * (b & 3))) & 0xff), row[b]);
+            unsafeAtomicAdd(dbuf + grp, load);
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (lane < NPW && v0 + lane < n_nodes) ((T*)p.d)[v0 + lane] = (T)(p.out.mask && p.out.mask[v0 + lane] ? 0.0 : dbuf[lane]);
+    if (p.out.mask && __any(touched)) eliminate<1, false, false>(p.out, v0, NPW, P0, n_wave, P, deg, v < n_nodes, sh + wbase, lane);
+    T* out = (T*)p.K + P0;
+    for (int t = lane; t < n_wave; t += kWave) __builtin_nontemporal_store((T)sh[wbase + t], out + t);
+}
+
+template <int FORM, typename T>
+mf_status launch_scalar_rows(const AssembleArgs& A)
+{
+    const mf_pattern_s* P = A.P;
+    ScalarParams p{};
+    p.form = *A.form;
+    p.n_el = P->n_elems;
+    p.conn = P->conn;
+    p.coords = A.coords;
+    p.adj_ptr = P->adj_ptr;
+    p.adj = P->adj;
+    p.nbr_ptr = P->nbr_ptr;
+    p.rank_t = P->rank_t;
+    p.out = {P->nbr, A.dirichlet, P->n_nodes, P->n_pairs};
+    p.elem_param = A.elem_param;
+    p.src = A.nodal_src;
+    p.wave_len = 8 * std::max(1, P->max_deg) + 8;  // at most 255 neighbours: 66 kB for four waves
+    p.K = A.K;
+    p.d = A.d;
+    p.status = P->status;
+    const size_t per_wave = sizeof(double) * (size_t)p.wave_len;
+    const int waves = 4 * per_wave <= 65536 ? 4 : 2;
+    const unsigned blocks = (unsigned)((P->n_nodes + waves * 8 - 1) / (waves * 8));
+    k_scalar_rows<FORM, T><<<blocks, waves * kWave, per_wave * waves, A.stream>>>(p);
+    MF_HIP(hipGetLastError());
+    return MF_OK;
+}
+
 template <typename T>
 BrickParams brick_params(const AssembleArgs& A, int64_t e0, int64_t e1, void* Ke, void* fe, uint8_t* emask)
 {
@@ -1225,12 +1381,23 @@ mf_status launch_rows(const AssembleArgs& A)
     return MF_OK;
 }
 
+// Rows with the geometry, in one launch without a workspace, against element blocks and their gather
+// (FP64, us): conduction 12^3 13 against 17, 28^3 18 against 36, 40^3 38 against 45, 48^3 58 against
+// 60, with Dirichlet rows 47 against 49 and 70 against 66, 64^3 126 against 120; FP32 40^3 39 against
+// 44, 48^3 the same; mass, with half the work, 48^3 45 against 57, 64^3 98 against 111, but FP32 120
+// against 104.  On a scattered mesh each of a node's elements reads its 24 coordinates from anywhere:
+// 24^3 27 against 31, 41x40x37 87 against 57.
+bool direct_wins(const AssembleArgs& A)
+{
+    return A.P->n_elems < (A.P->scattered ? 20000 : A.form->kind == MF_FORM_MASS ? 150000 : 70000);
+}
+
 template <typename T>
 mf_status dispatch_rows(const AssembleArgs& A)
 {
     switch (A.form->kind) {
-        case MF_FORM_MASS: return launch_scalar<MF_FORM_MASS, T>(A);
-        case MF_FORM_POISSON: return launch_scalar<MF_FORM_POISSON, T>(A);
+        case MF_FORM_MASS: return direct_wins(A) ? launch_scalar_rows<MF_FORM_MASS, T>(A) : launch_scalar<MF_FORM_MASS, T>(A);
+        case MF_FORM_POISSON: return direct_wins(A) ? launch_scalar_rows<MF_FORM_POISSON, T>(A) : launch_scalar<MF_FORM_POISSON, T>(A);
         case MF_FORM_ELASTICITY: return launch_rows<MF_FORM_ELASTICITY, T>(A);
         case MF_FORM_NS_SUPG: return launch_rows<MF_FORM_NS_SUPG, T>(A);
     }

@@ -93,13 +93,15 @@ def rowscaled_gpu(pat, K, Kref):
 
 
 # both sides of each line between the grid kernel and the rows, the last sizes of one and the
-# first of the other; nodes above and below the 30000 of the eight-nodes-per-wave gather; element
+# first of the other, and between rows with the geometry and element blocks; nodes above and below the 30000 of the eight-nodes-per-wave gather; element
 # records that go in two chunks; planes above and below 1 MB of records
 SIDES = [(O.NS_SUPG, 1, (21, 21, 22)), (O.NS_SUPG, 1, (22, 22, 21)), (O.NS_SUPG, 0, (3, 2, 4)),
          (O.ELASTICITY, 0, (27, 27, 27)), (O.ELASTICITY, 0, (28, 27, 27)), (O.POISSON, 0, (27, 27, 27)),
          (O.POISSON, 0, (28, 27, 27)), (O.MASS, 0, (32, 32, 30)), (O.POISSON, 1, (37, 37, 36)),
          (O.POISSON, 1, (37, 37, 37)), (O.POISSON, 0, (124, 123, 125)), (O.NS_SUPG, 1, (90, 88, 89)),
-         (O.ELASTICITY, 0, (38, 37, 15)), (O.NS_SUPG, 0, (40, 39, 1)), (O.NS_SUPG, 0, (25, 23, 9))]
+         (O.ELASTICITY, 0, (38, 37, 15)), (O.NS_SUPG, 0, (40, 39, 1)), (O.NS_SUPG, 0, (25, 23, 9)),
+         (O.POISSON, 0, (41, 41, 41)), (O.POISSON, 0, (42, 41, 41)), (O.POISSON, 1, (42, 41, 41)),
+         (O.MASS, 0, (53, 53, 53)), (O.MASS, 0, (54, 53, 53)), (O.MASS, 1, (54, 53, 53))]
 
 
 @pytest.mark.parametrize("numbering", [0, 1])
@@ -120,11 +122,12 @@ def test_rows_agree_with_scatter(mf, kind, prec, n, numbering):
 @pytest.mark.parametrize("masked", [False, True], ids=["free", "dirichlet"])
 @pytest.mark.parametrize("prec", [0, 1], ids=["f64", "f32"])
 @pytest.mark.parametrize("numbering", [0, 1])
-@pytest.mark.parametrize("kind", [O.ELASTICITY, O.NS_SUPG])
-def test_scattered_numbering(mf, kind, numbering, prec, masked):
+@pytest.mark.parametrize("kind,n", [(O.ELASTICITY, (22, 21, 20)), (O.NS_SUPG, (22, 21, 20)), (O.POISSON, (22, 21, 20)),
+                                    (O.POISSON, (29, 28, 27)), (O.MASS, (29, 28, 27))])
+def test_scattered_numbering(mf, kind, n, numbering, prec, masked):
     """Random numbering of enough elements for records by elements, against the scatter."""
-    say("scattered", kind, numbering, prec, masked)
-    mesh = W.permute_mesh(W.structured_mesh((22, 21, 20), jitter=0.2, seed=3), 4)[0]
+    say("scattered", kind, n, numbering, prec, masked)
+    mesh = W.permute_mesh(W.structured_mesh(n, jitter=0.2, seed=3), 4)[0]
     first = mesh.n_elems * np.ones(mesh.n_nodes, np.int64)  # each node's first element
     np.minimum.at(first, mesh.conn.ravel(), np.tile(np.arange(mesh.n_elems), 8))
     assert (np.abs(np.diff(first)) > 1024).sum() > mesh.n_nodes // 4
