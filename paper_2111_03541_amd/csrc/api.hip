@@ -51,19 +51,23 @@ mf_status mf::status_of(const unsigned long long (&v)[3], int64_t* first_bad_ele
 using namespace mf;
 
 // On a small structured grid the one launch of the column kernel beats the two of the elasticity
-// and flow rows (FP64, column against rows: elasticity 24^3 32 us against 33, 28^3 46 against 43,
-// 64^3 356 against 320).  The rows sum in FP64 also in FP32 builds, where the column kernel's
-// traffic halves: elasticity 48^3 124 against 116, but 64^3 262 against 289 and 32^3 46 against 52;
-// the flow form (matrix cores in the column kernel) 20^3 50 against 55, 24^3 76 against 63, 48^3
-// 431 against 404.  The scalar rows are one launch too (conduction 8^3 13 us both ways, 20^3 14
-// against 18, 28^3 18 against 35).
+// and flow rows, whose Dirichlet elimination costs less (column against rows in us, then with
+// constrained sides).  FP64 elasticity 20^3 24 against 29, 29 against 34; 24^3 35 both ways, 42
+// against 40; 28^3 47 against 50, 60 against 58; 36^3 87 against 80; 64^3 352 against 304, 422
+// against 373.  The rows sum in FP64 also in FP32 builds, where the column kernel's traffic halves:
+// elasticity 32^3 46 against 58, 68 against 70; 40^3 79 against 91, 117 against 119; 44^3 106 against
+// 102, 152 against 130; 64^3 262 against 257, 370 against 322.  The flow form in FP32 (matrix cores
+// in the column kernel) 20^3 51 against 57, 24^3 76 against 71, 48^3 431 against 368.  The scalar
+// rows are one launch too (conduction 8^3 13 us both ways, 20^3 14 against 18, 28^3 18 against 35).
 static bool column_wins(const AssembleArgs& A)
 {
     if (!A.P->is_grid || A.P->dim != 3) return false;
     const bool f32 = A.prec == MF_F32;
     switch (A.form->kind) {
         case MF_FORM_NS_SUPG: return f32 && A.P->n_elems < 10000;  // FP64: no column kernel
-        case MF_FORM_ELASTICITY: return f32 || A.P->n_elems < 20000;
+        case MF_FORM_ELASTICITY:
+            if (A.dirichlet) return A.P->n_elems < (f32 ? 45000 : 13000);
+            return A.P->n_elems < (f32 ? 80000 : 32000);
         default: return false;
     }
 }

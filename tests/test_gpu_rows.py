@@ -101,7 +101,9 @@ SIDES = [(O.NS_SUPG, 1, (21, 21, 22)), (O.NS_SUPG, 1, (22, 22, 21)), (O.NS_SUPG,
          (O.POISSON, 1, (37, 37, 37)), (O.POISSON, 0, (124, 123, 125)), (O.NS_SUPG, 1, (90, 88, 89)),
          (O.ELASTICITY, 0, (38, 37, 15)), (O.NS_SUPG, 0, (40, 39, 1)), (O.NS_SUPG, 0, (25, 23, 9)),
          (O.POISSON, 0, (41, 41, 41)), (O.POISSON, 0, (42, 41, 41)), (O.POISSON, 1, (42, 41, 41)),
-         (O.MASS, 0, (53, 53, 53)), (O.MASS, 0, (54, 53, 53)), (O.MASS, 1, (54, 53, 53))]
+         (O.MASS, 0, (53, 53, 53)), (O.MASS, 0, (54, 53, 53)), (O.MASS, 1, (54, 53, 53)),
+         (O.ELASTICITY, 0, (23, 23, 23)), (O.ELASTICITY, 0, (24, 23, 24)), (O.ELASTICITY, 1, (35, 35, 36)),
+         (O.ELASTICITY, 1, (36, 36, 35)), (O.ELASTICITY, 1, (62, 66, 61))]
 
 
 @pytest.mark.parametrize("numbering", [0, 1])
