@@ -24,10 +24,10 @@
 //   k_mg_restrict  one thread per coarse node and field gathers its 27 fine neighbours and
 //                  makes the coarse level's first sweep
 //   k_mg_prolong   one thread per fine node and field interpolates from its 1 to 8 parents
-//   k_mg_coarse    the coarsest level in one workgroup, the iterate in LDS, all sweeps in
-//                  one launch, rows cached in registers when there are at most 256 (levels
-//                  of more than kCoarseMax rows use k_mg_sweep); scalar levels of at most
-//                  1024 rows with one row per thread (k_mg_coarse_stencil)
+//   k_mg_coarse    the coarsest level in one workgroup, the iterate in LDS and the rows in
+//                  registers, all sweeps in one launch (at most 256 rows; scalar levels,
+//                  k_mg_coarse_stencil, one of at most 1024 rows per thread); on more rows
+//                  the sweeps are launches
 // Sweeps alternate between two buffers per level; the first one is chosen so that the last
 // sweep writes the level's output and no copy is needed.
 #include <hip/hip_runtime.h>
@@ -78,7 +78,6 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kMaxBlocks = 8192;
-constexpr int kCoarseMax = 4096;      // rows of a coarsest level solved in one workgroup
 constexpr int kCoarseThreads = 1024;
 constexpr int kCoarseLanes = 4;       // lanes per row in the coarsest-level kernel
 __device__ __forceinline__ int64_t dof_of(int64_t node, int f, int64_t n_nodes, int nf, int fm)
@@ -475,13 +474,11 @@ __global__ void __launch_bounds__(kThreads) k_mg_prolong(GridDofs F, GridDofs C,
 }
 
 // The coarsest level: `sweeps` damped Jacobi sweeps from x = 0 in one workgroup, the
-// iterate alternating between two LDS arrays (n <= kCoarseMax), kCoarseLanes lanes per row.
-// CACHED (n <= kCoarseGroups, rows of at most kCoarseLanes * kCoarseCache entries): each
-// row group keeps its row's entries and columns in registers for all sweeps, so a sweep
-// reads only LDS; otherwise the entries are read from memory (L2) every sweep.
+// iterate alternating between two LDS arrays, kCoarseLanes lanes per row (n <= kCoarseGroups,
+// rows of at most kCoarseLanes * kCoarseCache entries): each row group keeps its row's entries
+// and columns in registers for all sweeps, so a sweep reads only LDS.
 constexpr int kCoarseGroups = kCoarseThreads / kCoarseLanes;
 constexpr int kCoarseCache = 32;
-template <bool CACHED>
 __global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse(int n, const int32_t* __restrict__ rp,
                                                               const int32_t* __restrict__ ci,
                                                               const double* __restrict__ A,
@@ -489,56 +486,38 @@ __global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse(int n, const int32
                                                               const double* __restrict__ b, double* __restrict__ x,
                                                               double omega, int sweeps)
 {
-    __shared__ double xs[2][kCoarseMax];
+    __shared__ double xs[2][kCoarseGroups];
     const int lane = threadIdx.x % kCoarseLanes;
-    const int group = threadIdx.x / kCoarseLanes;
+    const int row = threadIdx.x / kCoarseLanes;  // one row per group
     if (sweeps <= 0) {
         for (int i = threadIdx.x; i < n; i += kCoarseThreads) x[i] = 0.0;
         return;
     }
     for (int i = threadIdx.x; i < n; i += kCoarseThreads) xs[0][i] = omega * dinv[i] * b[i];
     int cur = 0;
-    if (CACHED) {
-        const int row = group;  // n <= kCoarseGroups: one row per group
-        const bool live = row < n;
-        double a[kCoarseCache];
-        int c[kCoarseCache];
-        const int k0 = live ? rp[row] : 0, k1 = live ? rp[row + 1] : 0;
+    const bool live = row < n;
+    double a[kCoarseCache];
+    int c[kCoarseCache];
+    const int k0 = live ? rp[row] : 0, k1 = live ? rp[row + 1] : 0;
 #pragma unroll
-        for (int t = 0; t < kCoarseCache; ++t) {
-            const int k = k0 + lane + t * kCoarseLanes;
-            const bool in = k < k1;
-            a[t] = in ? A[k] : 0.0;
-            c[t] = in ? ci[k] : 0;  // a padded slot reads x[0] with weight 0
-        }
-        const double di = live ? omega * dinv[row] : 0.0, bi = live ? b[row] : 0.0;
+    for (int t = 0; t < kCoarseCache; ++t) {
+        const int k = k0 + lane + t * kCoarseLanes;
+        const bool in = k < k1;
+        a[t] = in ? A[k] : 0.0;
+        c[t] = in ? ci[k] : 0;  // a padded slot reads x[0] with weight 0
+    }
+    const double di = live ? omega * dinv[row] : 0.0, bi = live ? b[row] : 0.0;
+    __syncthreads();
+    for (int s = 1; s < sweeps; ++s) {
+        const double* xi = xs[cur];
+        double acc = 0.0;
+#pragma unroll
+        for (int t = 0; t < kCoarseCache; ++t) acc = fma(a[t], xi[c[t]], acc);
+#pragma unroll
+        for (int off = kCoarseLanes / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kCoarseLanes);
+        if (live && lane == 0) xs[cur ^ 1][row] = xi[row] + di * (bi - acc);
         __syncthreads();
-        for (int s = 1; s < sweeps; ++s) {
-            const double* xi = xs[cur];
-            double acc = 0.0;
-#pragma unroll
-            for (int t = 0; t < kCoarseCache; ++t) acc = fma(a[t], xi[c[t]], acc);
-#pragma unroll
-            for (int off = kCoarseLanes / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kCoarseLanes);
-            if (live && lane == 0) xs[cur ^ 1][row] = xi[row] + di * (bi - acc);
-            __syncthreads();
-            cur ^= 1;
-        }
-    } else {
-        __syncthreads();
-        for (int s = 1; s < sweeps; ++s) {
-            const double* xi = xs[cur];
-            double* xo = xs[cur ^ 1];
-            for (int row = group; row < n; row += kCoarseGroups) {
-                double acc = 0.0;
-                for (int k = rp[row] + lane; k < rp[row + 1]; k += kCoarseLanes) acc = fma(A[k], xi[ci[k]], acc);
-#pragma unroll
-                for (int off = kCoarseLanes / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kCoarseLanes);
-                if (lane == 0) xo[row] = xi[row] + omega * dinv[row] * (b[row] - acc);
-            }
-            __syncthreads();
-            cur ^= 1;
-        }
+        cur ^= 1;
     }
     for (int i = threadIdx.x; i < n; i += kCoarseThreads) x[i] = xs[cur][i];
 }
@@ -662,13 +641,14 @@ void vcycle(const mf_mg_s* mg, int l, const double* b, double* out, bool swept, 
         static_assert(27 * 4 <= kCoarseLanes * kCoarseCache, "row cache too small");
         if (Lv.eval && Lv.n_rows <= kCoarseThreads) {
             k_mg_coarse_stencil<<<1, ((unsigned)Lv.n_rows + 63) / 64 * 64, 0, s>>>(Lv.st, Lv.dinv, b, out, omega, cs);
-        } else if (Lv.n_rows <= kCoarseGroups) {
-            k_mg_coarse<true><<<1, kCoarseThreads, 0, s>>>((int)Lv.n_rows, Lv.Pv->row_ptr, Lv.Pv->col_idx, Lv.Kv,
-                                                           Lv.dinv, b, out, omega, cs);
-        } else if (Lv.n_rows <= kCoarseMax) {
-            k_mg_coarse<false><<<1, kCoarseThreads, 0, s>>>((int)Lv.n_rows, Lv.Pv->row_ptr, Lv.Pv->col_idx, Lv.Kv,
-                                                            Lv.dinv, b, out, omega, cs);
+        } else if (!Lv.eval && Lv.n_rows <= kCoarseGroups) {
+            k_mg_coarse<<<1, kCoarseThreads, 0, s>>>((int)Lv.n_rows, Lv.Pv->row_ptr, Lv.Pv->col_idx, Lv.Kv, Lv.dinv, b,
+                                                     out, omega, cs);
         } else {
+            // rows that one workgroup cannot keep in registers: a launch per sweep, 20 of them about
+            // 70 us (scalar and flow) or 100 (elasticity) at any of these sizes, where one
+            // workgroup that reads the rows again in every sweep took 121 us for 320 flow rows,
+            // 303 for 864 and 1055 for 2916, 146 for 1210 scalar rows and 482 for 4096
             double* cur = nullptr;
             double* first = (cs % 2 == 1) ? out : Lv.t;  // the last of cs sweeps writes out
             sweeps(Lv, nf, b, &cur, first, first == out ? Lv.t : out, cs, omega, &back, s);
@@ -941,10 +921,9 @@ extern "C" mf_status mf_mg_create(const mf_pattern_t* P, const mf_mg_opts* opts,
         mf_mg_s::Level& Lv = mg->L[l];
         Lv.node_cols = P->nf == 4 && !mg->fm && Lv.Pv->nnz == 16 * Lv.Pv->n_pairs;
     }
-    // scalar levels as stencils, but for a coarsest one that goes in one workgroup from CSR rows
+    // scalar levels as stencils
     for (int l = 0; l < n && st == MF_OK && P->nf == 1; ++l) {
         mf_mg_s::Level& Lv = mg->L[l];
-        if (l == n - 1 && Lv.n_rows > kCoarseThreads && Lv.n_rows <= kCoarseMax) break;
         Lv.eval = (double*)dalloc(sizeof(double) * 27 * (size_t)Lv.n_rows);
         if (!Lv.eval) {
             st = set_error(MF_ERR_OOM, "multigrid workspace allocation failed");
