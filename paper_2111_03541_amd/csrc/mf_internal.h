@@ -38,7 +38,9 @@ struct mf_pattern_s {
     char* ws = nullptr;
     size_t ws_bytes = 0;
     hipEvent_t ws_done = nullptr;
-    std::mutex ws_mu;  // held from a call's first kernel that uses the workspace to its last
+    // held from a call's first kernel that uses the workspace to its last, and while the
+    // colouring is made
+    std::mutex ws_mu;
     // workspaces of captured calls: one for each capture and stream in it
     struct Captured {
         char* p;

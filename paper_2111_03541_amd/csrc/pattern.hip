@@ -524,6 +524,7 @@ mf_status build_pattern(mf_pattern_s* P, const int32_t* conn_in, hipStream_t s)
 mf_status ensure_coloring(const mf_pattern_s* Pc)
 {
     mf_pattern_s* P = const_cast<mf_pattern_s*>(Pc);
+    const std::lock_guard<std::mutex> lock(P->ws_mu);  // (no caller holds a Workspace)
     if (P->color_elems || P->n_elems == 0) return MF_OK;
     // copies on a stream of its own: the caller's may be in capture (conn is complete since the
     // pattern was made)
