@@ -355,7 +355,11 @@ typedef struct {
  * edges: face_id 2 * axis + side as for hexahedra, 2 or 3 Gauss points along the edge,
  * 1 or 2 fields, sigma^l the leading 2x2 block of value[0..9)); MF_ERR_UNSUPPORTED
  * otherwise.
- * Queued on the stream without waiting on the host.  Reported by
+ * Queued on the stream without waiting on the host, but that a call whose faces need a larger
+ * workspace than the pattern has waits for the last one that used it.  Calls on other streams
+ * and threads take the workspace in turn, captured calls have their own (see mf_scatter); past
+ * the eighth capture the forms on 8-node hexahedra share one, and replays of those graphs must
+ * not overlap.  Reported by
  * mf_status_poll (until the next mf_assemble clears the status): a face whose element id
  * or local face is out of range (skipped; MF_ERR_ARG with the first such face), and a
  * degenerate face (zero area) or element (det J <= 0, flux form; MF_ERR_BAD_JACOBIAN).

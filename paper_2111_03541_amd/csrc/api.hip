@@ -90,7 +90,8 @@ static void free_pattern(mf_pattern_s* P)
     (void)hipFree(P->status);
     (void)hipFree(P->color_elems);
     (void)hipFree(P->elem_color);
-    (void)hipFree(P->face_elem_work);
+    (void)hipFree(P->color_at);
+    (void)hipFree(P->shared_faces);
     delete P;
 }
 

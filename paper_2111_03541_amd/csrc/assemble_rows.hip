@@ -59,7 +59,8 @@ Workspace::Workspace(const mf_pattern_s* Pc, size_t bytes, hipStream_t stream)
                 p = w.p;
                 return;
             }
-        if (P->cap_ws.size() >= kCaptured) return;
+        full = P->cap_ws.size() >= kCaptured;
+        if (full) return;
         RelaxedCapture relaxed;
         p = alloc();
         if (p) P->cap_ws.push_back({p, bytes, id, s});

@@ -1127,7 +1127,8 @@ mf_status launch_faces(BParams p, const mf_pattern_s* P, hipStream_t s, bool* do
 // 8-node hexahedra: mark the listed faces per element, then one launch per element
 // colour (elements of a colour share no node, so each row is added by one thread of the
 // launch, and the colours follow each other in the stream: the sums do not depend on
-// the run, and nothing waits on the host)
+// the run).  The face lists are in the pattern's workspace; past kCaptured captures in one buffer
+// that those captured calls share.
 template <int NF, typename T>
 mf_status launch_boundary(BParams p, const mf_pattern_s* Pc, hipStream_t s)
 {
@@ -1136,34 +1137,24 @@ mf_status launch_boundary(BParams p, const mf_pattern_s* Pc, hipStream_t s)
     mf_status st = ensure_coloring(P);
     if (st != MF_OK) return st;
     const int n_col = (int)P->color_ptr.size() - 1;
-    // workspace: mask [n_el], counts [6 n_el], colour lists [n_el], list lengths [n_col],
-    // colour offsets (int64) [n_col + 1]
+    // workspace: mask [n_el], counts [6 n_el], colour lists [n_el], list lengths [n_col]
     const int64_t n_el = P->n_elems;
-    const int64_t words = 8 * n_el + n_col + 2 * (n_col + 1) + 2;
-    if (!P->face_elem_work) {
-        // on a stream of its own: the caller's may be in capture
-        SideStream side;
-        MF_HIP(side.status);
-        uint32_t* w = nullptr;
-        MF_HIP(hipMalloc(&w, sizeof(uint32_t) * (size_t)words));
-        int64_t* at = (int64_t*)(w + 8 * n_el + n_col + ((8 * n_el + n_col) & 1));
-        hipError_t err = hipMemcpyAsync(at, P->color_ptr.data(), sizeof(int64_t) * (n_col + 1), hipMemcpyHostToDevice, side.s);
-        if (err == hipSuccess) err = hipStreamSynchronize(side.s);
-        if (err != hipSuccess) {
-            (void)hipFree(w);
-            return hip_error(err, "colour offsets");
-        }
-        P->face_elem_work = w;
+    const size_t bytes = sizeof(uint32_t) * (size_t)(8 * n_el + n_col);
+    const Workspace held(P, bytes, s);
+    uint32_t* mask = (uint32_t*)held.p;
+    if (held.full) {
+        const RelaxedCapture relaxed;
+        if (!P->shared_faces) MF_HIP(hipMalloc(&P->shared_faces, bytes));
+        mask = P->shared_faces;
     }
-    uint32_t* mask = P->face_elem_work;
+    if (!mask) return set_error(MF_ERR_OOM, "no memory for the boundary faces' workspace");
     uint32_t* cnt = mask + n_el;
     int32_t* clist = (int32_t*)(cnt + 6 * n_el);
     uint32_t* ccount = (uint32_t*)(clist + n_el);
-    const int64_t* cptr = (const int64_t*)(P->face_elem_work + 8 * n_el + n_col + ((8 * n_el + n_col) & 1));
     k_face_zero<<<(unsigned)((7 * n_el + kThreads - 1) / kThreads), kThreads, 0, s>>>(mask, 7 * n_el);
     k_face_zero<<<(unsigned)((n_col + kThreads - 1) / kThreads), kThreads, 0, s>>>(ccount, n_col);
     k_face_mark<<<(unsigned)((p.n_faces + kThreads - 1) / kThreads), kThreads, 0, s>>>(
-        p.face_elem, p.face_id, p.n_faces, n_el, P->elem_color, cptr, mask, cnt, clist, ccount, P->status);
+        p.face_elem, p.face_id, p.n_faces, n_el, P->elem_color, P->color_at, mask, cnt, clist, ccount, P->status);
     p.face_mask = mask;
     p.face_cnt = cnt;
     for (int c = 0; c < n_col; ++c) {

@@ -56,9 +56,9 @@ struct mf_pattern_s {
     int32_t* color_elems = nullptr;  // device [n_elems]
     int32_t* elem_color = nullptr;   // device [n_elems]: colour of each element
     std::vector<int64_t> color_ptr;
-    // 8-node hexahedra, faces per element of the colour-by-colour scatter (boundary.hip): mask
-    // [n_elems], counts [n_elems][6], colour lists
-    uint32_t* face_elem_work = nullptr;
+    int64_t* color_at = nullptr;  // device copy of color_ptr
+    // face lists (boundary.hip) of the captured calls that come after kCaptured captures
+    uint32_t* shared_faces = nullptr;
     // structured lexicographic grid detection
     int is_grid = 0;
     int64_t gx = 0, gy = 0, gz = 0;
@@ -155,6 +155,7 @@ struct Workspace {
     std::unique_lock<std::mutex> lock;
     char* p = nullptr;
     bool record = false;
+    bool full = false;  // kCaptured captures have one: that is why p is nullptr
     Workspace(const mf_pattern_s* P, size_t bytes, hipStream_t stream);
     ~Workspace();
     Workspace(const Workspace&) = delete;

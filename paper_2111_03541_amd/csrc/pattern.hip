@@ -570,8 +570,12 @@ mf_status ensure_coloring(const mf_pattern_s* Pc)
     for (int64_t e = 0; e < n_el; ++e) order[(size_t)at[(size_t)color[(size_t)e]]++] = (int32_t)e;
     int32_t* dev = nullptr;
     int32_t* ecol = nullptr;
-    MF_HIP(hipMalloc(&dev, sizeof(int32_t) * (size_t)n_el));
-    hipError_t err = hipMalloc(&ecol, sizeof(int32_t) * (size_t)n_el);
+    int64_t* at_dev = nullptr;
+    const size_t at_bytes = sizeof(int64_t) * P->color_ptr.size();
+    hipError_t err = hipMalloc(&dev, sizeof(int32_t) * (size_t)n_el);
+    if (err == hipSuccess) err = hipMalloc(&ecol, sizeof(int32_t) * (size_t)n_el);
+    if (err == hipSuccess) err = hipMalloc(&at_dev, at_bytes);
+    if (err == hipSuccess) err = hipMemcpyAsync(at_dev, P->color_ptr.data(), at_bytes, hipMemcpyHostToDevice, s);
     if (err == hipSuccess)
         err = hipMemcpyAsync(dev, order.data(), sizeof(int32_t) * (size_t)n_el, hipMemcpyHostToDevice, s);
     if (err == hipSuccess)
@@ -580,11 +584,13 @@ mf_status ensure_coloring(const mf_pattern_s* Pc)
     if (err != hipSuccess) {
         (void)hipFree(dev);
         (void)hipFree(ecol);
+        (void)hipFree(at_dev);
         P->color_ptr.clear();
         return hip_error(err, "colour upload");
     }
     P->color_elems = dev;
     P->elem_color = ecol;
+    P->color_at = at_dev;
     return MF_OK;
 }
 
