@@ -154,8 +154,10 @@ typedef struct { int32_t points_per_axis; } mf_quadrature;   /* Gauss-Legendre: 
    element-parallel scatter with hardware atomics in one launch (the paper's scheme).  In
    ATOMIC and in the column kernel (which sums a node's element blocks with LDS atomics) the
    order of the additions, and so the last bits, may vary between runs.  GATHER asks for
-   an owner-computes kernel.  A pattern keeps a workspace for the element data (at most
-   1 GiB or half of K) and up to eight more for calls that were captured. */
+   an owner-computes kernel.  A pattern keeps a workspace and up to eight more for calls that
+   were captured.  It holds the element data: in FP64 at most 1 GiB or half of K, in FP32, where
+   all of it is there at once so that sums are rounded once, up to about three times K; or the
+   rows of the faces of a boundary form. */
 typedef enum { MF_SCATTER_AUTO = 0, MF_SCATTER_ATOMIC = 1, MF_SCATTER_GATHER = 2 } mf_scatter;
 
 /*

@@ -14,8 +14,9 @@
 //     the first kernel stores only the geometry (and the flow state) of the 8 Gauss points,
 //     and the wave that owns the node forms the products.
 //
-// Workspaces are bounded: elements go in chunks of ascending id, and a node whose incidence
-// list spans several chunks adds onto its rows from the chunk before.
+// Workspaces are bounded in FP64: elements go in chunks of ascending id, and a node whose incidence
+// list spans several chunks adds onto its rows from the chunk before.  FP32 rows are summed in FP64
+// and rounded once, so all elements are one chunk.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -101,6 +102,8 @@ Workspace::~Workspace()
 
 int64_t ws_chunk_elems(const mf_pattern_s* P, size_t bytes_per_elem, size_t value_bytes)
 {
+    // (FP32: a node whose elements span two chunks would round its sums between them)
+    if (value_bytes < sizeof(double)) return P->n_elems;
     const size_t cap = std::max<size_t>((size_t)1 << 30, (size_t)P->nnz * value_bytes / 2);
     const int64_t n = std::max<int64_t>(1, (int64_t)(cap / bytes_per_elem));
     return std::min<int64_t>(P->n_elems, n);

@@ -35,7 +35,7 @@ struct ElemMask {
     }
 };
 
-// Elements per chunk of the workspace for records of bytes_per_elem.
+// Elements per chunk of the workspace for records of bytes_per_elem, for K of value_bytes an entry.
 int64_t ws_chunk_elems(const mf_pattern_s* P, size_t bytes_per_elem, size_t value_bytes);
 
 // Whether the row buffers of gather_blocks fit the LDS (not with hundreds of neighbours a node).
