@@ -154,8 +154,9 @@ typedef struct { int32_t points_per_axis; } mf_quadrature;   /* Gauss-Legendre: 
    element-parallel scatter with hardware atomics in one launch (the paper's scheme).  In
    ATOMIC and in the column kernel (which sums a node's element blocks with LDS atomics) the
    order of the additions, and so the last bits, may vary between runs.  GATHER asks for
-   an owner-computes kernel.  A pattern keeps a workspace and up to eight more for calls that
-   were captured.  It holds the element data: in FP64 at most 1 GiB or half of K, in FP32, where
+   an owner-computes kernel.  A pattern keeps a workspace, and others for the calls of the first
+   eight captures that it takes part in, until it is destroyed; assemblies captured later go as
+   without memory for a workspace.  It holds the element data: in FP64 at most 1 GiB or half of K, in FP32, where
    all of it is there at once so that sums are rounded once, up to about three times K; or the
    rows of the faces of a boundary form. */
 typedef enum { MF_SCATTER_AUTO = 0, MF_SCATTER_ATOMIC = 1, MF_SCATTER_GATHER = 2 } mf_scatter;
@@ -366,8 +367,9 @@ typedef struct {
  * or local face is out of range (skipped; MF_ERR_ARG with the first such face), and a
  * degenerate face (zero area) or element (det J <= 0, flux form; MF_ERR_BAD_JACOBIAN).
  * Errors: MF_ERR_ARG (a form/field-count mismatch or bad arguments), MF_ERR_UNSUPPORTED
- * (an element type the boundary kernels do not cover, or the flux and flow forms on
- * anything but 8-node hexahedra), MF_ERR_HIP.  Two calls with the same inputs give the
+ * (an element type the boundary kernels do not cover, the flux and flow forms on
+ * anything but 8-node hexahedra, or, on anything but those, a call in a ninth capture on the
+ * pattern: the capture goes on without it), MF_ERR_OOM, MF_ERR_HIP.  Two calls with the same inputs give the
  * same bits: face rows are summed node by node in a fixed order (the flow forms: element
  * colour by element colour).
  */

@@ -60,7 +60,11 @@ Workspace::Workspace(const mf_pattern_s* Pc, size_t bytes, hipStream_t stream)
                 p = w.p;
                 return;
             }
-        full = P->cap_ws.size() >= kCaptured;
+        // (a capture may hold several: other streams, a later and larger call)
+        std::vector<unsigned long long> others;
+        for (const auto& w : P->cap_ws)
+            if (w.id != id && std::find(others.begin(), others.end(), w.id) == others.end()) others.push_back(w.id);
+        full = others.size() >= kCaptured;
         if (full) return;
         RelaxedCapture relaxed;
         p = alloc();

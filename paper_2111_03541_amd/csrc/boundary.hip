@@ -1088,6 +1088,11 @@ mf_status launch_faces(BParams p, const mf_pattern_s* P, hipStream_t s, bool* do
     const Workspace held(P, rows_at + rows, s);
     char* ws = held.p;
     *done = ws != nullptr;
+    if (held.full && (DIM != 3 || NEN != 8))
+        return set_error(MF_ERR_UNSUPPORTED,
+                         "captured boundary forms on one pattern: %d captures have a workspace (until the pattern is "
+                         "destroyed), and this form has no other way",
+                         (int)Workspace::kCaptured);
     if (!ws) return MF_OK;
     uint32_t* cnt = (uint32_t*)ws;
     uint32_t* node_on = cnt + keys;

@@ -41,7 +41,7 @@ struct mf_pattern_s {
     // held from a call's first kernel that uses the workspace to its last, and while the
     // colouring is made
     std::mutex ws_mu;
-    // workspaces of captured calls: one for each capture and stream in it
+    // workspaces of captured calls: at least one for each capture and stream in it
     struct Captured {
         char* p;
         size_t bytes;
@@ -147,7 +147,9 @@ mf_status assemble_column(const AssembleArgs& a);
 mf_status assemble_rows(const AssembleArgs& a);
 // The pattern's workspace of at least `bytes` for kernels queued on the stream during its
 // lifetime (calls that are being captured get one of their own).  p is nullptr when there is
-// no memory for it, or kCaptured captures have one already.
+// no memory for it, or kCaptured captures have one already.  Those stay until the pattern goes: a
+// graph may be replayed for as long, and nothing that HIP offers tells when it no longer can be (a
+// user object of the graph is not kept by an executable graph that was updated from it).
 struct Workspace {
     static constexpr size_t kCaptured = 8;
     mf_pattern_s* P;
@@ -155,7 +157,7 @@ struct Workspace {
     std::unique_lock<std::mutex> lock;
     char* p = nullptr;
     bool record = false;
-    bool full = false;  // kCaptured captures have one: that is why p is nullptr
+    bool full = false;  // kCaptured other captures have one: that is why p is nullptr
     Workspace(const mf_pattern_s* P, size_t bytes, hipStream_t stream);
     ~Workspace();
     Workspace(const Workspace&) = delete;

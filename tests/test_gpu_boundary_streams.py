@@ -6,8 +6,10 @@ import threading
 import numpy as np
 import pytest
 
+import oracle as O
 import oracle.boundary as OB
 import workloads as W
+from helpers import TOL
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -76,3 +78,44 @@ def test_captured_flow_forms(mf):
         graphs[k].replay()
         torch.cuda.synchronize()
         assert torch.equal(K, want[k % 2][0]) and torch.equal(d, want[k % 2][1]), k
+
+
+@pytest.mark.parametrize("elem", ["tet10", "quad8"])
+def test_ninth_capture(mf, elem):
+    """Assembly and then faces enough for a larger workspace, in eight captures; a ninth refuses the
+    boundary form, names the captures as the reason and stays a capture."""
+    say("nine captures", elem)
+    mesh = W.tet10_mesh((2, 2, 2), jitter=0.1, seed=2) if elem == "tet10" else W.serendipity_mesh_2d((6, 5), jitter=0.1, seed=2)
+    keys = np.arange(4 * mesh.n_elems)
+    fe, fi = cuda((keys // 4).astype(np.int32)), cuda((keys % 4).astype(np.uint8))
+    pat, coords = mf.Pattern(cuda(mesh.conn), mesh.n_nodes, mesh.dim, 1), cuda(mesh.coords)
+    form = mf.Form(O.POISSON, coef=1.3)
+    K = torch.empty(pat.nnz, dtype=torch.float64, device="cuda")
+    d = torch.empty(pat.n_rows, dtype=torch.float64, device="cuda")
+
+    def system(K, d):
+        pat.assemble(form, coords, K=K, d=d)
+        pat.assemble_boundary(OB.CONVECTION, coords, fe, fi, coef=2.0, value=[0.3], K=K, d=d)
+
+    torch.cuda.synchronize()
+    graphs = [torch.cuda.CUDAGraph() for _ in range(9)]
+    for g in graphs[:8]:
+        with torch.cuda.graph(g):
+            system(K, d)
+    with torch.cuda.graph(graphs[8]):
+        pat.assemble(form, coords, K=K, d=d)
+        with pytest.raises(mf.MFError, match="8 captures") as err:
+            pat.assemble_boundary(OB.CONVECTION, coords, fe, fi, coef=2.0, value=[0.3], K=K, d=d)
+    assert err.value.status == mf.ERR_UNSUPPORTED
+    Kr, dr = torch.empty_like(K), torch.empty_like(d)
+    system(Kr, dr)
+    Kd, dd = pat.assemble(form, coords)
+    for k in (0, 8, 7, 0, 8, 3):
+        system(Kd.clone(), dd.clone())
+        K.fill_(-1.0)
+        d.fill_(-1.0)
+        graphs[k].replay()
+        torch.cuda.synchronize()
+        a, b = (Kd, dd) if k == 8 else (Kr, dr)
+        assert float((K - a).abs().max()) <= TOL[0] * float(a.abs().max()), k
+        assert float((d - b).abs().max()) <= TOL[0] * float(dr.abs().max()), k
