@@ -71,6 +71,8 @@ Workspace::Workspace(const mf_pattern_s* Pc, size_t bytes, hipStream_t stream)
         if (p) P->cap_ws.push_back({p, bytes, id, s});
         return;
     }
+    // (the thread may be capturing another stream, which an allocation would end)
+    const RelaxedCapture relaxed;
     if (!P->ws_done && hipEventCreateWithFlags(&P->ws_done, hipEventDisableTiming) != hipSuccess) {
         (void)hipGetLastError();
         P->ws_done = nullptr;
