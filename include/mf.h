@@ -156,9 +156,8 @@ typedef struct { int32_t points_per_axis; } mf_quadrature;   /* Gauss-Legendre: 
    order of the additions, and so the last bits, may vary between runs.  GATHER asks for
    an owner-computes kernel.  A pattern keeps a workspace, and others for the calls of the first
    eight captures that it takes part in, until it is destroyed; assemblies captured later go as
-   without memory for a workspace.  It holds the element data: in FP64 at most 1 GiB or half of K, in FP32, where
-   all of it is there at once so that sums are rounded once, up to about three times K; or the
-   rows of the faces of a boundary form. */
+   without memory for a workspace.  It holds the data of all elements (up to about three times the size of K),
+   or the rows of the faces of a boundary form. */
 typedef enum { MF_SCATTER_AUTO = 0, MF_SCATTER_ATOMIC = 1, MF_SCATTER_GATHER = 2 } mf_scatter;
 
 /*

@@ -194,8 +194,7 @@ struct Q2Params {
     int field_major;
     void* K;
     void* d;
-    // staged: element blocks of the elements e0.. (assemble_rows.hip) instead of K and d
-    int64_t e0;
+    // staged: element blocks (assemble_rows.hip) instead of K and d
     void* Ke;
     void* fe;
     ElemMask em;
@@ -310,7 +309,7 @@ __global__ void __launch_bounds__((Cfg<ET, FORM>::THREADS), (q2_min_blocks<ET, F
     const int lane = threadIdx.x;
     const int64_t li = blockIdx.x;
     const bool live = li < p.n_list;  // uniform across the workgroup
-    const int64_t e = live ? (STAGED ? p.e0 + li : (int64_t)p.elems[li]) : 0;
+    const int64_t e = live ? (STAGED ? li : (int64_t)p.elems[li]) : 0;
     if (live) {
         if (lane < NEN * DIM) {
             const int b = lane / DIM, m = lane % DIM;
@@ -598,7 +597,7 @@ __global__ void __launch_bounds__(256, 3) k_gram_blocks(Q2Params p)
     __syncthreads();
     auto& L = S.w[wave];
     for (int64_t li = (int64_t)blockIdx.x * G::WAVES + wave; li < p.n_list; li += (int64_t)gridDim.x * G::WAVES) {
-        const int64_t e = p.e0 + li;
+        const int64_t e = li;
         // (the operands' LDS addresses are not to be kept in registers from element to element)
         asm volatile("" : "+v"(lane));
         for (int t = lane; t < NEN * DIM; t += 64) {
@@ -784,15 +783,14 @@ mf_status launch(const AssembleArgs& A, bool* eliminated)
     if constexpr (ET != kHex8) {
         // element blocks in the workspace, then each node's rows written once
         constexpr size_t kPer = sizeof(T) * C::NEN * C::NF * (C::NEN * C::NF + 1) + 1;
-        const int64_t chunk = P->n_elems > 0 && gather_fits(P, C::NEN, C::NF) ? ws_chunk_elems(P, kPer, sizeof(T)) : 0;
-        if (chunk > 0) {
-            const Workspace ws(P, kPer * (size_t)chunk, A.stream);
-            char* w = ws.p;
-            p.Ke = w;
-            p.fe = w + sizeof(T) * C::NEN * C::NF * C::NEN * C::NF * (size_t)chunk;
-            p.em = {A.dirichlet, (uint8_t*)w + (kPer - 1) * (size_t)chunk, P->n_nodes, P->numbering == MF_FIELD_MAJOR};
-            for (p.e0 = 0; w && p.e0 < P->n_elems; p.e0 += chunk) {
-                p.n_list = std::min(P->n_elems - p.e0, chunk);
+        if (P->n_elems > 0) {
+            const size_t n = (size_t)P->n_elems;
+            const Workspace ws(P, kPer * n, A.stream);
+            if (char* w = ws.p) {
+                p.Ke = w;
+                p.fe = w + sizeof(T) * C::NEN * C::NF * C::NEN * C::NF * n;
+                p.em = {A.dirichlet, (uint8_t*)w + (kPer - 1) * n, P->n_nodes, P->numbering == MF_FIELD_MAJOR};
+                p.n_list = P->n_elems;
                 if constexpr (C::NS) {
                     k_assemble_quadratic<ET, FORM, T, true><<<(unsigned)p.n_list, C::THREADS, 0, A.stream>>>(p);
                 } else {
@@ -801,11 +799,9 @@ mf_status launch(const AssembleArgs& A, bool* eliminated)
                     k_gram_blocks<ET, FORM, T><<<(unsigned)blocks, 256, 0, A.stream>>>(p);
                 }
                 MF_HIP(hipGetLastError());
-                const mf_status gs = gather_blocks(A, C::NEN, C::NF, p.Ke, p.fe, p.em.flag, p.e0, p.e0 + p.n_list);
-                if (gs != MF_OK) return gs;
+                *eliminated = true;
+                return gather_blocks(A, C::NEN, C::NF, p.Ke, p.fe, p.em.flag);
             }
-            *eliminated = w != nullptr;
-            if (w) return MF_OK;
         }
     }
     if (P->nnz > 0) k_fill<T><<<blocks_for(P->nnz), kFillThreads, 0, A.stream>>>((T*)A.K, P->nnz);

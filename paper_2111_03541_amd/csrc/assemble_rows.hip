@@ -14,9 +14,11 @@
 //     the first kernel stores only the geometry (and the flow state) of the 8 Gauss points,
 //     and the wave that owns the node forms the products.
 //
-// Workspaces are bounded in FP64: elements go in chunks of ascending id, and a node whose incidence
-// list spans several chunks adds onto its rows from the chunk before.  FP32 rows are summed in FP64
-// and rounded once, so all elements are one chunk.
+// The workspace holds the data of all elements (up to about three times K), so that each row is
+// summed once, in FP64 to the end.  (In chunks of 1 GiB, a node at a cut read and wrote its rows
+// twice, FP32 rows were rounded between, and every node had to look for its entries and constrained
+// neighbours again: mass 128^3 FP64 1344 us against 1043 in one, with constrained sides 1828 against
+// 1150.)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -104,15 +106,6 @@ Workspace::~Workspace()
         (void)hipGetLastError();
         (void)hipStreamSynchronize(s);
     }
-}
-
-int64_t ws_chunk_elems(const mf_pattern_s* P, size_t bytes_per_elem, size_t value_bytes)
-{
-    // (FP32: a node whose elements span two chunks would round its sums between them)
-    if (value_bytes < sizeof(double)) return P->n_elems;
-    const size_t cap = std::max<size_t>((size_t)1 << 30, (size_t)P->nnz * value_bytes / 2);
-    const int64_t n = std::max<int64_t>(1, (int64_t)(cap / bytes_per_elem));
-    return std::min<int64_t>(P->n_elems, n);
 }
 
 namespace {
@@ -213,11 +206,9 @@ struct GatherParams {
     const int32_t* nbr_ptr;
     const uint8_t* rank_t;
     RowOut out;
-    const void* Ke;  // [c1 - c0][NF][NEN][NF] row blocks of the incidence entries c0..c1
-    const void* fe;  // [c1 - c0][NF] residual entries (d = sum)
-    const uint8_t* emask;  // flags of the chunk's elements (with out.mask)
-    int32_t c0, c1;  // incidence entries of this chunk: element * NEN + local node
-    int parts;       // more than one chunk
+    const void* Ke;  // [n_elems * NEN][NF][NEN][NF] row blocks of the incidence entries
+    const void* fe;  // [n_elems * NEN][NF] residual entries (d = sum)
+    const uint8_t* emask;  // flags of the elements (with out.mask)
     int buf_len;     // doubles of LDS per wave
     double lam, mu;  // Lame parameters of E = 1
     void* K;
@@ -241,6 +232,8 @@ struct GatherShape {
     static constexpr int UN = CH >= 4 ? 2 : CH >= 2 ? 4 : 8;
     // nodes per wave on large meshes: short rows leave lanes and loads to spare
     static constexpr int NPW = RB >= kWave ? 1 : 8;
+    // a node has at most 255 neighbours
+    static_assert(sizeof(double) * NPW * (NF * NF * 255 + NF) <= 65536, "a wave's row buffers exceed the LDS");
 };
 
 template <int NEN, int NF, int NPW, typename T, bool FM, bool LAME>
@@ -262,23 +255,10 @@ __global__ void __launch_bounds__(256) k_gather_blocks(GatherParams p)
     const int a0 = p.adj_ptr[vc], a1 = p.adj_ptr[vn], P = p.nbr_ptr[vc], deg = p.nbr_ptr[vn] - P;
     const int A0 = __shfl(a0, 0), A1 = __shfl(a1, NPW - 1), P0 = __shfl(P, 0);
     const int n_nbr = __shfl(P + deg, NPW - 1) - P0;
-    int k0 = a0, k1 = a1;
-    if (p.parts) {  // the node's entries of this chunk (ascending list)
-        while (k0 < k1 && p.adj[k0] < p.c0) ++k0;
-        while (k0 < k1 && p.adj[k1 - 1] >= p.c1) --k1;
-    }
-    const bool first = k0 == a0, last = k1 == a1;
-    // a node without elements has no columns; its d is written with the first chunk
-    const bool on = v < n_nodes && (k0 < k1 || (a0 == a1 && p.c0 == 0));
-    if (!__any(on)) return;
-    const bool elim = p.out.mask && last;
-    int touched = p.parts;  // an element around a node has a constrained DOF (other chunks: unknown)
+    const bool on = v < n_nodes;
+    int touched = 0;  // an element around a node has a constrained DOF
     for (int t = lane; t < n_nbr * NF * NF; t += kWave) buf[t] = 0.0;
-    for (int t = lane; t < NPW * NF; t += kWave) {
-        const int m = t / NF, j = t - m * NF;
-        const bool add = __shfl((int)(on && !first), m) != 0;
-        dbuf[t] = add ? (double)d[FM ? (int64_t)j * n_nodes + v0 + m : (int64_t)NF * (v0 + m) + j] : 0.0;
-    }
+    for (int t = lane; t < NPW * NF; t += kWave) dbuf[t] = 0.0;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     // the lane's values of a block row: column node, row and column field
     const int sl = SPP > 1 ? lane / RB : 0;
@@ -294,16 +274,14 @@ __global__ void __launch_bounds__(256) k_gather_blocks(GatherParams p)
     }
     for (int kb = A0; kb < A1; kb += kWave) {
         const int m = min(kWave, A1 - kb);
-        // lane's entry: its index in the chunk (-1: of another chunk), its node's buffer and width
-        int mine = -1, at = 0, width = 0, mydb = 0;
+        // lane's entry (-1: none), its node's buffer and width
+        const int k = kb + lane, mine = lane < m ? p.adj[k] : -1;
+        int at = 0, width = 0, mydb = 0;
         double fd[NF];
         {
-            const int k = kb + lane;
-            const int code = lane < m ? p.adj[k] : -1;
             int nd = 0;
 #pragma unroll
             for (int n = 1; n < NPW; ++n) nd += k >= __shfl(a0, n);
-            if (code >= p.c0 && code < p.c1) mine = code - p.c0;
             at = (__shfl(P, nd) - P0) * NF * NF;
             width = __shfl(deg, nd);
             if (p.out.mask && mine >= 0) touched |= p.emask[mine / NEN];
@@ -327,7 +305,7 @@ __global__ void __launch_bounds__(256) k_gather_blocks(GatherParams p)
 #pragma unroll
                 for (int u = 0; u < CH; ++u) {
                     const int t = SPP > 1 ? lane - sl * RB : min(lane + u * kWave, RB - 1);
-                    rk[w][u] = p.rank_t[(code + p.c0) * NEN + (tb[u] >= 0 ? tb[u] : 0)];
+                    rk[w][u] = p.rank_t[code * NEN + (tb[u] >= 0 ? tb[u] : 0)];
                     val[w][u] = (double)__builtin_nontemporal_load((const T*)p.Ke + code * RB + t);
                 }
             }
@@ -373,24 +351,13 @@ __global__ void __launch_bounds__(256) k_gather_blocks(GatherParams p)
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
-    if (__any(on && !first))  // rows of an earlier chunk
-        for (int n = 0; n < NPW; ++n) {
-            if (!__shfl((int)(on && !first), n)) continue;
-            const int Pn = __shfl(P, n), dg = __shfl(deg, n);
-            for (int c = lane; c < NF * dg; c += kWave)
-#pragma unroll
-                for (int i = 0; i < NF; ++i)
-                    buf[(Pn - P0) * NF * NF + i * NF * dg + c] += (double)K[row_entry<NF, FM>(p.out, Pn, dg, i, c)];
-        }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (p.out.mask && __any(touched)) eliminate<NF, FM, FM>(p.out, v0, NPW, P0, n_nbr, P, deg, on && elim, buf, lane);
+    if (p.out.mask && __any(touched)) eliminate<NF, FM, FM>(p.out, v0, NPW, P0, n_nbr, P, deg, on, buf, lane);
     for (int t = lane; t < NPW * NF; t += kWave) {
         const int m = t / NF, j = t - m * NF;
         const int64_t row = FM ? (int64_t)j * n_nodes + v0 + m : (int64_t)NF * (v0 + m) + j;
-        const bool gone = __shfl((int)elim, m) != 0;
-        if (__shfl((int)on, m)) d[row] = (T)(gone && p.out.mask[row] ? 0.0 : dbuf[t]);
+        if (v0 + m < n_nodes) d[row] = (T)(p.out.mask && p.out.mask[row] ? 0.0 : dbuf[t]);
     }
-    if (!FM && __all(on || v >= n_nodes)) {
+    if constexpr (!FM) {
         T* out = K + (int64_t)P0 * (NF * NF);
 #pragma unroll 4
         for (int t = lane; t < n_nbr * NF * NF; t += kWave) __builtin_nontemporal_store((T)buf[t], out + t);
@@ -398,15 +365,14 @@ __global__ void __launch_bounds__(256) k_gather_blocks(GatherParams p)
     }
 #pragma unroll 1
     for (int n = 0; n < NPW; ++n) {
-        if (!__shfl((int)on, n)) continue;
+        if (v0 + n >= n_nodes) break;
         const int Pn = __shfl(P, n);
         write_rows<NF, FM, FM, T>(p.out, Pn, __shfl(deg, n), buf + (Pn - P0) * (NF * NF), K, lane);
     }
 }
 
 template <int NEN, int NF, typename T, bool LAME = false>
-mf_status launch_gather(const AssembleArgs& A, const void* Ke, const void* fe, const uint8_t* emask, int64_t e0,
-                        int64_t e1)
+mf_status launch_gather(const AssembleArgs& A, const void* Ke, const void* fe, const uint8_t* emask)
 {
     const mf_pattern_s* P = A.P;
     GatherParams p{};
@@ -418,9 +384,6 @@ mf_status launch_gather(const AssembleArgs& A, const void* Ke, const void* fe, c
     p.Ke = Ke;
     p.fe = fe;
     p.emask = emask;
-    p.c0 = (int32_t)(e0 * NEN);
-    p.c1 = (int32_t)(e1 * NEN);
-    p.parts = e1 - e0 < P->n_elems;
     const double nu = A.form->nu;
     p.lam = nu / ((1.0 + nu) * (1.0 - 2.0 * nu));
     p.mu = 1.0 / (2.0 * (1.0 + nu));
@@ -502,7 +465,7 @@ __device__ __forceinline__ double brick_cofactors(const double* X, int q, double
     return cofactors(J, C);
 }
 
-// Two layouts of the records.  By values, [NR / 2][8 points][elements of the chunk][2], then the last
+// Two layouts of the records.  By values, [NR / 2][8 points][elements][2], then the last
 // value [8 points][elements]: the lanes of consecutive elements load one run.  By elements,
 // [elements][8 points][NR]: a lane's loads are one run, for meshes whose consecutive nodes have
 // elements anywhere, where a run of lanes would use 16 bytes of each line.  41x40x37 bricks, by
@@ -523,7 +486,6 @@ struct BrickParams {
     ElemMask em;
     mf_form form;
     int64_t n_el, n_nodes;
-    int64_t e0, e1;  // the elements of this chunk
     const int32_t* conn;
     const double* coords;
     const void* elem_param;
@@ -587,8 +549,8 @@ __global__ void __launch_bounds__(8 * kBE, 5) k_brick_scalar(BrickParams p)
     double(*sG)[kBE] = (double(*)[kBE])sW;
     __shared__ int sBad[kBE], sMask[kBE];
     const int el = threadIdx.x % kBE, q = threadIdx.x / kBE;
-    const int64_t e = p.e0 + (int64_t)blockIdx.x * kBE + el;
-    const bool live = e < p.e1;
+    const int64_t e = (int64_t)blockIdx.x * kBE + el;
+    const bool live = e < p.n_el;
     if (q == 0) sBad[el] = sMask[el] = 0;
     if (p.em.mask) __syncthreads();
     double chk = brick_load<1, T>(p, e, q, live, sX[el], sS[el], &sMask[el]);
@@ -645,14 +607,14 @@ __global__ void __launch_bounds__(8 * kBE, 5) k_brick_scalar(BrickParams p)
 #pragma unroll
     for (int b = 0; b < 8; ++b) sW[el * 65 + a * 8 + b] = bad ? 0.0 : row[b];
     if (live) {
-        if (p.em.mask && q == 0) p.em.flag[e - p.e0] = (uint8_t)sMask[el];
-        ((T*)p.fe)[(e - p.e0) * 8 + a] = bad ? T(0) : (T)load;
+        if (p.em.mask && q == 0) p.em.flag[e] = (uint8_t)sMask[el];
+        ((T*)p.fe)[e * 8 + a] = bad ? T(0) : (T)load;
     }
     __syncthreads();
     // the blocks of the workgroup's elements are one contiguous range
-    const int64_t e1 = p.e0 + (int64_t)blockIdx.x * kBE;
-    const int n = (int)(p.e1 - e1 < kBE ? p.e1 - e1 : kBE) * 64;
-    T* K = (T*)p.Ke + (e1 - p.e0) * 64;
+    const int64_t e0 = (int64_t)blockIdx.x * kBE;
+    const int n = (int)(p.n_el - e0 < kBE ? p.n_el - e0 : kBE) * 64;
+    T* K = (T*)p.Ke + e0 * 64;
 #pragma unroll
     for (int t = threadIdx.x; t < kBE * 64; t += 8 * kBE)
         if (t < n) K[t] = (T)sW[t / 64 * 65 + t % 64];
@@ -691,8 +653,8 @@ __global__ void __launch_bounds__(8 * kBE) k_brick_points(BrickParams p)
     __shared__ double sX[kBE][25], sS[kBE][8 * NF + 1], sL[8 * NL][kBE];
     __shared__ int sBad[kBE], sMask[kBE];
     const int el = threadIdx.x % kBE, q = threadIdx.x / kBE;
-    const int64_t e = p.e0 + (int64_t)blockIdx.x * kBE + el;
-    const bool live = e < p.e1;
+    const int64_t e = (int64_t)blockIdx.x * kBE + el;
+    const bool live = e < p.n_el;
     const double* S = sS[el];
     if (q == 0) sBad[el] = sMask[el] = 0;
     if (p.em.mask) __syncthreads();
@@ -764,16 +726,15 @@ __global__ void __launch_bounds__(8 * kBE) k_brick_points(BrickParams p)
     brick_flag(p, e, live, det, chk, &sBad[el]);
     __syncthreads();
     if (!live) return;
-    if (p.em.mask && q == 0) p.em.flag[e - p.e0] = (uint8_t)sMask[el];
+    if (p.em.mask && q == 0) p.em.flag[e] = (uint8_t)sMask[el];
     const bool bad = sBad[el] != 0;  // such an element adds nothing
-    const int64_t ec = e - p.e0;
-    char* rec = (char*)p.Ke + ec * p.lay.pe + q * p.lay.pq;
+    char* rec = (char*)p.Ke + e * p.lay.pe + q * p.lay.pq;
 #pragma unroll
     for (int k = 0; k < NR / 2; ++k) {
         const f64x2 x = {bad ? 0.0 : R[2 * k], bad ? 0.0 : R[2 * k + 1]};
         *(f64x2*)(rec + k * p.lay.pm) = x;
     }
-    *(double*)((char*)p.Ke + p.lay.last + ec * p.lay.le + q * p.lay.lq) = bad ? 0.0 : R[NR - 1];
+    *(double*)((char*)p.Ke + p.lay.last + e * p.lay.le + q * p.lay.lq) = bad ? 0.0 : R[NR - 1];
     // residual entries of node a
     const int a = q;
     double f[NF];
@@ -802,7 +763,7 @@ __global__ void __launch_bounds__(8 * kBE) k_brick_points(BrickParams p)
             f[3] -= N * x[(NR + 1) * kBE] + g[0] * x[(NR + 2) * kBE] + g[1] * x[(NR + 3) * kBE] + g[2] * x[(NR + 4) * kBE];
         }
     }
-    T* fe = (T*)p.fe + ec * p.lay.fe + a * p.lay.fa;
+    T* fe = (T*)p.fe + e * p.lay.fe + a * p.lay.fa;
 #pragma unroll
     for (int j = 0; j < NF; ++j) fe[j * p.lay.fj] = bad ? T(0) : (T)f[j];
 }
@@ -833,9 +794,7 @@ struct RowParams {
     const double* rec;
     RecLayout lay;
     const void* fe;
-    const uint8_t* emask;  // flags of the chunk's elements (with out.mask)
-    int32_t c0, c1;     // incidence entries of this chunk
-    int parts;          // more than one chunk
+    const uint8_t* emask;  // flags of the elements (with out.mask)
     int buf_len, wave_len;  // doubles of LDS per node and per wave
     int plane, slots;   // nodes of a grid plane, workgroups of a band in it (0: nodes in order)
     void* K;
@@ -997,34 +956,19 @@ __global__ void __launch_bounds__(256, (Rec<FORM>::WG)) k_brick_rows(RowParams p
     const int vc = min(v, n_nodes), vn = min(v + 1, n_nodes);
     const int a0 = p.adj_ptr[vc], a1 = p.adj_ptr[vn], P = p.nbr_ptr[vc], deg = p.nbr_ptr[vn] - P;
     const int P0 = __shfl(P, 0), n_wave = (__shfl(P + deg, NPW - 1) - P0) * NF * NF;
-    int k0 = a0, k1 = a1;
-    if (p.parts) {  // the node's entries of this chunk (ascending list)
-        while (k0 < k1 && p.adj[k0] < p.c0) ++k0;
-        while (k0 < k1 && p.adj[k1 - 1] >= p.c1) --k1;
-    }
-    const bool first = k0 == a0, last = k1 == a1;
-    // a node without elements: d with the first chunk
-    const bool on = v < n_nodes && (k0 < k1 || (a0 == a1 && p.c0 == 0));
+    const bool on = v < n_nodes;
     const int base = wbase + (P - P0) * (NF * NF);
     const int64_t drow = FM ? (int64_t)sub * n_nodes + v : (int64_t)NF * v + sub;
     T* K = (T*)p.K;
     T* d = (T*)p.d;
-    const bool elim = p.out.mask && last;
-    int touched = p.parts;  // an element around the node has a constrained DOF (other chunks: unknown)
+    int touched = 0;  // an element around the node has a constrained DOF
     for (int t = 2 * lane; t < n_wave; t += 2 * kWave) *(double2*)(sh + wbase + t) = make_double2(0.0, 0.0);
-    if (sub < NF) dbuf[sub] = on && !first ? (double)d[drow] : 0.0;
+    if (sub < NF) dbuf[sub] = 0.0;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (on && !first)
-        for (int c = sub; c < NF * deg; c += LPN)
-#pragma unroll
-            for (int i = 0; i < NF; ++i)
-                sh[base + i * NF * deg + (SPLIT && !FM ? c % NF * deg + c / NF : c)] =
-                    (double)K[row_entry<NF, FM>(p.out, P, deg, i, c)];
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    for (int k = k0 + slot; k < k1; k += 8) {
+    for (int k = a0 + slot; k < a1; k += 8) {
         const int code = p.adj[k];  // element * 8 + local node
         const int a = code & 7;
-        const uint32_t e = (uint32_t)(code - p.c0) >> 3;
+        const uint32_t e = (uint32_t)code >> 3;
         if (p.out.mask) touched |= p.emask[e];
         // value pairs [m0, m1) of the record at point q: uniform bases, 32-bit lane offset
         auto load_pairs = [&](int q, int m0, int m1, double* h) {
@@ -1117,11 +1061,11 @@ __global__ void __launch_bounds__(256, (Rec<FORM>::WG)) k_brick_rows(RowParams p
             for (int j = 0; j < NF; ++j) unsafeAtomicAdd(dbuf + j, fd[j]);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (on && sub < NF) d[drow] = (T)(elim && p.out.mask[drow] ? 0.0 : dbuf[sub]);
+    if (on && sub < NF) d[drow] = (T)(p.out.mask && p.out.mask[drow] ? 0.0 : dbuf[sub]);
     // (every lane takes part from here on)
     if (p.out.mask && __any(touched))
-        eliminate<NF, FM, SPLIT>(p.out, v0, NPW, P0, n_wave / (NF * NF), P, deg, on && elim, sh + wbase, lane);
-    if (!SPLIT && __all(on || v >= n_nodes)) {
+        eliminate<NF, FM, SPLIT>(p.out, v0, NPW, P0, n_wave / (NF * NF), P, deg, on, sh + wbase, lane);
+    if constexpr (!SPLIT) {
         T* out = K + (int64_t)P0 * (NF * NF);
 #pragma unroll 4
         for (int t = lane; t < n_wave; t += kWave) __builtin_nontemporal_store((T)sh[wbase + t], out + t);
@@ -1129,7 +1073,7 @@ __global__ void __launch_bounds__(256, (Rec<FORM>::WG)) k_brick_rows(RowParams p
     }
 #pragma unroll 1
     for (int n = 0; n < NPW; ++n) {
-        if (!__shfl((int)on, n)) continue;
+        if (v0 + n >= n_nodes) break;
         const int Pn = __shfl(P, n);
         write_rows<NF, FM, SPLIT, T>(p.out, Pn, __shfl(deg, n), sh + wbase + (Pn - P0) * (NF * NF), K, lane);
     }
@@ -1271,28 +1215,25 @@ mf_status launch_scalar_rows(const AssembleArgs& A)
     p.out = {P->nbr, A.dirichlet, P->n_nodes, P->n_pairs};
     p.elem_param = A.elem_param;
     p.src = A.nodal_src;
-    p.wave_len = 8 * std::max(1, P->max_deg) + 8;  // at most 255 neighbours: 66 kB for four waves
+    p.wave_len = 8 * std::max(1, P->max_deg) + 8;  // at most 255 neighbours: 64 kB for four waves
     p.K = A.K;
     p.d = A.d;
     p.status = P->status;
-    const size_t per_wave = sizeof(double) * (size_t)p.wave_len;
-    const int waves = 4 * per_wave <= 65536 ? 4 : 2;
-    const unsigned blocks = (unsigned)((P->n_nodes + waves * 8 - 1) / (waves * 8));
-    k_scalar_rows<FORM, T><<<blocks, waves * kWave, per_wave * waves, A.stream>>>(p);
+    constexpr int kWaves = 4;
+    const unsigned blocks = (unsigned)((P->n_nodes + kWaves * 8 - 1) / (kWaves * 8));
+    k_scalar_rows<FORM, T><<<blocks, kWaves * kWave, sizeof(double) * kWaves * (size_t)p.wave_len, A.stream>>>(p);
     MF_HIP(hipGetLastError());
     return MF_OK;
 }
 
 template <typename T>
-BrickParams brick_params(const AssembleArgs& A, int64_t e0, int64_t e1, void* Ke, void* fe, uint8_t* emask)
+BrickParams brick_params(const AssembleArgs& A, void* Ke, void* fe, uint8_t* emask)
 {
     const mf_pattern_s* P = A.P;
     BrickParams p{};
     p.form = *A.form;
     p.n_el = P->n_elems;
     p.n_nodes = P->n_nodes;
-    p.e0 = e0;
-    p.e1 = e1;
     p.conn = P->conn;
     p.coords = A.coords;
     p.elem_param = A.elem_param;
@@ -1308,23 +1249,16 @@ template <int FORM, typename T>
 mf_status launch_scalar(const AssembleArgs& A)
 {
     const mf_pattern_s* P = A.P;
-    if (!gather_fits(P, 8, 1)) return MF_ERR_UNSUPPORTED;
-    const size_t per = sizeof(T) * (64 + 8) + 1;
-    const int64_t chunk = ws_chunk_elems(P, per, sizeof(T));
-    const Workspace ws(P, per * (size_t)chunk, A.stream);
+    const size_t per = sizeof(T) * (64 + 8) + 1, n = (size_t)P->n_elems;
+    const Workspace ws(P, per * n, A.stream);
     char* w = ws.p;
     if (!w) return MF_ERR_UNSUPPORTED;
-    void* fe = w + sizeof(T) * 64 * (size_t)chunk;
-    uint8_t* emask = (uint8_t*)w + sizeof(T) * 72 * (size_t)chunk;
-    for (int64_t e0 = 0; e0 < P->n_elems; e0 += chunk) {
-        const int64_t e1 = std::min(P->n_elems, e0 + chunk);
-        const BrickParams p = brick_params<T>(A, e0, e1, w, fe, emask);
-        k_brick_scalar<FORM, T><<<(unsigned)((e1 - e0 + kBE - 1) / kBE), 8 * kBE, 0, A.stream>>>(p);
-        MF_HIP(hipGetLastError());
-        const mf_status st = launch_gather<8, 1, T>(A, w, fe, emask, e0, e1);
-        if (st != MF_OK) return st;
-    }
-    return MF_OK;
+    void* fe = w + sizeof(T) * 64 * n;
+    uint8_t* emask = (uint8_t*)w + sizeof(T) * 72 * n;
+    const BrickParams p = brick_params<T>(A, w, fe, emask);
+    k_brick_scalar<FORM, T><<<(unsigned)((P->n_elems + kBE - 1) / kBE), 8 * kBE, 0, A.stream>>>(p);
+    MF_HIP(hipGetLastError());
+    return launch_gather<8, 1, T>(A, w, fe, emask);
 }
 
 constexpr int64_t kPlaneBytes = 1 << 20;  // records of a grid plane that stay in an XCD's L2
@@ -1341,53 +1275,46 @@ mf_status launch_rows(const AssembleArgs& A)
     if (per_wave > 65536) return MF_ERR_UNSUPPORTED;  // hundreds of neighbours: the scatter
     const int waves = 4 * per_wave <= 65536 ? 4 : 2 * per_wave <= 65536 ? 2 : 1;
     const size_t rec = sizeof(double) * 8 * R::NR, per = rec + sizeof(T) * 8 * R::NF + 1;
-    const int64_t chunk = ws_chunk_elems(P, per, sizeof(T));
-    const Workspace ws(P, per * (size_t)chunk, A.stream);
+    const int64_t n = P->n_elems;
+    const Workspace ws(P, per * (size_t)n, A.stream);
     char* w = ws.p;
     if (!w) return MF_ERR_UNSUPPORTED;
-    void* fe = w + rec * (size_t)chunk;
-    uint8_t* emask = (uint8_t*)w + (per - 1) * (size_t)chunk;
-    for (int64_t e0 = 0; e0 < P->n_elems; e0 += chunk) {
-        const int64_t e1 = std::min(P->n_elems, e0 + chunk);
-        const int64_t n = e1 - e0;
-        // by elements on a scattered mesh (lane offsets have 32 bits)
-        const bool by_elem = P->scattered && n * 64 * R::NR < ((int64_t)1 << 32);
-        const RecLayout lay = by_elem ? RecLayout{64 * R::NR, 8 * R::NR, 16, 8 * (R::NR - 1), 64 * R::NR, 8 * R::NR, 8 * R::NF, R::NF, 1}
-                                      : RecLayout{16, 16 * n, 128 * n, 64 * (R::NR - 1) * n, 8, 8 * n, 1, R::NF * n, n};
-        BrickParams b = brick_params<T>(A, e0, e1, w, fe, emask);
-        b.lay = lay;
-        k_brick_points<FORM, T><<<(unsigned)((e1 - e0 + kBE - 1) / kBE), 8 * kBE, 0, A.stream>>>(b);
-        MF_HIP(hipGetLastError());
-        RowParams p{};
-        p.form = *A.form;
-        p.adj_ptr = P->adj_ptr;
-        p.adj = P->adj;
-        p.nbr_ptr = P->nbr_ptr;
-        p.rank_t = P->rank_t;
-        p.out = {P->nbr, A.dirichlet, P->n_nodes, P->n_pairs};
-        p.elem_param = A.elem_param;
-        p.rec = (const double*)w;
-        p.fe = fe;
-        p.emask = emask;
-        p.lay = lay;
-        p.c0 = (int32_t)(e0 * 8);
-        p.c1 = (int32_t)(e1 * 8);
-        p.parts = e1 - e0 < P->n_elems;
-        p.buf_len = buf_len;
-        p.wave_len = wave_len;
-        p.K = A.K;
-        p.d = A.d;
-        const int64_t per_block = (int64_t)waves * NPW;
-        unsigned blocks = (unsigned)((P->n_nodes + per_block - 1) / per_block);
-        if (P->is_grid && (int64_t)per * P->gx * P->gy > kPlaneBytes) {
-            p.plane = (int)((P->gx + 1) * (P->gy + 1));
-            p.slots = (int)((p.plane / kXcds + per_block) / per_block) + 1;
-            blocks = (unsigned)(kXcds * (P->gz + 1) * p.slots);
-        }
-        if (P->numbering == MF_FIELD_MAJOR) k_brick_rows<FORM, T, true><<<blocks, waves * kWave, per_wave * waves, A.stream>>>(p);
-        else k_brick_rows<FORM, T, false><<<blocks, waves * kWave, per_wave * waves, A.stream>>>(p);
-        MF_HIP(hipGetLastError());
+    void* fe = w + rec * (size_t)n;
+    uint8_t* emask = (uint8_t*)w + (per - 1) * (size_t)n;
+    // by elements on a scattered mesh (lane offsets have 32 bits)
+    const bool by_elem = P->scattered && n * 64 * R::NR < ((int64_t)1 << 32);
+    const RecLayout lay = by_elem ? RecLayout{64 * R::NR, 8 * R::NR, 16, 8 * (R::NR - 1), 64 * R::NR, 8 * R::NR, 8 * R::NF, R::NF, 1}
+                                  : RecLayout{16, 16 * n, 128 * n, 64 * (R::NR - 1) * n, 8, 8 * n, 1, R::NF * n, n};
+    BrickParams b = brick_params<T>(A, w, fe, emask);
+    b.lay = lay;
+    k_brick_points<FORM, T><<<(unsigned)((n + kBE - 1) / kBE), 8 * kBE, 0, A.stream>>>(b);
+    MF_HIP(hipGetLastError());
+    RowParams p{};
+    p.form = *A.form;
+    p.adj_ptr = P->adj_ptr;
+    p.adj = P->adj;
+    p.nbr_ptr = P->nbr_ptr;
+    p.rank_t = P->rank_t;
+    p.out = {P->nbr, A.dirichlet, P->n_nodes, P->n_pairs};
+    p.elem_param = A.elem_param;
+    p.rec = (const double*)w;
+    p.fe = fe;
+    p.emask = emask;
+    p.lay = lay;
+    p.buf_len = buf_len;
+    p.wave_len = wave_len;
+    p.K = A.K;
+    p.d = A.d;
+    const int64_t per_block = (int64_t)waves * NPW;
+    unsigned blocks = (unsigned)((P->n_nodes + per_block - 1) / per_block);
+    if (P->is_grid && (int64_t)per * P->gx * P->gy > kPlaneBytes) {
+        p.plane = (int)((P->gx + 1) * (P->gy + 1));
+        p.slots = (int)((p.plane / kXcds + per_block) / per_block) + 1;
+        blocks = (unsigned)(kXcds * (P->gz + 1) * p.slots);
     }
+    if (P->numbering == MF_FIELD_MAJOR) k_brick_rows<FORM, T, true><<<blocks, waves * kWave, per_wave * waves, A.stream>>>(p);
+    else k_brick_rows<FORM, T, false><<<blocks, waves * kWave, per_wave * waves, A.stream>>>(p);
+    MF_HIP(hipGetLastError());
     return MF_OK;
 }
 
@@ -1416,27 +1343,20 @@ mf_status dispatch_rows(const AssembleArgs& A)
 
 }  // namespace
 
-bool gather_fits(const mf_pattern_s* P, int nen, int nf)
-{
-    const int nodes = nf * nen * nf >= kWave ? 1 : GatherShape<8, 1>::NPW;
-    return sizeof(double) * (size_t)nodes * (nf * nf * (size_t)std::max(1, P->max_deg) + nf) <= 65536;
-}
-
-mf_status gather_blocks(const AssembleArgs& A, int nen, int nf, const void* Ke, const void* fe, const uint8_t* emask,
-                        int64_t e0, int64_t e1)
+mf_status gather_blocks(const AssembleArgs& A, int nen, int nf, const void* Ke, const void* fe, const uint8_t* emask)
 {
     auto run = [&](auto zero) -> mf_status {
         using T = decltype(zero);
         switch (nen * 8 + nf) {
-            case 20 * 8 + 1: return launch_gather<20, 1, T>(A, Ke, fe, emask, e0, e1);
-            case 20 * 8 + 3: return launch_gather<20, 3, T, true>(A, Ke, fe, emask, e0, e1);
-            case 20 * 8 + 4: return launch_gather<20, 4, T>(A, Ke, fe, emask, e0, e1);
-            case 10 * 8 + 1: return launch_gather<10, 1, T>(A, Ke, fe, emask, e0, e1);
-            case 10 * 8 + 3: return launch_gather<10, 3, T, true>(A, Ke, fe, emask, e0, e1);
-            case 10 * 8 + 4: return launch_gather<10, 4, T>(A, Ke, fe, emask, e0, e1);
-            case 8 * 8 + 1: return launch_gather<8, 1, T>(A, Ke, fe, emask, e0, e1);
-            case 8 * 8 + 2: return launch_gather<8, 2, T, true>(A, Ke, fe, emask, e0, e1);
-            case 8 * 8 + 3: return launch_gather<8, 3, T>(A, Ke, fe, emask, e0, e1);
+            case 20 * 8 + 1: return launch_gather<20, 1, T>(A, Ke, fe, emask);
+            case 20 * 8 + 3: return launch_gather<20, 3, T, true>(A, Ke, fe, emask);
+            case 20 * 8 + 4: return launch_gather<20, 4, T>(A, Ke, fe, emask);
+            case 10 * 8 + 1: return launch_gather<10, 1, T>(A, Ke, fe, emask);
+            case 10 * 8 + 3: return launch_gather<10, 3, T, true>(A, Ke, fe, emask);
+            case 10 * 8 + 4: return launch_gather<10, 4, T>(A, Ke, fe, emask);
+            case 8 * 8 + 1: return launch_gather<8, 1, T>(A, Ke, fe, emask);
+            case 8 * 8 + 2: return launch_gather<8, 2, T, true>(A, Ke, fe, emask);
+            case 8 * 8 + 3: return launch_gather<8, 3, T>(A, Ke, fe, emask);
         }
         return set_error(MF_ERR_ARG, "no gather for %d nodes and %d fields", nen, nf);
     };

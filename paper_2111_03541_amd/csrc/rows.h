@@ -18,11 +18,11 @@ __device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned n)
     return x * per + (x < rest ? x : rest) + k;
 }
 
-// Which elements of a chunk have a constrained DOF (one byte each), so that the waves that sum
+// Which elements have a constrained DOF (one byte each), so that the waves that sum
 // the rows look up Dirichlet flags only around those.
 struct ElemMask {
     const uint8_t* mask;  // [n_rows] or nullptr
-    uint8_t* flag;        // [elements of the chunk]
+    uint8_t* flag;        // [n_elems]
     int64_t n_nodes;
     int field_major;
     template <int NF>
@@ -35,16 +35,9 @@ struct ElemMask {
     }
 };
 
-// Elements per chunk of the workspace for records of bytes_per_elem, for K of value_bytes an entry.
-int64_t ws_chunk_elems(const mf_pattern_s* P, size_t bytes_per_elem, size_t value_bytes);
-
-// Whether the row buffers of gather_blocks fit the LDS (not with hundreds of neighbours a node).
-bool gather_fits(const mf_pattern_s* P, int nen, int nf);
-
-// K and d from element blocks (and residual entries) of the elements [e0, e1) in the
-// workspace, in A's precision; emask: the elements' flags (with A.dirichlet).  Ke
-// [e][a][i][b][j] (elasticity: E int dN_a,i dN_b,j, combined by the gather), fe [e][a][i].  Chunks in ascending order; eliminates the Dirichlet rows.
-mf_status gather_blocks(const AssembleArgs& A, int nen, int nf, const void* Ke, const void* fe, const uint8_t* emask,
-                        int64_t e0, int64_t e1);
+// K and d from the blocks (and residual entries) of all elements in the workspace, in A's
+// precision; emask: the elements' flags (with A.dirichlet).  Ke [e][a][i][b][j] (elasticity:
+// E int dN_a,i dN_b,j, combined by the gather), fe [e][a][i].  Eliminates the Dirichlet rows.
+mf_status gather_blocks(const AssembleArgs& A, int nen, int nf, const void* Ke, const void* fe, const uint8_t* emask);
 
 }  // namespace mf

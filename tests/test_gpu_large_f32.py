@@ -1,4 +1,4 @@
-"""FP32 rows on a mesh whose element records exceed the FP64 rows' workspace limit: the sums stay in
+"""FP32 rows on a mesh with more than 1 GiB of element records: the sums stay in
 FP64 and are rounded once."""
 import sys
 
@@ -12,8 +12,8 @@ torch = pytest.importorskip("torch")
 
 
 def test_rows_round_once(mf):
-    """The flow tangent of 636 thousand bricks in an order that is no grid's, in FP32 and in FP64 (in
-    two chunks of elements there).  Both form their sums in FP64, of at most 64 products a row entry
+    """The flow tangent of 636 thousand bricks in an order that is no grid's, in FP32 and in FP64.
+    Both form their sums in FP64, of at most 64 products a row entry
     and element pair, so an FP32 entry is one rounding (2^-24 of it) from the FP64 one, but for the
     FP64 sums' own order: 64 * 2^-53 of the row's largest entry, here with a margin of 16."""
     n = (87, 86, 85)
