@@ -148,16 +148,17 @@ typedef struct { int32_t points_per_axis; } mf_quadrature;   /* Gauss-Legendre: 
                                                                   4 for MF_TET10 (collapsed) */
 
 /* Assembly strategies.  AUTO picks an owner-computes gather for 4-node quadrilaterals and
-   8-node bricks (elasticity and the FP32 flow form on a small structured grid: the column
-   kernel, else the rows kernels, which take any mesh), and otherwise (or without memory for their workspace) the element-parallel scatter colour
+   8-node bricks (on small and on some large structured grids, and for the FP32 elasticity form
+   without constrained DOFs on any, the column kernel, else the rows kernels, which take any
+   mesh), and otherwise (or without memory for their workspace) the element-parallel scatter colour
    by colour with plain adds, whose sums are the same on every run.  ATOMIC is the
    element-parallel scatter with hardware atomics in one launch (the paper's scheme).  In
    ATOMIC and in the column kernel (which sums a node's element blocks with LDS atomics) the
    order of the additions, and so the last bits, may vary between runs.  GATHER asks for
    an owner-computes kernel.  A pattern keeps a workspace, and others for the calls of the first
    eight captures that it takes part in, until it is destroyed; assemblies captured later go as
-   without memory for a workspace.  It holds the data of all elements (up to about three times the size of K),
-   or the rows of the faces of a boundary form. */
+   without memory for a workspace.  It holds the data of all elements (up to about three times the
+   size of K), or the rows of the faces of a boundary form. */
 typedef enum { MF_SCATTER_AUTO = 0, MF_SCATTER_ATOMIC = 1, MF_SCATTER_GATHER = 2 } mf_scatter;
 
 /*

@@ -50,25 +50,50 @@ mf_status mf::status_of(const unsigned long long (&v)[3], int64_t* first_bad_ele
 
 using namespace mf;
 
-// On a small structured grid the one launch of the column kernel beats the two of the elasticity
-// and flow rows, whose Dirichlet elimination costs less (column against rows in us, then with
-// constrained sides).  FP64 elasticity 20^3 24 against 29, 29 against 34; 24^3 35 both ways, 42
-// against 40; 28^3 47 against 50, 60 against 58; 36^3 87 against 80; 64^3 352 against 304, 422
-// against 373.  The rows sum in FP64 also in FP32 builds, where the column kernel's traffic halves:
-// elasticity 32^3 46 against 58, 68 against 70; 40^3 79 against 91, 117 against 119; 44^3 106 against
-// 102, 152 against 130; 64^3 262 against 257, 370 against 322.  The flow form in FP32 (matrix cores
-// in the column kernel) 20^3 51 against 57, 24^3 76 against 71, 48^3 431 against 368.  The scalar
-// rows are one launch too (conduction 8^3 13 us both ways, 20^3 14 against 18, 28^3 18 against 35).
+// Whether the column kernel takes the call (structured grids; column against rows in us, best of
+// several loops; "fixed": with constrained sides).
+//
+// Small grids: its one launch beats the two of the elasticity and flow rows.  FP64 elasticity 20^3
+// 25 against 29, 24^3 35 both, 28^3 47 against 50, 36^3 87 against 80; its Dirichlet elimination
+// costs more: fixed 20^3 29 against 34, 24^3 42 against 40, 28^3 60 against 58.  FP32 flow 20^3 51
+// against 57, 24^3 76 against 71, 48^3 431 against 368.  The scalar rows are one launch too, but the
+// chain of loads that finds a node's constrained neighbours takes 2 us: fixed conduction 8^3 12.3
+// against 14.3 (FP32 12.4 against 14.8), 14^3 12.4 against 14.3 (12.4 against 14.8), 16^3 14.5
+// against 14.1 (12.4 against 14.6), 21^3 21.7 against 17.2 (15.0 against 17.3), 22^3 FP32 17.9
+// against 17.2; mass 14^3 12.3 against 13.8, 20^3 14.4 against 14.9, 21^3 16.8 against 15.2 (FP32
+// 14.1 against 15.4), 22^3 FP32 16.1 against 15.2; without constraints 14^3 12.2 against 12.1 in all.
+//
+// FP32: the rows sum in FP64, so the column kernel's time halves with K and theirs does not.
+// Elasticity 36^3 65 against 66, 44^3 111 against 108, 48^3 132 against 135, 52^3 151 against 164,
+// 64^3 267 both ways, 72^3 382 against 419, 96^3 797 against 981 (field-major 435 against 462, 925
+// against 1068); fixed 32^3 68 against 70, 40^3 117 against 119, 44^3 152 against 130, 64^3 374
+// against 334, 72^3 582 against 522.
+//
+// Large grids: above some 250 MB the element data no longer waits in the last-level cache between
+// the two kernels, while the column kernel forms it again.  FP64 elasticity 84^3 798 against 772,
+// 96^3 1134 against 1125, 104^3 1374 against 1425, 128^3 2503 against 2659; fixed 80^3 798 against 773,
+// 88^3 1004 against 1032, 104^3 1570 against 1640; fixed FP32 76^3 611 against 613, 80^3 672 against 699,
+// 96^3 1105 against 1161.  FP32 flow 60^3 824 against 796, 64^3 942 against 961, 80^3 1777 against
+// 1820; fixed 64^3 1105 against 1072, 96^3 3450 against 3378.  FP32 mass 124^3 773 against 751,
+// 128^3 819 against 835, 160^3 1549 against 1615; FP64 mass and conduction stay with the rows
+// (160^3 2219 against 1991, 3380 against 1818).  Field-major rows are four runs a node to the column
+// kernel's scattered ones: FP64 elasticity 104^3 1587 against 1529, 128^3 2872 against 2866; fixed FP32
+// 96^3 1405 against 1260, 128^3 3226 against 3198; FP32 flow 64^3 1035 against 964.
 static bool column_wins(const AssembleArgs& A)
 {
     if (!A.P->is_grid || A.P->dim != 3) return false;
-    const bool f32 = A.prec == MF_F32;
+    const bool f32 = A.prec == MF_F32, fixed = A.dirichlet != nullptr, mass = A.form->kind == MF_FORM_MASS;
+    const bool node_major = A.P->numbering == MF_NODE_MAJOR;
+    const int64_t n = A.P->n_elems;
     switch (A.form->kind) {
-        case MF_FORM_NS_SUPG: return f32 && A.P->n_elems < 10000;  // FP64: no column kernel
+        case MF_FORM_NS_SUPG:
+            return f32 && (n < 10000 || (node_major && !fixed && n >= 240000));  // FP64: no column kernel
         case MF_FORM_ELASTICITY:
-            if (A.dirichlet) return A.P->n_elems < (f32 ? 45000 : 13000);
-            return A.P->n_elems < (f32 ? 80000 : 32000);
-        default: return false;
+            if (f32) return !fixed || n < 45000 || (node_major && n >= 400000);
+            return n < (fixed ? 13000 : 32000) || (node_major && n >= (fixed ? 600000 : 1000000));
+        default:
+            if (fixed) return n < (f32 ? 10000 : mass ? 8500 : 3500);
+            return mass && f32 && n >= 2000000;
     }
 }
 
