@@ -45,7 +45,10 @@ constexpr int kUnroll = 8;                       // row loads issued together (3
 constexpr int kSpmvBlocks = 2048;                // a multiple of the 8 XCDs
 constexpr int kVecBlocks = 2048;
 constexpr int kStencilBlocks = 4096;              // a multiple of the 8 XCDs
-constexpr int kReduceThreads = 1024;             // of a one-block reduction
+constexpr int kReduceThreads = 1024;             // of a one-block reduction, at most
+// Threads of a one-block reduction of nb partials: 1024 have the 2048 of a large system in flight at
+// once, but their barriers cost a small one 1 us a reduction.
+int reduce_threads(int nb) { return nb > 2 * kThreads ? kReduceThreads : kThreads; }
 constexpr int kXcds = 8;
 
 // Scalars (device): RZ = r.z, PQ, ALPHA, BETA, RR, FALLBACK, BREAK
@@ -347,7 +350,7 @@ struct Dots {
 __device__ __forceinline__ Dots sum_dots(const double* __restrict__ partial, int nb, double (*sh)[3])
 {
     double v[3] = {0.0, 0.0, 0.0};
-    for (int k = threadIdx.x; k < nb; k += kReduceThreads)
+    for (int k = threadIdx.x; k < nb; k += blockDim.x)
 #pragma unroll
         for (int c = 0; c < 3; ++c) v[c] += partial[c * nb + k];
 #pragma unroll
@@ -359,7 +362,7 @@ __device__ __forceinline__ Dots sum_dots(const double* __restrict__ partial, int
         for (int c = 0; c < 3; ++c) sh[threadIdx.x / 64][c] = v[c];
     __syncthreads();
     Dots d = {0.0, 0.0, 0.0};
-    for (int k = 0; k < kReduceThreads / 64; ++k) {
+    for (int k = 0; k < (int)(blockDim.x / 64); ++k) {
         d.rz += sh[k][0];
         d.rr += sh[k][1];
         d.zq += sh[k][2];
@@ -937,6 +940,7 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
             eval = nullptr;
         }
     }
+    const int pq_blocks = grid.v ? stencil_blocks : spmv_blocks, vec_reduce = reduce_threads(vec_blocks);
     auto spmv_pq = [&]() {
         if (grid.v)
             k_spmv_stencil_dot<<<stencil_blocks, kThreads, 0, s>>>(grid, p, q, p, pq_part);
@@ -952,14 +956,13 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
                                            partial);
     k_reduce2<<<1, kThreads, 0, s>>>(partial, vec_blocks, sc + S_COUNT);
     double hb2[2] = {0, 0};
-    MF_HIP(hipMemcpyAsync(hb2, sc + S_COUNT, sizeof(hb2), hipMemcpyDeviceToHost, s));
     auto precondition = [&](const double* qv, int flexible, int init) -> mf_status {
         const mf_status st = a.apply(a.apply_ctx, r, z, s);
         if (st != MF_OK) return st;
         k_dots<<<vec_blocks, kThreads, 0, s>>>(n, r, z, qv, partial);
-        k_check_beta<<<1, kReduceThreads, 0, s>>>(partial, vec_blocks, sc, flag, flexible, init);
+        k_check_beta<<<1, vec_reduce, 0, s>>>(partial, vec_blocks, sc, flag, flexible, init);
         k_fallback<<<vec_blocks, kThreads, 0, s>>>(n, flag, dinv, r, qv, z, partial);
-        k_fallback_beta<<<1, kReduceThreads, 0, s>>>(partial, vec_blocks, flag, sc, flexible, init);
+        k_fallback_beta<<<1, vec_reduce, 0, s>>>(partial, vec_blocks, flag, sc, flexible, init);
         return MF_OK;
     };
     if (external) {
@@ -968,9 +971,11 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
         MF_HIP(hipMemcpyAsync(p, z, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
     } else {
         k_dots<<<vec_blocks, kThreads, 0, s>>>(n, r, z, nullptr, partial);
-        k_reduce_beta<<<1, kReduceThreads, 0, s>>>(partial, vec_blocks, sc, 1);
+        k_reduce_beta<<<1, vec_reduce, 0, s>>>(partial, vec_blocks, sc, 1);
     }
     MF_HIP(hipGetLastError());
+    // (behind the launches: a copy to the host waits)
+    MF_HIP(hipMemcpyAsync(hb2, sc + S_COUNT, sizeof(hb2), hipMemcpyDeviceToHost, s));
     MF_HIP(hipStreamSynchronize(s));
     const double bnorm = std::sqrt(hb2[1]);
     if (bnorm == 0.0) {
@@ -980,10 +985,10 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
 
     auto iteration = [&]() -> mf_status {
         spmv_pq();
-        k_reduce_alpha<<<1, kReduceThreads, 0, s>>>(pq_part, grid.v ? stencil_blocks : spmv_blocks, sc);
+        k_reduce_alpha<<<1, reduce_threads(pq_blocks), 0, s>>>(pq_part, pq_blocks, sc);
         if (!external) {
             k_update_dots<<<vec_blocks, kThreads, 0, s>>>(n, sc, a.x, r, p, q, dinv, z, jac, partial);
-            k_reduce_beta<<<1, kReduceThreads, 0, s>>>(partial, vec_blocks, sc, 0);
+            k_reduce_beta<<<1, vec_reduce, 0, s>>>(partial, vec_blocks, sc, 0);
         } else {
             k_update_ext<<<vec_blocks, kThreads, 0, s>>>(n, sc, a.x, r, p, q);
             const mf_status st = precondition(q, 1, 0);
@@ -1041,7 +1046,7 @@ mf_status run_pcg(const PcgArgs& a, mf_pcg_result* res, double* scratch)
         }
         k_restart<<<spmv_blocks, kThreads, 0, s>>>(n, a.row_ptr, a.col_idx, a.values, a.x, a.b, dinv, jac, r, z, p);
         k_dots<<<vec_blocks, kThreads, 0, s>>>(n, r, z, nullptr, partial);
-        k_reduce_beta<<<1, kReduceThreads, 0, s>>>(partial, vec_blocks, sc, 1);
+        k_reduce_beta<<<1, vec_reduce, 0, s>>>(partial, vec_blocks, sc, 1);
         MF_HIP(hipGetLastError());
         ++res->restarts;
         it_best = it;
