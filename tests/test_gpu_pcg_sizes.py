@@ -9,7 +9,7 @@ torch = pytest.importorskip("torch")
 
 
 @pytest.mark.parametrize("call", ["pcg", "noalloc"])
-@pytest.mark.parametrize("n", [1, 255, 257, 32768, 32769, 131072, 131073])  # 512 and 513 partials of products, of vectors
+@pytest.mark.parametrize("n", [255, 257, 32768, 32769, 131072, 131073])  # 512 and 513 partials of products, of vectors
 def test_known_solution(mf, n, call):
     """b = A x for a known x; A has eigenvalues in [1, 5], so |x - x*| <= |b - A x| <= tol |b| <= 5 tol |x*|."""
     print("[case] tridiagonal", n, call, file=sys.stderr, flush=True)
