@@ -303,19 +303,14 @@ __device__ __forceinline__ bool inverse_jacobian(const double (&J)[3][3], double
 }
 
 // Row (a, i) of one face (local face fid) of an 8-node hexahedron by the 2x2 Gauss rule,
-// times mult, added to krow and rrow.  FI >= 0 fixes the field at compile time (the flow forms,
-// so that every per-field array index is static); FI < 0 takes the runtime field fi, and then
-// only field fi of the state and target and the (a, fi) x (b, fi) block are held.  Returns false
-// (status set) on a degenerate face or element.
-template <int NF, int FI, typename T>
-__device__ __forceinline__ bool face_integral(const BParams& p, int64_t e, int fid, double mult, int a, int fi,
-                                              const double (&x)[8][3], const double (&U)[8][NF == 4 ? 4 : 1],
-                                              const double (&G)[8][NF == 4 ? 4 : 1],
-                                              double (&krow)[8][NF == 4 ? 4 : 1], double& rrow)
+// times mult, added to krow and rrow, for the forms that do not couple fields: only field i of the
+// state and target and the (a, i) x (b, i) block are held.  Returns false (status set) on a
+// degenerate face or element.
+template <typename T>
+__device__ __forceinline__ bool face_integral(const BParams& p, int64_t e, int fid, double mult, int a, int i,
+                                              const double (&x)[8][3], const double (&U)[8][1],
+                                              const double (&G)[8][1], double (&krow)[8][1], double& rrow)
 {
-    const int i = FI >= 0 ? FI : fi;
-    constexpr int NL = NF == 4 ? 4 : 1;
-    const int li = NL == 1 ? 0 : i;
     const T* tg = (const T*)p.target;
     const mf_bform_kind kind = p.form.kind;
     const double c = p.form.coef;
@@ -355,84 +350,27 @@ __device__ __forceinline__ bool face_integral(const BParams& p, int64_t e, int f
         const double nv[3] = {nr[0] / dS, nr[1] / dS, nr[2] / dS};
         const double w = mult * dS;  // unit Gauss weights on [-1, 1]^2, times the face's count
         const double Na = N[a];
-        double uq[NL], gq[NL];
+        double uq = 0.0, gq = 0.0;
 #pragma unroll
-        for (int j = 0; j < NL; ++j) {
-            uq[j] = 0.0;
-            gq[j] = 0.0;
-#pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                uq[j] = fma(N[b], U[b][j], uq[j]);
-                gq[j] = fma(N[b], G[b][j], gq[j]);
-            }
+        for (int b = 0; b < 8; ++b) {
+            uq = fma(N[b], U[b][0], uq);
+            gq = fma(N[b], G[b][0], gq);
         }
-        if constexpr (NF == 4) {
-            // flow forms (value: u^w [0..3), rho [3], mu [4]; coef = tau^b)
-            double Ji[3][3];
-            if (!inverse_jacobian(J, Ji)) {
-                atomicMin(p.status, (unsigned long long)e);
-                return false;
-            }
-            double gn[8];  // n . grad N_b
-#pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                gn[b] = 0.0;
-#pragma unroll
-                for (int m = 0; m < 3; ++m)
-                    gn[b] += nv[m] * (Ji[0][m] * dN[b][0] + Ji[1][m] * dN[b][1] + Ji[2][m] * dN[b][2]);
-            }
-            const double rho = p.form.value[3], mu = p.form.value[4], tau = c;
-            const bool wall = kind != MF_BFORM_NS_OUTFLOW;
-            double uw[3];
-#pragma unroll
-            for (int m = 0; m < 3; ++m) uw[m] = kind == MF_BFORM_NS_INFLOW ? gq[m] : 0.0;
-            const double un = uq[0] * nv[0] + uq[1] * nv[1] + uq[2] * nv[2];
-            if (i < 3) {
-                // base: p n_i - mu u_i,j n_j
-                double gu = 0.0;
-#pragma unroll
-                for (int b = 0; b < 8; ++b) {
-                    gu = fma(gn[b], U[b][i], gu);
-                    krow[b][3] += w * Na * nv[i] * N[b];
-                    krow[b][i] -= w * mu * Na * gn[b];
-                }
-                rrow += w * Na * (uq[3] * nv[i] - mu * gu);
-                if (wall) {
-                    const double uwn = uw[0] * nv[0] + uw[1] * nv[1] + uw[2] * nv[2];
-                    rrow += w * (rho * Na * uw[i] * uwn + mu * gn[a] * (uw[i] - uq[i]) +
-                                 tau * rho * Na * (uq[i] - uw[i]));
-#pragma unroll
-                    for (int b = 0; b < 8; ++b) krow[b][i] += w * (tau * rho * Na - mu * gn[a]) * N[b];
-                } else {
-                    rrow += w * rho * Na * uq[i] * un;
-#pragma unroll
-                    for (int b = 0; b < 8; ++b)
-#pragma unroll
-                        for (int k = 0; k < 3; ++k)
-                            krow[b][k] += w * rho * Na * N[b] * ((k == i ? un : 0.0) + uq[i] * nv[k]);
-                }
-            } else if (wall) {
-                rrow += w * Na * ((uw[0] - uq[0]) * nv[0] + (uw[1] - uq[1]) * nv[1] + (uw[2] - uq[2]) * nv[2]);
-#pragma unroll
-                for (int b = 0; b < 8; ++b)
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) krow[b][k] -= w * Na * N[b] * nv[k];
-            }
-        } else if (kind == MF_BFORM_PENALTY || kind == MF_BFORM_CONVECTION) {
+        if (kind == MF_BFORM_PENALTY || kind == MF_BFORM_CONVECTION) {
             // R = int c N_a (u_i - g_i)
 #pragma unroll
-            for (int b = 0; b < 8; ++b) krow[b][li] += c * w * Na * N[b];
-            rrow += c * w * Na * (uq[li] - gq[li]);
+            for (int b = 0; b < 8; ++b) krow[b][0] += c * w * Na * N[b];
+            rrow += c * w * Na * (uq - gq);
         } else if (kind == MF_BFORM_RADIATION) {
             // R = int c N_a (T^4 - T_env^4), c = e_m sigma
-            const double T1 = uq[0], Te = gq[0];
+            const double T1 = uq, Te = gq;
 #pragma unroll
-            for (int b = 0; b < 8; ++b) krow[b][li] += c * w * Na * 4.0 * T1 * T1 * T1 * N[b];
+            for (int b = 0; b < 8; ++b) krow[b][0] += c * w * Na * 4.0 * T1 * T1 * T1 * N[b];
             rrow += c * w * Na * (T1 * T1 * T1 * T1 - Te * Te * Te * Te);
         } else if (kind == MF_BFORM_TRACTION) {
             // R = -int N_a t_i, t = sigma^l n or the interpolated nodal traction
             const double* S = p.form.value;
-            const double ti = tg ? gq[li] : S[3 * i] * nv[0] + S[3 * i + 1] * nv[1] + S[3 * i + 2] * nv[2];
+            const double ti = tg ? gq : S[3 * i] * nv[0] + S[3 * i + 1] * nv[1] + S[3 * i + 2] * nv[2];
             rrow -= w * Na * ti;
         } else {  // MF_BFORM_FLUX: R = -int c N_a n . grad T
             double Ji[3][3];
@@ -447,10 +385,117 @@ __device__ __forceinline__ bool face_integral(const BParams& p, int64_t e, int f
 #pragma unroll
                 for (int m = 0; m < 3; ++m)
                     ng += nv[m] * (Ji[0][m] * dN[b][0] + Ji[1][m] * dN[b][1] + Ji[2][m] * dN[b][2]);
-                krow[b][li] -= c * w * Na * ng;
-                ngT = fma(ng, U[b][li], ngT);
+                krow[b][0] -= c * w * Na * ng;
+                ngT = fma(ng, U[b][0], ngT);
             }
             rrow -= c * w * Na * ngT;
+        }
+    }
+    return true;
+}
+
+// Row (a, FI) of one face for the flow forms (value: u^w [0..3), rho [3], mu [4]; coef = tau^b), which
+// carry the test gradient: any node of the element, all four columns.  Field and kind are known at
+// compile time, so that every index of a register array is static.  Basis and gradients of the nodes are
+// formed twice, before and after the geometry, as held between they would not fit the registers with
+// the element's data and the row.  Bound by the instructions of few waves, whose lanes have different
+// faces: the six sides of 32^3 bricks 337 us (inflow) and 359 (outflow), 410 and 405 with the kind
+// looked up and the basis held; 1000 single faces 588 and 772, 822 and 900 so.  Returns false (status set) on a
+// degenerate face or element.
+template <int FI, int KIND, typename T>
+__device__ __forceinline__ bool flow_face(const BParams& p, int64_t e, int fid, double mult, int a,
+                                          const double (&x)[8][3], const double (&U)[8][4], const double (&G)[8][4],
+                                          double (&krow)[8][4], double& rrow)
+{
+    constexpr bool kWall = KIND != MF_BFORM_NS_OUTFLOW;
+    const double rho = p.form.value[3], mu = p.form.value[4], tau = p.form.coef;
+    const int axis = fid >> 1, side = fid & 1;
+    const int u = (axis + 1) % 3, v = (axis + 2) % 3;
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+        double xi[3];
+        xi[axis] = side ? 1.0 : -1.0;
+        xi[u] = (q & 1) ? kGaussPt : -kGaussPt;
+        xi[v] = (q >> 1) ? kGaussPt : -kGaussPt;
+        // N_b and its reference gradient
+        auto basis = [&](int b, double (&dN)[3]) {
+            const int bx = b & 1, by = (b >> 1) & 1, bz = b >> 2;
+            const double Fx = lin1(bx, xi[0]), Fy = lin1(by, xi[1]), Fz = lin1(bz, xi[2]);
+            dN[0] = (bx ? 0.5 : -0.5) * (Fy * Fz);
+            dN[1] = (by ? 0.5 : -0.5) * (Fx * Fz);
+            dN[2] = (bz ? 0.5 : -0.5) * (Fx * Fy);
+            return Fx * Fy * Fz;
+        };
+        double J[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};  // J[m][n] = dx_m / dxi_n
+        double uq[4] = {0, 0, 0, 0}, uw[3] = {0, 0, 0};
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            double dN[3];
+            const double N = basis(b, dN);
+#pragma unroll
+            for (int m = 0; m < 3; ++m)
+#pragma unroll
+                for (int n = 0; n < 3; ++n) J[m][n] = fma(x[b][m], dN[n], J[m][n]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) uq[j] = fma(N, U[b][j], uq[j]);
+            if constexpr (KIND == MF_BFORM_NS_INFLOW)
+#pragma unroll
+                for (int m = 0; m < 3; ++m) uw[m] = fma(N, G[b][m], uw[m]);
+        }
+        const double tu[3] = {J[0][u], J[1][u], J[2][u]}, tv[3] = {J[0][v], J[1][v], J[2][v]};
+        const double sg = side ? 1.0 : -1.0;
+        const double nr[3] = {sg * (tu[1] * tv[2] - tu[2] * tv[1]), sg * (tu[2] * tv[0] - tu[0] * tv[2]),
+                              sg * (tu[0] * tv[1] - tu[1] * tv[0])};
+        const double dS = sqrt(nr[0] * nr[0] + nr[1] * nr[1] + nr[2] * nr[2]);
+        double Ji[3][3];
+        if (!(dS > 0.0) || !inverse_jacobian(J, Ji)) {
+            atomicMin(p.status, (unsigned long long)e);
+            return false;
+        }
+        const double nv[3] = {nr[0] / dS, nr[1] / dS, nr[2] / dS};
+        double g[3];  // n . grad N_b = g . dN_b
+#pragma unroll
+        for (int n = 0; n < 3; ++n) g[n] = nv[0] * Ji[n][0] + nv[1] * Ji[n][1] + nv[2] * Ji[n][2];
+        asm volatile("" : "+v"(xi[0]), "+v"(xi[1]), "+v"(xi[2]));  // (formed again from here on)
+        double da[3];
+        const double Na = basis(a, da), gna = g[0] * da[0] + g[1] * da[1] + g[2] * da[2];
+        const double w = mult * dS, wN = w * Na;  // unit Gauss weights on [-1, 1]^2, times the face's count
+        if constexpr (FI == 3) {
+            rrow += wN * ((uw[0] - uq[0]) * nv[0] + (uw[1] - uq[1]) * nv[1] + (uw[2] - uq[2]) * nv[2]);
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                double dN[3];
+                const double N = basis(b, dN);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) krow[b][k] = fma(-wN * nv[k], N, krow[b][k]);
+            }
+        } else {
+            const double un = uq[0] * nv[0] + uq[1] * nv[1] + uq[2] * nv[2];
+            const double wall = w * (tau * rho * Na - mu * gna);
+            double gu = 0.0, t[3];  // base: p n_i - mu u_i,j n_j
+#pragma unroll
+            for (int k = 0; k < 3; ++k) t[k] = rho * wN * ((k == FI ? un : 0.0) + uq[FI] * nv[k]);
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                double dN[3];
+                const double N = basis(b, dN), gn = g[0] * dN[0] + g[1] * dN[1] + g[2] * dN[2];
+                gu = fma(gn, U[b][FI], gu);
+                krow[b][3] = fma(wN * nv[FI], N, krow[b][3]);
+                krow[b][FI] = fma(-mu * wN, gn, krow[b][FI]);
+                if constexpr (kWall) {
+                    krow[b][FI] = fma(wall, N, krow[b][FI]);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) krow[b][k] = fma(N, t[k], krow[b][k]);
+                }
+            }
+            rrow += wN * (uq[3] * nv[FI] - mu * gu);
+            if constexpr (kWall) {
+                const double uwn = uw[0] * nv[0] + uw[1] * nv[1] + uw[2] * nv[2];
+                rrow += w * (rho * Na * uw[FI] * uwn + mu * gna * (uw[FI] - uq[FI]) + tau * rho * Na * (uq[FI] - uw[FI]));
+            } else {
+                rrow += rho * wN * uq[FI] * un;
+            }
         }
     }
     return true;
@@ -491,7 +536,7 @@ __global__ void __launch_bounds__(kThreads) k_face_rows8(BParams p)
     load_element<NF, T>(p, r.e, r.i, node, x, U, G);
 #pragma unroll
     for (int b = 0; b < 8; ++b) krow[b][0] = 0.0;
-    const bool ok = face_integral<NF, -1, T>(p, r.e, r.fid, 1.0, F::node(r.fid, r.k), r.i, x, U, G, krow, rrow);
+    const bool ok = face_integral<T>(p, r.e, r.fid, 1.0, F::node(r.fid, r.k), r.i, x, U, G, krow, rrow);
 #pragma unroll
     for (int b = 0; b < 8; ++b) out[b] = ok ? krow[b][0] : 0.0;
     store_row<F, NF>(p, r, out, ok ? rrow : 0.0);
@@ -501,7 +546,7 @@ __global__ void __launch_bounds__(kThreads) k_face_rows8(BParams p)
 // counted cnt[6 e + fid] times), for 8-node hexahedra.  The caller runs one element colour
 // per launch: no other thread of the launch touches row a, so the row is added with plain
 // stores.
-template <int NF, int FI, typename T>
+template <int NF, int FI, int KIND, typename T>
 __device__ __forceinline__ void boundary_row(const BParams& p, int64_t e, uint32_t fmask, int a, int fi)
 {
     const int i = FI >= 0 ? FI : fi;
@@ -522,7 +567,12 @@ __device__ __forceinline__ void boundary_row(const BParams& p, int64_t e, uint32
         // the row nodes of a face are its four nodes (every node of the element for the
         // flow forms, whose terms carry the test gradient)
         if (NF != 4 && ((a >> (fid >> 1)) & 1) != (fid & 1)) continue;
-        if (!face_integral<NF, FI, T>(p, e, fid, (double)p.face_cnt[6 * e + fid], a, fi, x, U, G, krow, rrow)) return;
+        const double mult = (double)p.face_cnt[6 * e + fid];
+        if constexpr (NF == 4) {
+            if (!flow_face<FI, KIND, T>(p, e, fid, mult, a, x, U, G, krow, rrow)) return;
+        } else {
+            if (!face_integral<T>(p, e, fid, mult, a, fi, x, U, G, krow, rrow)) return;
+        }
     }
 
     const int64_t va = node[a];
@@ -561,7 +611,7 @@ __device__ __forceinline__ void boundary_row(const BParams& p, int64_t e, uint32
 
 // Items (element with listed faces of the colour, element node a, field i), strided over
 // the grid; the colour's element list and its length come from k_face_mark.
-template <int NF, typename T>
+template <int NF, int KIND, typename T>
 __global__ void __launch_bounds__(kThreads) k_boundary(BParams p, const int32_t* __restrict__ elems,
                                                        const uint32_t* __restrict__ n_el_c)
 {
@@ -574,13 +624,14 @@ __global__ void __launch_bounds__(kThreads) k_boundary(BParams p, const int32_t*
         const int a = ki / NF, i = ki % NF;
         if constexpr (NF == 4) {
             switch (i) {
-                case 0: boundary_row<NF, 0, T>(p, e, fmask, a, i); break;
-                case 1: boundary_row<NF, 1, T>(p, e, fmask, a, i); break;
-                case 2: boundary_row<NF, 2, T>(p, e, fmask, a, i); break;
-                default: boundary_row<NF, 3, T>(p, e, fmask, a, i); break;
+                case 0: boundary_row<NF, 0, KIND, T>(p, e, fmask, a, i); break;
+                case 1: boundary_row<NF, 1, KIND, T>(p, e, fmask, a, i); break;
+                case 2: boundary_row<NF, 2, KIND, T>(p, e, fmask, a, i); break;
+                default:  // (the outflow form has no continuity rows)
+                    if constexpr (KIND != MF_BFORM_NS_OUTFLOW) boundary_row<NF, 3, KIND, T>(p, e, fmask, a, i);
             }
         } else {
-            boundary_row<NF, -1, T>(p, e, fmask, a, i);
+            boundary_row<NF, -1, KIND, T>(p, e, fmask, a, i);
         }
     }
 }
@@ -1167,7 +1218,16 @@ mf_status launch_boundary(BParams p, const mf_pattern_s* Pc, hipStream_t s)
         const int64_t bound = std::min<int64_t>(P->color_ptr[c + 1] - P->color_ptr[c], p.n_faces) * 8 * NF;
         if (bound == 0) continue;
         const unsigned blocks = (unsigned)std::min<int64_t>(2048, (bound + kThreads - 1) / kThreads);
-        k_boundary<NF, T><<<blocks, kThreads, 0, s>>>(p, clist + P->color_ptr[c], ccount + c);
+        auto run = [&](auto kernel) { kernel<<<blocks, kThreads, 0, s>>>(p, clist + P->color_ptr[c], ccount + c); };
+        if constexpr (NF == 4) {
+            switch (p.form.kind) {
+                case MF_BFORM_NS_INFLOW: run(k_boundary<4, MF_BFORM_NS_INFLOW, T>); break;
+                case MF_BFORM_NS_OUTFLOW: run(k_boundary<4, MF_BFORM_NS_OUTFLOW, T>); break;
+                default: run(k_boundary<4, MF_BFORM_NS_FIX, T>);
+            }
+        } else {
+            run(k_boundary<NF, -1, T>);
+        }
     }
     MF_HIP(hipGetLastError());
     return MF_OK;
