@@ -12,10 +12,17 @@ namespace {
 constexpr int kWave = 64;
 constexpr int kSlots = 4;                 // lanes of a row
 constexpr int kRows = kWave / kSlots;     // rows of a wave
-// Up to 64 rows go as one workgroup that resets the status itself: one launch (1 x 1 element, all
-// host work included: 10 us against 13).  More rows go as one wave per workgroup after the reset's
-// launch, so that they spread over the chip.
-constexpr int kAlone = 4;  // waves
+// Few rows go as one workgroup that resets the status itself, in one launch: 9.5 us with all host work
+// (1 x 1 to 15 x 15 conduction; 18 x 18 9.8, with constrained sides 11.4) against 12.4 in two (12.6).  More
+// rows go as one wave per workgroup after the reset's launch, so that they spread over the chip: in
+// one workgroup 21 x 21 take 12.8 and 15.0 us, and elasticity on 6 x 6, of 98 rows, in two passes of four
+// waves 15.5.
+template <int FORM>
+struct Alone {
+    static constexpr bool SCALAR = FORM == MF_FORM_MASS || FORM == MF_FORM_POISSON;
+    static constexpr int WAVES = SCALAR ? 16 : 4;  // of the workgroup
+    static constexpr int MOST = SCALAR ? 24 : 4;   // passes of a wave over kRows rows, in all waves
+};
 
 struct QuadParams {
     mf_form form;
@@ -30,7 +37,7 @@ struct QuadParams {
     const void* elem_param;
     const void* src;  // nodal sources (mass, conduction, elasticity) or state (flow)
     const uint8_t* mask;
-    int field_major, max_deg, alone;
+    int field_major, max_deg;
     void* K;
     void* d;
     unsigned long long* status;
@@ -50,112 +57,115 @@ __device__ __forceinline__ void wave_sync()
 // conduction on 32^2 12 us a call, of which the launches take most, against 37 in one workgroup
 // colour by colour; flow 32^2 13 against 654.  Large ones are bound by the FP64 geometry, formed
 // for each row: conduction 1024^2 119 us against 332, flow 1620 against 3309.
-template <int FORM, typename T>
-__global__ void __launch_bounds__(kAlone * kWave) k_quad_rows(QuadParams p)
+template <int FORM, typename T, bool ALONE>
+__global__ void __launch_bounds__((ALONE ? Alone<FORM>::WAVES : 1) * kWave) k_quad_rows(QuadParams p)
 {
     constexpr int NEN = 4;
     constexpr int NF = FormTraits<FORM, 2>::NF;
     constexpr int NSRC = FormTraits<FORM, 2>::NSRC;
     extern __shared__ double lds[];
-    if (p.alone) {
+    if constexpr (ALONE) {
         if (threadIdx.x < 3) p.status[threadIdx.x] = ~0ull;
         __syncthreads();
     }
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, slot = lane % kSlots;
-    const int64_t r0 = ((int64_t)blockIdx.x * (blockDim.x / kWave) + wave) * kRows, r1 = min(r0 + kRows, p.n_rows);
-    if (r0 >= r1) return;
     // [values of the wave's rows], then [kRows] of d
     double* const buf = lds + wave * kRows * (NF * p.max_deg + 1);
-    const int64_t r = min(r0 + lane / kSlots, r1 - 1);
-    const bool live = r0 + lane / kSlots < r1;
-    const int64_t va = p.field_major ? r % p.n_nodes : r / NF;
-    const int i = (int)(p.field_major ? r / p.n_nodes : r % NF);
-    const int a0 = p.adj_ptr[va], n_adj = live ? p.adj_ptr[va + 1] - a0 : 0;
-    const int64_t k0 = p.row_ptr[r0], rs = p.row_ptr[r];
-    const int len = (int)(p.row_ptr[r + 1] - rs), deg = len / NF, total = (int)(p.row_ptr[r1] - k0);
-    double* const row = buf + (rs - k0);
-    double* const dsum = buf + kRows * NF * p.max_deg;
-    for (int k = lane; k < total; k += kWave) buf[k] = 0.0;
-    if (lane < kRows) dsum[lane] = 0.0;
-    wave_sync();
-    const T* src = (const T*)p.src;
-    for (int s0 = 0; __any(s0 < n_adj); s0 += kSlots) {
-        const bool on = s0 + slot < n_adj;
-        T krow[NEN * NF];
-        T rrow = T(0);
+    const int n_waves = blockDim.x / kWave;
+    for (int64_t r0 = ((int64_t)blockIdx.x * n_waves + wave) * kRows; r0 < p.n_rows; r0 += (int64_t)gridDim.x * n_waves * kRows) {
+        const int64_t r1 = min(r0 + kRows, p.n_rows);
+        const int64_t r = min(r0 + lane / kSlots, r1 - 1);
+        const bool live = r0 + lane / kSlots < r1;
+        const int64_t va = p.field_major ? r % p.n_nodes : r / NF;
+        const int i = (int)(p.field_major ? r / p.n_nodes : r % NF);
+        const int a0 = p.adj_ptr[va], n_adj = live ? p.adj_ptr[va + 1] - a0 : 0;
+        const int64_t k0 = p.row_ptr[r0], rs = p.row_ptr[r];
+        const int len = (int)(p.row_ptr[r + 1] - rs), deg = len / NF, total = (int)(p.row_ptr[r1] - k0);
+        double* const row = buf + (rs - k0);
+        double* const dsum = buf + kRows * NF * p.max_deg;
+        for (int k = lane; k < total; k += kWave) buf[k] = 0.0;
+        if (lane < kRows) dsum[lane] = 0.0;
+        wave_sync();
+        const T* src = (const T*)p.src;
+        for (int s0 = 0; __any(s0 < n_adj); s0 += kSlots) {
+            const bool on = s0 + slot < n_adj;
+            T krow[NEN * NF];
+            T rrow = T(0);
 #pragma unroll
-        for (int k = 0; k < NEN * NF; ++k) krow[k] = T(0);
-        int at[NEN] = {0, 0, 0, 0};
-        if (on) {
-            const int32_t ent = p.adj[a0 + s0 + slot];
-            const int64_t e = ent / NEN;
-            const int a = ent % NEN;
-            const uint32_t rk = *(const uint32_t*)(p.rank_t + (int64_t)ent * NEN);
-            double x[NEN][2];
-            T U[NEN][NSRC];
-#pragma unroll
-            for (int b = 0; b < NEN; ++b) {
-                const int64_t node = p.conn[b * p.n_el + e];
-#pragma unroll
-                for (int m = 0; m < 2; ++m) x[b][m] = p.coords[m * p.n_nodes + node];
-#pragma unroll
-                for (int s = 0; s < NSRC; ++s) U[b][s] = src ? src[s * p.n_nodes + node] : T(0);
-                at[b] = (int)(rk >> 8 * b & 255u) * (p.field_major ? 1 : NF);
-            }
-            const Coef<T> C = make_coef<T>(FORM, p.form, p.elem_param ? (double)((const T*)p.elem_param)[e] : 1.0);
-            bool bad = false;
-#pragma unroll
-            for (int q = 0; q < NEN; ++q) {  // 2 x 2 Gauss points, unit weights
-                double gd[NEN][2];
-                const double det = geometry_at<2>(x, q, gd);
-                bad |= !(det > 0.0);
-                T N[NEN], g[NEN][2];
+            for (int k = 0; k < NEN * NF; ++k) krow[k] = T(0);
+            int at[NEN] = {0, 0, 0, 0};
+            if (on) {
+                const int32_t ent = p.adj[a0 + s0 + slot];
+                const int64_t e = ent / NEN;
+                const int a = ent % NEN;
+                const uint32_t rk = *(const uint32_t*)(p.rank_t + (int64_t)ent * NEN);
+                double x[NEN][2];
+                T U[NEN][NSRC];
 #pragma unroll
                 for (int b = 0; b < NEN; ++b) {
-                    N[b] = (T)ref_N<2>(b, q);
+                    const int64_t node = p.conn[b * p.n_el + e];
 #pragma unroll
-                    for (int m = 0; m < 2; ++m) g[b][m] = (T)gd[b][m];
+                    for (int m = 0; m < 2; ++m) x[b][m] = p.coords[m * p.n_nodes + node];
+#pragma unroll
+                    for (int s = 0; s < NSRC; ++s) U[b][s] = src ? src[s * p.n_nodes + node] : T(0);
+                    at[b] = (int)(rk >> 8 * b & 255u) * (p.field_major ? 1 : NF);
                 }
-                row_update<FORM, 2, T>(a, i, C, N, g, (T)det, U, krow, rrow);
+                const Coef<T> C = make_coef<T>(FORM, p.form, p.elem_param ? (double)((const T*)p.elem_param)[e] : 1.0);
+                bool bad = false;
+#pragma unroll
+                for (int q = 0; q < NEN; ++q) {  // 2 x 2 Gauss points, unit weights
+                    double gd[NEN][2];
+                    const double det = geometry_at<2>(x, q, gd);
+                    bad |= !(det > 0.0);
+                    T N[NEN], g[NEN][2];
+#pragma unroll
+                    for (int b = 0; b < NEN; ++b) {
+                        N[b] = (T)ref_N<2>(b, q);
+#pragma unroll
+                        for (int m = 0; m < 2; ++m) g[b][m] = (T)gd[b][m];
+                    }
+                    row_update<FORM, 2, T>(a, i, C, N, g, (T)det, U, krow, rrow);
+                }
+                T chk = rrow;
+#pragma unroll
+                for (int k = 0; k < NEN * NF; ++k) chk += krow[k];
+                if (bad) atomicMin(p.status, (unsigned long long)e);
+                else if (!isfinite(chk)) atomicMin(p.status + 2, (unsigned long long)e);
+                if (bad) {  // such an element adds nothing
+#pragma unroll
+                    for (int k = 0; k < NEN * NF; ++k) krow[k] = T(0);
+                    rrow = T(0);
+                }
             }
-            T chk = rrow;
+            const int step = p.field_major ? deg : 1;
+            for (int turn = 0; turn < kSlots; ++turn) {
+                if (on && turn == slot) {
 #pragma unroll
-            for (int k = 0; k < NEN * NF; ++k) chk += krow[k];
-            if (bad) atomicMin(p.status, (unsigned long long)e);
-            else if (!isfinite(chk)) atomicMin(p.status + 2, (unsigned long long)e);
-            if (bad) {  // such an element adds nothing
+                    for (int b = 0; b < NEN; ++b)
 #pragma unroll
-                for (int k = 0; k < NEN * NF; ++k) krow[k] = T(0);
-                rrow = T(0);
+                        for (int j = 0; j < NF; ++j) row[at[b] + j * step] += (double)krow[b * NF + j];
+                    dsum[lane / kSlots] -= (double)rrow;
+                }
+                wave_sync();
             }
         }
-        const int step = p.field_major ? deg : 1;
-        for (int turn = 0; turn < kSlots; ++turn) {
-            if (on && turn == slot) {
-#pragma unroll
-                for (int b = 0; b < NEN; ++b)
-#pragma unroll
-                    for (int j = 0; j < NF; ++j) row[at[b] + j * step] += (double)krow[b * NF + j];
-                dsum[lane / kSlots] -= (double)rrow;
+        // homogeneous Dirichlet elimination: a constrained row becomes a unit row with d = 0, a
+        // constrained column is zeroed in the other rows
+        if (p.mask && live) {
+            const bool fixed = p.mask[r] != 0;
+            for (int k = slot; k < len; k += kSlots) {
+                const int32_t c = p.col_idx[rs + k];
+                if (fixed) row[k] = c == r ? 1.0 : 0.0;
+                else if (p.mask[c]) row[k] = 0.0;
             }
-            wave_sync();
+            if (fixed && slot == 0) dsum[lane / kSlots] = 0.0;
         }
+        wave_sync();
+        T* K = (T*)p.K + k0;
+        for (int k = lane; k < total; k += kWave) K[k] = (T)buf[k];
+        if (lane < (int)(r1 - r0)) ((T*)p.d)[r0 + lane] = (T)dsum[lane];
+        wave_sync();
     }
-    // homogeneous Dirichlet elimination: a constrained row becomes a unit row with d = 0, a
-    // constrained column is zeroed in the other rows
-    if (p.mask && live) {
-        const bool fixed = p.mask[r] != 0;
-        for (int k = slot; k < len; k += kSlots) {
-            const int32_t c = p.col_idx[rs + k];
-            if (fixed) row[k] = c == r ? 1.0 : 0.0;
-            else if (p.mask[c]) row[k] = 0.0;
-        }
-        if (fixed && slot == 0) dsum[lane / kSlots] = 0.0;
-    }
-    wave_sync();
-    T* K = (T*)p.K + k0;
-    for (int k = lane; k < total; k += kWave) K[k] = (T)buf[k];
-    if (lane < (int)(r1 - r0)) ((T*)p.d)[r0 + lane] = (T)dsum[lane];
 }
 
 template <int FORM, typename T>
@@ -185,13 +195,13 @@ mf_status launch_quads(const AssembleArgs& A)
     const size_t lds = sizeof(double) * kRows * ((size_t)P->nf * p.max_deg + 1);  // a wave's
     if (lds > 65536) return MF_ERR_UNSUPPORTED;
     const int64_t waves = (P->n_rows + kRows - 1) / kRows;
-    p.alone = waves <= kAlone && lds * (size_t)waves <= 65536;
-    if (p.alone) {
-        k_quad_rows<FORM, T><<<1, (unsigned)waves * kWave, lds * (size_t)waves, A.stream>>>(p);
+    const int64_t alone = std::min<int64_t>(waves, Alone<FORM>::WAVES);
+    if (waves <= Alone<FORM>::MOST && lds * (size_t)alone <= 65536) {
+        k_quad_rows<FORM, T, true><<<1, (unsigned)alone * kWave, lds * (size_t)alone, A.stream>>>(p);
     } else {
         const mf_status st = reset_status(P, A.stream);
         if (st != MF_OK) return st;
-        k_quad_rows<FORM, T><<<(unsigned)waves, kWave, lds, A.stream>>>(p);
+        k_quad_rows<FORM, T, false><<<(unsigned)waves, kWave, lds, A.stream>>>(p);
     }
     MF_HIP(hipGetLastError());
     return MF_OK;
