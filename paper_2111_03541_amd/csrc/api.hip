@@ -100,19 +100,10 @@ static bool column_wins(const AssembleArgs& A)
 static void free_pattern(mf_pattern_s* P)
 {
     if (!P) return;
-    (void)hipFree(P->conn);
-    (void)hipFree(P->nbr_ptr);
-    (void)hipFree(P->nbr);
-    (void)hipFree(P->row_ptr);
-    (void)hipFree(P->col_idx);
-    (void)hipFree(P->rank);
-    (void)hipFree(P->adj_ptr);
-    (void)hipFree(P->adj);
-    (void)hipFree(P->rank_t);
+    for (void* m : P->mem) (void)hipFree(m);
     (void)hipFree(P->ws);
     for (const auto& w : P->cap_ws) (void)hipFree(w.p);
     if (P->ws_done) (void)hipEventDestroy(P->ws_done);
-    (void)hipFree(P->status);
     (void)hipFree(P->color_elems);
     (void)hipFree(P->elem_color);
     (void)hipFree(P->color_at);

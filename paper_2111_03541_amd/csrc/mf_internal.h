@@ -18,7 +18,8 @@ struct mf_pattern_s {
     int64_t n_nodes = 0, n_elems = 0, n_rows = 0, nnz = 0, n_pairs = 0;
     uint8_t coupling[16] = {0};
     bool full_coupling = false;
-    // device arrays, all owned
+    // device arrays, in two allocations (pattern.hip)
+    void* mem[2] = {nullptr, nullptr};
     int32_t* conn = nullptr;     // [nen][n_elems] copy of the caller's connectivity
     int32_t* nbr_ptr = nullptr;  // [n_nodes+1] node graph offsets
     int32_t* nbr = nullptr;      // [n_pairs] sorted neighbours N(v)

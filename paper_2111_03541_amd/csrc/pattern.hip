@@ -288,41 +288,39 @@ __global__ void k_scan_add(int64_t* __restrict__ out, int64_t n, const int64_t* 
     if (i < n) out[i] += tile_off[i / kScanTile];
 }
 
+int64_t scan_tiles(int64_t n) { return std::max<int64_t>(1, (n + kScanTile - 1) / kScanTile); }
+
+// Scratch of a scan of n counts: per level the sums of its tiles and their offsets.
+int64_t scan_scratch(int64_t n)
+{
+    const int64_t tiles = scan_tiles(n);
+    return 2 * tiles + 1 + (tiles > 1 ? scan_scratch(tiles) : 0);
+}
+
 // out[0..n] = exclusive prefix sums of in[0..n-1], out[n] = total.
 template <typename TIn>
-mf_status exclusive_scan(const TIn* in, int64_t n, int64_t* out, hipStream_t s)
+mf_status exclusive_scan(const TIn* in, int64_t n, int64_t* out, int64_t* scratch, hipStream_t s)
 {
-    int64_t tiles = (n + kScanTile - 1) / kScanTile;
-    if (tiles == 0) tiles = 1;
-    int64_t* sums = nullptr;
-    int64_t* offs = nullptr;
-    MF_HIP(hipMalloc(&sums, sizeof(int64_t) * tiles));
-    MF_HIP(hipMalloc(&offs, sizeof(int64_t) * (tiles + 1)));
     if (n == 0) {
         MF_HIP(hipMemsetAsync(out, 0, sizeof(int64_t), s));
-        MF_HIP(hipStreamSynchronize(s));
-        MF_HIP(hipFree(sums));
-        MF_HIP(hipFree(offs));
         return MF_OK;
     }
+    const int64_t tiles = scan_tiles(n);
+    int64_t* sums = scratch;
+    int64_t* offs = sums + tiles;
     k_scan_tiles<TIn><<<(unsigned)tiles, kThreads, 0, s>>>(in, n, out, sums);
     MF_HIP(hipGetLastError());
-    mf_status st = MF_OK;
     if (tiles > 1) {
-        st = exclusive_scan<int64_t>(sums, tiles, offs, s);
+        const mf_status st = exclusive_scan<int64_t>(sums, tiles, offs, offs + tiles + 1, s);
+        if (st != MF_OK) return st;
     } else {
         MF_HIP(hipMemsetAsync(offs, 0, sizeof(int64_t), s));
         MF_HIP(hipMemcpyAsync(offs + 1, sums, sizeof(int64_t), hipMemcpyDeviceToDevice, s));
     }
-    if (st == MF_OK) {
-        k_scan_add<<<blocks_for(n, kThreads), kThreads, 0, s>>>(out, n, offs);
-        MF_HIP(hipGetLastError());
-        MF_HIP(hipMemcpyAsync(out + n, offs + tiles, sizeof(int64_t), hipMemcpyDeviceToDevice, s));
-    }
-    MF_HIP(hipStreamSynchronize(s));
-    MF_HIP(hipFree(sums));
-    MF_HIP(hipFree(offs));
-    return st;
+    k_scan_add<<<blocks_for(n, kThreads), kThreads, 0, s>>>(out, n, offs);
+    MF_HIP(hipGetLastError());
+    MF_HIP(hipMemcpyAsync(out + n, offs + tiles, sizeof(int64_t), hipMemcpyDeviceToDevice, s));
+    return MF_OK;
 }
 
 __global__ void k_i64_to_i32(const int64_t* __restrict__ in, int64_t n, int32_t* __restrict__ out)
@@ -331,21 +329,38 @@ __global__ void k_i64_to_i32(const int64_t* __restrict__ in, int64_t n, int32_t*
     if (i < n) out[i] = (int32_t)in[i];
 }
 
-struct Scratch {
-    std::vector<void*> ptrs;
-    ~Scratch() {
-        for (void* p : ptrs) (void)hipFree(p);
-    }
+// Arrays one after another in one allocation, each at a multiple of 256 bytes: an allocation and its
+// release cost tens of microseconds each, and a pattern has some twenty arrays.
+struct Layout {
+    char* base;  // nullptr: only the size is asked for
+    size_t used = 0;
     template <typename T>
-    mf_status alloc(T** p, int64_t n) {
-        void* q = nullptr;
-        hipError_t e = hipMalloc(&q, (size_t)(n > 0 ? n : 1) * sizeof(T));
-        if (e != hipSuccess) return set_error(MF_ERR_OOM, "device allocation of %lld bytes failed",
-                                              (long long)(n * (int64_t)sizeof(T)));
-        ptrs.push_back(q);
-        *p = (T*)q;
-        return MF_OK;
+    void take(T** p, int64_t n)
+    {
+        if (base) *p = (T*)(base + used);
+        used += (sizeof(T) * (size_t)n + 255) / 256 * 256;
     }
+};
+
+// lay(Layout&) takes the arrays; *mem is the caller's to free.
+template <typename F>
+mf_status allocate(void** mem, F&& lay)
+{
+    Layout size{nullptr};
+    lay(size);
+    if (hipMalloc(mem, std::max<size_t>(size.used, 256)) != hipSuccess) {
+        (void)hipGetLastError();
+        *mem = nullptr;
+        return set_error(MF_ERR_OOM, "device allocation of %lld bytes failed", (long long)size.used);
+    }
+    Layout l{(char*)*mem};
+    lay(l);
+    return MF_OK;
+}
+
+struct Scratch {
+    void* p = nullptr;
+    ~Scratch() { (void)hipFree(p); }
 };
 
 #define MF_TRY(x)                          \
@@ -365,21 +380,30 @@ mf_status build_pattern(mf_pattern_s* P, const int32_t* conn_in, hipStream_t s)
     int *flag = nullptr, *stats = nullptr;
     int32_t *cnt = nullptr, *cursor = nullptr, *deg = nullptr;
     int64_t *inc_ptr = nullptr, *nbr_ptr64 = nullptr;
-    MF_TRY(tmp.alloc(&flag, 1));
-    MF_TRY(tmp.alloc(&stats, 2));
-    MF_TRY(tmp.alloc(&cnt, n_nodes));
-    MF_TRY(tmp.alloc(&cursor, n_nodes));
-    MF_TRY(tmp.alloc(&deg, n_nodes));
-    MF_TRY(tmp.alloc(&inc_ptr, n_nodes + 1));
-    MF_TRY(tmp.alloc(&nbr_ptr64, n_nodes + 1));
-
-    // library-owned copy of the connectivity
-    MF_HIP(hipMalloc(&P->conn, sizeof(int32_t) * (size_t)(n_ent > 0 ? n_ent : 1)));
+    int64_t* scan = nullptr;
+    MF_TRY(allocate(&tmp.p, [&](Layout& l) {
+        l.take(&flag, 1);
+        l.take(&stats, 2);
+        l.take(&cnt, n_nodes);
+        l.take(&cursor, n_nodes);
+        l.take(&deg, n_nodes);
+        l.take(&inc_ptr, n_nodes + 1);
+        l.take(&nbr_ptr64, n_nodes + 1);
+        l.take(&scan, scan_scratch(n_nodes));
+    }));
+    MF_TRY(allocate(&P->mem[0], [&](Layout& l) {
+        l.take(&P->conn, n_ent);  // library-owned copy of the connectivity
+        l.take(&P->adj_ptr, n_nodes + 1);
+        l.take(&P->adj, n_ent);
+        l.take(&P->nbr_ptr, n_nodes + 1);
+        l.take(&P->row_ptr, P->n_rows + 1);
+        l.take(&P->rank, nen * n_ent);
+        l.take(&P->rank_t, nen * n_ent);
+        l.take(&P->status, 3);  // bad element, bad face, non-finite element
+    }));
     if (n_ent > 0)
         MF_HIP(hipMemcpyAsync(P->conn, conn_in, sizeof(int32_t) * (size_t)n_ent, hipMemcpyDeviceToDevice, s));
     const int32_t* conn = P->conn;
-    MF_HIP(hipMalloc(&P->adj_ptr, sizeof(int32_t) * (size_t)(n_nodes + 1)));
-    MF_HIP(hipMalloc(&P->adj, sizeof(int32_t) * (size_t)(n_ent > 0 ? n_ent : 1)));
     int32_t* inc = P->adj;
 
     k_fill_i32<<<1, 1, 0, s>>>((int32_t*)flag, 1, 0);
@@ -396,7 +420,7 @@ mf_status build_pattern(mf_pattern_s* P, const int32_t* conn_in, hipStream_t s)
     MF_HIP(hipStreamSynchronize(s));
     if (hflag & 1) return set_error(MF_ERR_BAD_MESH, "conn holds a node id outside [0, %lld)",
                                     (long long)n_nodes);
-    MF_TRY(exclusive_scan<int32_t>(cnt, n_nodes, inc_ptr, s));
+    MF_TRY(exclusive_scan<int32_t>(cnt, n_nodes, inc_ptr, scan, s));
     if (n_ent > 0)
         k_fill_incidence<<<blocks_for(n_ent, kThreads), kThreads, 0, s>>>(conn, n_el, nen, inc_ptr, cursor, inc);
     k_i64_to_i32<<<blocks_for(n_nodes + 1, kThreads), kThreads, 0, s>>>(inc_ptr, n_nodes + 1, P->adj_ptr);
@@ -417,7 +441,7 @@ mf_status build_pattern(mf_pattern_s* P, const int32_t* conn_in, hipStream_t s)
             deg, n_nodes, inc_ptr, inc, nen, stats);
     }
     MF_HIP(hipGetLastError());
-    MF_TRY(exclusive_scan<int32_t>(deg, n_nodes, nbr_ptr64, s));
+    MF_TRY(exclusive_scan<int32_t>(deg, n_nodes, nbr_ptr64, scan, s));
     MF_HIP(hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, s));
     int hstats[2] = {0, 0};
     MF_HIP(hipMemcpyAsync(hstats, stats, sizeof(hstats), hipMemcpyDeviceToHost, s));
@@ -448,13 +472,10 @@ mf_status build_pattern(mf_pattern_s* P, const int32_t* conn_in, hipStream_t s)
     P->n_pairs = n_pairs;
     P->nnz = nnz;
 
-    MF_HIP(hipMalloc(&P->nbr_ptr, sizeof(int32_t) * (size_t)(n_nodes + 1)));
-    MF_HIP(hipMalloc(&P->nbr, sizeof(int32_t) * (size_t)(n_pairs > 0 ? n_pairs : 1)));
-    MF_HIP(hipMalloc(&P->row_ptr, sizeof(int32_t) * (size_t)(P->n_rows + 1)));
-    MF_HIP(hipMalloc(&P->col_idx, sizeof(int32_t) * (size_t)(nnz > 0 ? nnz : 1)));
-    MF_HIP(hipMalloc(&P->rank, (size_t)(nen * nen * (n_el > 0 ? n_el : 1))));
-    MF_HIP(hipMalloc(&P->rank_t, (size_t)(nen * nen * (n_el > 0 ? n_el : 1))));
-    MF_HIP(hipMalloc(&P->status, 3 * sizeof(unsigned long long)));  // bad element, bad face, non-finite element
+    MF_TRY(allocate(&P->mem[1], [&](Layout& l) {
+        l.take(&P->nbr, n_pairs);
+        l.take(&P->col_idx, nnz);
+    }));
 
     k_i64_to_i32<<<blocks_for(n_nodes + 1, kThreads), kThreads, 0, s>>>(nbr_ptr64, n_nodes + 1, P->nbr_ptr);
     if (n_nodes > 0) node_neighbours(nbr_ptr64, P->nbr);
