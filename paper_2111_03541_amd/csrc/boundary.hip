@@ -1193,7 +1193,7 @@ mf_status launch_boundary(BParams p, const mf_pattern_s* Pc, hipStream_t s)
     mf_status st = ensure_coloring(P);
     if (st != MF_OK) return st;
     const int n_col = (int)P->color_ptr.size() - 1;
-    // workspace: mask [n_el], counts [6 n_el], colour lists [n_el], list lengths [n_col]
+    // workspace: mask [n_el], counts [6 n_el], list lengths [n_col], colour lists [n_el]
     const int64_t n_el = P->n_elems;
     const size_t bytes = sizeof(uint32_t) * (size_t)(8 * n_el + n_col);
     const Workspace held(P, bytes, s);
@@ -1205,10 +1205,10 @@ mf_status launch_boundary(BParams p, const mf_pattern_s* Pc, hipStream_t s)
     }
     if (!mask) return set_error(MF_ERR_OOM, "no memory for the boundary faces' workspace");
     uint32_t* cnt = mask + n_el;
-    int32_t* clist = (int32_t*)(cnt + 6 * n_el);
-    uint32_t* ccount = (uint32_t*)(clist + n_el);
-    k_face_zero<<<(unsigned)((7 * n_el + kThreads - 1) / kThreads), kThreads, 0, s>>>(mask, 7 * n_el);
-    k_face_zero<<<(unsigned)((n_col + kThreads - 1) / kThreads), kThreads, 0, s>>>(ccount, n_col);
+    uint32_t* ccount = cnt + 6 * n_el;
+    int32_t* clist = (int32_t*)(ccount + n_col);
+    const int64_t clear = 7 * n_el + n_col;
+    k_face_zero<<<(unsigned)((clear + kThreads - 1) / kThreads), kThreads, 0, s>>>(mask, clear);
     k_face_mark<<<(unsigned)((p.n_faces + kThreads - 1) / kThreads), kThreads, 0, s>>>(
         p.face_elem, p.face_id, p.n_faces, n_el, P->elem_color, P->color_at, mask, cnt, clist, ccount, P->status);
     p.face_mask = mask;
