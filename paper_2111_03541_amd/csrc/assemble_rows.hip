@@ -1319,14 +1319,22 @@ mf_status launch_rows(const AssembleArgs& A)
 }
 
 // Rows with the geometry, in one launch without a workspace, against element blocks and their gather
-// (FP64, us): conduction 12^3 13 against 17, 28^3 18 against 36, 40^3 38 against 45, 48^3 58 against
-// 60, with Dirichlet rows 47 against 49 and 70 against 66, 64^3 126 against 120; FP32 40^3 39 against
-// 44, 48^3 the same; mass, with half the work, 48^3 45 against 57, 64^3 98 against 111, but FP32 120
-// against 104.  On a scattered mesh each of a node's elements reads its 24 coordinates from anywhere:
-// 24^3 27 against 31, 41x40x37 87 against 57.
+// (us; "fixed": with constrained sides).  Conduction 12^3 12 against 16, 28^3 17 against 35, 40^3 36
+// against 44 (FP32 37 against 43, fixed 45 against 48, FP32 fixed 47 both), 48^3 56 against 59 (57
+// against 56, 69 against 64, 71 against 63).  Mass, with half the work, 48^3 43 against 56, 52^3 55
+// against 68 (FP32 59 to 64 against 62), 56^3 71 against 81 (81 against 74); fixed, where each lane
+// looks up its element's flags, 46^3 53 against 58 (53 against 54), 48^3 60 against 62 (61 against 59),
+// 50^3 71 against 68 (72 against 65), 52^3 79 against 74 (81 against 70).  On a scattered mesh each of a
+// node's elements reads its 24 coordinates from anywhere: conduction 24^3 26 against 30 (FP32 26
+// against 27), 27^3 32 against 36 (34 against 33), 30^3 41 both (44 against 38), 41x40x37 86 against 55;
+// fixed 20^3 26 both (26 against 24), 24^3 32 both (31 against 29), 27^3 41 against 39 (43 against 37).
 bool direct_wins(const AssembleArgs& A)
 {
-    return A.P->n_elems < (A.P->scattered ? 20000 : A.form->kind == MF_FORM_MASS ? 150000 : 70000);
+    const bool f32 = A.prec == MF_F32, fixed = A.dirichlet != nullptr;
+    const int64_t n = A.P->n_elems;
+    if (A.P->scattered) return n < (fixed ? (f32 ? 8000 : 14000) : f32 ? 16000 : 20000);
+    if (A.form->kind == MF_FORM_MASS) return n < (!fixed ? 150000 : f32 ? 100000 : 115000);
+    return n < 70000;
 }
 
 template <typename T>
