@@ -803,11 +803,14 @@ struct RowParams {
 
 // The workgroup's nodes, in units of per_block, or -1.  A record is read by the eight nodes around
 // its element.  In node order an XCD has passed a whole plane of the grid before the next reads it
-// again, and a plane above some 1 MB of records has left the XCD's 4 MB of L2 by then, with all of K
+// again, and a plane above some 2.5 MB of records has left the XCD's 4 MB of L2 by then, with all of K
 // streaming through: each record was fetched twice (elasticity 64^3: 400 MB for 201).  So each XCD
-// takes a band of an eighth of every plane, and goes through the planes: 255 MB fetched, and the
-// flow form on 48^3 FP64 460 -> 432 us, FP32 419 -> 404 (elasticity 64^3 320 us both ways: it waits
-// for latencies rather than bytes).
+// takes a band of an eighth of every plane, and goes through the planes: 255 MB fetched.  Whole calls,
+// nodes in order against bands: flow 48^3 FP64 411 against 383 us, FP32 405 against 388, 40^3 FP64 226
+// against 225, with constrained DOFs 255 against 250; elasticity 64^3 318 against 311, 62^3 313 against
+// 285, 58^3 263 against 247.  Below, where the records stay, the bands' uneven ends only cost: flow 36^3 168
+// against 175 (FP32, constrained 182 against 193), elasticity 48^3 137 against 140 (constrained 176
+// against 180, FP32 162 against 167), 56^3 FP32 252 against 264.
 __device__ __forceinline__ int row_block(const RowParams& p, int per_block)
 {
     if (p.plane == 0) return (int)xcd_block(blockIdx.x, gridDim.x);
@@ -1261,7 +1264,7 @@ mf_status launch_scalar(const AssembleArgs& A)
     return launch_gather<8, 1, T>(A, w, fe, emask);
 }
 
-constexpr int64_t kPlaneBytes = 1 << 20;  // records of a grid plane that stay in an XCD's L2
+constexpr int64_t kPlaneBytes = 2500000;  // records of a grid plane that stay in an XCD's L2
 
 template <int FORM, typename T>
 mf_status launch_rows(const AssembleArgs& A)

@@ -1,5 +1,5 @@
-"""Bricks on both sides of each line between scalar rows with the geometry and element blocks, against the
-independent scatter."""
+"""Bricks on both sides of each line between scalar rows with the geometry and element blocks, and between
+rows in node order and in bands of a grid's planes, against the independent scatter."""
 import sys
 
 import numpy as np
@@ -21,7 +21,11 @@ LINES = [(O.MASS, 0, FIXED, GRID, (48, 49, 48)), (O.MASS, 0, FIXED, GRID, (49, 4
          (O.POISSON, 0, FREE, RANDOM, (27, 27, 27)), (O.POISSON, 0, FREE, RANDOM, (28, 27, 27)),
          (O.MASS, 1, FREE, RANDOM, (25, 25, 25)), (O.POISSON, 1, FREE, RANDOM, (25, 26, 25)),
          (O.POISSON, 0, FIXED, RANDOM, (24, 24, 24)), (O.MASS, 0, FIXED, RANDOM, (24, 25, 24)),
-         (O.POISSON, 1, FIXED, RANDOM, (20, 20, 19)), (O.POISSON, 1, FIXED, RANDOM, (20, 20, 20))]
+         (O.POISSON, 1, FIXED, RANDOM, (20, 20, 19)), (O.POISSON, 1, FIXED, RANDOM, (20, 20, 20)),
+         (O.ELASTICITY, 0, FIXED, GRID, (57, 57, 5)), (O.ELASTICITY, 0, FIXED, GRID, (58, 57, 5)),
+         (O.ELASTICITY, 1, FIXED, GRID, (60, 61, 13)), (O.ELASTICITY, 1, FIXED, GRID, (62, 60, 13)),
+         (O.NS_SUPG, 0, FREE, GRID, (36, 37, 2)), (O.NS_SUPG, 0, FREE, GRID, (37, 37, 2)),
+         (O.NS_SUPG, 1, FIXED, GRID, (38, 38, 8)), (O.NS_SUPG, 1, FIXED, GRID, (39, 38, 8))]
 
 
 @pytest.mark.parametrize("kind,prec,fixed,random,n", LINES)
