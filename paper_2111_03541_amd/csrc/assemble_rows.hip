@@ -469,9 +469,9 @@ __device__ __forceinline__ double brick_cofactors(const double* X, int q, double
 // value [8 points][elements]: the lanes of consecutive elements load one run.  By elements,
 // [elements][8 points][NR]: a lane's loads are one run, for meshes whose consecutive nodes have
 // elements anywhere, where a run of lanes would use 16 bytes of each line.  41x40x37 bricks, by
-// values against by elements: renumbered at random elasticity 317 us against 137, flow 973 against
-// 276; nodes shuffled among 64 neighbours 92 against 104 and 219 against 249; 64^3 in grid order 278
-// against 317 and 1000 against 1072.  Elements some thousand apart still meet in the L2 (4 MB), so
+// values against by elements: renumbered at random elasticity 324 us against 143, flow 970 against
+// 271; nodes shuffled among 64 neighbours 85 against 101 and 211 against 245; 64^3 in grid order 275
+// against 328 and 982 against 1054.  Elements some thousand apart still meet in the L2 (4 MB), so
 // the line lies at a quarter of the nodes with a first element more than 1024 from the next node's.
 //
 // Byte offsets in the records: pair m of point q of element e at e * pe + q * pq + m * pm, the last
@@ -641,8 +641,8 @@ struct Rec<MF_FORM_NS_SUPG> {
 
 // Thread (point, element): the geometry once per element instead of once per row, as records
 // of value pairs so that the lanes' stores and the row waves' loads are 16 bytes.  Bound by the
-// latency of the node gathers and the stores: elasticity 64^3 60 us for 151 MB, flow 48^3 76 us
-// for 177 MB.
+// latency of the node gathers and the stores: elasticity 64^3 60 us for 201 MB, flow 48^3 72 us
+// for 205 MB.
 template <int FORM, typename T>
 __global__ void __launch_bounds__(8 * kBE) k_brick_points(BrickParams p)
 {
@@ -931,8 +931,8 @@ __device__ __forceinline__ void point_flow_tail(const mf_form& fm, int q, const 
 // in registers, adds them to the node's row buffer in LDS, and the rows of the wave's nodes
 // leave as one contiguous run.  Two waves per SIMD (the node blocks take half the registers),
 // the next point's record is in flight during the products of the present one.  Elasticity 64^3
-// FP64: 260 us, VALU busy 48 %; with k_brick_points 318 us, the column kernel 356; 41x40x37 renumbered
-// bricks 137 us, the coloured scatter 1600.  Flow 48^3 FP64: 385 + 76 us, the coloured kernel 1540.
+// FP64: 256 us, VALU busy 48 %; with k_brick_points 315 us, the column kernel 356; 41x40x37 renumbered
+// bricks 143 us, the coloured scatter 1600.  Flow 48^3 FP64: 357 + 72 us, the coloured kernel 1540.
 // FP32 builds sum in FP64 too: without packed math the rates are the same.
 template <int FORM, typename T, bool FM>
 __global__ void __launch_bounds__(256, (Rec<FORM>::WG)) k_brick_rows(RowParams p)
