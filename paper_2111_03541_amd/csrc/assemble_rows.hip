@@ -796,12 +796,12 @@ struct RowParams {
     const void* fe;
     const uint8_t* emask;  // flags of the elements (with out.mask)
     int buf_len, wave_len;  // doubles of LDS per node and per wave
-    int plane, slots;   // nodes of a grid plane, workgroups of a band in it (0: nodes in order)
+    uint32_t plane, slots, shift;  // nodes of a grid plane (0: nodes in order), workgroups of a band in it; 2^shift nodes a workgroup
     void* K;
     void* d;
 };
 
-// The workgroup's nodes, in units of per_block, or -1.  A record is read by the eight nodes around
+// The workgroup's nodes, in units of 2^shift, or -1.  A record is read by the eight nodes around
 // its element.  In node order an XCD has passed a whole plane of the grid before the next reads it
 // again, and a plane above some 2.5 MB of records has left the XCD's 4 MB of L2 by then, with all of K
 // streaming through: each record was fetched twice (elasticity 64^3: 400 MB for 201).  So each XCD
@@ -811,14 +811,15 @@ struct RowParams {
 // 285, 58^3 263 against 247.  Below, where the records stay, the bands' uneven ends only cost: flow 36^3 168
 // against 175 (FP32, constrained 182 against 193), elasticity 48^3 137 against 140 (constrained 176
 // against 180, FP32 162 against 167), 56^3 FP32 252 against 264.
-__device__ __forceinline__ int row_block(const RowParams& p, int per_block)
+__device__ __forceinline__ int row_block(const RowParams& p)
 {
     if (p.plane == 0) return (int)xcd_block(blockIdx.x, gridDim.x);
-    const uint32_t band = blockIdx.x % kXcds, r = blockIdx.x / kXcds, z = r / (uint32_t)p.slots;
-    const int64_t at = (int64_t)z * p.plane;
-    const int64_t lo = at + (int64_t)band * p.plane / kXcds, hi = at + (int64_t)(band + 1) * p.plane / kXcds;
-    const int64_t b = (lo + per_block - 1) / per_block + (r - z * (uint32_t)p.slots);
-    return b < (hi + per_block - 1) / per_block ? (int)b : -1;
+    const uint32_t band = blockIdx.x % kXcds, r = blockIdx.x / kXcds, z = r / p.slots, plane = p.plane;
+    const uint32_t part = plane / kXcds, rest = plane % kXcds, up = (1u << p.shift) - 1;
+    const uint32_t lo = z * plane + band * part + band * rest / kXcds;  // (node ids have 31 bits)
+    const uint32_t hi = z * plane + (band + 1) * part + (band + 1) * rest / kXcds;
+    const uint32_t b = ((lo + up) >> p.shift) + (r - z * p.slots);
+    return b < (hi + up) >> p.shift ? (int)b : -1;
 }
 
 // Products of one Gauss point: adds the blocks (a, b) of the lane's BPL column nodes.
@@ -949,9 +950,8 @@ __global__ void __launch_bounds__(256, (Rec<FORM>::WG)) k_brick_rows(RowParams p
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     // lanes: node fastest, then group of column nodes, then slot
     const int grp = lane % NPW, half = lane / NPW % GRP, slot = lane / (NPW * GRP), sub = lane / NPW;
-    const int waves = blockDim.x / kWave, n_nodes = (int)p.out.n_nodes;
-    const int blk = row_block(p, waves * NPW);
-    const int v0 = (blk * waves + wave) * NPW, v = v0 + grp;
+    const int n_nodes = (int)p.out.n_nodes, blk = row_block(p);
+    const int v0 = (blk << p.shift) + wave * NPW, v = v0 + grp;
     if (blk < 0 || v0 >= n_nodes) return;
     const int wbase = wave * p.wave_len;  // the wave's row buffers, one after another
     double* dbuf = sh + wbase + NPW * p.buf_len + grp * NF;
@@ -1308,11 +1308,12 @@ mf_status launch_rows(const AssembleArgs& A)
     p.wave_len = wave_len;
     p.K = A.K;
     p.d = A.d;
-    const int64_t per_block = (int64_t)waves * NPW;
+    const int64_t per_block = (int64_t)waves * NPW;  // a power of two
+    while ((int64_t)1 << p.shift < per_block) ++p.shift;
     unsigned blocks = (unsigned)((P->n_nodes + per_block - 1) / per_block);
     if (P->is_grid && (int64_t)per * P->gx * P->gy > kPlaneBytes) {
-        p.plane = (int)((P->gx + 1) * (P->gy + 1));
-        p.slots = (int)((p.plane / kXcds + per_block) / per_block) + 1;
+        p.plane = (uint32_t)((P->gx + 1) * (P->gy + 1));
+        p.slots = (uint32_t)((p.plane / kXcds + per_block) / per_block) + 1;
         blocks = (unsigned)(kXcds * (P->gz + 1) * p.slots);
     }
     if (P->numbering == MF_FIELD_MAJOR) k_brick_rows<FORM, T, true><<<blocks, waves * kWave, per_wave * waves, A.stream>>>(p);
