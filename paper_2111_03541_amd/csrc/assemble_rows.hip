@@ -972,7 +972,6 @@ __global__ void __launch_bounds__(256, (Rec<FORM>::WG)) k_brick_rows(RowParams p
         const int code = p.adj[k];  // element * 8 + local node
         const int a = code & 7;
         const uint32_t e = (uint32_t)code >> 3;
-        if (p.out.mask) touched |= p.emask[e];
         // value pairs [m0, m1) of the record at point q: uniform bases, 32-bit lane offset
         auto load_pairs = [&](int q, int m0, int m1, double* h) {
             uint32_t eo = e * (uint32_t)p.lay.pe;
@@ -1026,6 +1025,8 @@ __global__ void __launch_bounds__(256, (Rec<FORM>::WG)) k_brick_rows(RowParams p
                 point_flow_tail<BPL>(p.form, q, r, f, acc);
             }
         }
+        // (here, as the wait for it would come before the first record's loads)
+        if (p.out.mask) touched |= p.emask[code >> 3];
         uint32_t ranks[BPL / 4];
 #pragma unroll
         for (int u = 0; u < BPL / 4; ++u) ranks[u] = *(const uint32_t*)(p.rank_t + (int64_t)code * 8 + (half + u) * 4);
