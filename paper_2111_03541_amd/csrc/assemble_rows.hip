@@ -933,7 +933,7 @@ __device__ __forceinline__ void point_flow_tail(const mf_form& fm, int q, const 
 // leave as one contiguous run.  Two waves per SIMD (the node blocks take half the registers),
 // the next point's record is in flight during the products of the present one.  Elasticity 64^3
 // FP64: 256 us, VALU busy 48 %; with k_brick_points 315 us, the column kernel 356; 41x40x37 renumbered
-// bricks 143 us, the coloured scatter 1600.  Flow 48^3 FP64: 357 + 72 us, the coloured kernel 1540.
+// bricks 143 us, the coloured scatter 1600.  Flow 48^3 FP64: 359 + 74 us, the coloured kernel 1540.
 // FP32 builds sum in FP64 too: without packed math the rates are the same.
 template <int FORM, typename T, bool FM>
 __global__ void __launch_bounds__(256, (Rec<FORM>::WG)) k_brick_rows(RowParams p)
